@@ -36,25 +36,26 @@ struct GemmArgs {
   KvView kv;
   int layer, Rseq, n_heads;
   uint32_t* status;
-  // k split across workgroups (products with few strips and more than 8 rows): partial sums [group][strip][row group][split]
-  // of 256 floats, and one zeroed counter per group (left zeroed); null = no split
+  // k split across workgroups (products with few strips and more than 8 rows): partial sums ([group][strip][row group][split] of
+  // 256 floats and one zeroed counter per group, left zeroed; many-row products [split][row][feature]); null = no split
   float* part;
   int* counters;
   size_t part_floats;  // capacity of `part` in floats and of `counters` in ints: a launch that would need more does not split
   int counters_n;
-  // scratch for the many-row kernel: the pass's activations rewritten in B-operand fragment order; null = not offered
+  // scratch for many-row products on plane input: the activations rewritten in B-operand fragment order; null = not offered
   // (such products then run on the skinny kernels)
   bf16_t* xfrag;
   size_t xfrag_elems;
 };
 
-hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s);
-// the same product for passes of many rows, activations staged through LDS (kernels_gemm_tiled.hip); chosen by launch_gemm_bf16
-hipError_t launch_gemm_bf16_tiled(const GemmArgs& a, int epi, hipStream_t s);
-bool gemm_tiled_wide(int N);  // enough strips for workgroups of 8
-size_t gemm_tiled_split_floats(int N);
-size_t gemm_tiled_xfrag_elems(int R, int K);  // scratch elements a product with R rows and reduction width K wants
-int gemm_tiled_split_counters(int N);
+// *np (may be null): partial sums of squares per row an EPI_RESID product left in ssq_out
+hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, int* np = nullptr);
+// the same product for passes of many rows, fragments copied to LDS by the loads themselves (kernels_gemm_dma.hip); chosen by
+// launch_gemm_bf16
+hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* np);
+size_t gemm_dma_xfrag_elems(int R, int K);  // scratch a product of R rows on plane input wants
+size_t gemm_dma_split_floats();  // workspace its cut of the reduction dimension may take
+bool gemm_dma_wide(int N);       // enough strips to give half of the compute units a workgroup of 8
 // workspace a context should offer for the k split of a product with N outputs (0 if it would never be split)
 size_t gemm_split_floats(int N);
 int gemm_split_counters(int N);

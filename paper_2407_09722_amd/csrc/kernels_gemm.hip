@@ -426,14 +426,10 @@ static int device_cus() {
 constexpr int SPLIT_MAX_STRIPS = 384, SPLIT_S = 4, SPLIT_KS = 4, SPLIT_NG_MAX = 8;
 size_t gemm_split_floats(int N) {
   const int NT = N / 16;
-  const size_t skinny = NT > SPLIT_MAX_STRIPS ? 0 : (size_t)((NT + SPLIT_S - 1) / SPLIT_S) * SPLIT_S * SPLIT_NG_MAX * SPLIT_KS * 256;
-  const size_t tiled = gemm_tiled_split_floats(N);
-  return skinny > tiled ? skinny : tiled;
+  return NT > SPLIT_MAX_STRIPS ? 0 : (size_t)((NT + SPLIT_S - 1) / SPLIT_S) * SPLIT_S * SPLIT_NG_MAX * SPLIT_KS * 256;
 }
 int gemm_split_counters(int N) {
-  const int skinny = N / 16 > SPLIT_MAX_STRIPS ? 0 : (N / 16 + 1) / 2;  // groups of at least 2 strips
-  const int tiled = gemm_tiled_split_counters(N);
-  return skinny > tiled ? skinny : tiled;
+  return N / 16 > SPLIT_MAX_STRIPS ? 0 : (N / 16 + 1) / 2;  // groups of at least 2 strips
 }
 
 // Strips per workgroup for a product with NT strips and NG row groups.  Cost model (fits the measured times at 17, 41
@@ -511,19 +507,23 @@ static hipError_t run_epi(GemmArgs a, int tag, hipStream_t s) {
   return hipSuccess;
 }
 
-// Passes of many rows stage both operands through LDS (kernels_gemm_tiled.hip).  Measured against the kernels above at
-// the 7B- and 13B-shaped products: it wins from 65 rows up everywhere, and from 25 rows up for products wide enough
-// to give every compute unit a workgroup of 8 strips (at 17 rows it loses also with activations that are already in
-// fragment order: C4 verify 4.50 against 4.24 ms).
-static bool use_tiled(const GemmArgs& a) {
-  if (!a.ncg && (!a.xfrag || a.xfrag_elems < gemm_tiled_xfrag_elems(a.R, a.K))) return false;  // needs fragment order or its scratch
-  return a.R >= 65 || (a.R >= 25 && gemm_tiled_wide(a.N));
+// Passes of many rows take both operands through LDS (kernels_gemm_dma.hip).  Measured against the kernels above at the 7B- and
+// 13B-shaped products: it wins from 65 rows up everywhere (4096 x 4096 at 64 rows: 21.1 -> 14.3 us), from 33 rows up for narrow
+// products with a long reduction, which it cuts into ranges (4096 x 11008 at 40 rows: 37.8 -> 26.7 us), and from 25 rows up for
+// products wide enough to give half of the compute units a workgroup of 8 strips (22016 x 4096 at 40 rows: 46.2 -> 38.8 us);
+// between, one of 12288 x 4096 takes 24.6 us above and 27.4 us there at 40 rows.
+static bool use_dma(const GemmArgs& a, int epi) {
+  if (!a.ncg && (!a.xfrag || a.xfrag_elems < gemm_dma_xfrag_elems(a.R, a.K))) return false;  // needs fragment order or its scratch
+  if (a.R >= 65) return true;
+  if (a.R < 25) return false;
+  return gemm_dma_wide(a.N) || (a.R >= 33 && epi == EPI_RESID && a.part && a.K >= 4096);
 }
 
-hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s) {
+hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, int* np) {
+  if (np) *np = a.N >> 4;
   if (a.R <= 0) return hipSuccess;
   if ((a.N % 16) || (a.K % 32) || a.R > 256) return hipErrorInvalidValue;
-  if (use_tiled(a) && (epi != EPI_STORE || (a.ldy % 4) == 0)) return launch_gemm_bf16_tiled(a, epi, s);
+  if (use_dma(a, epi) && (epi != EPI_STORE || (a.ldy % 4) == 0)) return launch_gemm_bf16_dma(a, epi, s, np);
   switch (epi) {
     case EPI_STORE: return (a.ldy % 4) ? hipErrorInvalidValue : run_epi<EPI_STORE>(a, tag, s);
     case EPI_RESID: return run_epi<EPI_RESID>(a, tag, s);

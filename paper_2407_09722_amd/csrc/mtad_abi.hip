@@ -32,6 +32,7 @@ struct mtad_ctx {
   size_t gemm_part_n;  // floats
   int* gemm_cnt;
   int gemm_cnt_n;
+  int pass_np;     // partial sums of squares per row the pass in flight left for its lm_head
   int pass_ncg;    // activation layout of the pass in flight (0 planes, else row groups of the fragment order): its lm_head reads it
   int warp_k;      // > 0: next-token distributions of both models are warped (mtad_set_warp)
   float warp_p;
@@ -129,12 +130,13 @@ void carve(mtad_ctx* c, char* base) {
         if (gemm_split_counters(N) > pc) pc = gemm_split_counters(N);
       }
     }
+    if (rows > 24 && (t.dtype == 1 || d.dtype == 1) && gemm_dma_split_floats() > pf) pf = gemm_dma_split_floats();
     c->gemm_part_n = pf + 64;
     c->gemm_part = k.take<float>(c->gemm_part_n);
     c->gemm_cnt_n = pc + 1;
     c->gemm_cnt = k.take<int>((size_t)c->gemm_cnt_n);
     // widest reduction dimension of any product: the model widths and FFN widths
-    c->gemm_xfrag_n = gemm_tiled_xfrag_elems((int)rows, imax(imax(dmax, fmax), hhd));
+    c->gemm_xfrag_n = gemm_dma_xfrag_elems(imax((int)rows, 256), imax(imax(dmax, fmax), hhd));
     c->gemm_xfrag = k.take<bf16_t>(c->gemm_xfrag_n);
   }
   {  // the one-launch pass: versions of what its steps hand on, sized for FLOW_MAX_ROWS rows of the larger need of the two models
@@ -377,8 +379,7 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
     a.W = (const bf16_t*)L[2]; a.X = (const bf16_t*)c->xn; a.N = d; a.K = H * hd;
     a.ssq = nullptr; a.NP = 0;
     a.h = c->h; a.g_next = (const float*)L[3]; a.planes_out = (bf16_t*)c->xg; a.ssq_out = c->ssq;
-    HIP_TRY(c, launch_gemm_bf16(a, EPI_RESID, tag, s));
-    np = d / 16;
+    HIP_TRY(c, launch_gemm_bf16(a, EPI_RESID, tag, s, &np));
     // gate/up + SwiGLU
     a.W = (const bf16_t*)L[4]; a.X = (const bf16_t*)c->xg; a.N = 2 * f; a.K = d;
     a.ssq = c->ssq; a.NP = np;
@@ -388,8 +389,9 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
     a.W = (const bf16_t*)L[5]; a.X = (const bf16_t*)c->xn; a.N = d; a.K = f;
     a.ssq = nullptr; a.NP = 0;
     a.g_next = (const float*)(l + 1 < m->n_layers ? W[1 + 6 * (l + 1)] : W[tail]);
-    HIP_TRY(c, launch_gemm_bf16(a, EPI_RESID, tag, s));
+    HIP_TRY(c, launch_gemm_bf16(a, EPI_RESID, tag, s, &np));
   }
+  c->pass_np = np;
   return logits ? lm_head(c, m, rows, logits, lse, s) : MTAD_OK;
 }
 
@@ -409,7 +411,7 @@ int lm_head(mtad_ctx* c, const mtad_model* m, int rows, float* logits, float* ls
     memset(&a, 0, sizeof(a));
     a.W = (const bf16_t*)W[tail + 1]; a.X = (const bf16_t*)c->xg; a.R = rows; a.N = m->vocab; a.K = m->d_model;
     a.ncg = c->pass_ncg;
-    a.ssq = c->ssq; a.NP = m->d_model / 16; a.eps = m->rms_eps;
+    a.ssq = c->ssq; a.NP = c->pass_np; a.eps = m->rms_eps;
     a.Y = logits; a.ldy = m->vocab; a.lse_part = c->lse_part;
     a.part = c->gemm_part; a.counters = c->gemm_cnt; a.part_floats = c->gemm_part_n; a.counters_n = c->gemm_cnt_n;
     a.xfrag = c->gemm_xfrag; a.xfrag_elems = c->gemm_xfrag_n;
@@ -703,7 +705,7 @@ int mtad_k_gemm_x(mtad_ctx* c, int32_t dtype, const void* W, const void* X, floa
     a.part_floats = c->gemm_part_n;
     a.counters_n = c->gemm_cnt_n;
   }
-  if (c && c->ws && gemm_tiled_xfrag_elems(R, K) <= c->gemm_xfrag_n) {  // the many-row kernel needs its scratch
+  if (c && c->ws && gemm_dma_xfrag_elems(R, K) <= c->gemm_xfrag_n) {  // the many-row kernel needs its scratch
     a.xfrag = c->gemm_xfrag;
     a.xfrag_elems = c->gemm_xfrag_n;
   }

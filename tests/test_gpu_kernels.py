@@ -125,6 +125,25 @@ def test_gemm_bf16_fragment_order_input(R, N, K):
     mb.mtad_destroy(ctx)
 
 
+@pytest.mark.parametrize("R,N,K", [(65, 16, 32), (128, 80, 64), (129, 96, 96), (192, 112, 288), (193, 1040, 544), (255, 4112, 1056), (256, 2064, 4096),
+                                   (65, 5120, 4096), (130, 2080, 8192), (200, 11264, 512), (250, 15360, 160), (164, 27648, 64)])
+def test_gemm_bf16_many_rows(R, N, K):
+    """The many-row kernel at the edges of its tiles: 64, 128, 192 and 256 rows and one more or less, every count of strips per
+    workgroup with strips left over, one to many k tiles (fewer than the ring holds, odd counts), reductions cut into ranges;
+    stored and added."""
+    mb = _mb()
+    shape = si.ModelShape(1, 8192, 64, 64, 128, 8192, 32000, "bf16")
+    desc = mb.mtad_model(shape.n_layers, shape.d_model, shape.n_heads, shape.n_kv_heads, shape.head_dim, shape.d_ffn, shape.vocab, 1, shape.rms_eps,
+                         shape.rope_theta, None)
+    ctx = mb.mtad_create(mb.mtad_config(4, 4, 4, 1, 64, 256), desc, desc)
+    ws = torch.empty(mb.mtad_workspace_bytes(ctx), dtype=torch.uint8, device=DEV)
+    mb.mtad_bind_workspace(ctx, ws)
+    for acc, order in ((False, mb.MTAD_X_FRAGMENTS), (True, mb.MTAD_X_PLANES)):
+        print(f"gemm bf16 many rows R={R} N={N} K={K} accumulate={acc}", flush=True)
+        _gemm_case(mb, R, N, K, 1, seed=R * 5 + N, ctx=ctx, accumulate=acc, x_order=order, ldy=N + 16)
+    mb.mtad_destroy(ctx)
+
+
 def test_gemm_bf16_c5_gate_up_product_at_full_size():
     """The largest product of C5's target pass at its real size: 164 rows (4 trees of 41) x 27648 gate/up features x 5120,
     activations in fragment order, on the kernel the pass takes for it (8 strips per workgroup, 24 column groups, 64 KiB
