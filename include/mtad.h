@@ -129,7 +129,8 @@ typedef struct {
 typedef struct {
   int32_t batch, gamma, beam;
   int32_t mode;         /* MTAD_MODE_* : fixes the rows of the target pass (1+gamma or 1+beam*gamma) */
-  int32_t prefill_rows; /* rows per sequence in one prefill chunk, 1..64 */
+  int32_t prefill_rows; /* rows per sequence in one prefill chunk, 1..64; a bfloat16 model takes a longer prompt in larger chunks
+                           (up to 2048 rows of all sequences together, which the workspace holds) */
   int32_t max_context;  /* upper bound on committed + speculative tokens per sequence */
 } mtad_config;
 

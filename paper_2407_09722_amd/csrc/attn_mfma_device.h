@@ -94,8 +94,8 @@ __device__ __forceinline__ int token_index(const KvView& kv, int seq, int pos) {
 // compute units with two workgroups and the rest with one, fill every resident slot and are taken only where every
 // wave still gets four tiles.
 constexpr int ATTN_WAVES = 4;
-__device__ __forceinline__ int attn_keys(const KvView& kv, const RowDesc& rd, int seq) {
-  const int nspec = max(0, min(rd.nspec[seq], 64));
+__device__ __forceinline__ int attn_keys(const KvView& kv, const RowDesc& rd, int seq, bool causal = false) {
+  const int nspec = max(0, causal ? rd.nspec[seq] : min(rd.nspec[seq], 64));
   return min(kv.len[seq] + nspec, kv_capacity(kv));
 }
 __device__ __forceinline__ int attn_splits(int ktot, int n_splits, int want_splits) {
@@ -207,10 +207,12 @@ __device__ __forceinline__ void attn_merge_row(const float* __restrict__ pp, int
 // rows produce, i.e. the queries and the K / V of speculative positions.  K and V tiles that lie inside the committed
 // context are requested BEFORE it: a caller whose queries are still being computed has the cache reads of the context
 // in flight meanwhile.  (Items without work return before the call.)
+// CAUSAL: the rows are a chunk of a prompt, of any number: row r sees the committed context and rows 0 .. r, and an item
+// stops at the last key any of its rows sees; rd.mask is not read.
 struct AttnNoWait {
   __device__ __forceinline__ void operator()() const {}
 };
-template <int HD, int NRG, int AW, int NSET, int NTH, bool COH, int DS = 1, typename WaitFn = AttnNoWait>
+template <int HD, int NRG, int AW, int NSET, int NTH, bool COH, int DS = 1, bool CAUSAL = false, typename WaitFn = AttnNoWait>
 __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm, const float* __restrict__ q, int q_stride, const RowDesc& rd,
                                               const KvView& kv, int layer, int B, int R, int n_heads, int n_chunks, float scale,
                                               float* __restrict__ partial, int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg,
@@ -238,19 +240,28 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   auto pair_head = [&](int r) { return g * G + (pair0 + r) / R; };  // query head and tree row of pair r of this item
   auto pair_row = [&](int r) { return (pair0 + r) % R; };
   const int len = kv.len[seq];
-  const int ktot = attn_keys(kv, rd, seq);
+  const int ktot = attn_keys(kv, rd, seq, CAUSAL);
   const int eff = attn_splits(ktot, n_splits, want_splits);  // splits actually used for this sequence
   if (split >= eff) return eff;
   int per = (ktot + eff - 1) / eff;
   per = ((per + ATK - 1) / ATK) * ATK;
-  const int kbeg = split * per, kend = min(ktot, kbeg + per);
+  const int kbeg = split * per;
+  int kend = min(ktot, kbeg + per), seen_by_all = len;  // keys below seen_by_all are visible to every row of the item
+  if constexpr (CAUSAL) {
+    const bool one_head = pair0 / R == (pair0 + nrows - 1) / R;  // else its rows wrap around: first and last row of the chunk are among them
+    kend = min(kend, len + 1 + (one_head ? pair_row(nrows - 1) : R - 1));
+    seen_by_all = len + 1 + (one_head ? pair_row(0) : 0);
+  }
   const int n_tiles = (active && kend > kbeg) ? (kend - kbeg + ATK - 1) / ATK : 0;  // none for the waves that only pass barriers
   const int wv = active ? wave : 0;  // this wave's V tile in LDS
 
   const int srow = lane & 15, sg4 = lane >> 4;  // this lane's query row (within a row group) and key group
-  unsigned long long rmask[NRG];
+  unsigned long long rmask[NRG];  // CAUSAL: the first key the row does not see
 #pragma unroll
-  for (int rg = 0; rg < NRG; ++rg) rmask[rg] = (rg * 16 + srow < nrows) ? rd.mask[seq * R + pair_row(rg * 16 + srow)] : 0ull;
+  for (int rg = 0; rg < NRG; ++rg) {
+    if constexpr (CAUSAL) rmask[rg] = (rg * 16 + srow < nrows) ? (unsigned)(len + 1 + pair_row(rg * 16 + srow)) : 0u;
+    else rmask[rg] = (rg * 16 + srow < nrows) ? rd.mask[seq * R + pair_row(rg * 16 + srow)] : 0ull;
+  }
 
   // token index of key (tile start + lane % 32), looked up once per tile and handed round by shuffles
   auto lookup = [&](int ti) -> int {
@@ -414,7 +425,7 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
     // visibility, scale, running softmax per row; probabilities become the B operand of the second product
     half8 ph[NRG], pl[NRG];
     // a tile that lies inside the committed context (all but the last one or two) is visible to every row: no mask
-    const bool plain = kbeg + (ti + 1) * ATK <= min(len, kend);  // uniform over the wave
+    const bool plain = kbeg + (ti + 1) * ATK <= min(seen_by_all, kend);  // uniform over the wave
 #pragma unroll
     for (int rg = 0; rg < NRG; ++rg) {
       float tmax = -INFINITY;
@@ -434,7 +445,8 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
           for (int i = 0; i < 4; ++i) {
             const int kj = kbeg + ti * ATK + blk * 16 + sg4 * 4 + i;
             bool vis = kj < kend;
-            if (vis && kj >= len) vis = (rmask[rg] >> (kj - len)) & 1ull;
+            if constexpr (CAUSAL) vis = vis && kj < (int)rmask[rg];
+            else if (vis && kj >= len) vis = (rmask[rg] >> (kj - len)) & 1ull;
             const float sv = vis ? s2[rg][blk][i] * scale : -INFINITY;
             s2[rg][blk][i] = sv;
             tmax = fmaxf(tmax, sv);

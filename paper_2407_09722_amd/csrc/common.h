@@ -122,6 +122,9 @@ hipError_t launch_attention(int dtype, const float* q, int q_stride, const RowDe
 // n_splits = upper bound on the key splits (the kernel uses fewer for short contexts)
 hipError_t launch_attention_mfma(const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads,
                                  float* partial, int n_splits, void* out, int ncg, hipStream_t s);
+// the same for a chunk of a prompt: any number of rows per sequence, row r sees the committed context and rows 0 .. r
+hipError_t launch_attention_prompt(const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads, float* partial,
+                                   int n_splits, void* out, int ncg, hipStream_t s);
 // lse[row] from per-strip (max, sum exp) partials [rows][NP]
 hipError_t launch_lse_finish(const float* lse_part, float* lse, int rows, int NP, hipStream_t s);
 // lse as above for B*M rows, plus logp_cond[s][c] = logits[s][parent(c)][tok(c)] - lse[s][parent(c)] (0 for c = 0)

@@ -18,7 +18,7 @@ namespace mtad {
 
 namespace {
 
-template <int HD, int NRG, int AW>
+template <int HD, int NRG, int AW, bool CAUSAL>
 __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(2))) void tree_attn_mfma_kernel(const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer,
                                                                int R, int n_heads, int n_chunks, float scale, float* __restrict__ partial,
                                                                int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg) {
@@ -27,9 +27,12 @@ __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   Smem& sm = *reinterpret_cast<Smem*>(smem_raw);
   // the kernels with registers to spare (head dim 64, or a single row group) hold two register sets for K and V
   constexpr int NSET = (HD == 64 || NRG == 1) ? 2 : 1;
-  tree_attn_item<HD, NRG, AW, NSET, AW * 64, false>(sm, q, q_stride, rd, kv, layer, (int)gridDim.z, R, n_heads, n_chunks, scale, partial, n_splits,
-                                                   out, want_splits, ncg, (int)blockIdx.x, (int)blockIdx.y / n_chunks, (int)blockIdx.y % n_chunks,
-                                                   (int)blockIdx.z, (int)threadIdx.x);
+  // a chunk of a prompt: the items that see the most keys first
+  const int by = CAUSAL ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y;
+  const int g = CAUSAL ? by % (int)(gridDim.y / n_chunks) : by / n_chunks, chunk = CAUSAL ? by / (int)(gridDim.y / n_chunks) : by % n_chunks;
+  tree_attn_item<HD, NRG, AW, NSET, AW * 64, false, 1, CAUSAL>(sm, q, q_stride, rd, kv, layer, (int)gridDim.z, R, n_heads, n_chunks, scale, partial,
+                                                              n_splits, out, want_splits, ncg, (int)blockIdx.x, g, chunk, (int)blockIdx.z,
+                                                              (int)threadIdx.x);
 }
 
 // Merge of the key splits, a kernel of its own: one wave per (sequence, query head, row).  As a separate launch it is
@@ -38,24 +41,24 @@ __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // 4 splits and 5 rows, 8 us of 28 at 8 splits and 17 rows) made more splits cost more than they gained.
 template <int HD>
 __global__ __launch_bounds__(256) void attn_merge_kernel(RowDesc rd, KvView kv, int B, int R, int n_heads, const float* __restrict__ partial,
-                                                         int n_splits, int want_splits, bf16_t* __restrict__ out, int ncg) {
+                                                         int n_splits, int want_splits, bf16_t* __restrict__ out, int ncg, bool causal) {
   const int lane = threadIdx.x & 63;
   const int item = blockIdx.x * 4 + (threadIdx.x >> 6);  // (seq, head, row)
   if (item >= B * n_heads * R) return;
   const int row = item % R, head = (item / R) % n_heads, seq = item / (R * n_heads);
-  const int eff = attn_splits(attn_keys(kv, rd, seq), n_splits, want_splits);
+  const int eff = attn_splits(attn_keys(kv, rd, seq, causal), n_splits, want_splits);
   if (eff == 1) return;  // the attention kernel wrote the output itself
   const float* pp = partial + (((int64_t)seq * n_heads + head) * R + row) * n_splits * (HD + 2);
   attn_merge_row<HD, false>(pp, eff, out, ncg, B * R, n_heads * HD, seq * R + row, head, lane);
 }
 
-template <int HD, int NRG, int AW>
+template <int HD, int NRG, int AW, bool CAUSAL = false>
 hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvView& kv, int layer, int B, int R, int n_heads, float* partial,
                     int n_splits, void* out, int ncg, hipStream_t s) {
   const int KVH = kv.n_kv_heads, G = n_heads / KVH;
   const int n_chunks = (G * R + NRG * 16 - 1) / (NRG * 16);  // chunks of (query head, row) pairs per KV head
   const float scale = 1.0f / sqrtf((float)HD);
-  auto kern = tree_attn_mfma_kernel<HD, NRG, AW>;
+  auto kern = tree_attn_mfma_kernel<HD, NRG, AW, CAUSAL>;
   constexpr size_t lds = sizeof(MfmaAttnSmem<HD, NRG, AW>);
   static const hipError_t attr = lds > 64 * 1024 ? hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
                                                  : hipSuccess;
@@ -87,7 +90,7 @@ hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvVie
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || gx == 1) return e;  // one split: every workgroup wrote its output
   hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3((B * n_heads * R + 3) / 4), dim3(256), 0, s, rd, kv, B, R, n_heads, (const float*)partial,
-                     n_splits, want, (bf16_t*)out, ncg);
+                     n_splits, want, (bf16_t*)out, ncg, CAUSAL);
   return hipGetLastError();
 }
 
@@ -107,6 +110,15 @@ hipError_t launch_attention_mfma(const float* q, int q_stride, const RowDesc& rd
   if (hd == 128) return run_mfma<128, 2, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
   if (hd == 64 && pairs <= 16) return run_mfma<64, 1, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
   if (hd == 64) return run_mfma<64, 2, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  return hipErrorInvalidValue;
+}
+
+// the rows of a prompt chunk (any number per sequence; causal)
+hipError_t launch_attention_prompt(const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads, float* partial,
+                                   int n_splits, void* out, int ncg, hipStream_t s) {
+  if (kv.n_kv_heads < 1 || n_heads % kv.n_kv_heads) return hipErrorInvalidValue;
+  if (kv.head_dim == 128) return run_mfma<128, 2, 4, true>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (kv.head_dim == 64) return run_mfma<64, 2, 4, true>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
   return hipErrorInvalidValue;
 }
 

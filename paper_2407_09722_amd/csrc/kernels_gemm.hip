@@ -522,8 +522,9 @@ static bool use_dma(const GemmArgs& a, int epi) {
 hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, int* np) {
   if (np) *np = a.N >> 4;
   if (a.R <= 0) return hipSuccess;
-  if ((a.N % 16) || (a.K % 32) || a.R > 256) return hipErrorInvalidValue;
+  if ((a.N % 16) || (a.K % 32)) return hipErrorInvalidValue;
   if (use_dma(a, epi) && (epi != EPI_STORE || (a.ldy % 4) == 0)) return launch_gemm_bf16_dma(a, epi, s, np);
+  if (a.R > 256) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_STORE: return (a.ldy % 4) ? hipErrorInvalidValue : run_epi<EPI_STORE>(a, tag, s);
     case EPI_RESID: return run_epi<EPI_RESID>(a, tag, s);

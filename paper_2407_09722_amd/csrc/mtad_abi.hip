@@ -21,10 +21,13 @@ struct mtad_ctx {
   int M;                      // rows per sequence of the target pass
   int Rmax;                   // most rows per sequence of any pass
   int draft_rows;             // rows per sequence of a draft step (max over steps)
+  int prompt_rows;            // most rows per sequence of a prompt chunk of a bf16 model
   size_t ws_need;
   char* ws;
   // workspace carve-up
   float *h, *qkv, *gu, *dlogits, *lse, *partial, *part_key, *ssq, *lse_part;
+  float* ssq_sum;    // [rows of a prompt chunk]
+  size_t partial_n;  // floats
   float* qrows;  // [batch][gamma][draft vocab]: log q of every draft step's live row when the beam is one wide (mtad_accept_spd)
   void *xn, *xg;  // xn: attention output / FFN activation; xg: h*gain planes feeding the next normalised product
   int* attn_cnt;
@@ -90,6 +93,13 @@ int splits_for(const mtad_ctx* c, const mtad_model* m, int R) {
   return imax(1, imin(32, s));
 }
 
+// Rows of one prompt pass of a bf16 model, all sequences together.  From about 256 rows on a product is bound by the matrix
+// cores, no longer by its weights; 2048 rows fill the machine with 256-row tiles also where the output is narrow (4096
+// features: 256 workgroups), and cost a 13B-shaped model 270 MB of workspace.  Four 7B-shaped layers on 2047 tokens: 21.5 ms in
+// chunks of 64 rows, 5.25 ms in one pass; four 13B-shaped ones on 4 x 509: 13.4 -> 7.8 ms; the 22-layer draft on 4 x 1023:
+// 62.9 -> 21.3 ms (the last layer's share of these, 3 products and the attention that nothing reads, is left out in both models).
+constexpr int PROMPT_PASS_ROWS = 2048;
+
 struct Carver {
   size_t off = 0;
   char* base;
@@ -105,17 +115,19 @@ struct Carver {
 void carve(mtad_ctx* c, char* base) {
   const mtad_model &t = c->tshape, &d = c->dshape;
   const size_t rows = (size_t)c->cfg.batch * c->Rmax;
+  const size_t prompt = (size_t)c->cfg.batch * c->prompt_rows, wide = imax64(rows, prompt);  // rows of the largest pass
   const int dmax = imax(t.d_model, d.d_model), fmax = imax(t.d_ffn, d.d_ffn);
   const int hhd = imax(t.n_heads * t.head_dim, d.n_heads * d.head_dim);
   const int qkv = imax((t.n_heads + 2 * t.n_kv_heads) * t.head_dim, (d.n_heads + 2 * d.n_kv_heads) * d.head_dim);
   const int hdmax = imax(t.head_dim, d.head_dim);
   Carver k(base);
   c->status = k.take<uint32_t>(64);
-  c->h = k.take<float>(rows * dmax);
-  const size_t rows8 = (rows + 7) / 8 * 8;  // operand-fragment order holds whole groups of 8 rows
+  c->h = k.take<float>(wide * dmax);
+  const size_t rows8 = (wide + 7) / 8 * 8;  // operand-fragment order holds whole groups of 8 rows
   c->xn = k.take<float>(rows8 * imax(imax(dmax, hhd), fmax));
   c->xg = k.take<float>(rows8 * dmax);
-  c->ssq = k.take<float>(rows * (size_t)(dmax / 16 + 1));
+  c->ssq = k.take<float>(wide * (size_t)(dmax / 16 + 1));
+  c->ssq_sum = k.take<float>(prompt);
   c->lse_part = k.take<float>(rows * (size_t)(imax(t.vocab, d.vocab) / 16 + 1) * 2);
   c->attn_cnt_n = (size_t)c->cfg.batch * imax(t.n_heads, d.n_heads) * (size_t)((c->Rmax + 7) / 8);
   c->attn_cnt = k.take<int>(c->attn_cnt_n);
@@ -164,19 +176,20 @@ void carve(mtad_ctx* c, char* base) {
     c->flow_prof = k.take<unsigned long long>((size_t)4 * 100000);
 #endif
   }
-  c->qkv = k.take<float>(rows * qkv);
+  c->qkv = k.take<float>(imax64(rows * qkv, prompt * hhd));  // float32 models: q, k and v; bf16 models: q
   c->gu = k.take<float>(rows * 2 * fmax);
   c->dlogits = k.take<float>((size_t)c->cfg.batch * c->draft_rows * d.vocab);
   c->qrows = k.take<float>(c->cfg.beam == 1 ? (size_t)c->cfg.batch * c->cfg.gamma * d.vocab : 1);
   c->lse = k.take<float>(rows);
   const size_t pt = attention_partial_floats(c->cfg.batch, c->Rmax, t.n_heads, t.head_dim, 32);
   const size_t pd = attention_partial_floats(c->cfg.batch, c->Rmax, d.n_heads, d.head_dim, 32);
-  c->partial = k.take<float>(pt > pd ? pt : pd);
-  c->rope = k.take<float2>(rows * (hdmax / 2));
-  c->rd.tok = k.take<int32_t>(rows);
-  c->rd.pos = k.take<int32_t>(rows);
-  c->rd.slot = k.take<int32_t>(rows);
-  c->rd.mask = k.take<uint64_t>(rows);
+  c->partial_n = pt > pd ? pt : pd;
+  c->partial = k.take<float>(c->partial_n);
+  c->rope = k.take<float2>(wide * (hdmax / 2));
+  c->rd.tok = k.take<int32_t>(wide);
+  c->rd.pos = k.take<int32_t>(wide);
+  c->rd.slot = k.take<int32_t>(wide);
+  c->rd.mask = k.take<uint64_t>(wide);
   c->rd.nspec = k.take<int32_t>(c->cfg.batch);
   c->part_key = k.take<float>((size_t)c->cfg.batch * TOPB_BLOCKS * 8);
   c->part_idx = k.take<int>((size_t)c->cfg.batch * TOPB_BLOCKS * 8);
@@ -231,10 +244,11 @@ int finish_lse(mtad_ctx* c, const mtad_model* m, int rows, const float* logits, 
   return MTAD_OK;
 }
 
-// The decoder pass over B*R rows described by ctx->rd.  float32 models: hidden states end in ctx->h.
+// The decoder pass over B*R rows described by ctx->rd.  Without `logits` (a prompt) it ends with the last layer's keys and
+// values: nothing reads what that layer would compute from them.  float32 models: hidden states end in ctx->h.
 // bf16 models: additionally ctx->xg holds the planes of h*g_final and ctx->ssq the per-strip sums of squares,
 // ready for the lm_head product.
-int decoder_pass_f32(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStream_t s) {
+int decoder_pass_f32(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStream_t s, bool cache_only) {
   const int B = c->cfg.batch, rows = B * R;
   const int d = m->d_model, f = m->d_ffn, H = m->n_heads, hd = m->head_dim;
   const int qkvw = (H + 2 * m->n_kv_heads) * hd;
@@ -247,6 +261,7 @@ int decoder_pass_f32(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R,
     HIP_TRY(c, launch_rmsnorm(0, c->h, (const float*)L[0], c->xn, rows, d, m->rms_eps, s));
     HIP_TRY(c, launch_gemm_f32(L[1], c->xn, c->qkv, rows, qkvw, d, qkvw, false, s));
     HIP_TRY(c, launch_rope_kv(0, c->qkv, c->rope, c->rd, kvv, l, B, R, H, c->status, s));
+    if (cache_only && l + 1 == m->n_layers) break;  // nothing reads the last layer's hidden states
     HIP_TRY(c, launch_attention(0, c->qkv, qkvw, c->rd, kvv, l, B, R, H, c->partial, n_splits, c->attn_cnt, c->xn, 0, s));
     HIP_TRY(c, launch_gemm_f32(L[2], c->xn, c->h, rows, d, H * hd, d, true, s));
     HIP_TRY(c, launch_rmsnorm(0, c->h, (const float*)L[3], c->xn, rows, d, m->rms_eps, s));
@@ -305,7 +320,7 @@ int flow_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStr
     fa.units[FK_ATTN] = fa.attn_gx * KVH * fa.attn_chunks * B;
     if (B * KVH * fa.attn_chunks > c->flow_sync_n - flow_sync_ints(0)) return MTAD_ECAP;
   }
-  const int s_last = 5 * L + (logits ? 1 : 0);
+  const int s_last = logits ? 5 * L + 1 : 5 * L - 4;  // without logits: up to the last layer's QKV product
   HIP_TRY(c, launch_flow_setup(fa, c->flow_args, c->flow_sync, c->flow_sync_n, s));
   HIP_TRY(c, launch_embed(1, W[0], c->rd.tok, c->h, rows, d, m->vocab, (const float*)W[1], c->flow_xg, c->flow_ssq, c->rd.pos, c->rope, hd,
                           m->rope_theta, ncg, s));
@@ -315,6 +330,7 @@ int flow_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStr
     int s0 = 0;
     for (int l = 0; l < L; ++l) {
       HIP_TRY(c, launch_flow(fa, c->flow_args, s0, 5 * l + 1, s));  // up to this layer's QKV product
+      if (!logits && l + 1 == L) return MTAD_OK;
       HIP_TRY(c, launch_attention_mfma(c->flow_q + (size_t)l * fa.q_stride, hhd, c->rd, kvv, l, B, R, H, c->partial, fa.n_splits,
                                        c->flow_xattn + (size_t)l * fa.xattn_stride, ncg, s));
       s0 = 5 * l + 2;
@@ -339,7 +355,7 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
   const int tag = same_shape(m, &c->tshape) ? 1 : 0;
   const void* const* W = m->weights;
   const int tail = 1 + 6 * m->n_layers;
-  if (c->flow_on && rows <= FLOW_MAX_ROWS && m->n_layers <= FLOW_MAX_LAYERS) {
+  if (c->flow_on && rows <= FLOW_MAX_ROWS && R <= c->Rmax && m->n_layers <= FLOW_MAX_LAYERS) {
     // Steps hand over through counters and flags in memory, about as dear as a kernel boundary each; what the one launch
     // gains is the weights requested across those handovers, which counts where a layer streams tens of megabytes
     // (7B-shaped target, 405 MB per layer: pass 2.78 -> 2.61 ms) and not for small models (two 14 MB layers: 95 -> 106 us).
@@ -354,7 +370,21 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
   c->pass_ncg = ncg;
   HIP_TRY(c, launch_embed(1, W[0], c->rd.tok, c->h, rows, d, m->vocab, (const float*)W[1], c->xg, c->ssq, c->rd.pos, c->rope, hd, m->rope_theta,
                           ncg, s));
-  int np = 1;  // partial sums of squares per row currently in ctx->ssq
+  // a prompt chunk of more rows than a row mask and the attention's exchange buffer are made for; its key splits are as many as
+  // that buffer takes (a chunk that needs them to fill the machine is small enough for several)
+  const bool prompt = R > c->Rmax;
+  const int prompt_splits = prompt ? imax(1, (int)(c->partial_n / attention_partial_floats(B, R, H, hd, 1))) : 0;
+  int np = 1;  // partial sums of squares per row currently at ssq
+  const float* ssq = c->ssq;
+  auto sum_ssq = [&]() -> int {
+    ssq = c->ssq;
+    if (prompt && np > 1 && rows > 256) {
+      HIP_TRY(c, launch_ssq_rows(c->ssq, c->ssq_sum, rows, np, s));
+      ssq = c->ssq_sum;
+      np = 1;
+    }
+    return MTAD_OK;
+  };
   for (int l = 0; l < m->n_layers; ++l) {
     const void* const* L = W + 1 + 6 * l;
     GemmArgs a;
@@ -370,19 +400,30 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
     a.xfrag_elems = c->gemm_xfrag_n;
     // qkv
     a.W = (const bf16_t*)L[1]; a.X = (const bf16_t*)c->xg; a.N = qkvw; a.K = d;
-    a.ssq = c->ssq; a.NP = np;
+    a.ssq = ssq; a.NP = np;
     a.q_out = c->qkv; a.rope = c->rope; a.slot = c->rd.slot; a.kv = kvv; a.layer = l; a.Rseq = R; a.n_heads = H; a.status = c->status;
+    if (!logits && l + 1 == m->n_layers) {  // only the key and value heads, which follow the query heads in the packed matrix
+      a.W += (size_t)H * hd * d;
+      a.N = 2 * m->n_kv_heads * hd;
+      a.n_heads = 0;
+      HIP_TRY(c, launch_gemm_bf16(a, EPI_QKV, tag, s));
+      break;
+    }
     HIP_TRY(c, launch_gemm_bf16(a, EPI_QKV, tag, s));
-    HIP_TRY(c, launch_attention(1, c->qkv, H * hd, c->rd, kvv, l, B, R, H, c->partial, imin(32, (c->cfg.max_context + 127) / 128), c->attn_cnt,
-                                c->xn, ncg, s));
+    if (prompt)
+      HIP_TRY(c, launch_attention_prompt(c->qkv, H * hd, c->rd, kvv, l, B, R, H, c->partial, prompt_splits, c->xn, ncg, s));
+    else
+      HIP_TRY(c, launch_attention(1, c->qkv, H * hd, c->rd, kvv, l, B, R, H, c->partial, imin(32, (c->cfg.max_context + 127) / 128), c->attn_cnt,
+                                  c->xn, ncg, s));
     // o projection + residual; prepares the FFN's normalised input
     a.W = (const bf16_t*)L[2]; a.X = (const bf16_t*)c->xn; a.N = d; a.K = H * hd;
     a.ssq = nullptr; a.NP = 0;
     a.h = c->h; a.g_next = (const float*)L[3]; a.planes_out = (bf16_t*)c->xg; a.ssq_out = c->ssq;
     HIP_TRY(c, launch_gemm_bf16(a, EPI_RESID, tag, s, &np));
+    if (const int rc = sum_ssq()) return rc;
     // gate/up + SwiGLU
     a.W = (const bf16_t*)L[4]; a.X = (const bf16_t*)c->xg; a.N = 2 * f; a.K = d;
-    a.ssq = c->ssq; a.NP = np;
+    a.ssq = ssq; a.NP = np;
     a.act_out = (bf16_t*)c->xn;
     HIP_TRY(c, launch_gemm_bf16(a, EPI_SWIGLU, tag, s));
     // down projection + residual; prepares the next layer's (or the final) normalised input
@@ -390,6 +431,7 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
     a.ssq = nullptr; a.NP = 0;
     a.g_next = (const float*)(l + 1 < m->n_layers ? W[1 + 6 * (l + 1)] : W[tail]);
     HIP_TRY(c, launch_gemm_bf16(a, EPI_RESID, tag, s, &np));
+    if (const int rc = sum_ssq()) return rc;
   }
   c->pass_np = np;
   return logits ? lm_head(c, m, rows, logits, lse, s) : MTAD_OK;
@@ -398,7 +440,7 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
 // The pass, followed by final norm + lm_head + row logsumexp when `logits` is given.
 int decoder_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStream_t s, float* logits, float* lse) {
   if (m->dtype == 1) return decoder_pass_bf16(c, m, kv, R, s, logits, lse);
-  int rc = decoder_pass_f32(c, m, kv, R, s);
+  int rc = decoder_pass_f32(c, m, kv, R, s, !logits);
   if (rc || !logits) return rc;
   return lm_head(c, m, c->cfg.batch * R, logits, lse, s);
 }
@@ -474,6 +516,7 @@ int mtad_create(mtad_ctx** out, const mtad_config* cfg, const mtad_model* target
     delete c;
     return MTAD_ESHAPE;
   }
+  if (target->dtype == 1 || draft->dtype == 1) c->prompt_rows = imax(c->cfg.prefill_rows, imin(PROMPT_PASS_ROWS / cfg->batch, cfg->max_context));
   c->flow_on = 1;
   if (const char* e = getenv("MTAD_FUSED_PASS")) c->flow_on = atoi(e) < 0 ? 0 : (atoi(e) > 2 ? 2 : atoi(e));
   carve(c, nullptr);
@@ -532,7 +575,14 @@ int mtad_prefill(mtad_ctx* c, const mtad_model* model, mtad_kv* kv, const int32_
   if (!same_shape(model, &c->tshape) && !same_shape(model, &c->dshape)) return MTAD_ESHAPE;
   if (n_tokens > kv->page_size * kv->max_pages) return MTAD_ECAP;
   hipStream_t s = (hipStream_t)stream;
-  const int R = c->cfg.prefill_rows, B = c->cfg.batch, cap = kv->page_size * kv->max_pages;
+  const int B = c->cfg.batch, cap = kv->page_size * kv->max_pages;
+  // chunks: prefill_rows rows per sequence; a bf16 model takes a longer prompt in as few and as equal chunks as the workspace
+  // allows (multiples of 64 rows), so that its weights are read once per chunk and not once per 64 tokens
+  int R = c->cfg.prefill_rows;
+  if (model->dtype == 1 && n_tokens > R && c->prompt_rows > R) {
+    const int chunks = (n_tokens + c->prompt_rows - 1) / c->prompt_rows;
+    R = imin(c->prompt_rows, ((n_tokens + chunks - 1) / chunks + 63) / 64 * 64);
+  }
   for (int c0 = 0; c0 < n_tokens; c0 += R) {
     const int r = imin(R, n_tokens - c0);
     HIP_TRY(c, launch_prefill_rows(c->rd, kv->len, tokens, n_tokens, c0, B, r, cap, c->status, s));

@@ -261,3 +261,45 @@ def test_multi_token_joint_decoding_matches(kind, K, beam, sample):
     if kind == "fp32":
         assert st["excused"] == 0 and all(len(t) == 5 * K for t in st["tokens"])
     assert sum(len(t) for t in st["tokens"]) >= 2 * K
+
+
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,n,prefill_rows", [
+    (64, 8, 2, 2, 151, 64),      # grouped queries, 16-row items that hold the end of one head and the start of the next
+    (128, 2, 2, 1, 334, 16),     # a chunk of more rows than prefill_rows, key splits
+    (64, 4, 4, 32, 150, 8),      # 32 sequences: several chunks of 64 rows each, the last one ragged
+    (128, 4, 1, 3, 66, 32),      # one more token than a row mask holds
+    (64, 2, 1, 1, 1301, 64),     # more than 1024 rows in one pass
+])
+def test_prompt_chunks_of_many_rows(hd, heads, kv_heads, batch, n, prefill_rows):
+    """Prompts longer than prefill_rows run in chunks of any number of rows with causal attention: caches and every later
+    iteration against the oracle."""
+    ts = si.ModelShape(2, heads * hd, heads, kv_heads, hd, 352, 512, "bf16")
+    ds = si.ModelShape(1, 128, 2, 1, 64, 160, 512, "bf16")
+    wt, wd = _weights(ts, 23, "target", boost=2.0), _weights(ds, 23, "draft", boost=2.0)
+    prompt = np.random.default_rng(n).integers(0, ts.vocab, (batch, n)).astype(np.int32)
+    print(f"prompt chunks hd {hd} heads {heads}/{kv_heads} batch {batch} n {n}", flush=True)
+    st = run_pair(ts, ds, wt, wd, prompt, 6, gamma=2, beam=2, mode="mtad", tau=0.0, seed=5, prefill_rows=prefill_rows, check_kv=True)
+    assert st["excused"] == 0 and all(e == 2 for e in st["eta"])
+
+
+def test_prompt_chunk_past_the_cache_end():
+    """Tokens that do not fit are not stored: the status bit is set, the length stops at the capacity, and what fits is what a
+    prompt of just those tokens leaves."""
+    from paper_2407_09722_amd import binding as mb
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    ts = si.ModelShape(2, 256, 4, 2, 64, 352, 512, "bf16")
+    m = DeviceModel(ts, _weights(ts, 29, "target", boost=2.0), DEV)
+    toks = torch.from_numpy(np.random.default_rng(3).integers(0, 512, (1, 180)).astype(np.int32)).to(DEV)
+    caches = []
+    for extra in (80, 20):                                       # 100 + 80 tokens into 120 slots; 100 + 20 fit
+        eng = Engine(m, m, batch=1, gamma=2, beam=2, mode="mtad", max_context=120, page_size=8, prefill_rows=16)
+        eng.tkv.len.zero_()
+        mb.mtad_prefill(eng.ctx, m.desc, eng.tkv.desc, toks, 100)
+        mb.mtad_prefill(eng.ctx, m.desc, eng.tkv.desc, toks[:, 100:].contiguous(), extra)
+        torch.cuda.synchronize()
+        assert int(eng.tkv.len.item()) == 120
+        assert mb.mtad_device_status(eng.ctx) == (1 if extra == 80 else 0)
+        caches.append(eng.tkv.gather(0, 120))
+        eng.close()
+    for a, b in zip(*caches):
+        assert np.all(np.abs(a - b) <= 2e-3 * np.maximum(1, np.abs(b)))   # two roundings to half precision (2^-11 each) and chunk orders
