@@ -507,23 +507,25 @@ static hipError_t run_epi(GemmArgs a, int tag, hipStream_t s) {
   return hipSuccess;
 }
 
-// Passes of many rows take both operands through LDS (kernels_gemm_dma.hip).  Measured against the kernels above at the 7B- and
-// 13B-shaped products: it wins from 65 rows up everywhere (4096 x 4096 at 64 rows: 21.1 -> 14.3 us), from 33 rows up for narrow
-// products with a long reduction, which it cuts into ranges (4096 x 11008 at 40 rows: 37.8 -> 26.7 us), and from 25 rows up for
-// products wide enough to give half of the compute units a workgroup of 8 strips (22016 x 4096 at 40 rows: 46.2 -> 38.8 us);
-// between, one of 12288 x 4096 takes 24.6 us above and 27.4 us there at 40 rows.
-static bool use_dma(const GemmArgs& a, int epi) {
+// Passes of many rows take both operands through LDS (kernels_gemm_dma.hip).  Measured against the kernels above at the shapes of
+// the 7B-, 13B- and 1B-shaped models: it wins from 65 rows up everywhere (4096 x 4096 at 64 rows: 21.1 -> 15.2 us).  From 25 rows
+// up it wins where the output gives half of the compute units a workgroup of 8 strips (22016 x 4096 at 40 rows: 46.2 -> 38.8 us)
+// or the reduction is long enough to be worth cutting (2048 x 5632 at 32 rows 15.9 -> 12.7 us, 15360 x 5120 40.2 -> 35.8 us),
+// and for narrow outputs from 40 rows up at 4096 (14.9 -> 14.5 us, at 48 rows 16.6 -> 14.6) and from 57 at any length (2560 x 2048
+// at 64 rows 16.1 -> 11.5 us); 12288 x 4096 at 40 rows takes 24.4 us above and 27.8 us there.
+static bool use_dma(const GemmArgs& a) {
   if (!a.ncg && (!a.xfrag || a.xfrag_elems < gemm_dma_xfrag_elems(a.R, a.K))) return false;  // needs fragment order or its scratch
   if (a.R >= 65) return true;
   if (a.R < 25) return false;
-  return gemm_dma_wide(a.N) || (a.R >= 33 && epi == EPI_RESID && a.part && a.K >= 4096);
+  const bool narrow = a.N / 16 <= SPLIT_MAX_STRIPS;
+  return gemm_dma_wide(a.N) || (a.part && (a.K >= 5120 || (narrow && (a.R >= 57 || (a.R >= 40 && a.K >= 4096)))));
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, int* np) {
   if (np) *np = a.N >> 4;
   if (a.R <= 0) return hipSuccess;
   if ((a.N % 16) || (a.K % 32)) return hipErrorInvalidValue;
-  if (use_dma(a, epi) && (epi != EPI_STORE || (a.ldy % 4) == 0)) return launch_gemm_bf16_dma(a, epi, s, np);
+  if (use_dma(a) && (epi != EPI_STORE || (a.ldy % 4) == 0)) return launch_gemm_bf16_dma(a, epi, s, np);
   if (a.R > 256) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_STORE: return (a.ldy % 4) ? hipErrorInvalidValue : run_epi<EPI_STORE>(a, tag, s);

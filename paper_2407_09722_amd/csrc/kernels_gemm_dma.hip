@@ -17,16 +17,22 @@
 //     that ends the reads), and every wave waits for its own share of k tile j + 1 before the barrier that ends interval j.
 //   * an activation fragment holds 8 rows, hi and lo in alternate 128-byte pieces; a B operand takes every other piece of two
 //     fragments (shifting the second one by 128 bytes, so that an LDS beat touches other banks, measured the same).
-// Measured (us per launch, the kernel before this one -> this one): 27648 x 5120 at 164 rows 122 -> 104 and at 256 rows 193 -> 133
-// (1.09 PFLOP/s, hi and lo counted), 15360 x 5120 at 164 rows 90 -> 66, 5120 x 5120 51 -> 30, 5120 x 13824 96 -> 61, 22016 x 4096
-// at 64 rows 48 -> 43.  At 256 rows of the first shape the matrix instructions alone take 88 us, the activations' way to LDS 61 and
-// the weights' 60 (24 of each are launch, epilogue and barriers), all together 133: a compute unit's loads return in the order
-// they were made, so activations that lie in L2 wait behind weights that come from HBM, and the two do not overlap.
+//   * TALL: with more rows than a workgroup takes (prompts) and for cut reductions the groups own strips of their own and both
+//     take every k tile: 256 features x 256 rows bring 48 KiB per 512 matrix instructions of a SIMD's share, against 40 KiB per
+//     256.  What counts is bytes per instruction: a compute unit has about 64 KiB of requests outstanding and its loads
+//     return in the order they were made, so activations that lie in L2 wait behind weights that come from HBM, and the fill
+//     runs at 58 bytes per ns instead of the 140 that activations alone reach.
+// Measured (us per launch on the kernel before this one -> here): 27648 x 5120 at 164 rows 122 -> 104 and at 256 rows 193 -> 133
+// (1.09 PFLOP/s, hi and lo counted), 15360 x 5120 at 164 rows 90 -> 66 uncut and 58 cut in three, 5120 x 5120 51 -> 30, 5120 x
+// 13824 96 -> 61.  At 256 rows of the first shape the matrix instructions alone take 88 us, the activations' way to LDS 61, the
+// weights' 60, launch, epilogue and barriers 24.  At 2047 rows TALL runs at 1.5 PFLOP/s while all compute units have a tile (a
+// library product of 16384^3 reaches 1.58): 22016 x 4096 622 -> 537 us, 27648 x 5120 898 -> 811, 12288 x 4096 346 -> 329.
 #include "common.h"
 #include "gemm.h"
 #include "gemm_device.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace mtad {
 
@@ -36,17 +42,18 @@ constexpr int NW = 8;                    // waves per workgroup: two groups of f
 constexpr int LDS_MOST = 160 * 1024 - 1536;  // of a compute unit, less the static arrays
 constexpr int PAIR = 2048;  // bytes of two activation fragments (16 rows)
 
-template <int A, int B>
+// A strips per wave; TALL: the groups own A strips each and both take every k tile, else both own the same A strips
+template <int A, int B, bool TALL>
 struct DmaShape {
   static constexpr int ROWS = 64 * B;                // rows per workgroup
-  static constexpr int A0 = (A + 1) / 2;             // strips group 0 finishes
-  static constexpr int FRAGS = A + 8 * B;            // KiB that one k tile brings: A weight tiles, then 8 B activation fragments
+  static constexpr int TS = TALL ? 2 * A : A;        // strips per workgroup
+  static constexpr int FRAGS = TS + 8 * B;           // KiB that one k tile brings: weight tiles, then 8 B activation fragments
   static constexpr int LPW = (FRAGS + NW - 1) / NW;  // of them per wave
-  static constexpr int SLOT = A * 1024 + 4 * B * PAIR;
+  static constexpr int SLOT = FRAGS * 1024;
   static constexpr int D0 = LDS_MOST / SLOT;
-  static constexpr int D = D0 > 16 ? 16 : D0;         // ring slots
+  static constexpr int D = D0 > 16 ? 16 : D0;        // ring slots
   static_assert(D >= 3, "one slot read, one arriving, one being requested");
-  static constexpr int RED = 4 * 64 * 16 * B * A;    // bytes the groups exchange
+  static constexpr int RED = TALL ? 0 : 4 * 64 * 16 * B * A;  // bytes the groups exchange
   static constexpr int LDS = D * SLOT > RED ? D * SLOT : RED;
   static_assert((D - 2) * LPW <= 63, "wait counter");
   static_assert(LDS + ROWS * 4 <= 160 * 1024, "a compute unit's LDS");
@@ -58,10 +65,164 @@ constexpr int wait_vm_lds(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; 
 typedef const __attribute__((address_space(1))) uint32_t* GlobalWords;
 typedef __attribute__((address_space(3))) uint32_t* LdsWords;
 
-template <int A, int B, int EPI>
+// ---- epilogues -----------------------------------------------------------------------------------------------------
+// The values are those of gemm_epilogue (gemm_device.h); what differs is who computes and how it is stored.  A wave holds, per
+// (strip, row group), features kg * 4 .. + 3 of row c in lane (kg, c), for a whole tile of strips at a time:
+//   * paired strips (rotary pairs, gate and up) hold partners 32 lanes apart.  Two strips trade halves (one row-half swap per
+//     register), after which lanes 0 .. 31 have both partners of the first strip and lanes 32 .. 63 those of the second.
+//   * 16-bit results leave as 16 bytes per lane: lanes 16 apart hold neighbouring groups of four features; a row swap of two
+//     results (hi and lo terms, or a head's first and second half) gives one lane eight features of the first and the other
+//     lane eight of the second.
+// With one item per (strip, row group) and 8-byte stores a tile's epilogue took 20 to 28 us of a workgroup's 180 at 2047 rows.
+
+__device__ __forceinline__ void swap_halves(float& a, float& b) {  // a = (a's lower lanes, b's lower lanes), b = the upper ones
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+// lanes of even rows (kg 0, 2): x of this lane, then x of the lane 16 further; of odd rows: y of the lane 16 before, then its own y
+__device__ __forceinline__ uint4 join_rows(uint2 x, uint2 y) {
+  const auto r0 = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false), r1 = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+  return make_uint4(r0[0], r1[0], r0[1], r1[1]);
+}
+__device__ __forceinline__ float sum_kg(float v) {  // over the four key groups of a row, in every lane
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// two strips' results (nt and nt + 1; the second one may not exist: have2) of B row groups; rows m[j], live[j], factor inv[j]
+template <int EPI, int B>
+struct PairEpilogue {
+  const GemmArgs& a;
+  int kg;
+  int m[B];
+  bool live[B];
+  float inv[B];
+  int64_t kv_row[B];  // EPI_QKV: element offset of the row's cache slot, -1 = not stored
+
+  __device__ __forceinline__ PairEpilogue(const GemmArgs& a_, int row0, int wr, int c, int kg_, int rows_here, const float* inv_s, bool need_kv) : a(a_), kg(kg_) {
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const int mrel = (j * 4 + wr) * 16 + c;
+      live[j] = mrel < rows_here;
+      m[j] = row0 + min(mrel, rows_here - 1);
+      inv[j] = (a.ssq && live[j]) ? inv_s[mrel] : 1.0f;
+      kv_row[j] = -1;
+    }
+    if constexpr (EPI == EPI_QKV) {
+      if (need_kv) {
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+          const int slot = a.slot[m[j]];
+          if (live[j] && slot >= 0) {
+            if (slot >= kv_capacity(a.kv)) atomicOr(a.status, (uint32_t)ST_KV_CAP);
+            else kv_row[j] = (int64_t)a.layer * a.kv.layer_stride + kv_token_offset(a.kv, m[j] / a.Rseq, slot);
+          }
+        }
+      }
+    }
+  }
+  // fragment-order address (16 bytes) of row m, features k .. k + 7 (k a multiple of 8), one plane; the pass has more than 24 rows
+  __device__ __forceinline__ bf16_t* frag(bf16_t* base, int mm, int k, int plane) const {
+    return base + ((((int64_t)(k >> 5) * a.ncg + (mm >> 3)) * 64 + ((k >> 3) & 3) * 16 + plane * 8 + (mm & 7)) << 3);
+  }
+  __device__ __forceinline__ void resid(int nt, const floatx4 (&s)[B]) const {
+    const int n = nt * 16 + kg * 4;
+    const float4 gn = *(const float4*)(a.g_next + n);
+    float4 h[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) h[j] = *(const float4*)(a.h + (int64_t)m[j] * a.N + n);
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const float4 hn = make_float4(h[j].x + s[j][0], h[j].y + s[j][1], h[j].z + s[j][2], h[j].w + s[j][3]);
+      const float x[4] = {hn.x * gn.x, hn.y * gn.y, hn.z * gn.z, hn.w * gn.w};
+      uint2 hi, lo;
+      split_bf16_x4(x, hi, lo);
+      const uint4 v = join_rows(hi, lo);
+      const float q = sum_kg(hn.x * hn.x + hn.y * hn.y + hn.z * hn.z + hn.w * hn.w);
+      if (live[j]) {
+        *(float4*)(a.h + (int64_t)m[j] * a.N + n) = hn;
+        *(uint4*)frag(a.planes_out, m[j], nt * 16 + (kg >> 1) * 8, kg & 1) = v;
+        if (kg == 0) a.ssq_out[(int64_t)m[j] * (a.N >> 4) + nt] = q;
+      }
+    }
+  }
+
+  __device__ __forceinline__ void paired(int nt, floatx4 (&s)[B], floatx4 (&s2)[B], bool have2) const {
+    const bool mine = kg < 2 || have2;
+    const int ntl = nt + (kg >> 1);  // the strip this lane now works on
+    if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        float x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float g = s[j][e], u = s2[j][e];
+          swap_halves(g, u);
+          g *= inv[j];
+          u *= inv[j];
+          x[e] = g / (1.0f + expf(-g)) * u;
+        }
+        uint2 hi, lo;
+        split_bf16_x4(x, hi, lo);
+        const uint4 v = join_rows(hi, lo);
+        if (live[j] && mine) *(uint4*)frag(a.act_out, m[j], ntl * 8, kg & 1) = v;
+      }
+    } else {  // EPI_QKV
+      typedef kv16_t half4_t __attribute__((ext_vector_type(4)));
+      const int hd = a.kv.head_dim, half = hd >> 1, tph = hd >> 4, H = a.n_heads, KVH = a.kv.n_kv_heads;
+      const int head = ntl / tph, i8 = (ntl % tph) * 8, i = i8 + (kg & 1) * 4;
+      const bool turned = mine && head < H + KVH;  // q and k heads are rotated
+      float4 cs[B][2];
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        cs[j][0] = cs[j][1] = make_float4(1.f, 0.f, 1.f, 0.f);
+        if (turned) {
+          const float4* t = (const float4*)(a.rope + (int64_t)m[j] * half + i);
+          cs[j][0] = t[0];
+          cs[j][1] = t[1];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        float x1[4], x2[4];
+        const float co[4] = {cs[j][0].x, cs[j][0].z, cs[j][1].x, cs[j][1].z}, si[4] = {cs[j][0].y, cs[j][0].w, cs[j][1].y, cs[j][1].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float p = s[j][e], r = s2[j][e];
+          swap_halves(p, r);
+          p *= inv[j];
+          r *= inv[j];
+          x1[e] = turned ? p * co[e] - r * si[e] : p;
+          x2[e] = turned ? r * co[e] + p * si[e] : r;
+        }
+        half4_t v1, v2;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v1[e] = (kv16_t)x1[e];
+          v2[e] = (kv16_t)x2[e];
+        }
+        const uint4 v = join_rows(*(uint2*)&v1, *(uint2*)&v2);
+        if (!live[j] || !mine) continue;
+        if (head < H) {
+          float* const q = a.q_out + (int64_t)m[j] * H * hd + head * hd + i;
+          *(float4*)q = make_float4(x1[0], x1[1], x1[2], x1[3]);
+          *(float4*)(q + half) = make_float4(x2[0], x2[1], x2[2], x2[3]);
+        } else if (kv_row[j] >= 0) {
+          const bool is_k = head < H + KVH;
+          const int gh = head - (is_k ? H : H + KVH);
+          *(uint4*)((kv16_t*)(is_k ? a.kv.k : a.kv.v) + kv_row[j] + gh * hd + (kg & 1) * half + i8) = v;
+        }
+      }
+    }
+  }
+};
+
+template <int A, int B, bool TALL, int EPI>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_dma_kernel(GemmArgs a, int tiles_n, int tiles_m, int KS) {
-  using Sh = DmaShape<A, B>;
-  constexpr int LPW = Sh::LPW, D = Sh::D, SLOT = Sh::SLOT;
+  using Sh = DmaShape<A, B, TALL>;
+  constexpr int LPW = Sh::LPW, D = Sh::D, SLOT = Sh::SLOT, TS = Sh::TS;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dma[];
   __shared__ float inv_s[Sh::ROWS];
 
@@ -79,11 +240,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int per_group = 4 * tiles_n, mg = l / per_group, lg = l - mg * per_group;
   const int gm = min(4, tiles_m - mg * 4);
   const int tm = mg * 4 + lg % gm, tn = lg / gm;
-  const int nt0 = tn * A, row0 = tm * Sh::ROWS;
+  const int nt0 = tn * TS, row0 = tm * Sh::ROWS;
   const int per = (KT_all + KS - 1) / KS, k_lo = ks * per;
   const int n_kt = min(KT_all, k_lo + per) - k_lo;  // the launcher leaves no range empty
 
-  // What this wave requests per k tile: fragment f = i * 8 + wave is weight tile f, or activation fragment f - A; those past
+  // What this wave requests per k tile: fragment f = i * 8 + wave is weight tile f, or activation fragment f - TS; those past
   // the last one read it again, to the same place with the same contents.  (Weights on waves of their own, requested much
   // earlier than the activations, were no faster: a compute unit's loads return in the order of their requests, so the
   // activations behind them wait for HBM all the same, and the ring holds fewer of them.)
@@ -94,28 +255,31 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
     const int f = min(i * NW + wave, Sh::FRAGS - 1);
-    if (f < A) {
+    if (f < TS) {
       src[i] = (const char*)a.W + (((size_t)min(nt0 + f, NT - 1) * KT_all + k_lo) << 10);
       step[i] = 1024;
       dst[i] = (unsigned)f * 1024u;
     } else {
-      const int x = f - A;
+      const int x = f - TS;
       src[i] = (const char*)a.X + (((size_t)k_lo * a.ncg + min(cg0 + x, cg_last)) << 10);
       step[i] = (size_t)a.ncg << 10;
-      dst[i] = (unsigned)(A * 1024 + x * 1024);
+      dst[i] = (unsigned)f * 1024u;
     }
   }
   int s_in = 0;  // ring slot of the next request, in bytes
-  auto request = [&]() {
+  auto request = [&](auto FROM, auto TO) {  // its share of a k tile, or part of it; the slot moves on with the last part
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) {
+    for (int i = FROM; i < TO; ++i) {
       __builtin_amdgcn_global_load_lds((GlobalWords)(src[i] + (unsigned)lane * 16u), (LdsWords)(lds_dma + s_in + dst[i]), 16, 0, 0);
       src[i] += step[i];
     }
-    s_in = s_in + SLOT == D * SLOT ? 0 : s_in + SLOT;
+    if constexpr (TO == LPW) s_in = s_in + SLOT == D * SLOT ? 0 : s_in + SLOT;
   };
+  constexpr std::integral_constant<int, 0> NONE{};
+  constexpr std::integral_constant<int, LPW / 2> HALF{};
+  constexpr std::integral_constant<int, LPW> ALL{};
   constexpr int ahead = D - 1;
-  for (int j = 0; j < ahead && j < n_kt; ++j) request();
+  for (int j = 0; j < ahead && j < n_kt; ++j) request(NONE, ALL);
   {
     GemmArgs ar = a;
     ar.row0 = row0;
@@ -128,10 +292,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int j = 0; j < B; ++j) acc[si][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   // lane (kg, row) of a B operand: fragment row / 8 of the pair, piece (kg, plane), row % 8
-  const unsigned w_off = (unsigned)lane * 16u;
-  const unsigned x_off = (unsigned)(A * 1024 + wr * PAIR + (c >> 3) * 1024 + (kg * 16 + (c & 7)) * 16);
+  const unsigned w_off = (unsigned)((TALL ? grp * A * 1024 : 0) + lane * 16);
+  const unsigned x_off = (unsigned)(TS * 1024 + wr * PAIR + (c >> 3) * 1024 + (kg * 16 + (c & 7)) * 16);
   Frag fw[A], fx[B][2];
-  int s_out = grp * SLOT;  // ring slot of this group's next k tile
+  constexpr int STRIDE = TALL ? SLOT : 2 * SLOT;
+  int s_out = TALL ? 0 : grp * SLOT;  // ring slot of this group's next k tile
   auto fetch = [&]() {
     const unsigned char *const wp = lds_dma + s_out + w_off, *const xp = lds_dma + s_out + x_off;
 #pragma unroll
@@ -141,7 +306,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       fx[j][0].n = *(const uintx4*)(xp + j * (4 * PAIR));
       fx[j][1].n = *(const uintx4*)(xp + j * (4 * PAIR) + 128);
     }
-    s_out += 2 * SLOT;
+    s_out += STRIDE;
     if (s_out >= D * SLOT) s_out -= D * SLOT;
   };
   // An interval ends: this wave's requests for the next k tile have arrived (all but its requests for later ones, or all
@@ -157,92 +322,143 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  interval_end(n_kt >= ahead);  // k tile 0 is there (and the row factors)
-  int i = 0;  // interval: k tile i + ahead is requested in it
-  if (grp == 1) {
-    const bool more = i + ahead < n_kt;
-    if (more) request();
-    interval_end(more);
-    ++i;
-  }
-  const int trips = (n_kt + 1) >> 1;
-#pragma unroll 1
-  for (int t = 0; t < trips; ++t) {
-    // memory interval: fragments of this group's k tile
-    {
-      const bool more = i + ahead < n_kt;
-      fetch();
-      if (more) request();
-      interval_end(more);
-      ++i;
-    }
-    // compute interval
-    {
-      const bool more = i + ahead < n_kt;
-      if (more) request();
-      __builtin_amdgcn_sched_barrier(0);
-      if (grp == 0 || 2 * t + 1 < n_kt) {
+  auto barrier = [&]() {  // an interval after which nothing new has to have arrived
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(wait_vm_lds(63));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&]() {
 #pragma unroll
-        for (int j = 0; j < B; ++j)
+    for (int j = 0; j < B; ++j)
 #pragma unroll
-          for (int p = 0; p < 2; ++p)
+      for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int si = 0; si < A; ++si) acc[si][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[si].v, fx[j][p].v, acc[si][j], 0, 0, 0);
-      }
-      interval_end(more);
-      ++i;
-    }
-  }
-  if (grp == 0) interval_end(false);
+        for (int si = 0; si < A; ++si) acc[si][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[si].v, fx[j][p].v, acc[si][j], 0, 0, 0);
+  };
 
-  // the groups' sums meet in LDS: group 0 finishes strips 0 .. A0 - 1, group 1 the others
-  constexpr int A0 = Sh::A0;
-  floatx4* const red = reinterpret_cast<floatx4*>(lds_dma);  // [4 waves][A][B][64]
-#pragma unroll
-  for (int si = 0; si < A; ++si)
-    if ((si < A0) == (grp == 1)) {
-#pragma unroll
-      for (int j = 0; j < B; ++j) red[((wr * A + si) * B + j) * 64 + lane] = acc[si][j];
+  interval_end(n_kt >= ahead);  // k tile 0 is there (and the row factors)
+  if constexpr (!TALL) {
+    int i = 0;  // interval: k tile i + ahead is requested in it
+    if (grp == 1) {
+      const bool more = i + ahead < n_kt;
+      if (more) request(NONE, ALL);
+      interval_end(more);
+      ++i;
     }
-  __syncthreads();
-  const int rows_here = min(Sh::ROWS, a.R - row0);
-#pragma unroll
-  for (int si = 0; si < A; ++si)
-    if ((si < A0) == (grp == 0) && nt0 + si < NT) {
-      const int nt = nt0 + si;
-      floatx4 s[B];
-#pragma unroll
-      for (int j = 0; j < B; ++j) {
-        const floatx4 o = red[((wr * A + si) * B + j) * 64 + lane];
-        // even k tiles first, whichever group adds
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[j][e] = acc[si][j][e] + o[e];
+    const int trips = (n_kt + 1) >> 1;
+#pragma unroll 1
+    for (int t = 0; t < trips; ++t) {
+      {  // memory interval: fragments of this group's k tile
+        const bool more = i + ahead < n_kt;
+        fetch();
+        if (more) request(NONE, ALL);
+        interval_end(more);
+        ++i;
       }
-      if (KS > 1) {  // the launch after this one adds the ranges: part[range][row][feature]
+      {  // compute interval
+        const bool more = i + ahead < n_kt;
+        if (more) request(NONE, ALL);
+        __builtin_amdgcn_sched_barrier(0);
+        if (grp == 0 || 2 * t + 1 < n_kt) multiply();
+        interval_end(more);
+        ++i;
+      }
+    }
+    if (grp == 0) interval_end(false);
+  } else {
+    // two intervals per k tile: group 0 reads k tile j in interval 2j and multiplies in 2j + 1, group 1 one interval later; k tile
+    // j + ahead goes out in halves in the same two intervals (its slot was last read in interval 2j - 1), and k tile j + 1 has
+    // arrived at the end of 2j + 1
+    if (grp == 0) {
+#pragma unroll 1
+      for (int j = 0; j < n_kt; ++j) {
+        const bool more = j + ahead < n_kt;
+        fetch();
+        if (more) request(NONE, HALF);
+        barrier();
+        if (more) request(HALF, ALL);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply();
+        interval_end(more);
+      }
+      barrier();
+    } else {
+      if (ahead < n_kt) request(NONE, HALF);
+      barrier();
+#pragma unroll 1
+      for (int j = 0; j < n_kt; ++j) {
+        const bool more = j + ahead < n_kt;
+        fetch();
+        if (more) request(HALF, ALL);
+        interval_end(more);
+        if (j + 1 + ahead < n_kt) request(NONE, HALF);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply();
+        barrier();
+      }
+    }
+  }
+
+  // not TALL: the groups' sums meet in LDS; group 0 finishes the first half of the pairs of strips, group 1 the others
+  constexpr int PAIRS = (A + 1) / 2, PH = (PAIRS + 1) / 2;
+  floatx4* const red = reinterpret_cast<floatx4*>(lds_dma);  // [4 waves][A][B][64]
+  auto owns = [&](int p) { return TALL || (p < PH) == (grp == 0); };
+  if constexpr (!TALL) {
+#pragma unroll
+    for (int si = 0; si < A; ++si)
+      if (!owns(si >> 1)) {
+#pragma unroll
+        for (int j = 0; j < B; ++j) red[((wr * A + si) * B + j) * 64 + lane] = acc[si][j];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int si = 0; si < A; ++si)
+      if (owns(si >> 1)) {
 #pragma unroll
         for (int j = 0; j < B; ++j) {
-          const int mrel = (j * 4 + wr) * 16 + c;
-          if (mrel < rows_here) *(floatx4*)(a.part + ((size_t)ks * a.R + row0 + mrel) * a.N + nt * 16 + kg * 4) = s[j];
-        }
-      } else {
-        float4 ph[B], pg = float4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (EPI == EPI_RESID) {  // the residual values of all row groups first: one latency, not B
-          pg = *(const float4*)(a.g_next + nt * 16 + kg * 4);
+          const floatx4 o = red[((wr * A + si) * B + j) * 64 + lane];
 #pragma unroll
-          for (int j = 0; j < B; ++j) {
-            const int mrel = min((j * 4 + wr) * 16 + c, rows_here - 1);
-            ph[j] = *(const float4*)(a.h + (int64_t)(row0 + mrel) * a.N + nt * 16 + kg * 4);
+          for (int e = 0; e < 4; ++e) acc[si][j][e] += o[e];
+        }
+      }
+  }
+  const int rows_here = min(Sh::ROWS, a.R - row0);
+  const int nt_wave = nt0 + (TALL ? grp * A : 0);
+  const bool need_kv = EPI == EPI_QKV && KS == 1 && (nt_wave + A) * 16 > a.n_heads * a.kv.head_dim;
+  const PairEpilogue<EPI, B> fin(a, row0, wr, c, kg, rows_here, inv_s, need_kv);
+#pragma unroll
+  for (int p = 0; p < PAIRS; ++p) {
+    constexpr int LAST = A - 1;
+    const int nt = nt_wave + 2 * p;
+    if (!owns(p) || nt >= NT) continue;
+    const bool have2 = 2 * p + 1 < A && nt + 1 < NT;
+    if (KS > 1) {  // the launch after this one adds the ranges: part[range][row][packed feature]
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+        if (o == 0 || have2) {
+#pragma unroll
+          for (int j = 0; j < B; ++j)
+            if (fin.live[j]) *(floatx4*)(a.part + ((size_t)ks * a.R + fin.m[j]) * a.N + (nt + o) * 16 + kg * 4) = acc[2 * p + o < A ? 2 * p + o : LAST][j];
+        }
+    } else if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
+      fin.paired(nt, acc[2 * p], acc[2 * p + 1 < A ? 2 * p + 1 : LAST], have2);
+    } else {
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+        if (o == 0 || have2) {
+          floatx4 (&s)[B] = acc[2 * p + o < A ? 2 * p + o : LAST];
+          if constexpr (EPI == EPI_RESID) {
+            fin.resid(nt + o, s);
+          } else {
+#pragma unroll
+            for (int j = 0; j < B; ++j) gemm_epilogue<EPI>(a, nt + o, s[j], fin.m[j], fin.live[j], fin.inv[j], kg);
           }
         }
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-          const int mrel = (j * 4 + wr) * 16 + c;
-          const bool live = mrel < rows_here;
-          const float inv = (a.ssq && live) ? inv_s[mrel] : 1.0f;
-          gemm_epilogue<EPI, false, EPI == EPI_RESID>(a, nt, s[j], row0 + mrel, live, inv, kg, ph[j], pg);
-        }
-      }
     }
+  }
 }
 
 // After a product whose reduction dimension was cut into KS ranges: one workgroup per row adds the ranges in order.
@@ -276,13 +492,11 @@ __global__ __launch_bounds__(RT) void gemm_rows_kernel(GemmArgs a) {
       const float4 o = *hp, gn = *(const float4*)(a.g_next + n);
       s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
       *hp = s;
-      ushort4 hi, lo;
-      split_bf16(s.x * gn.x, hi.x, lo.x);
-      split_bf16(s.y * gn.y, hi.y, lo.y);
-      split_bf16(s.z * gn.z, hi.z, lo.z);
-      split_bf16(s.w * gn.w, hi.w, lo.w);
-      *(ushort4*)(a.planes_out + act_offset(a.ncg, a.R, N, 0, m, n)) = hi;
-      *(ushort4*)(a.planes_out + act_offset(a.ncg, a.R, N, 1, m, n)) = lo;
+      const float x[4] = {s.x * gn.x, s.y * gn.y, s.z * gn.z, s.w * gn.w};
+      uint2 hi, lo;
+      split_bf16_x4(x, hi, lo);
+      *(uint2*)(a.planes_out + act_offset(a.ncg, a.R, N, 0, m, n)) = hi;
+      *(uint2*)(a.planes_out + act_offset(a.ncg, a.R, N, 1, m, n)) = lo;
       q += s.x * s.x + s.y * s.y + s.z * s.z + s.w * s.w;
     }
   }
@@ -293,6 +507,82 @@ __global__ __launch_bounds__(RT) void gemm_rows_kernel(GemmArgs a) {
     if (threadIdx.x == 0) {
       for (int w = 1; w < RT / 64; ++w) q += sh[w];
       a.ssq_out[m] = q;
+    }
+  }
+}
+
+// The same for products whose strips hold partners 8 features apart (rotary pairs, gate and up): one thread per (row, strip,
+// four pairs), grid (quads of the row, rows).
+template <int KS, int EPI>
+__global__ __launch_bounds__(256) void gemm_pairs_kernel(GemmArgs a) {
+  const int m = blockIdx.y, lane = threadIdx.x & 63, NT = a.N >> 4;
+  float inv = 1.0f;
+  if (a.ssq) {
+    float s = 0.f;
+    for (int p = lane; p < a.NP; p += 64) s += a.ssq[(int64_t)m * a.NP + p];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    inv = 1.0f / sqrtf(s / (float)a.K + a.eps);
+  }
+  const int item = blockIdx.x * 256 + threadIdx.x, nt = item >> 1, i0 = (item & 1) * 4;
+  if (nt >= NT) return;
+  const float* const p = a.part + (size_t)m * a.N + nt * 16 + i0;
+  const size_t range = (size_t)a.R * a.N;
+  float4 t1[KS], t2[KS];
+#pragma unroll
+  for (int k = 0; k < KS; ++k) {
+    t1[k] = *(const float4*)(p + k * range);
+    t2[k] = *(const float4*)(p + k * range + 8);
+  }
+  float4 s1 = t1[0], s2 = t2[0];
+#pragma unroll
+  for (int k = 1; k < KS; ++k) {
+    s1.x += t1[k].x; s1.y += t1[k].y; s1.z += t1[k].z; s1.w += t1[k].w;
+    s2.x += t2[k].x; s2.y += t2[k].y; s2.z += t2[k].z; s2.w += t2[k].w;
+  }
+  float x1[4] = {s1.x * inv, s1.y * inv, s1.z * inv, s1.w * inv}, x2[4] = {s2.x * inv, s2.y * inv, s2.z * inv, s2.w * inv};
+  if constexpr (EPI == EPI_SWIGLU) {
+    float x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = x1[e] / (1.0f + expf(-x1[e])) * x2[e];
+    uint2 hi, lo;
+    split_bf16_x4(x, hi, lo);
+    *(uint2*)(a.act_out + act_offset(a.ncg, a.R, a.N >> 1, 0, m, nt * 8 + i0)) = hi;
+    *(uint2*)(a.act_out + act_offset(a.ncg, a.R, a.N >> 1, 1, m, nt * 8 + i0)) = lo;
+  } else {
+    const int hd = a.kv.head_dim, half = hd >> 1, tph = hd >> 4, H = a.n_heads, KVH = a.kv.n_kv_heads;
+    const int head = nt / tph, i = (nt % tph) * 8 + i0;
+    if (head < H + KVH) {  // q and k heads are rotated
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float2 cs = a.rope[(int64_t)m * half + i + e];
+        const float y1 = x1[e] * cs.x - x2[e] * cs.y, y2 = x2[e] * cs.x + x1[e] * cs.y;
+        x1[e] = y1;
+        x2[e] = y2;
+      }
+    }
+    if (head < H) {
+      float* const q = a.q_out + (int64_t)m * H * hd + head * hd + i;
+      *(float4*)q = make_float4(x1[0], x1[1], x1[2], x1[3]);
+      *(float4*)(q + half) = make_float4(x2[0], x2[1], x2[2], x2[3]);
+    } else {
+      const int slot = a.slot[m];
+      if (slot < 0) return;
+      if (slot >= kv_capacity(a.kv)) {
+        atomicOr(a.status, (uint32_t)ST_KV_CAP);
+        return;
+      }
+      typedef kv16_t half4_t __attribute__((ext_vector_type(4)));
+      half4_t v1, v2;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v1[e] = (kv16_t)x1[e];
+        v2[e] = (kv16_t)x2[e];
+      }
+      const bool is_k = head < H + KVH;
+      kv16_t* const dst = (kv16_t*)(is_k ? a.kv.k : a.kv.v) + (int64_t)a.layer * a.kv.layer_stride + kv_token_offset(a.kv, m / a.Rseq, slot) +
+                          (head - (is_k ? H : H + KVH)) * hd + i;
+      *(uint2*)dst = *(uint2*)&v1;
+      *(uint2*)(dst + half) = *(uint2*)&v2;
     }
   }
 }
@@ -332,45 +622,54 @@ int device_cus() {
 
 struct Plan {
   int A, B, KS, tiles_n, tiles_m;
+  bool tall;
 };
 constexpr int KS_MAX = 8;
 
-// Rows per workgroup: row tiles of at most 256 rows, as equal as steps of 64 allow.  Strips per workgroup (4 to 8) and ranges of
-// the reduction dimension: the cheapest by a count of clocks per compute unit.  An interval (one k tile) lasts as long as its
-// matrix instructions, its LDS traffic or its weights from HBM (about 10 bytes per clock and compute unit), plus the barrier.
-// A cut costs its partial sums' way through memory and a launch.
+// Rows per workgroup (64 to 256), strips per workgroup (4 to 8, or 10 to 16 with the groups side by side where 129 rows and more
+// meet) and ranges of the reduction dimension: the cheapest by a count of clocks per compute unit.  A k tile lasts as long as its
+// matrix instructions, its LDS traffic, its way to LDS (about 25 bytes per clock where weights from HBM and activations from L2
+// alternate) or its weights from HBM (10 bytes per clock and compute unit), plus the barriers.  A cut costs its partial
+// sums' way through memory and a launch.
 Plan plan_for(const GemmArgs& a, int epi) {
   Plan best{};
   const int NT = a.N >> 4, KT = a.K >> 5, cus = device_cus();
-  const int tm = (a.R + 255) / 256, B = ((a.R + tm - 1) / tm + 63) / 64;
+  const bool can_cut = a.part && !(epi == EPI_STORE && (a.lse_part || a.ssq));
   double best_cost = 0;
-  for (int A = 8; A >= 4; --A) {
-    const int tn = (NT + A - 1) / A;
-    const int mfma = 32 * A * B, lds = 32 * (A + 2 * B) + 8 * (A + 8 * B), hbm = 98 * A;
-    const int interval = (mfma > lds ? (mfma > hbm ? mfma : hbm) : (lds > hbm ? lds : hbm)) + 100;
-    for (int KS = 1; KS <= KS_MAX; ++KS) {
-      const int total = tn * tm * KS;
-      if (KS > 1) {
-        if (!a.part || (epi != EPI_RESID && !(epi == EPI_STORE && !a.lse_part && !a.ssq))) break;
-        if (total > cus || KT < 16 * KS || (size_t)KS * a.R * a.N > a.part_floats) break;
-        if (((KT + KS - 1) / KS) * (KS - 1) >= KT) continue;  // a range would be empty
-      }
-      const int rounds = (total + cus - 1) / cus;
-      double cost = (double)rounds * (((KT + KS - 1) / KS) * (double)interval + 8000);
-      if (KS > 1) cost += 6000 + (double)(2 * KS) * a.R * a.N * 4 / 2000;
-      if (best.A == 0 || cost < best_cost) {
-        best_cost = cost;
-        best = Plan{A, B, KS, tn, tm};
+  for (int B = 4; B >= 1; --B) {
+    const int tm = (a.R + 64 * B - 1) / (64 * B);
+    if (B > 1 && (a.R + 64 * (B - 1) - 1) / (64 * (B - 1)) == tm) continue;  // as many tiles of fewer rows
+    for (int TS : {16, 14, 12, 10, 8, 7, 6, 5, 4}) {
+      const bool tall = TS > 8;
+      if (tall && B < 3) continue;
+      const int tn = (NT + TS - 1) / TS, frags = TS + 8 * B;
+      const int mfma = 32 * TS * B, lds = 32 * (tall ? TS + 4 * B : TS + 2 * B) + 8 * frags, fill = 40 * frags, hbm = 98 * TS / tm;
+      int interval = mfma;
+      for (int x : {lds, fill, hbm}) interval = x > interval ? x : interval;
+      interval += tall ? 250 : 100;
+      for (int KS = 1; KS <= KS_MAX; ++KS) {
+        const int total = tn * tm * KS;
+        if (KS > 1) {
+          if (!can_cut || total > cus || KT < 16 * KS || (size_t)KS * a.R * a.N > a.part_floats) break;
+          if (((KT + KS - 1) / KS) * (KS - 1) >= KT) continue;  // a range would be empty
+        }
+        const int rounds = (total + cus - 1) / cus;
+        double cost = (double)rounds * (((KT + KS - 1) / KS) * (double)interval + 8000);
+        if (KS > 1) cost = 1.08 * (cost + 6000 + (double)(2 * KS) * a.R * a.N * 4 / 2000);  // worth it when clearly better
+        if (best.A == 0 || cost < best_cost) {
+          best_cost = cost;
+          best = Plan{tall ? TS / 2 : TS, B, KS, tn, tm, tall};
+        }
       }
     }
   }
   return best;
 }
 
-template <int A, int B, int EPI>
+template <int A, int B, bool TALL, int EPI>
 hipError_t run_shape(const GemmArgs& a, const Plan& p, hipStream_t s) {
-  using Sh = DmaShape<A, B>;
-  auto kern = gemm_bf16_dma_kernel<A, B, EPI>;
+  using Sh = DmaShape<A, B, TALL>;
+  auto kern = gemm_bf16_dma_kernel<A, B, TALL, EPI>;
   // more than 64 KiB of dynamic LDS needs the attribute; a success is remembered, a failure is reported and tried again
   static std::atomic<bool> attr_set{false};
   if (!attr_set.load(std::memory_order_acquire)) {
@@ -385,28 +684,39 @@ hipError_t run_shape(const GemmArgs& a, const Plan& p, hipStream_t s) {
 template <int A, int EPI>
 hipError_t run_rows(const GemmArgs& a, const Plan& p, hipStream_t s) {
   switch (p.B) {
-    case 1: return run_shape<A, 1, EPI>(a, p, s);
-    case 2: return run_shape<A, 2, EPI>(a, p, s);
-    case 3: return run_shape<A, 3, EPI>(a, p, s);
-    case 4: return run_shape<A, 4, EPI>(a, p, s);
+    case 1: return run_shape<A, 1, false, EPI>(a, p, s);
+    case 2: return run_shape<A, 2, false, EPI>(a, p, s);
+    case 3: return run_shape<A, 3, false, EPI>(a, p, s);
+    case 4: return run_shape<A, 4, false, EPI>(a, p, s);
   }
   return hipErrorInvalidValue;
 }
 
+template <int A, int EPI>
+hipError_t run_tall(const GemmArgs& a, const Plan& p, hipStream_t s) {
+  return p.B == 4 ? run_shape<A, 4, true, EPI>(a, p, s) : run_shape<A, 3, true, EPI>(a, p, s);
+}
+
+template <int KS, int EPI>
+hipError_t run_sum_ks(const GemmArgs& a, hipStream_t s) {
+  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV)
+    hipLaunchKernelGGL((gemm_pairs_kernel<KS, EPI>), dim3((unsigned)((a.N / 8 + 255) / 256), (unsigned)a.R), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_rows_kernel<KS, EPI>), dim3((unsigned)a.R), dim3(RT), 0, s, a);
+  return hipGetLastError();
+}
 template <int EPI>
 hipError_t run_sum(const GemmArgs& a, int KS, hipStream_t s) {
-  const dim3 grid((unsigned)a.R), block(RT);
   switch (KS) {
-    case 2: hipLaunchKernelGGL((gemm_rows_kernel<2, EPI>), grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((gemm_rows_kernel<3, EPI>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((gemm_rows_kernel<4, EPI>), grid, block, 0, s, a); break;
-    case 5: hipLaunchKernelGGL((gemm_rows_kernel<5, EPI>), grid, block, 0, s, a); break;
-    case 6: hipLaunchKernelGGL((gemm_rows_kernel<6, EPI>), grid, block, 0, s, a); break;
-    case 7: hipLaunchKernelGGL((gemm_rows_kernel<7, EPI>), grid, block, 0, s, a); break;
-    case 8: hipLaunchKernelGGL((gemm_rows_kernel<8, EPI>), grid, block, 0, s, a); break;
-    default: return hipErrorInvalidValue;
+    case 2: return run_sum_ks<2, EPI>(a, s);
+    case 3: return run_sum_ks<3, EPI>(a, s);
+    case 4: return run_sum_ks<4, EPI>(a, s);
+    case 5: return run_sum_ks<5, EPI>(a, s);
+    case 6: return run_sum_ks<6, EPI>(a, s);
+    case 7: return run_sum_ks<7, EPI>(a, s);
+    case 8: return run_sum_ks<8, EPI>(a, s);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 template <int EPI>
@@ -422,7 +732,13 @@ hipError_t run_dma(GemmArgs a, hipStream_t s, int* np) {
   }
   const Plan p = plan_for(a, EPI);
   hipError_t e = hipErrorInvalidValue;
-  switch (p.A) {
+  if (p.tall) switch (p.A) {
+    case 5: e = run_tall<5, EPI>(a, p, s); break;
+    case 6: e = run_tall<6, EPI>(a, p, s); break;
+    case 7: e = run_tall<7, EPI>(a, p, s); break;
+    case 8: e = run_tall<8, EPI>(a, p, s); break;
+  }
+  else switch (p.A) {
     case 4: e = run_rows<4, EPI>(a, p, s); break;
     case 5: e = run_rows<5, EPI>(a, p, s); break;
     case 6: e = run_rows<6, EPI>(a, p, s); break;
@@ -430,9 +746,7 @@ hipError_t run_dma(GemmArgs a, hipStream_t s, int* np) {
     case 8: e = run_rows<8, EPI>(a, p, s); break;
   }
   if (e != hipSuccess) return e;
-  if constexpr (EPI == EPI_RESID || EPI == EPI_STORE) {
-    if (p.KS > 1) e = run_sum<EPI>(a, p.KS, s);
-  }
+  if (p.KS > 1) e = run_sum<EPI>(a, p.KS, s);
   if (np) *np = p.KS > 1 ? 1 : a.N >> 4;
   return e;
 }
@@ -441,8 +755,8 @@ hipError_t run_dma(GemmArgs a, hipStream_t s, int* np) {
 
 size_t gemm_dma_xfrag_elems(int R, int K) { return (size_t)(K >> 5) * ((R + 7) / 8) * 512; }
 
-// floats of workspace the ranges of a cut reduction may take: at most one workgroup per compute unit, 256 rows x 8 strips each
-size_t gemm_dma_split_floats() { return (size_t)device_cus() * 256 * 128; }
+// floats of workspace the ranges of a cut reduction may take: at most one workgroup per compute unit, 256 rows x 16 strips each
+size_t gemm_dma_split_floats() { return (size_t)device_cus() * 256 * 256; }
 
 hipError_t launch_ssq_rows(const float* in, float* out, int R, int NP, hipStream_t s) {
   hipLaunchKernelGGL(ssq_rows_kernel, dim3((unsigned)((R + 3) / 4)), dim3(256), 0, s, in, out, R, NP);

@@ -126,7 +126,8 @@ def test_gemm_bf16_fragment_order_input(R, N, K):
 
 
 @pytest.mark.parametrize("R,N,K", [(65, 16, 32), (128, 80, 64), (129, 96, 96), (192, 112, 288), (193, 1040, 544), (255, 4112, 1056), (256, 2064, 4096),
-                                   (65, 5120, 4096), (130, 2080, 8192), (200, 11264, 512), (250, 15360, 160), (164, 27648, 64)])
+                                   (65, 5120, 4096), (130, 2080, 8192), (200, 11264, 512), (250, 15360, 160), (164, 27648, 64),
+                                   (222, 1664, 5728), (164, 12288, 4096), (250, 15360, 5120), (25, 15360, 5120), (58, 2576, 2048)])
 def test_gemm_bf16_many_rows(R, N, K):
     """The many-row kernel at the edges of its tiles: 64, 128, 192 and 256 rows and one more or less, every count of strips per
     workgroup with strips left over, one to many k tiles (fewer than the ring holds, odd counts), reductions cut into ranges;
