@@ -53,6 +53,89 @@ __host__ __device__ __forceinline__ int64_t act_offset(int ncg, int R, int K, in
   return ((((int64_t)(k >> 5) * ncg + (row >> 3)) * 64 + ((k >> 3) & 3) * 16 + plane * 8 + (row & 7)) << 3) + (k & 7);
 }
 
+// Exchanges between lanes in the vector ALU (swaps of rows of 16 lanes and of halves, rotations inside a row): about a dozen
+// clocks each, where a shuffle goes through LDS and takes over a hundred.
+template <int N>  // the value N lanes before, around a row of 16 lanes (8: the lane 8 away)
+__device__ __forceinline__ float row_turn(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_xor16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);  // even rows; odd rows
+  return __uint_as_float(((threadIdx.x >> 4) & 1) ? r[0] : r[1]);
+}
+__device__ __forceinline__ float lane_xor32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);  // lower half; upper half
+  return __uint_as_float(((threadIdx.x >> 5) & 1) ? r[0] : r[1]);
+}
+// sum and maximum over the wave, in every lane: the pairs of a butterfly over lane distances 32, 16, 8, 4, 2, 1 (from distance
+// 4 on the values repeat with that period, so that a rotation brings the partner's)
+__device__ __forceinline__ float wave_sum(float v) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  v += row_turn<8>(v);
+  v += row_turn<4>(v);
+  v += row_turn<2>(v);
+  v += row_turn<1>(v);
+  return v;
+}
+__device__ __forceinline__ float wave_max(float v) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  v = fmaxf(v, row_turn<8>(v));
+  v = fmaxf(v, row_turn<4>(v));
+  v = fmaxf(v, row_turn<2>(v));
+  v = fmaxf(v, row_turn<1>(v));
+  return v;
+}
+// over a workgroup of at most 16 waves, in every thread (waves added in order); sh: one float per wave, free again after the next barrier
+__device__ __forceinline__ float block_sum(float v, float* sh) {
+  v = wave_sum(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float t = sh[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t += sh[w];
+  return t;
+}
+__device__ __forceinline__ float block_max(float v, float* sh) {
+  v = wave_max(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float t = sh[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t = fmaxf(t, sh[w]);
+  return t;
+}
+// log sum exp of a logits row from the (max, sum exp) partials of its NP strips, by a workgroup of 256 threads.  Rows of up to
+// 32768 logits are held in registers between the two reductions, their loads in flight together.
+__device__ __forceinline__ float lse_of_row(const float2* __restrict__ p, int NP, float* sh) {
+  constexpr int U = 8;
+  const int t = threadIdx.x;
+  float m = -INFINITY, sum = 0.f;
+  if (NP <= 256 * U) {
+    float2 v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) v[j] = p[min(t + 256 * j, NP - 1)];
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (t + 256 * j < NP) m = fmaxf(m, v[j].x);
+    m = block_max(m, sh);
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (t + 256 * j < NP) sum += v[j].y * expf(v[j].x - m);
+  } else {
+    for (int i = t; i < NP; i += 256) m = fmaxf(m, p[i].x);
+    m = block_max(m, sh);
+    for (int i = t; i < NP; i += 256) sum += p[i].y * expf(p[i].x - m);
+  }
+  sum = block_sum(sum, sh);
+  return m + logf(sum);
+}
+
 // Device-scope ("coherent") accesses for data that workgroups of ONE kernel hand to each other.  The XCDs' L2
 // caches are not coherent with each other; relaxed device-scope atomics compile to write-through stores and
 // cache-bypassing loads, which avoids flushing or invalidating whole caches.  COH = false: plain accesses (data

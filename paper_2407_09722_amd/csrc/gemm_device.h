@@ -95,8 +95,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int nt, floatx4
       if (a.lse_part) {  // (max, sum exp) over this strip's 16 features of row m, merged over the four lane groups
         float mx = fmaxf(fmaxf(o.x, o.y), fmaxf(o.z, o.w));
         float sm = expf(o.x - mx) + expf(o.y - mx) + expf(o.z - mx) + expf(o.w - mx);
+#pragma unroll
         for (int off = 16; off <= 32; off <<= 1) {
-          const float omx = __shfl_xor(mx, off, 64), osm = __shfl_xor(sm, off, 64);
+          const float omx = off == 16 ? lane_xor16(mx) : lane_xor32(mx), osm = off == 16 ? lane_xor16(sm) : lane_xor32(sm);
           const float nm = fmaxf(mx, omx);
           sm = sm * expf(mx - nm) + osm * expf(omx - nm);
           mx = nm;
@@ -134,14 +135,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int nt, floatx4
         st8<COH>(a.planes_out + act_offset(a.ncg, R, a.N, 1, m, n), *(uint2*)&lo);
       }
       float q = hn.x * hn.x + hn.y * hn.y + hn.z * hn.z + hn.w * hn.w;
-      q += __shfl_xor(q, 16, 64);
-      q += __shfl_xor(q, 32, 64);
+      q += lane_xor16(q);
+      q += lane_xor32(q);
       if (live && kg == 0) st4<COH>(a.ssq_out + (int64_t)m * NT + nt, q);
     } else {
       // paired strips: packed features 0..7 (kg 0, 1) and their partners 8..15 (kg 2, 3 = lane + 32)
       floatx4 t;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) t[i] = __shfl_xor(s[i], 32, 64);
+      for (int i = 0; i < 4; ++i) t[i] = lane_xor32(s[i]);
       if (kg < 2 && live) {
         const int i0 = kg * 4;  // 0 or 4 within the strip's 8 pairs
         if constexpr (EPI == EPI_SWIGLU) {
@@ -234,7 +235,7 @@ __device__ __forceinline__ void gemm_finish_sum(const GemmArgs& a, int nt, int g
                                                 float4 pre_h = float4{0.f, 0.f, 0.f, 0.f}, float4 pre_gn = float4{0.f, 0.f, 0.f, 0.f}) {
   const int c = lane & 15, kg = lane >> 4;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) s[i] += __shfl_xor(s[i], 8, 64);  // columns c and c + 8 are the hi and lo terms of one row
+  for (int i = 0; i < 4; ++i) s[i] += row_turn<8>(s[i]);  // columns c and c + 8 are the hi and lo terms of one row
   const int mrel = g * 8 + (c & 7);
   const bool live = c < 8 && mrel < rows_here;
   const float inv = (a.ssq && live) ? inv_s[mrel] : 1.0f;
@@ -249,7 +250,7 @@ __device__ __forceinline__ void gemm_finish_group(const GemmArgs& a, int nt, int
   const int c = lane & 15, kg = lane >> 4;
   floatx4 s = gemm_sum_waves<NG, NWAVES>(g, red, lane);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) s[i] += __shfl_xor(s[i], 8, 64);  // columns c and c + 8 are the hi and lo terms of one row
+  for (int i = 0; i < 4; ++i) s[i] += row_turn<8>(s[i]);  // columns c and c + 8 are the hi and lo terms of one row
   const int mrel = g * 8 + (c & 7);
   const bool live = c < 8 && mrel < rows_here;
   const float inv = (a.ssq && live) ? inv_s[mrel] : 1.0f;
@@ -268,7 +269,7 @@ __device__ __forceinline__ void gemm_row_factors(const GemmArgs& a, float* inv_s
     for (int m = wave; m < rows_here; m += n_waves) {
       float s = 0.f;
       for (int p = lane; p < a.NP; p += 64) s += ld4<COH>(a.ssq + (int64_t)(a.row0 + m) * a.NP + p);
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+      s = wave_sum(s);
       if (lane == 0) inv_s[m] = 1.0f / sqrtf(s / (float)a.K + a.eps);
     }
     return;
@@ -289,7 +290,7 @@ __device__ __forceinline__ void gemm_row_factors(const GemmArgs& a, float* inv_s
 #pragma unroll
       for (int i = 0; i < NPI; ++i)
         if (i < npi && lane + 64 * i < a.NP) s += v[r][i];
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+      s = wave_sum(s);
       const int m = m0 + r * n_waves;
       if (lane == 0 && m < rows_here) inv_s[m] = 1.0f / sqrtf(s / (float)a.K + a.eps);
     }

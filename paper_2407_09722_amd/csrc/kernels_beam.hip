@@ -196,56 +196,83 @@ __device__ __forceinline__ void list_pop(TopList& L) {
   L.idx[MAXB - 1] = 0x7FFFFFFF;
 }
 
-// block-wide argmax of (key, idx) over up to 1024 threads (shk, shi: 16 entries), ties to the lowest idx; result to every thread
-__device__ __forceinline__ void block_best(float& k, int& i, float* shk, int* shi) {
-  for (int off = 32; off > 0; off >>= 1) {
-    const float ok = __shfl_xor(k, off, 64);
-    const int oi = __shfl_xor(i, off, 64);
-    if (better(ok, oi, k, i)) { k = ok; i = oi; }
-  }
+// (key, idx) as one unsigned number that is larger exactly where better() says so: the key's bits in an order that compares as
+// unsigned (both zeros alike; no NaN), then the complement of idx.
+__device__ __forceinline__ uint64_t rank_of(float k, int i) {
+  const uint32_t u = __float_as_uint(k + 0.0f);  // -0 becomes +0
+  return ((uint64_t)(u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u)) << 32) | (uint32_t)~i;
+}
+__device__ __forceinline__ float rank_key(uint64_t r) {
+  const uint32_t u = (uint32_t)(r >> 32);
+  return __uint_as_float(u ^ ((u >> 31) ? 0x80000000u : 0xFFFFFFFFu));
+}
+__device__ __forceinline__ int rank_idx(uint64_t r) { return (int)~(uint32_t)r; }
+
+// one step of a maximum over lanes: the value CTRL's lane pattern brings, where ROWS lets it in
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t max_step(uint64_t v) {
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(v >> 32), (int)(v >> 32), CTRL, ROWS, 0xf, false);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)v, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
+  const uint64_t o = ((uint64_t)hi << 32) | lo;
+  return o > v ? o : v;
+}
+template <int LANE>
+__device__ __forceinline__ uint64_t from_lane(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), LANE) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, LANE);
+}
+// largest value of lanes 0 .. 15, and of the whole wave, in every lane: data-parallel-primitive moves in the vector ALU, a
+// dozen clocks a step where a shuffle through LDS takes over a hundred
+__device__ __forceinline__ uint64_t row_max(uint64_t v) {
+  v = max_step<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8: lane 15 of a row of 16 has the row's maximum
+  v = max_step<0x112, 0xf>(v);
+  v = max_step<0x114, 0xf>(v);
+  v = max_step<0x118, 0xf>(v);
+  return from_lane<15>(v);
+}
+__device__ __forceinline__ uint64_t wave_max_rank(uint64_t v) {
+  v = max_step<0x111, 0xf>(v);
+  v = max_step<0x112, 0xf>(v);
+  v = max_step<0x114, 0xf>(v);
+  v = max_step<0x118, 0xf>(v);
+  v = max_step<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
+  v = max_step<0x143, 0xc>(v);
+  return from_lane<63>(v);
+}
+// of a workgroup of at most 16 waves; sh: 16 entries.  One barrier; the caller may use sh again only after another one.
+__device__ __forceinline__ uint64_t block_max_rank(uint64_t v, uint64_t* sh) {
+  v = wave_max_rank(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) { shk[threadIdx.x >> 6] = k; shi[threadIdx.x >> 6] = i; }
-  __syncthreads();
-  k = shk[0]; i = shi[0];
   const int nw = (int)blockDim.x >> 6;
-  for (int w = 1; w < nw; ++w)
-    if (better(shk[w], shi[w], k, i)) { k = shk[w]; i = shi[w]; }
+  return row_max(sh[min((int)(threadIdx.x & 15), nw - 1)]);
 }
 
-// The same for a workgroup of exactly 1024 threads with the second level on the shuffle network of wave 0 (16 entries):
-// shorter than 15 serial comparisons in every thread when it runs many times in a row.  shk, shi: 17 entries.
-__device__ __forceinline__ void block_best_1024(float& k, int& i, float* shk, int* shi) {
-  for (int off = 32; off > 0; off >>= 1) {
-    const float ok = __shfl_xor(k, off, 64);
-    const int oi = __shfl_xor(i, off, 64);
-    if (better(ok, oi, k, i)) { k = ok; i = oi; }
-  }
-  if ((threadIdx.x & 63) == 0) { shk[threadIdx.x >> 6] = k; shi[threadIdx.x >> 6] = i; }
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    float k2 = shk[threadIdx.x & 15];
-    int i2 = shi[threadIdx.x & 15];
-    for (int off = 8; off > 0; off >>= 1) {
-      const float ok = __shfl_xor(k2, off, 64);
-      const int oi = __shfl_xor(i2, off, 64);
-      if (better(ok, oi, k2, i2)) { k2 = ok; i2 = oi; }
-    }
-    if (threadIdx.x == 0) { shk[16] = k2; shi[16] = i2; }
-  }
-  __syncthreads();
-  k = shk[16];
-  i = shi[16];
-}
-
-// b rounds of "best head wins and is popped"; thread 0 receives the winners in order
-__device__ __forceinline__ void block_merge(TopList& L, int b, float* out_key, int* out_idx, float* shk, int* shi) {
+// The b best entries of a workgroup of 256 threads with a sorted list each: every wave takes its b best (best head wins and is
+// popped), then wave 0 the b best of those.  All threads call it; out receives them, best first, before the barrier that ends it.
+// sh: 4 * MAXB entries.
+__device__ __forceinline__ void block_merge(TopList& L, int b, float* out_key, int* out_idx, uint64_t* sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int j = 0; j < b; ++j) {
-    float k = L.key[0];
-    int i = L.idx[0];
-    block_best(k, i, shk, shi);
-    if (L.idx[0] == i && i != 0x7FFFFFFF) list_pop(L);  // candidate indices are unique, so exactly one owner
-    if (threadIdx.x == 0) { out_key[j] = k; out_idx[j] = i; }
+    const uint64_t head = rank_of(L.key[0], L.idx[0]);
+    const uint64_t w = wave_max_rank(head);
+    if (head == w && L.idx[0] != 0x7FFFFFFF) list_pop(L);  // candidate indices are unique, so exactly one owner
+    if (lane == 0) sh[wave * MAXB + j] = w;
   }
+  __syncthreads();
+  if (wave == 0) {
+    const int list = lane / MAXB, pos = lane % MAXB;
+    uint64_t v = rank_of(-INFINITY, 0x7FFFFFFF);
+    if (list < 4 && pos < b) v = sh[list * MAXB + pos];
+    for (int j = 0; j < b; ++j) {
+      const uint64_t w = wave_max_rank(v);
+      if (v == w) v = rank_of(-INFINITY, 0x7FFFFFFF);
+      if (lane == 0) {
+        out_key[j] = rank_key(w);
+        out_idx[j] = rank_idx(w);
+      }
+    }
+  }
+  __syncthreads();
 }
 
 // score of candidate (live beam r, token v): cum_logq[r] + (logit - lse), float32, in this order
@@ -258,9 +285,10 @@ __device__ __forceinline__ float cand_score(const float* logits, const float* ls
 __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restrict__ logits, const float* __restrict__ lse, BeamView hist,
                                                           const int32_t* __restrict__ cu_cnt, const int32_t* __restrict__ len, int step,
                                                           int R, int gamma, int beam, int V, int sample, uint64_t seed,
-                                                          float* __restrict__ part_key, int* __restrict__ part_idx) {
-  __shared__ float shk[4];
-  __shared__ int shi[4];
+                                                          float* __restrict__ part_key, int* __restrict__ part_idx,
+                                                          const float2* __restrict__ lse_part, int NP, float* __restrict__ lse_out) {
+  __shared__ uint64_t sh[4 * MAXB];
+  __shared__ float lse_sh[4], lse_s[MAXB];
   __shared__ float cum_s[MAXB];
   __shared__ float okey[MAXB];
   __shared__ int oidx[MAXB];
@@ -276,17 +304,38 @@ __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restric
   const int per = (total + G - 1) / G;
   const int c0 = blockIdx.x * per, c1 = min(total, c0 + per);
   const uint64_t nk = noise_key(seed, s * STREAMS_PER_SEQ + STREAM_BEAM, len[s] + cnt + step);
+  // lse_part: the rows' logsumexps are still partial sums per strip of the lm_head; every workgroup finishes those of its slice
+  // (all write the same value) instead of a launch in between
+  if (lse_part && c0 < c1)
+    for (int r = c0 / V; r <= (c1 - 1) / V; ++r) {
+      const float l = lse_of_row(lse_part + (int64_t)(row0 + r) * NP, NP, lse_sh);
+      if (threadIdx.x == 0) {
+        lse_s[r] = l;
+        lse_out[row0 + r] = l;
+      }
+    }
+  __syncthreads();
   TopList L;
   list_init(L);
-  for (int c = c0 + threadIdx.x; c < c1; c += 256) {
-    const int r = c / V, v = c % V;
-    float k = cand_score(logits, lse, cum_s, row0, r, v, V);
-    if (sample) k += gumbel(nk, (uint64_t)c);
-    if (!(k == k)) k = -INFINITY;  // a NaN score never wins and never leaves an empty slot behind
-    list_insert(L, beam, k, c);
+  // eight candidates at a time, their logits requested together: one memory latency, not eight (the insertion branches)
+  constexpr int U = 8;
+  for (int cb = c0 + (int)threadIdx.x; cb < c1; cb += 256 * U) {
+    float k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = min(cb + 256 * u, c1 - 1), r = c / V, v = c % V;
+      k[u] = lse_part ? cum_s[r] + (logits[(int64_t)(row0 + r) * V + v] - lse_s[r]) : cand_score(logits, lse, cum_s, row0, r, v, V);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = cb + 256 * u;
+      if (c >= c1) continue;
+      if (sample) k[u] += gumbel(nk, (uint64_t)c);
+      if (!(k[u] == k[u])) k[u] = -INFINITY;  // a NaN score never wins and never leaves an empty slot behind
+      list_insert(L, beam, k[u], c);
+    }
   }
-  block_merge(L, beam, okey, oidx, shk, shi);
-  __syncthreads();
+  block_merge(L, beam, okey, oidx, sh);
   if (threadIdx.x < beam) {
     part_key[(s * G + blockIdx.x) * MAXB + threadIdx.x] = okey[threadIdx.x];
     part_idx[(s * G + blockIdx.x) * MAXB + threadIdx.x] = oidx[threadIdx.x];
@@ -298,8 +347,7 @@ __global__ __launch_bounds__(256) void topb_stage2_kernel(const float* __restric
                                                           const int32_t* __restrict__ cu_cnt, int step, int R, int gamma, int beam,
                                                           int V, int G, const float* __restrict__ part_key,
                                                           const int* __restrict__ part_idx) {
-  __shared__ float shk[4];
-  __shared__ int shi[4];
+  __shared__ uint64_t sh[4 * MAXB];
   __shared__ float cum_s[MAXB];
   __shared__ float okey[MAXB];
   __shared__ int oidx[MAXB];
@@ -311,13 +359,20 @@ __global__ __launch_bounds__(256) void topb_stage2_kernel(const float* __restric
     cum_s[threadIdx.x] = (step == 0 || (int)threadIdx.x >= beam) ? 0.f : hist.cum[(s * gamma + step - 1) * beam + threadIdx.x];
   TopList L;
   list_init(L);
-  for (int e = threadIdx.x; e < G * beam; e += 256) {
-    const int g = e / beam, j = e % beam;
-    const int i = part_idx[(s * G + g) * MAXB + j];
-    if (i != 0x7FFFFFFF) list_insert(L, beam, part_key[(s * G + g) * MAXB + j], i);
+  for (int eb = threadIdx.x; eb < G * beam; eb += 512) {
+    float k[2];
+    int i[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = min(eb + 256 * u, G * beam - 1), at = (s * G + e / beam) * MAXB + e % beam;
+      k[u] = part_key[at];
+      i[u] = part_idx[at];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (eb + 256 * u < G * beam && i[u] != 0x7FFFFFFF) list_insert(L, beam, k[u], i[u]);
   }
-  block_merge(L, beam, okey, oidx, shk, shi);
-  __syncthreads();
+  block_merge(L, beam, okey, oidx, sh);
   if (threadIdx.x < beam) {
     int c = oidx[threadIdx.x];
     if (c < 0 || c >= ((step == 0) ? 1 : beam) * V) c = 0;  // only reachable with non-finite logits: stay in bounds
@@ -331,9 +386,9 @@ __global__ __launch_bounds__(256) void topb_stage2_kernel(const float* __restric
 
 hipError_t launch_topb(const float* logits, const float* lse, BeamView hist, const int32_t* cu_cnt, const int32_t* len, int step,
                        int B, int R, int gamma, int beam, int V, int sample, uint64_t seed, float* part_key, int* part_idx, int G,
-                       hipStream_t s) {
+                       hipStream_t s, const float* lse_part, int NP, float* lse_out) {
   hipLaunchKernelGGL(topb_stage1_kernel, dim3(G, B), dim3(256), 0, s, logits, lse, hist, cu_cnt, len, step, R, gamma, beam, V, sample,
-                     seed, part_key, part_idx);
+                     seed, part_key, part_idx, (const float2*)lse_part, NP, lse_out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(topb_stage2_kernel, dim3(B), dim3(256), 0, s, logits, lse, hist, cu_cnt, step, R, gamma, beam, V, G, part_key,
@@ -343,54 +398,65 @@ hipError_t launch_topb(const float* logits, const float* lse, BeamView hist, con
 
 // ---- tree of the target pass --------------------------------------------------------------------------
 
-__global__ void build_tree_kernel(BeamView hist, TreeView tree, int B, int gamma, int beam, int mode) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= B) return;
-  const int M = tree.M;
-  const int32_t* htok = hist.tok + (int64_t)s * gamma * beam;
-  const int32_t* hpar = hist.parent + (int64_t)s * gamma * beam;
-  const float* hcum = hist.cum + (int64_t)s * gamma * beam;
-  // x**: final beam with the largest stored likelihood (first maximum), traced back through the parents
-  int j = 0;
-  for (int k = 1; k < beam; ++k)
-    if (hcum[(gamma - 1) * beam + k] > hcum[(gamma - 1) * beam + j]) j = k;
-  int beams[MTAD_MAX_GAMMA];
-  for (int i = gamma - 1; i >= 0; --i) {
-    beams[i] = j;
-    j = min(max(hpar[i * beam + j], 0), beam - 1);  // caller-owned memory: stay in range
+// One wave per sequence: the history goes to LDS once (read by one thread it was a chain of dependent loads), lane 0 traces x**,
+// then every lane fills one row and walks its own ancestors.
+__global__ __launch_bounds__(64) void build_tree_kernel(BeamView hist, TreeView tree, int B, int gamma, int beam, int mode) {
+  __shared__ int par_s[MTAD_MAX_GAMMA * MAXB], tok_s[MTAD_MAX_GAMMA * MAXB];
+  __shared__ float cum_s[MTAD_MAX_GAMMA * MAXB];
+  __shared__ int beams[MTAD_MAX_GAMMA];
+  const int s = blockIdx.x, lane = threadIdx.x, M = tree.M, n = gamma * beam;
+  for (int e = lane; e < n; e += 64) {
+    tok_s[e] = hist.tok[(int64_t)s * n + e];
+    par_s[e] = min(max(hist.parent[(int64_t)s * n + e], 0), beam - 1);  // caller-owned memory: stay in range
+    cum_s[e] = hist.cum[(int64_t)s * n + e];
   }
-  int32_t* tok = tree.tok + (int64_t)s * M;
-  int32_t* par = tree.parent + (int64_t)s * M;
-  int32_t* dep = tree.depth + (int64_t)s * M;
-  int32_t* src = tree.src_beam + (int64_t)s * M;
-  uint64_t* am = tree.anc_mask + (int64_t)s * M;
-  tok[0] = -1; par[0] = -1; dep[0] = 0; src[0] = -1; am[0] = 1ull;
-  for (int i = 0; i < gamma; ++i) tree.qref[s * gamma + i] = hcum[i * beam + beams[i]];
-  if (mode == 0) {
-    for (int i = 0; i < gamma; ++i) {
-      const int r = i + 1;
-      tok[r] = htok[i * beam + beams[i]];
-      par[r] = i;
-      dep[r] = i + 1;
-      src[r] = beams[i];
-      am[r] = chain_bits(r);
+  __syncthreads();
+  if (lane == 0) {
+    // x**: final beam with the largest stored likelihood (first maximum), traced back through the parents
+    int j = 0;
+    for (int k = 1; k < beam; ++k)
+      if (cum_s[(gamma - 1) * beam + k] > cum_s[(gamma - 1) * beam + j]) j = k;
+    for (int i = gamma - 1; i >= 0; --i) {
+      beams[i] = j;
+      j = par_s[i * beam + j];
     }
-  } else {
-    for (int i = 0; i < gamma; ++i)
-      for (int k = 0; k < beam; ++k) {
-        const int r = 1 + i * beam + k;
-        const int p = (i == 0) ? 0 : 1 + (i - 1) * beam + min(max(hpar[i * beam + k], 0), beam - 1);
-        tok[r] = htok[i * beam + k];
-        par[r] = p;
-        dep[r] = i + 1;
-        src[r] = k;
-        am[r] = am[p] | (1ull << r);
+  }
+  __syncthreads();
+  for (int i = lane; i < gamma; i += 64) tree.qref[s * gamma + i] = cum_s[i * beam + beams[i]];
+  for (int r = lane; r < M; r += 64) {
+    int tok = -1, par = -1, dep = 0, src = -1;
+    uint64_t am = 1ull;
+    if (r > 0 && mode == 0) {
+      const int i = r - 1;
+      tok = tok_s[i * beam + beams[i]];
+      par = i;
+      dep = i + 1;
+      src = beams[i];
+      am = chain_bits(r);
+    } else if (r > 0) {
+      const int i = (r - 1) / beam;
+      int k = (r - 1) % beam;
+      tok = tok_s[i * beam + k];
+      src = k;
+      dep = i + 1;
+      par = (i == 0) ? 0 : 1 + (i - 1) * beam + par_s[i * beam + k];
+      for (int ii = i; ii >= 0; --ii) {
+        am |= 1ull << (1 + ii * beam + k);
+        k = par_s[ii * beam + k];
       }
+    }
+    const int64_t o = (int64_t)s * M + r;
+    tree.tok[o] = tok;
+    tree.parent[o] = par;
+    tree.depth[o] = dep;
+    tree.src_beam[o] = src;
+    tree.anc_mask[o] = am;
   }
 }
 
 hipError_t launch_build_tree(BeamView hist, TreeView tree, int B, int gamma, int beam, int mode, hipStream_t s) {
-  hipLaunchKernelGGL(build_tree_kernel, dim3((B + 63) / 64), dim3(64), 0, s, hist, tree, B, gamma, beam, mode);
+  if (gamma > MTAD_MAX_GAMMA || beam > MAXB) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(build_tree_kernel, dim3(B), dim3(64), 0, s, hist, tree, B, gamma, beam, mode);
   return hipGetLastError();
 }
 
@@ -417,70 +483,131 @@ hipError_t launch_gather_logp(const float* logits, const float* lse, TreeView tr
 
 // ---- joint-likelihood acceptance and bonus token -----------------------------------------------------------
 
-__global__ __launch_bounds__(1024) void accept_kernel(TreeView tree, const float* __restrict__ logp_cond, const float* __restrict__ logits,
-                                                     int V, const int32_t* __restrict__ len, float log_tau, int mode, int gamma,
-                                                     int sample, uint64_t seed, AcceptView out) {
-  __shared__ float joint[MTAD_MAX_ROWS];
-  __shared__ int sel[2];  // eta, node
-  __shared__ float shk[16];
-  __shared__ int shi[16];
-  const int s = blockIdx.x, M = tree.M;
-  const int32_t* par = tree.parent + (int64_t)s * M;
-  const int32_t* dep = tree.depth + (int64_t)s * M;
-  const int32_t* tok = tree.tok + (int64_t)s * M;
-  if (threadIdx.x == 0) {
+// The walk over a sequence's rows: eta and the accepted node.  The rows go to LDS first (from memory every row was a chain of
+// dependent loads).  All threads of a workgroup of at least 64 call it; the result is in w.eta, w.node after the barrier that
+// ends it.
+struct AcceptWalk {
+  float joint[MTAD_MAX_ROWS], cond[MTAD_MAX_ROWS], qref[MTAD_MAX_ROWS];
+  int par[MTAD_MAX_ROWS], dep[MTAD_MAX_ROWS], tok[MTAD_MAX_ROWS];
+  int eta, node;
+};
+__device__ __forceinline__ void accept_walk(AcceptWalk& w, const TreeView& tree, const float* __restrict__ logp_cond, int s, float log_tau, int mode,
+                                            int gamma) {
+  const int M = tree.M, t = threadIdx.x;
+  if (t < M) {
+    const int64_t o = (int64_t)s * M + t;
+    w.par[t] = tree.parent[o];
+    w.dep[t] = tree.depth[o];
+    w.tok[t] = tree.tok[o];
+    w.cond[t] = logp_cond[o];
+  }
+  const bool q_in = gamma <= MTAD_MAX_ROWS;
+  if (q_in && t < gamma) w.qref[t] = tree.qref[s * gamma + t];
+  __syncthreads();
+  if (t == 0) {
     // log p of every branch: conditionals summed from the first level down (parents precede children)
-    joint[0] = 0.f;
+    w.joint[0] = 0.f;
     int eta = 0, node = 0;
     float best = -INFINITY;
     for (int c = 1; c < M; ++c) {
-      const int p = par[c];
-      const float jp = joint[(p >= 0 && p < c) ? p : 0] + logp_cond[(int64_t)s * M + c];
-      joint[c] = jp;
-      const int i = dep[c];
+      const int p = w.par[c];
+      const float jp = w.joint[(p >= 0 && p < c) ? p : 0] + w.cond[c];
+      w.joint[c] = jp;
+      const int i = w.dep[c];
       if (i < 1 || i > gamma) continue;
-      const float diff = jp - tree.qref[s * gamma + i - 1];
+      const float diff = jp - (q_in ? w.qref[i - 1] : tree.qref[s * gamma + i - 1]);
       if (mode == 0) {
         if (fminf(0.f, diff) > log_tau && i >= eta) { eta = i; node = c; }  // rows of a chain come in depth order
       } else {
         if (diff >= log_tau && (i > eta || (i == eta && jp > best))) { eta = i; node = c; best = jp; }
       }
     }
-    sel[0] = eta;
-    sel[1] = node;
-    out.eta[s] = eta;
-    out.bonus_row[s] = node;
-    out.out_cnt[s] = eta + 1;
-    for (int i = 0; i < gamma; ++i) out.path[s * gamma + i] = -1;
-    int c = node;
-    for (int i = eta; i >= 1 && c > 0; --i) {
-      out.path[s * gamma + i - 1] = c;
-      out.out_tok[s * (gamma + 1) + i - 1] = tok[c];
-      c = par[c];
-    }
+    w.eta = eta;
+    w.node = node;
   }
   __syncthreads();
-  const int eta = sel[0], node = sel[1];
-  const float* row = logits + ((int64_t)s * M + node) * V;
-  const uint64_t nk = noise_key(seed, s * STREAMS_PER_SEQ + STREAM_BONUS, len[s] + 1 + eta);
+}
+// what the walk alone decides (one thread)
+__device__ __forceinline__ void accept_store(const AcceptWalk& w, const AcceptView& out, int s, int M, int gamma) {
+  out.eta[s] = w.eta;
+  out.bonus_row[s] = w.node;
+  out.out_cnt[s] = w.eta + 1;
+  for (int i = 0; i < gamma; ++i) out.path[s * gamma + i] = -1;
+  int c = w.node;
+  for (int i = w.eta; i >= 1 && c > 0 && c < M; --i) {
+    out.path[s * gamma + i - 1] = c;
+    out.out_tok[s * (gamma + 1) + i - 1] = w.tok[c];
+    c = w.par[c];
+  }
+}
+// best entry of v = first, first + step, ... of a (noisy) logits row, eight loads in flight
+__device__ __forceinline__ uint64_t best_of_row(const float* __restrict__ row, int V, int first, int step, int sample, uint64_t nk) {
   float bk = -INFINITY;
   int bi = 0x7FFFFFFF;
-  for (int v = threadIdx.x; v < V; v += (int)blockDim.x) {
-    float k = row[v];
-    if (sample) k += gumbel(nk, (uint64_t)v);
-    if (better(k, v, bk, bi)) { bk = k; bi = v; }
+  constexpr int U = 8;
+  for (int vb = first; vb < V; vb += step * U) {
+    float k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) k[u] = row[min(vb + step * u, V - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int v = vb + step * u;
+      if (v >= V) continue;
+      if (sample) k[u] += gumbel(nk, (uint64_t)v);
+      if (better(k[u], v, bk, bi)) { bk = k[u]; bi = v; }  // (never with a NaN)
+    }
   }
-  block_best(bk, bi, shk, shi);
+  return rank_of(bk, bi);
+}
+
+// Acceptance and bonus token by one workgroup per sequence (part == null), or, with 2 x gridDim.x words of workspace per
+// sequence at `part`, the bonus token's argmax by gridDim.x workgroups, which leave their best entries to accept_finish_kernel:
+// 32000 Gumbel keys are 11 us of one compute unit's arithmetic and 1 us of sixteen's.
+__global__ __launch_bounds__(1024) void accept_kernel(TreeView tree, const float* __restrict__ logp_cond, const float* __restrict__ logits,
+                                                     int V, const int32_t* __restrict__ len, float log_tau, int mode, int gamma,
+                                                     int sample, uint64_t seed, AcceptView out, uint64_t* __restrict__ part) {
+  __shared__ AcceptWalk w;
+  __shared__ uint64_t sh[16];
+  const int s = blockIdx.y, M = tree.M;
+  accept_walk(w, tree, logp_cond, s, log_tau, mode, gamma);
+  if (blockIdx.x == 0 && threadIdx.x == 0) accept_store(w, out, s, M, gamma);
+  const float* row = logits + ((int64_t)s * M + w.node) * V;
+  const uint64_t nk = noise_key(seed, s * STREAMS_PER_SEQ + STREAM_BONUS, len[s] + 1 + w.eta);
+  const uint64_t best = block_max_rank(best_of_row(row, V, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, sample, nk), sh);
+  if (threadIdx.x != 0) return;
+  if (part) {
+    part[s * gridDim.x + blockIdx.x] = best;
+    return;
+  }
+  int bi = rank_idx(best);
   if (bi < 0 || bi >= V) bi = 0;  // only reachable with non-finite logits: stay in the vocabulary
-  if (threadIdx.x == 0) {
-    out.bonus_tok[s] = bi;
-    out.out_tok[s * (gamma + 1) + eta] = bi;
-  }
+  out.bonus_tok[s] = bi;
+  out.out_tok[s * (gamma + 1) + w.eta] = bi;
+}
+__global__ __launch_bounds__(64) void accept_finish_kernel(const uint64_t* __restrict__ part, int G, int V, int gamma, AcceptView out) {
+  const int s = blockIdx.x;
+  const uint64_t best = row_max(part[s * G + min((int)(threadIdx.x & 15), G - 1)]);  // G <= 16
+  if (threadIdx.x != 0) return;
+  int bi = rank_idx(best);
+  if (bi < 0 || bi >= V) bi = 0;  // only reachable with non-finite logits: stay in the vocabulary
+  out.bonus_tok[s] = bi;
+  out.out_tok[s * (gamma + 1) + out.out_cnt[s] - 1] = bi;
 }
 
 hipError_t launch_accept(TreeView tree, const float* logp_cond, const float* logits, int V, const int32_t* len, float log_tau, int mode,
-                         int B, int gamma, int sample, uint64_t seed, AcceptView out, hipStream_t s) {
-  hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(1024), 0, s, tree, logp_cond, logits, V, len, log_tau, mode, gamma, sample, seed, out);
+                         int B, int gamma, int sample, uint64_t seed, AcceptView out, void* part, hipStream_t s) {
+  // sixteen workgroups of 256 threads where their partial results have a place and there is noise to compute
+  const bool wide = part && sample && V >= 8192;
+  if (!wide) {
+    hipLaunchKernelGGL(accept_kernel, dim3(1, B), dim3(1024), 0, s, tree, logp_cond, logits, V, len, log_tau, mode, gamma, sample, seed, out,
+                       (uint64_t*)nullptr);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(accept_kernel, dim3(ACCEPT_PARTS, B), dim3(256), 0, s, tree, logp_cond, logits, V, len, log_tau, mode, gamma, sample, seed, out,
+                     (uint64_t*)part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(accept_finish_kernel, dim3(B), dim3(64), 0, s, (const uint64_t*)part, ACCEPT_PARTS, V, gamma, out);
   return hipGetLastError();
 }
 
@@ -518,8 +645,7 @@ __global__ __launch_bounds__(1024) void accept_spd_kernel(TreeView tree, const f
                                                          const float* __restrict__ qrows, int V, const int32_t* __restrict__ len, int gamma,
                                                          uint64_t seed, AcceptView out) {
   __shared__ int eta_s;
-  __shared__ float shk[16];
-  __shared__ int shi[16];
+  __shared__ uint64_t sh[16];
   const int s = blockIdx.x, M = tree.M;
   const int32_t* tok = tree.tok + (int64_t)s * M;
   if (threadIdx.x == 0) {
@@ -559,7 +685,7 @@ __global__ __launch_bounds__(1024) void accept_spd_kernel(TreeView tree, const f
     k += gumbel(nk, (uint64_t)v);
     if (better(k, v, bk, bi)) { bk = k; bi = v; }
   }
-  block_best(bk, bi, shk, shi);
+  bi = rank_idx(block_max_rank(rank_of(bk, bi), sh));
   if (bi < 0 || bi >= V) bi = 0;  // only reachable with non-finite rows: stay in the vocabulary
   if (threadIdx.x == 0) {
     out.bonus_tok[s] = bi;
@@ -578,80 +704,135 @@ hipError_t launch_accept_spd(TreeView tree, const float* logits, const float* ls
 // One workgroup per logits row: the row becomes the row of log p~ of the warped distribution (appendix
 // "Hyper-parameter Details": the top_k most likely tokens, normalised; of those, in descending order, the shortest
 // prefix whose cumulative probability exceeds top_p; normalised again), minus infinity outside the support, and the
-// row's logsumexp becomes 0, so that every consumer of (logits, lse) rows works on p~ unchanged.  The top_k tokens
-// are found by top_k rounds of a workgroup-wide argmax over every thread's best remaining entry; after a round only the
-// winner's owner looks for its next best, among its entries that rank after the winner (value descending, token id
-// ascending): no bookkeeping of removed entries.  The ten-element arithmetic runs on one thread
-// in a fixed order (float32, sums in descending order of probability).
-constexpr int WARP_MAXK = 16;
+// row's logsumexp becomes 0, so that every consumer of (logits, lse) rows works on p~ unchanged.  Entries rank by value
+// descending, token id ascending; a NaN ranks last.
+//   1. every thread's best entry; top_k rounds of a workgroup-wide maximum over those give the top_k-th best of them, T
+//   2. the top_k entries of the row are among the entries that rank T or better, and those lie in the top_k threads whose best
+//      ranks T or better: they are listed in LDS (10 to 30 of them in a row of 32000 distinct logits, never more than
+//      top_k * V / 1024)
+//   3. wave 0 takes the top_k best of the list and does the arithmetic, one token per lane, sums in descending order
+// A round costs one barrier and no look at the row (the owner of each winner searching its entries again, round by round,
+// was two thirds of 32 us per row).  The first 32768 entries of the row live in registers.
+constexpr int WARP_MAXK = 16, WARP_LIST = 2048;
 __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ logits, float* __restrict__ lse, int V, int top_k, float top_p) {
-  __shared__ float shk[17];
-  __shared__ int shi[17];
+  __shared__ uint64_t sh[2][16];
+  __shared__ uint64_t list[WARP_LIST];
+  __shared__ int count;
   __shared__ float tv[WARP_MAXK];
-  __shared__ int ti[WARP_MAXK];
-  __shared__ int keep_s;
+  __shared__ int ti[WARP_MAXK], keep_s;
   float* row = logits + (int64_t)blockIdx.x * V;
-  const int k = min(min(top_k, WARP_MAXK), V);
-  // the first 32768 entries of the row live in registers for all rounds (entry tid + 1024*j in x[j]); longer rows read
-  // the rest from memory in every round
+  const int t = threadIdx.x, lane = t & 63, k = min(min(top_k, WARP_MAXK), V);
   constexpr int PT = 32;
   float x[PT];
 #pragma unroll
   for (int j = 0; j < PT; ++j) {
-    const int v = (int)threadIdx.x + 1024 * j;
-    float t = v < V ? row[v] : -INFINITY;
-    x[j] = (t == t) ? t : -INFINITY;                                // a NaN logit ranks last
+    const float v = row[min(t + 1024 * j, V - 1)];
+    x[j] = (v == v) ? v : -INFINITY;
   }
-  // this thread's best entry among those that rank after (pv, pi) (value descending, token id ascending)
-  auto local_best = [&](float pv, int pi, float& bk, int& bi) {
-    bk = -INFINITY;
-    bi = 0x7FFFFFFF;
+  auto at = [&](int v) {  // entries beyond the registers
+    const float y = row[v];
+    return (y == y) ? y : -INFINITY;
+  };
+  if (t == 0) count = 0;
+  uint64_t mine = rank_of(-INFINITY, 0x7FFFFFFF);
+#pragma unroll
+  for (int j = 0; j < PT; ++j) {
+    const uint64_t r = rank_of(x[j], t + 1024 * j);
+    if (t + 1024 * j < V && r > mine) mine = r;
+  }
+  for (int v = t + 1024 * PT; v < V; v += 1024) {
+    const uint64_t r = rank_of(at(v), v);
+    if (r > mine) mine = r;
+  }
+  // a row that lies in registers whole is overwritten now, while the rounds run
+  const bool held = V <= 1024 * PT;
+  if (held)
+    for (int v = t; v < V; v += 1024) row[v] = -INFINITY;
+  uint64_t T = 0, left = mine;
+  const int rounds = min(k, min(V, 1024));  // threads with an entry
+  for (int r = 0; r < rounds; ++r) {
+    T = block_max_rank(left, sh[r & 1]);  // (everybody has read the other buffer before this one's barrier)
+    if (left == T) left = 0;
+  }
+  if (mine >= T) {
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
-      const int v = (int)threadIdx.x + 1024 * j;
-      const bool after = x[j] < pv || (x[j] == pv && v > pi);
-      if (v < V && after && better(x[j], v, bk, bi)) { bk = x[j]; bi = v; }
+      const uint64_t r = rank_of(x[j], t + 1024 * j);
+      if (t + 1024 * j < V && r >= T) {
+        const int o = atomicAdd(&count, 1);
+        if (o < WARP_LIST) list[o] = r;
+      }
     }
-    for (int v = (int)threadIdx.x + 1024 * PT; v < V; v += 1024) {
-      float t = row[v];
-      if (!(t == t)) t = -INFINITY;
-      const bool after = t < pv || (t == pv && v > pi);
-      if (after && better(t, v, bk, bi)) { bk = t; bi = v; }
+    for (int v = t + 1024 * PT; v < V; v += 1024) {
+      const uint64_t r = rank_of(at(v), v);
+      if (r >= T) {
+        const int o = atomicAdd(&count, 1);
+        if (o < WARP_LIST) list[o] = r;
+      }
     }
-  };
-  float lk;
-  int li;
-  local_best(INFINITY, -1, lk, li);
-  for (int r = 0; r < k; ++r) {
-    float bk = lk;
-    int bi = li;
-    block_best_1024(bk, bi, shk, shi);  // its first barrier also orders this round after the previous round's reads
-    if (threadIdx.x == 0) { tv[r] = bk; ti[r] = bi; }
-    // only the winner's owner has lost its best entry: all its other entries rank after the winner
-    if (li == bi && bi != 0x7FFFFFFF) local_best(bk, bi, lk, li);
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    float e[WARP_MAXK], p[WARP_MAXK];
+  int n = count;
+  if (n > WARP_LIST) {  // only with more than 131072 tokens, and rows whose best entries share a few threads: one token a round
+    uint64_t prev = ~0ull;
+    for (int r = 0; r < k; ++r) {
+      uint64_t b = 0;
+      for (int v = t; v < V; v += 1024) {
+        const uint64_t rk = rank_of(at(v), v);
+        if (rk < prev && rk > b) b = rk;
+      }
+      prev = block_max_rank(b, sh[r & 1]);
+      if (t == 0) list[r] = prev;
+    }
+    n = k;
+    __syncthreads();
+  }
+  if (t < 64) {
+    auto lane_best = [&]() {
+      uint64_t b = 0;
+      for (int o = lane; o < n; o += 64) b = list[o] > b ? list[o] : b;
+      return b;
+    };
+    uint64_t b = lane_best(), own = 0;  // own: lane i keeps the i-th best
+    for (int r = 0; r < k; ++r) {
+      const uint64_t w = wave_max_rank(b);
+      if (lane == r) own = w;
+      if (b == w) {
+        for (int o = lane; o < n; o += 64)
+          if (list[o] == w) list[o] = 0;
+        b = lane_best();
+      }
+    }
+    const bool in = lane < k;
+    const float v = in ? rank_key(own) : -INFINITY, top = __shfl(v, 0, 64);
+    const float e = in ? expf(v - top) : 0.f;
     float S = 0.f;
-    for (int i = 0; i < k; ++i) { e[i] = expf(tv[i] - tv[0]); S += e[i]; }
+    for (int i = 0; i < k; ++i) S += __shfl(e, i, 64);
+    const float p = e / S;
     float c = 0.f;
     int K = k;
     for (int i = 0; i < k; ++i) {
-      p[i] = e[i] / S;
-      c += p[i];
+      c += __shfl(p, i, 64);
       if (K == k && c > top_p) K = i + 1;
     }
     float s2 = 0.f;
-    for (int i = 0; i < K; ++i) s2 += p[i];
-    for (int i = 0; i < K; ++i) tv[i] = logf(p[i] / s2);
-    keep_s = K;
-    lse[blockIdx.x] = 0.f;
+    for (int i = 0; i < K; ++i) s2 += __shfl(p, i, 64);
+    if (in) {
+      tv[lane] = logf(p / s2);
+      ti[lane] = rank_idx(own);
+    }
+    if (lane == 0) {
+      keep_s = K;
+      lse[blockIdx.x] = 0.f;
+    }
   }
+  if (!held) {
+    __syncthreads();  // wave 0 does not read the row, but others may still be listing it
+    for (int v = t; v < V; v += 1024) row[v] = -INFINITY;
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // the row's old values are overwritten before its new ones are written
   __syncthreads();
-  for (int v = threadIdx.x; v < V; v += (int)blockDim.x) row[v] = -INFINITY;
-  __syncthreads();
-  if ((int)threadIdx.x < keep_s && ti[threadIdx.x] >= 0 && ti[threadIdx.x] < V) row[ti[threadIdx.x]] = tv[threadIdx.x];
+  if (t < keep_s && ti[t] >= 0 && ti[t] < V) row[ti[t]] = tv[t];
 }
 
 hipError_t launch_warp_rows(float* logits, float* lse, int rows, int V, int top_k, float top_p, hipStream_t s) {

@@ -396,7 +396,7 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 #pragma unroll
             for (int i = 0; i < 4; ++i)
               if (lane + 64 * i < NP) sum += e.sv[i];
-            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+            sum = wave_sum(sum);
             if (lane == 0) sm.inv_s[wave] = 1.0f / sqrtf(sum / (float)p.K + ga.eps);
           }
         } else {

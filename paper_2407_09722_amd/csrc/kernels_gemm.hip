@@ -362,8 +362,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   }
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
-    float v = acc[r];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    const float v = wave_sum(acc[r]);
     if (lane == 0 && r0 + r < R) {
       float* y = Y + (int64_t)(r0 + r) * ldy + n;
       *y = accumulate ? (*y + v) : v;

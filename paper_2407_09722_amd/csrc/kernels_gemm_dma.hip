@@ -501,7 +501,7 @@ __global__ __launch_bounds__(RT) void gemm_rows_kernel(GemmArgs a) {
     }
   }
   if constexpr (EPI == EPI_RESID) {
-    for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off, 64);
+    q = wave_sum(q);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = q;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(256) void gemm_pairs_kernel(GemmArgs a) {
   if (a.ssq) {
     float s = 0.f;
     for (int p = lane; p < a.NP; p += 64) s += a.ssq[(int64_t)m * a.NP + p];
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    s = wave_sum(s);
     inv = 1.0f / sqrtf(s / (float)a.K + a.eps);
   }
   const int item = blockIdx.x * 256 + threadIdx.x, nt = item >> 1, i0 = (item & 1) * 4;
@@ -594,7 +594,7 @@ __global__ __launch_bounds__(256) void ssq_rows_kernel(const float* __restrict__
   if (m >= R) return;
   float s = 0.f;
   for (int p = lane; p < NP; p += 64) s += in[(int64_t)m * NP + p];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  s = wave_sum(s);
   if (lane == 0) out[m] = s;
 }
 

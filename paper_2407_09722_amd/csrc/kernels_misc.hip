@@ -5,35 +5,6 @@
 
 namespace mtad {
 
-__device__ __forceinline__ float wave_sum(float v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
-}
-
-// block-wide reductions for 256-thread blocks; every thread gets the result
-__device__ __forceinline__ float block_sum(float v, float* sh) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float t = sh[0];
-  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t += sh[w];
-  return t;
-}
-__device__ __forceinline__ float block_max(float v, float* sh) {
-  v = wave_max(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float t = sh[0];
-  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t = fmaxf(t, sh[w]);
-  return t;
-}
-
 // The inputs of a pass, one workgroup per row: h[row] = E[tok[row]]; bf16 models: also planes of h*g0 (input of the
 // first fused RMSNorm) and ssq[row] = sum h^2; and the row's rotary table, table[row][i] = (cos, sin)(pos[row] *
 // theta^(-2i/head_dim)), evaluated in double so that positions in the thousands keep float32-exact angles.
@@ -225,29 +196,13 @@ hipError_t launch_row_lse(const float* logits, float* lse, int rows, int vocab, 
 // lse[row] = log sum exp over the row from per-strip partials (max, sum exp), merged in strip order
 __global__ __launch_bounds__(256) void lse_finish_kernel(const float2* __restrict__ part, float* __restrict__ lse, int NP) {
   __shared__ float sh[4];
-  const float2* p = part + (int64_t)blockIdx.x * NP;
-  float m = -INFINITY;
-  for (int i = threadIdx.x; i < NP; i += 256) m = fmaxf(m, p[i].x);
-  m = block_max(m, sh);
-  float sum = 0.f;
-  for (int i = threadIdx.x; i < NP; i += 256) sum += p[i].y * expf(p[i].x - m);
-  sum = block_sum(sum, sh);
-  if (threadIdx.x == 0) lse[blockIdx.x] = m + logf(sum);
+  const float l = lse_of_row(part + (int64_t)blockIdx.x * NP, NP, sh);
+  if (threadIdx.x == 0) lse[blockIdx.x] = l;
 }
 
 // The same, fused with the gather of the tree nodes' conditional log-likelihoods: workgroup (sequence s, row c) writes
 // lse[s][c] and, for c > 0, logp_cond[s][c] = logits[s][parent(c)][tok(c)] - lse[s][parent(c)], reducing the
 // parent row's partials itself (same code, same order: the value equals the one the parent's workgroup writes).
-__device__ __forceinline__ float lse_of_row(const float2* __restrict__ p, int NP, float* sh) {
-  float m = -INFINITY;
-  for (int i = threadIdx.x; i < NP; i += 256) m = fmaxf(m, p[i].x);
-  m = block_max(m, sh);
-  float sum = 0.f;
-  for (int i = threadIdx.x; i < NP; i += 256) sum += p[i].y * expf(p[i].x - m);
-  sum = block_sum(sum, sh);
-  return m + logf(sum);
-}
-
 __global__ __launch_bounds__(256) void lse_gather_kernel(const float2* __restrict__ part, float* __restrict__ lse, int NP,
                                                          const float* __restrict__ logits, int M, int V, const int32_t* __restrict__ parent,
                                                          const int32_t* __restrict__ tok, float* __restrict__ logp_cond) {

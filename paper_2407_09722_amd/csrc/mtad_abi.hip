@@ -61,6 +61,7 @@ struct mtad_ctx {
   // set by mtad_verify_tree around its pass: the logsumexp kernel of a bf16 pass then also gathers logp_cond
   const mtad_tree* gather_tree;
   float* gather_out;
+  bool lse_later;  // set by mtad_draft_beam_step around its pass: the beam's selection finishes the row logsumexps of a bf16 pass itself
   int last_hip;
 };
 
@@ -240,7 +241,7 @@ int finish_lse(mtad_ctx* c, const mtad_model* m, int rows, const float* logits, 
     c->gather_out = nullptr;  // done: the caller skips its separate gather
     return MTAD_OK;
   }
-  HIP_TRY(c, launch_lse_finish(c->lse_part, lse, rows, m->vocab / 16, s));
+  if (!c->lse_later) HIP_TRY(c, launch_lse_finish(c->lse_part, lse, rows, m->vocab / 16, s));
   return MTAD_OK;
 }
 
@@ -606,13 +607,16 @@ int mtad_draft_beam_step(mtad_ctx* c, const mtad_model* draft, mtad_kv* dkv, mta
   const BeamView hv{hist->tok, hist->parent, hist->cum_logq};
   HIP_TRY(c, launch_draft_rows(c->rd, dkv->len, hv, st->catchup_tok, st->catchup_cnt, step, B, R, gamma, beam,
                                dkv->page_size * dkv->max_pages, c->status, s));
+  c->lse_later = draft->dtype == 1 && c->warp_k == 0 && beam > 1;  // (warping and a saved row of log q read them first)
+  const bool lse_later = c->lse_later;
   int rc = decoder_pass(c, draft, dkv, R, s, c->dlogits, c->lse);
+  c->lse_later = false;
   if (rc) return rc;
   if (c->warp_k > 0) HIP_TRY(c, launch_warp_rows(c->dlogits, c->lse, B * R, draft->vocab, c->warp_k, c->warp_p, s));
   if (beam == 1)  // a chain drawn token by token: keep log q of each step for token-wise acceptance (mtad_accept_spd)
     HIP_TRY(c, launch_save_logq_row(c->dlogits, c->lse, st->catchup_cnt, step, B, R, gamma, draft->vocab, c->qrows, s));
   HIP_TRY(c, launch_topb(c->dlogits, c->lse, hv, st->catchup_cnt, dkv->len, step, B, R, gamma, beam, draft->vocab, sample_beam ? 1 : 0,
-                         seed, c->part_key, c->part_idx, TOPB_BLOCKS, s));
+                         seed, c->part_key, c->part_idx, TOPB_BLOCKS, s, lse_later ? c->lse_part : nullptr, draft->vocab / 16, c->lse));
   return MTAD_OK;
 }
 
@@ -659,7 +663,7 @@ int mtad_accept(mtad_ctx* c, const mtad_tree* tree, const float* logp_cond, cons
   const float log_tau = (tau > 0.f) ? (float)log((double)tau) : -INFINITY;
   const AcceptView av{out->eta, out->path, out->bonus_row, out->bonus_tok, out->out_tok, out->out_cnt};
   HIP_TRY(c, launch_accept(tview(tree), logp_cond, logits, vocab, tkv->len, log_tau, mode, c->cfg.batch, c->cfg.gamma,
-                           sample_bonus ? 1 : 0, seed, av, (hipStream_t)stream));
+                           sample_bonus ? 1 : 0, seed, av, c->ws ? c->part_key : nullptr, (hipStream_t)stream));
   return MTAD_OK;
 }
 

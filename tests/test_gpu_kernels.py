@@ -246,3 +246,35 @@ def test_row_lse():
         xx = x.astype(np.float64)
         want = xx.max(1) + np.log(np.exp(xx - xx.max(1, keepdims=True)).sum(1))
         assert np.allclose(lse.cpu().numpy(), want, rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("V,k,kind", [(1000, 10, "plain"), (7, 16, "plain"), (1024, 16, "same"), (32768, 10, "plain"), (32769, 16, "plain"), (33000, 10, "same"),
+                                      (40000, 16, "low"), (140000, 16, "stride"), (200000, 3, "plain"), (32000, 10, "zeros")])
+def test_warp_rows_supports_of_every_layout(V, k, kind):
+    """The support of the warped row is that of a stable descending sort: rows shorter and longer than the registers hold, one
+    value everywhere, minus infinities, zeros of both signs, best entries that all fall to one thread (more than its list holds)."""
+    mb = _mb()
+    g = np.random.default_rng(V + k)
+    x = g.standard_normal((3, V)).astype(np.float32)
+    if kind == "same":
+        x[:] = 0.25
+    elif kind == "low":
+        x[:, 5:] = -np.inf
+    elif kind == "zeros":
+        x[:] = -0.0
+        x[:, ::3] = 0.0
+    elif kind == "stride":                                            # 137 entries per thread, the largest in threads 0 .. 15
+        x[:, np.arange(V) % 1024 < 16] += 100.0
+    xd = torch.from_numpy(x).to(DEV)
+    lse = torch.full((3,), 7.0, device=DEV)
+    print(f"warp rows V={V} k={k} {kind}", flush=True)
+    mb.mtad_k_warp_rows(xd, lse, 3, V, k, 2.0)                        # top_p above 1 keeps all top_k tokens
+    torch.cuda.synchronize()
+    got = xd.cpu().numpy()
+    for r in range(3):
+        order = np.lexsort((np.arange(V), -(x[r].astype(np.float64))))[:min(k, V)]
+        keep = order[np.isfinite(x[r][order])]
+        assert np.array_equal(np.sort(np.flatnonzero(np.isfinite(got[r]))), np.sort(keep))
+        e = np.exp(x[r][keep].astype(np.float64) - x[r][keep[0]])
+        assert np.allclose(got[r][keep], np.log(e / e.sum()), rtol=0, atol=4e-6)   # ten float32 operations on numbers of order 10
+    assert np.all(lse.cpu().numpy() == 0)
