@@ -161,40 +161,7 @@ hipError_t launch_advance_len(int32_t* len, const int32_t* nspec, int B, int cap
 
 constexpr int MAXB = 8;
 
-struct TopList {
-  float key[MAXB];
-  int idx[MAXB];
-};
 __device__ __forceinline__ bool better(float k1, int i1, float k2, int i2) { return k1 > k2 || (k1 == k2 && i1 < i2); }
-
-__device__ __forceinline__ void list_init(TopList& L) {
-#pragma unroll
-  for (int p = 0; p < MAXB; ++p) { L.key[p] = -INFINITY; L.idx[p] = 0x7FFFFFFF; }
-}
-// keep the b best (sorted, best first); positions >= b stay empty
-__device__ __forceinline__ void list_insert(TopList& L, int b, float k, int i) {
-#pragma unroll
-  for (int p = MAXB - 1; p >= 0; --p) {
-    if (p == b - 1) {
-      if (!better(k, i, L.key[p], L.idx[p])) return;
-      L.key[p] = k;
-      L.idx[p] = i;
-    }
-    if (p < b - 1) {
-      if (better(L.key[p + 1], L.idx[p + 1], L.key[p], L.idx[p])) {
-        const float tk = L.key[p]; const int ti = L.idx[p];
-        L.key[p] = L.key[p + 1]; L.idx[p] = L.idx[p + 1];
-        L.key[p + 1] = tk; L.idx[p + 1] = ti;
-      }
-    }
-  }
-}
-__device__ __forceinline__ void list_pop(TopList& L) {
-#pragma unroll
-  for (int p = 0; p < MAXB - 1; ++p) { L.key[p] = L.key[p + 1]; L.idx[p] = L.idx[p + 1]; }
-  L.key[MAXB - 1] = -INFINITY;
-  L.idx[MAXB - 1] = 0x7FFFFFFF;
-}
 
 // (key, idx) as one unsigned number that is larger exactly where better() says so: the key's bits in an order that compares as
 // unsigned (both zeros alike; no NaN), then the complement of idx.
@@ -247,32 +214,70 @@ __device__ __forceinline__ uint64_t block_max_rank(uint64_t v, uint64_t* sh) {
   return row_max(sh[min((int)(threadIdx.x & 15), nw - 1)]);
 }
 
-// The b best entries of a workgroup of 256 threads with a sorted list each: every wave takes its b best (best head wins and is
-// popped), then wave 0 the b best of those.  All threads call it; out receives them, best first, before the barrier that ends it.
-// sh: 4 * MAXB entries.
-__device__ __forceinline__ void block_merge(TopList& L, int b, float* out_key, int* out_idx, uint64_t* sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int j = 0; j < b; ++j) {
-    const uint64_t head = rank_of(L.key[0], L.idx[0]);
-    const uint64_t w = wave_max_rank(head);
-    if (head == w && L.idx[0] != 0x7FFFFFFF) list_pop(L);  // candidate indices are unique, so exactly one owner
-    if (lane == 0) sh[wave * MAXB + j] = w;
+// The b best (b <= 8) of the entries the lanes of a wave hold, N each, and of `kept` (what an earlier call left): lane j < b gets
+// the j-th best, the others the empty entry.  b rounds over the lanes' best entries give a threshold; what reaches it (in at
+// most b lanes) is listed in LDS, and b more rounds pick from the list.  No lane searches its entries more than twice.
+// list: TOP_LIST entries of the wave's own.
+constexpr uint64_t NO_RANK = ((uint64_t)0x007FFFFFu << 32) | 0x80000000u;  // rank_of(-infinity, 0x7FFFFFFF)
+constexpr int TOP_N = 16, TOP_LIST = MAXB * (TOP_N + 1);
+template <int N>
+__device__ __forceinline__ uint64_t wave_top(const uint64_t (&e)[N], uint64_t kept, int b, uint64_t* list, int* count) {
+  static_assert(N <= TOP_N, "list size");
+  const int lane = threadIdx.x & 63;
+  uint64_t mine = kept;
+#pragma unroll
+  for (int j = 0; j < N; ++j) mine = e[j] > mine ? e[j] : mine;
+  uint64_t left = mine, T = 0;
+  for (int r = 0; r < b; ++r) {
+    T = wave_max_rank(left);
+    if (left == T) left = 0;
   }
+  T = T > NO_RANK ? T : NO_RANK + 1;  // empty entries are not listed
+  if (lane == 0) *count = 0;
+  __builtin_amdgcn_wave_barrier();
+  if (mine >= T) {
+    if (kept >= T) list[atomicAdd(count, 1)] = kept;
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if (e[j] >= T) list[atomicAdd(count, 1)] = e[j];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int n = *(volatile int*)count;
+  constexpr int P = (TOP_LIST + 63) / 64;
+  uint64_t c[P], top = NO_RANK;
+#pragma unroll
+  for (int p = 0; p < P; ++p) c[p] = lane + 64 * p < n ? ((volatile uint64_t*)list)[lane + 64 * p] : NO_RANK;
+  for (int r = 0; r < b; ++r) {
+    uint64_t m = c[0];
+#pragma unroll
+    for (int p = 1; p < P; ++p) m = c[p] > m ? c[p] : m;
+    m = wave_max_rank(m);
+    if (lane == r) top = m;
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      if (c[p] == m) c[p] = NO_RANK;
+  }
+  return top;
+}
+struct TopShared {
+  uint64_t list[4][TOP_LIST], best[4 * MAXB];
+  int count[4];
+};
+// the b best of a workgroup of 256 threads whose waves hold theirs as wave_top leaves them: lane j < b of wave 0 gets the j-th
+__device__ __forceinline__ uint64_t block_top(uint64_t top, int b, TopShared& sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane < MAXB) sh.best[wave * MAXB + lane] = lane < b ? top : NO_RANK;
   __syncthreads();
   if (wave == 0) {
-    const int list = lane / MAXB, pos = lane % MAXB;
-    uint64_t v = rank_of(-INFINITY, 0x7FFFFFFF);
-    if (list < 4 && pos < b) v = sh[list * MAXB + pos];
+    uint64_t v = lane < 4 * MAXB ? sh.best[lane] : NO_RANK;
     for (int j = 0; j < b; ++j) {
-      const uint64_t w = wave_max_rank(v);
-      if (v == w) v = rank_of(-INFINITY, 0x7FFFFFFF);
-      if (lane == 0) {
-        out_key[j] = rank_key(w);
-        out_idx[j] = rank_idx(w);
-      }
+      const uint64_t m = wave_max_rank(v);
+      if (v == m) v = NO_RANK;
+      if (lane == j) top = m;
     }
   }
-  __syncthreads();
+  return top;
 }
 
 // score of candidate (live beam r, token v): cum_logq[r] + (logit - lse), float32, in this order
@@ -287,11 +292,9 @@ __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restric
                                                           int R, int gamma, int beam, int V, int sample, uint64_t seed,
                                                           float* __restrict__ part_key, int* __restrict__ part_idx,
                                                           const float2* __restrict__ lse_part, int NP, float* __restrict__ lse_out) {
-  __shared__ uint64_t sh[4 * MAXB];
+  __shared__ TopShared sh;
   __shared__ float lse_sh[4], lse_s[MAXB];
   __shared__ float cum_s[MAXB];
-  __shared__ float okey[MAXB];
-  __shared__ int oidx[MAXB];
   const int s = blockIdx.y, G = gridDim.x;
   const int n_live = (step == 0) ? 1 : beam;
   int cnt = cu_cnt[s];
@@ -315,30 +318,33 @@ __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restric
       }
     }
   __syncthreads();
-  TopList L;
-  list_init(L);
-  // eight candidates at a time, their logits requested together: one memory latency, not eight (the insertion branches)
-  constexpr int U = 8;
-  for (int cb = c0 + (int)threadIdx.x; cb < c1; cb += 256 * U) {
-    float k[U];
+  // sixteen candidates per thread at a time, their logits requested together
+  const int wave = threadIdx.x >> 6;
+  uint64_t top = NO_RANK;
+  for (int cb = c0 + (int)threadIdx.x; cb - (int)threadIdx.x < c1; cb += 256 * TOP_N) {
+    uint64_t e[TOP_N];
+    float x[TOP_N];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int c = min(cb + 256 * u, c1 - 1), r = c / V, v = c % V;
-      k[u] = lse_part ? cum_s[r] + (logits[(int64_t)(row0 + r) * V + v] - lse_s[r]) : cand_score(logits, lse, cum_s, row0, r, v, V);
+    for (int u = 0; u < TOP_N; ++u) {
+      const int c = min(cb + 256 * u, c1 - 1), r = c / V;
+      x[u] = logits[(int64_t)row0 * V + c];  // rows of the live beams follow each other
+      x[u] = cum_s[r] + (x[u] - (lse_part ? lse_s[r] : lse[row0 + r]));
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < TOP_N; ++u) {
       const int c = cb + 256 * u;
-      if (c >= c1) continue;
-      if (sample) k[u] += gumbel(nk, (uint64_t)c);
-      if (!(k[u] == k[u])) k[u] = -INFINITY;  // a NaN score never wins and never leaves an empty slot behind
-      list_insert(L, beam, k[u], c);
+      e[u] = NO_RANK;
+      if (c < c1) {
+        if (sample) x[u] += gumbel(nk, (uint64_t)c);
+        e[u] = rank_of(x[u] == x[u] ? x[u] : -INFINITY, c);  // a NaN score never wins and never leaves an empty slot behind
+      }
     }
+    top = wave_top(e, top, beam, sh.list[wave], &sh.count[wave]);
   }
-  block_merge(L, beam, okey, oidx, sh);
-  if (threadIdx.x < beam) {
-    part_key[(s * G + blockIdx.x) * MAXB + threadIdx.x] = okey[threadIdx.x];
-    part_idx[(s * G + blockIdx.x) * MAXB + threadIdx.x] = oidx[threadIdx.x];
+  top = block_top(top, beam, sh);
+  if ((int)threadIdx.x < beam) {
+    part_key[(s * G + blockIdx.x) * MAXB + threadIdx.x] = rank_key(top);
+    part_idx[(s * G + blockIdx.x) * MAXB + threadIdx.x] = rank_idx(top);
   }
 }
 
@@ -347,34 +353,30 @@ __global__ __launch_bounds__(256) void topb_stage2_kernel(const float* __restric
                                                           const int32_t* __restrict__ cu_cnt, int step, int R, int gamma, int beam,
                                                           int V, int G, const float* __restrict__ part_key,
                                                           const int* __restrict__ part_idx) {
-  __shared__ uint64_t sh[4 * MAXB];
+  __shared__ TopShared sh;
   __shared__ float cum_s[MAXB];
-  __shared__ float okey[MAXB];
-  __shared__ int oidx[MAXB];
   const int s = blockIdx.x;
   int cnt = cu_cnt[s];
   if (cnt < 1 || cnt > gamma + 1) cnt = 1;
   const int row0 = s * R + ((step == 0) ? cnt - 1 : 0);
   if (threadIdx.x < MAXB)
     cum_s[threadIdx.x] = (step == 0 || (int)threadIdx.x >= beam) ? 0.f : hist.cum[(s * gamma + step - 1) * beam + threadIdx.x];
-  TopList L;
-  list_init(L);
-  for (int eb = threadIdx.x; eb < G * beam; eb += 512) {
-    float k[2];
-    int i[2];
+  const int wave = threadIdx.x >> 6;
+  uint64_t top = NO_RANK;
+  for (int eb = threadIdx.x; eb - (int)threadIdx.x < G * beam; eb += 512) {
+    uint64_t e[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int e = min(eb + 256 * u, G * beam - 1), at = (s * G + e / beam) * MAXB + e % beam;
-      k[u] = part_key[at];
-      i[u] = part_idx[at];
+      const int n = min(eb + 256 * u, G * beam - 1), at = (s * G + n / beam) * MAXB + n % beam;
+      const float k = part_key[at];
+      const int i = part_idx[at];
+      e[u] = eb + 256 * u < G * beam ? rank_of(k, i) : NO_RANK;
     }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (eb + 256 * u < G * beam && i[u] != 0x7FFFFFFF) list_insert(L, beam, k[u], i[u]);
+    top = wave_top(e, top, beam, sh.list[wave], &sh.count[wave]);
   }
-  block_merge(L, beam, okey, oidx, sh);
+  top = block_top(top, beam, sh);  // (its barrier also covers cum_s)
   if (threadIdx.x < beam) {
-    int c = oidx[threadIdx.x];
+    int c = rank_idx(top);
     if (c < 0 || c >= ((step == 0) ? 1 : beam) * V) c = 0;  // only reachable with non-finite logits: stay in bounds
     const int o = (s * gamma + step) * beam + threadIdx.x;
     const int r = c / V, v = c % V;
@@ -714,6 +716,7 @@ hipError_t launch_accept_spd(TreeView tree, const float* logits, const float* ls
 // A round costs one barrier and no look at the row (the owner of each winner searching its entries again, round by round,
 // was two thirds of 32 us per row).  The first 32768 entries of the row live in registers.
 constexpr int WARP_MAXK = 16, WARP_LIST = 2048;
+__device__ __forceinline__ float lane_value(float v, int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); }  // i uniform
 __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ logits, float* __restrict__ lse, int V, int top_k, float top_p) {
   __shared__ uint64_t sh[2][16];
   __shared__ uint64_t list[WARP_LIST];
@@ -804,19 +807,19 @@ __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ log
       }
     }
     const bool in = lane < k;
-    const float v = in ? rank_key(own) : -INFINITY, top = __shfl(v, 0, 64);
+    const float v = in ? rank_key(own) : -INFINITY, top = lane_value(v, 0);
     const float e = in ? expf(v - top) : 0.f;
     float S = 0.f;
-    for (int i = 0; i < k; ++i) S += __shfl(e, i, 64);
+    for (int i = 0; i < k; ++i) S += lane_value(e, i);
     const float p = e / S;
     float c = 0.f;
     int K = k;
     for (int i = 0; i < k; ++i) {
-      c += __shfl(p, i, 64);
+      c += lane_value(p, i);
       if (K == k && c > top_p) K = i + 1;
     }
     float s2 = 0.f;
-    for (int i = 0; i < K; ++i) s2 += __shfl(p, i, 64);
+    for (int i = 0; i < K; ++i) s2 += lane_value(p, i);
     if (in) {
       tv[lane] = logf(p / s2);
       ti[lane] = rank_idx(own);
@@ -830,9 +833,10 @@ __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ log
     __syncthreads();  // wave 0 does not read the row, but others may still be listing it
     for (int v = t; v < V; v += 1024) row[v] = -INFINITY;
   }
-  __builtin_amdgcn_s_waitcnt(0);  // the row's old values are overwritten before its new ones are written
   __syncthreads();
-  if (t < keep_s && ti[t] >= 0 && ti[t] < V) row[ti[t]] = tv[t];
+  // an entry's new value is written by the thread that overwrote its old one: one thread's stores to an address stay in order
+  for (int i = 0; i < keep_s; ++i)
+    if ((ti[i] & 1023) == t && ti[i] >= 0 && ti[i] < V) row[ti[i]] = tv[i];
 }
 
 hipError_t launch_warp_rows(float* logits, float* lse, int rows, int V, int top_k, float top_p, hipStream_t s) {
