@@ -14,15 +14,6 @@ struct AttnCfg {
   static constexpr int KSTRIDE = (sizeof(T) == 2) ? HD + 2 : HD + 1;  // odd dword stride: no bank conflicts
 };
 
-__device__ __forceinline__ float wsum(float v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-__device__ __forceinline__ float wmax(float v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
-}
-
 template <typename T, int HD, int NTHR>
 struct AttnSmem {
   using C = AttnCfg<T, HD>;
@@ -146,10 +137,10 @@ __device__ __forceinline__ void attn_item(AttnSmem<T, HD, NTHR>& sm, const float
       for (int r = w; r < RB; r += NW) {
         const float s = (lane < TK) ? s_s[r][lane] : -INFINITY;
         const float m_old = m_s[r];
-        const float m_new = fmaxf(m_old, wmax(s));
+        const float m_new = fmaxf(m_old, wave_max(s));
         const float p = (s == -INFINITY) ? 0.f : expf(s - m_new);
         const float alpha = (m_old == -INFINITY) ? 0.f : expf(m_old - m_new);
-        const float l_new = l_s[r] * alpha + wsum(p);
+        const float l_new = l_s[r] * alpha + wave_sum(p);
         if (lane < TK) s_s[r][lane] = p;
         if (lane == 0) {
           m_s[r] = m_new;

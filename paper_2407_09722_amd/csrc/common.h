@@ -206,9 +206,6 @@ hipError_t launch_embed(int dtype, const void* E, const int32_t* tok, float* h, 
                         void* planes, float* ssq, const int32_t* pos, float2* table, int head_dim, float theta, int ncg, hipStream_t s);
 // out = rmsnorm(h) * g, written as hi/lo bf16 planes [2][rows][d] (dtype 1) or f32 [rows][d] (dtype 0)
 hipError_t launch_rmsnorm(int dtype, const float* h, const float* g, void* out, int rows, int d, float eps, hipStream_t s);
-// rotate q (in place in qkv, float32), rotate k and write k, v to the cache in its storage type
-hipError_t launch_rope_kv(int dtype, float* qkv, const float2* table, const RowDesc& rd, KvView kv, int layer, int B, int R,
-                          int n_heads, uint32_t* status, hipStream_t s);
 // q: [rows][q_stride] float32 with head h at column h*head_dim; counters: zeroed ints [B][n_heads][ceil(R/16)], used by
 // the float32 kernel only (its last workgroup per item merges the key splits; bf16 models merge in a kernel of their own)
 hipError_t launch_attention(int dtype, const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads,
@@ -225,7 +222,6 @@ hipError_t launch_lse_finish(const float* lse_part, float* lse, int rows, int NP
 // lse as above for B*M rows, plus logp_cond[s][c] = logits[s][parent(c)][tok(c)] - lse[s][parent(c)] (0 for c = 0)
 hipError_t launch_lse_gather(const float* lse_part, float* lse, int B, int M, int NP, const float* logits, int V, const int32_t* parent,
                              const int32_t* tok, float* logp_cond, hipStream_t s);
-hipError_t launch_silu_mul(int dtype, const float* gu, void* act, int rows, int f, hipStream_t s);
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t s);
 hipError_t launch_row_lse(const float* logits, float* lse, int rows, int vocab, hipStream_t s);
 

@@ -60,7 +60,20 @@ bool gemm_dma_wide(int N);       // enough strips to give half of the compute un
 // workspace a context should offer for the k split of a product with N outputs (0 if it would never be split)
 size_t gemm_split_floats(int N);
 int gemm_split_counters(int N);
-hipError_t launch_gemm_f32(const void* W, const void* X, float* Y, int R, int N, int K, int ldy, bool accumulate, hipStream_t s);
+// float32 models (row-major W [N][K], X [R][K]): EPI_STORE Y (+)= product; EPI_SWIGLU Y[R][N/2] = silu(gate) * up; EPI_QKV rotated q
+// to Y (columns 0 .. n_heads * head_dim), rotated k and v to the cache.  With `gain` the input is RMS-normalised first.
+struct GemmF32Args {
+  const float *W, *X, *gain;
+  float* Y;
+  int R, N, K, ldy, accumulate;
+  float eps;
+  const float2* rope;
+  const int32_t* slot;
+  KvView kv;
+  int layer, Rseq, n_heads;
+  uint32_t* status;
+};
+hipError_t launch_gemm_f32(const GemmF32Args& a, int epi, hipStream_t s);
 hipError_t launch_pack_matrix(const void* src, void* dst, int N, int K, int kind, int head_dim, hipStream_t s);
 
 }  // namespace mtad

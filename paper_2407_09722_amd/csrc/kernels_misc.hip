@@ -1,5 +1,5 @@
 // Row-wise pieces of the decoder pass: embedding gather, RMSNorm (wavefront reductions), the rotary
-// table, rotary + KV-cache write, SwiGLU gating and the row-wise logsumexp of the logits.
+// table and the row-wise logsumexp of the logits.
 // All of them move a few KB..MB per launch; they are latency bound, not bandwidth bound.
 #include "common.h"
 
@@ -107,70 +107,6 @@ hipError_t launch_rmsnorm(int dtype, const float* h, const float* g, void* out, 
   if (d % 4) return hipErrorInvalidValue;
   if (dtype == 1) hipLaunchKernelGGL((rmsnorm_kernel<bf16_t>), dim3(rows), dim3(256), 0, s, h, g, (bf16_t*)out, d, eps);
   else hipLaunchKernelGGL((rmsnorm_kernel<float>), dim3(rows), dim3(256), 0, s, h, g, (float*)out, d, eps);
-  return hipGetLastError();
-}
-
-// grid (rows, n_heads + 2*n_kv_heads), block head_dim/2.  q heads: rotated in place (float32).
-// k heads: rotated and stored to the cache in its storage type; v heads: stored to the cache.
-template <typename T>
-__global__ void rope_kv_kernel(float* __restrict__ qkv, const float2* __restrict__ table, RowDesc rd, KvView kv, int layer, int R,
-                               int n_heads, uint32_t* __restrict__ status) {
-  const int row = blockIdx.x, head = blockIdx.y, i = threadIdx.x;
-  const int hd = kv.head_dim, half = hd >> 1, KVH = kv.n_kv_heads;
-  const int width = (n_heads + 2 * KVH) * hd;
-  float* p = qkv + (int64_t)row * width + (int64_t)head * hd;
-  const float x1 = p[i], x2 = p[i + half];
-  const float2 cs = table[(int64_t)row * half + i];
-  if (head < n_heads) {
-    p[i] = x1 * cs.x - x2 * cs.y;
-    p[i + half] = x2 * cs.x + x1 * cs.y;
-    return;
-  }
-  const int slot = rd.slot[row];
-  if (slot < 0) return;
-  if (slot >= kv_capacity(kv)) {
-    if (i == 0) atomicOr(status, (uint32_t)ST_KV_CAP);
-    return;
-  }
-  const int seq = row / R;
-  const bool is_k = head < n_heads + KVH;
-  const int g = is_k ? head - n_heads : head - n_heads - KVH;
-  const int64_t off = (int64_t)layer * kv.layer_stride + kv_token_offset(kv, seq, slot) + (int64_t)g * hd;
-  T* dst = (T*)(is_k ? kv.k : kv.v) + off;
-  float y1 = x1, y2 = x2;
-  if (is_k) { y1 = x1 * cs.x - x2 * cs.y; y2 = x2 * cs.x + x1 * cs.y; }
-  dst[i] = (T)y1;
-  dst[i + half] = (T)y2;
-}
-
-hipError_t launch_rope_kv(int dtype, float* qkv, const float2* table, const RowDesc& rd, KvView kv, int layer, int B, int R,
-                          int n_heads, uint32_t* status, hipStream_t s) {
-  const int rows = B * R;
-  if (rows <= 0) return hipSuccess;
-  dim3 grid(rows, n_heads + 2 * kv.n_kv_heads), block(kv.head_dim / 2);
-  if (dtype == 1) return hipErrorInvalidValue;  // bf16 models rotate and store in the QKV product's epilogue
-  else hipLaunchKernelGGL((rope_kv_kernel<float>), grid, block, 0, s, qkv, table, rd, kv, layer, R, n_heads, status);
-  return hipGetLastError();
-}
-
-// act[row][j] = silu(gu[row][j]) * gu[row][f + j]
-template <typename T>
-__global__ void silu_mul_kernel(const float* __restrict__ gu, T* __restrict__ act, int rows, int f) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)rows * f) return;
-  const int row = (int)(idx / f), j = (int)(idx % f);
-  const float g = gu[(int64_t)row * 2 * f + j], u = gu[(int64_t)row * 2 * f + f + j];
-  const float a = g / (1.0f + expf(-g)) * u;
-  if constexpr (sizeof(T) == 2) split_bf16(a, act[idx], act[(int64_t)rows * f + idx]);
-  else act[idx] = a;
-}
-
-hipError_t launch_silu_mul(int dtype, const float* gu, void* act, int rows, int f, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  const int64_t n = (int64_t)rows * f;
-  const int blocks = (int)((n + 255) / 256);
-  if (dtype == 1) hipLaunchKernelGGL((silu_mul_kernel<bf16_t>), dim3(blocks), dim3(256), 0, s, gu, (bf16_t*)act, rows, f);
-  else hipLaunchKernelGGL((silu_mul_kernel<float>), dim3(blocks), dim3(256), 0, s, gu, (float*)act, rows, f);
   return hipGetLastError();
 }
 

@@ -25,7 +25,7 @@ struct mtad_ctx {
   size_t ws_need;
   char* ws;
   // workspace carve-up
-  float *h, *qkv, *gu, *dlogits, *lse, *partial, *part_key, *ssq, *lse_part;
+  float *h, *qkv, *dlogits, *lse, *partial, *part_key, *ssq, *lse_part;
   float* ssq_sum;    // [rows of a prompt chunk]
   size_t partial_n;  // floats
   float* qrows;  // [batch][gamma][draft vocab]: log q of every draft step's live row when the beam is one wide (mtad_accept_spd)
@@ -178,7 +178,6 @@ void carve(mtad_ctx* c, char* base) {
 #endif
   }
   c->qkv = k.take<float>(imax64(rows * qkv, prompt * hhd));  // float32 models: q, k and v; bf16 models: q
-  c->gu = k.take<float>(rows * 2 * fmax);
   c->dlogits = k.take<float>((size_t)c->cfg.batch * c->draft_rows * d.vocab);
   c->qrows = k.take<float>(c->cfg.beam == 1 ? (size_t)c->cfg.batch * c->cfg.gamma * d.vocab : 1);
   c->lse = k.take<float>(rows);
@@ -257,18 +256,24 @@ int decoder_pass_f32(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R,
   const int n_splits = splits_for(c, m, R);
   const void* const* W = m->weights;
   HIP_TRY(c, launch_embed(0, W[0], c->rd.tok, c->h, rows, d, m->vocab, nullptr, nullptr, nullptr, c->rd.pos, c->rope, hd, m->rope_theta, 0, s));
+  GemmF32Args a;
+  memset(&a, 0, sizeof(a));
+  a.R = rows; a.eps = m->rms_eps;
+  a.rope = c->rope; a.slot = c->rd.slot; a.kv = kvv; a.Rseq = R; a.n_heads = H; a.status = c->status;
+  auto product = [&](int epi, const void* w, const float* x, const void* gain, float* y, int N, int K, int ldy, int accumulate) {
+    a.W = (const float*)w; a.X = x; a.gain = (const float*)gain; a.Y = y; a.N = N; a.K = K; a.ldy = ldy; a.accumulate = accumulate;
+    return launch_gemm_f32(a, epi, s);
+  };
+  float* const xn = (float*)c->xn;
   for (int l = 0; l < m->n_layers; ++l) {
     const void* const* L = W + 1 + 6 * l;
-    HIP_TRY(c, launch_rmsnorm(0, c->h, (const float*)L[0], c->xn, rows, d, m->rms_eps, s));
-    HIP_TRY(c, launch_gemm_f32(L[1], c->xn, c->qkv, rows, qkvw, d, qkvw, false, s));
-    HIP_TRY(c, launch_rope_kv(0, c->qkv, c->rope, c->rd, kvv, l, B, R, H, c->status, s));
+    a.layer = l;
+    HIP_TRY(c, product(EPI_QKV, L[1], c->h, L[0], c->qkv, qkvw, d, qkvw, 0));
     if (cache_only && l + 1 == m->n_layers) break;  // nothing reads the last layer's hidden states
     HIP_TRY(c, launch_attention(0, c->qkv, qkvw, c->rd, kvv, l, B, R, H, c->partial, n_splits, c->attn_cnt, c->xn, 0, s));
-    HIP_TRY(c, launch_gemm_f32(L[2], c->xn, c->h, rows, d, H * hd, d, true, s));
-    HIP_TRY(c, launch_rmsnorm(0, c->h, (const float*)L[3], c->xn, rows, d, m->rms_eps, s));
-    HIP_TRY(c, launch_gemm_f32(L[4], c->xn, c->gu, rows, 2 * f, d, 2 * f, false, s));
-    HIP_TRY(c, launch_silu_mul(0, c->gu, c->xn, rows, f, s));
-    HIP_TRY(c, launch_gemm_f32(L[5], c->xn, c->h, rows, d, f, d, true, s));
+    HIP_TRY(c, product(EPI_STORE, L[2], xn, nullptr, c->h, d, H * hd, d, 1));
+    HIP_TRY(c, product(EPI_SWIGLU, L[4], c->h, L[3], xn, 2 * f, d, f, 0));
+    HIP_TRY(c, product(EPI_STORE, L[5], xn, nullptr, c->h, d, f, d, 1));
   }
   return MTAD_OK;
 }
@@ -461,8 +466,11 @@ int lm_head(mtad_ctx* c, const mtad_model* m, int rows, float* logits, float* ls
     HIP_TRY(c, launch_gemm_bf16(a, EPI_STORE, same_shape(m, &c->tshape) ? 1 : 0, s));
     return finish_lse(c, m, rows, logits, lse, s);
   }
-  HIP_TRY(c, launch_rmsnorm(0, c->h, (const float*)W[tail], c->xn, rows, m->d_model, m->rms_eps, s));
-  HIP_TRY(c, launch_gemm_f32(W[tail + 1], c->xn, logits, rows, m->vocab, m->d_model, m->vocab, false, s));
+  GemmF32Args a;
+  memset(&a, 0, sizeof(a));
+  a.W = (const float*)W[tail + 1]; a.X = c->h; a.gain = (const float*)W[tail]; a.Y = logits;
+  a.R = rows; a.N = m->vocab; a.K = m->d_model; a.ldy = m->vocab; a.eps = m->rms_eps;
+  HIP_TRY(c, launch_gemm_f32(a, EPI_STORE, s));
   HIP_TRY(c, launch_row_lse(logits, lse, rows, m->vocab, s));
   return MTAD_OK;
 }
@@ -747,7 +755,13 @@ int mtad_k_gemm_x(mtad_ctx* c, int32_t dtype, const void* W, const void* X, floa
   if (dtype == 0 && x_order != MTAD_X_PLANES) return MTAD_EINVAL;
   if (dtype == 1 && ((N % 16) || (K % 32) || (ldy % 4) || R > 256)) return MTAD_ESHAPE;
   if (dtype == 0 && (K % 4)) return MTAD_ESHAPE;
-  if (dtype == 0) return launch_gemm_f32(W, X, Y, R, N, K, ldy, accumulate != 0, (hipStream_t)stream) == hipSuccess ? MTAD_OK : MTAD_EHIP;
+  if (dtype == 0) {
+    GemmF32Args f;
+    memset(&f, 0, sizeof(f));
+    f.W = (const float*)W; f.X = (const float*)X; f.Y = Y;
+    f.R = R; f.N = N; f.K = K; f.ldy = ldy; f.accumulate = accumulate != 0;
+    return launch_gemm_f32(f, EPI_STORE, (hipStream_t)stream) == hipSuccess ? MTAD_OK : MTAD_EHIP;
+  }
   GemmArgs a;
   memset(&a, 0, sizeof(a));
   a.W = (const bf16_t*)W; a.X = (const bf16_t*)X; a.R = R; a.N = N; a.K = K;
