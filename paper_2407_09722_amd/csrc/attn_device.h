@@ -101,23 +101,38 @@ __device__ __forceinline__ void attn_item(AttnSmem<T, HD, NTHR>& sm, const float
 #pragma unroll
       for (int i = 0; i < RPT; ++i) sacc[i] = 0.f;
       const T* krow = k_s + j * KS;
-#pragma unroll 8
-      for (int d = 0; d < HD; d += 2) {
-        float k0, k1;
+      auto key2 = [&](int d) {
         if constexpr (sizeof(T) == 2) {
           typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
           const half2_t w = *(const half2_t*)(krow + d);
-          k0 = (float)w[0];
-          k1 = (float)w[1];
+          return make_float2((float)w[0], (float)w[1]);
         } else {
-          k0 = krow[d];
-          k1 = krow[d + 1];
+          return make_float2(krow[d], krow[d + 1]);
         }
+      };
+      // Up to half the item's rows: row after row, and only the rows there are, instead of all RB rows per key element.  The
+      // dot products bound the item (256 threads, serial over HD): 4 heads x 64, 5 rows, 82 keys 11.4 -> 10.6 us.
+      if (nrows <= RB / 2) {
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          const float2 qq = *(const float2*)&q_s[rg + NRG * i][d];
-          sacc[i] = fmaf(qq.x, k0, sacc[i]);
-          sacc[i] = fmaf(qq.y, k1, sacc[i]);
+        for (int i = 0; i < RPT; ++i)
+          if (rg + NRG * i < nrows) {
+#pragma unroll 8
+            for (int d = 0; d < HD; d += 2) {
+              const float2 kk = key2(d), qq = *(const float2*)&q_s[rg + NRG * i][d];
+              sacc[i] = fmaf(qq.x, kk.x, sacc[i]);
+              sacc[i] = fmaf(qq.y, kk.y, sacc[i]);
+            }
+          }
+      } else {
+#pragma unroll 8
+        for (int d = 0; d < HD; d += 2) {
+          const float2 kk = key2(d);
+#pragma unroll
+          for (int i = 0; i < RPT; ++i) {
+            const float2 qq = *(const float2*)&q_s[rg + NRG * i][d];
+            sacc[i] = fmaf(qq.x, kk.x, sacc[i]);
+            sacc[i] = fmaf(qq.y, kk.y, sacc[i]);
+          }
         }
       }
       const int kj = tile + j;
@@ -134,7 +149,7 @@ __device__ __forceinline__ void attn_item(AttnSmem<T, HD, NTHR>& sm, const float
     // running softmax statistics: wave w owns rows w, w+4, ...
     {
       const int lane = t & 63, w = t >> 6;
-      for (int r = w; r < RB; r += NW) {
+      for (int r = w; r < nrows; r += NW) {
         const float s = (lane < TK) ? s_s[r][lane] : -INFINITY;
         const float m_old = m_s[r];
         const float m_new = fmaxf(m_old, wave_max(s));
@@ -154,12 +169,22 @@ __device__ __forceinline__ void attn_item(AttnSmem<T, HD, NTHR>& sm, const float
     // output accumulation: thread (dim d, row group rg2)
     {
       const int d = t % HD, rg2 = t / HD;
+      if (nrows <= RB / 2) {
 #pragma unroll
-      for (int i = 0; i < RPT2; ++i) acc[i] *= a_s[rg2 + NRG2 * i];
-      for (int j = 0; j < TK; ++j) {
-        const float v = (float)v_s[j * HD + d];
+        for (int i = 0; i < RPT2; ++i)
+          if (rg2 + NRG2 * i < nrows) {
+            acc[i] *= a_s[rg2 + NRG2 * i];
+#pragma unroll 8
+            for (int j = 0; j < TK; ++j) acc[i] = fmaf(s_s[rg2 + NRG2 * i][j], (float)v_s[j * HD + d], acc[i]);
+          }
+      } else {
 #pragma unroll
-        for (int i = 0; i < RPT2; ++i) acc[i] = fmaf(s_s[rg2 + NRG2 * i][j], v, acc[i]);
+        for (int i = 0; i < RPT2; ++i) acc[i] *= a_s[rg2 + NRG2 * i];
+        for (int j = 0; j < TK; ++j) {
+          const float v = (float)v_s[j * HD + d];
+#pragma unroll
+          for (int i = 0; i < RPT2; ++i) acc[i] = fmaf(s_s[rg2 + NRG2 * i][j], v, acc[i]);
+        }
       }
     }
   }
