@@ -207,13 +207,14 @@ hipError_t launch_embed(int dtype, const void* E, const int32_t* tok, float* h, 
 // out = rmsnorm(h) * g, written as hi/lo bf16 planes [2][rows][d] (dtype 1) or f32 [rows][d] (dtype 0)
 hipError_t launch_rmsnorm(int dtype, const float* h, const float* g, void* out, int rows, int d, float eps, hipStream_t s);
 // q: [rows][q_stride] float32 with head h at column h*head_dim; counters: zeroed ints [B][n_heads][ceil(R/16)], used by
-// the float32 kernel only (its last workgroup per item merges the key splits; bf16 models merge in a kernel of their own)
+// the last workgroup of an item, which merges the key splits (bf16 models: in passes of few rows, else a kernel of its own does)
 hipError_t launch_attention(int dtype, const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads,
                             float* partial, int n_splits, int* counters, void* out, int ncg, hipStream_t s);
 // bf16 models (kernels_attn_mfma.hip): half-precision cache, output = bf16 hi / lo terms (layout: act_offset with ncg);
-// n_splits = upper bound on the key splits (the kernel uses fewer for short contexts)
+// n_splits = upper bound on the key splits (the kernel uses fewer for short contexts); counters (zeroed, [B][n_kv_heads], or null): a pass
+// of few rows merges its key splits in the same launch
 hipError_t launch_attention_mfma(const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads,
-                                 float* partial, int n_splits, void* out, int ncg, hipStream_t s);
+                                 float* partial, int n_splits, void* out, int ncg, hipStream_t s, int* counters = nullptr);
 // the same for a chunk of a prompt: any number of rows per sequence, row r sees the committed context and rows 0 .. r
 hipError_t launch_attention_prompt(const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads, float* partial,
                                    int n_splits, void* out, int ncg, hipStream_t s);

@@ -18,6 +18,8 @@ namespace mtad {
 
 namespace {
 
+constexpr int FEW_ROWS = 64;  // (sequence, query head, row) triples of a pass that merges its key splits in the attention launch
+
 template <int HD, int NRG, int AW, bool CAUSAL>
 __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(2))) void tree_attn_mfma_kernel(const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer,
                                                                int R, int n_heads, int n_chunks, float scale, float* __restrict__ partial,
@@ -33,6 +35,39 @@ __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   tree_attn_item<HD, NRG, AW, NSET, AW * 64, false, 1, CAUSAL>(sm, q, q_stride, rd, kv, layer, (int)gridDim.z, R, n_heads, n_chunks, scale, partial,
                                                               n_splits, out, want_splits, ncg, (int)blockIdx.x, g, chunk, (int)blockIdx.z,
                                                               (int)threadIdx.x);
+}
+
+// The same item for passes of few rows in all (small models): the key split that arrives last for an item merges its rows,
+// one wave a row, instead of a launch of its own for a handful of waves.  Bound by latency: 12 heads x 64, one row, 256 keys:
+// 9.0 us against 6.3 + 3.1 in two launches and the gap between them (12 layers: 323 -> 311 us).
+// counters: one zeroed word per item, left zeroed.  At most ATTN_WAVES rows an item.
+template <int HD>
+__global__ __launch_bounds__(ATTN_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2))) void tree_attn_few_kernel(
+    const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int R, int n_heads, float scale, float* __restrict__ partial, int n_splits,
+    bf16_t* __restrict__ out, int want_splits, int ncg, int* __restrict__ counters) {
+  __shared__ MfmaAttnSmem<HD, 1, ATTN_WAVES> sm;
+  __shared__ int last_s;
+  const int B = gridDim.z, split = blockIdx.x, g = blockIdx.y, seq = blockIdx.z, t = threadIdx.x;
+  const int eff = tree_attn_item<HD, 1, ATTN_WAVES, 2, ATTN_WAVES * 64, true>(sm, q, q_stride, rd, kv, layer, B, R, n_heads, 1, scale, partial, n_splits, out,
+                                                                            want_splits, ncg, split, g, 0, seq, t);
+  if (eff == 1 || split >= eff) return;  // uniform: the item wrote its output itself, or there was no such split
+  __builtin_amdgcn_s_waitcnt(0);  // the partial results have been acknowledged
+  __syncthreads();
+  if (t == 0) {
+    int* const c = counters + seq * gridDim.y + g;
+    const int prev = __hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last_s = prev == eff - 1;
+    if (prev == eff - 1) __hip_atomic_store(c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // clean for the next launch
+  }
+  __syncthreads();
+  if (!last_s) return;
+  const int G = n_heads / kv.n_kv_heads;
+  const int p = t >> 6;
+  if (p < G * R) {
+    const int head = g * G + p / R, row = p % R;
+    attn_merge_row<HD, true>(partial + (((int64_t)seq * n_heads + head) * R + row) * n_splits * (HD + 2), eff, out, ncg, B * R, n_heads * HD, seq * R + row, head,
+                             t & 63);
+  }
 }
 
 // Merge of the key splits, a kernel of its own: one wave per (sequence, query head, row).  As a separate launch it is
@@ -54,7 +89,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(RowDesc rd, KvView kv, 
 
 template <int HD, int NRG, int AW, bool CAUSAL = false>
 hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvView& kv, int layer, int B, int R, int n_heads, float* partial,
-                    int n_splits, void* out, int ncg, hipStream_t s) {
+                    int n_splits, void* out, int ncg, hipStream_t s, int* counters = nullptr) {
   const int KVH = kv.n_kv_heads, G = n_heads / KVH;
   const int n_chunks = (G * R + NRG * 16 - 1) / (NRG * 16);  // chunks of (query head, row) pairs per KV head
   const float scale = 1.0f / sqrtf((float)HD);
@@ -85,6 +120,17 @@ hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvVie
   const int want = fill8 | (more8 << 8);
   const int widest = fill8 > more8 ? fill8 : more8;
   const int gx = n_splits < widest ? n_splits : widest;
+  if constexpr (NRG == 1 && !CAUSAL) {
+    // Six layers, us, two launches / one (rows = sequences x heads x rows each): 12 heads x 64, 12 rows, 256 / 2048 keys 164 / 153,
+    // 179 / 171; 48 rows 170 / 159, 216 / 208; 32 heads x 64, 64 rows 218 / 198, 241 / 234.  Beyond, the last workgroups' merges
+    // are no longer hidden: 96 rows, 2048 keys 252 / 261; 512 rows 292 / 315, 584 / 618.  Items of 8 rows (8 query heads on a key
+    // head), two to a wave and few items to split the keys over: 2048 keys 204 / 211.
+    if (counters && gx > 1 && B * n_heads * R <= FEW_ROWS && G * R <= ATTN_WAVES) {
+      hipLaunchKernelGGL((tree_attn_few_kernel<HD>), dim3(gx, KVH, B), dim3(AW * 64), 0, s, q, q_stride, rd, kv, layer, R, n_heads, scale, partial, n_splits,
+                         (bf16_t*)out, want, ncg, counters);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL(kern, dim3(gx, KVH * n_chunks, B), dim3(AW * 64), lds, s, q, q_stride, rd, kv, layer, R, n_heads, n_chunks, scale,
                      partial, n_splits, (bf16_t*)out, want, ncg);
   hipError_t e = hipGetLastError();
@@ -100,15 +146,15 @@ hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvVie
 // bf16 models: q float32 [B*R][q_stride], half-precision cache, output = bf16 hi / lo planes [2][B*R][n_heads*hd].
 // Passes of up to 16 rows per sequence use 16-row work items, larger ones 32-row items (K and V are read once per item).
 hipError_t launch_attention_mfma(const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads,
-                                 float* partial, int n_splits, void* out, int ncg, hipStream_t s) {
+                                 float* partial, int n_splits, void* out, int ncg, hipStream_t s, int* counters) {
   const int hd = kv.head_dim;
   if (kv.n_kv_heads < 1 || n_heads % kv.n_kv_heads) return hipErrorInvalidValue;
   const int pairs = n_heads / kv.n_kv_heads * R;  // (query head, row) pairs that share a KV head
-  if (hd == 128 && pairs <= 16) return run_mfma<128, 1, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (hd == 128 && pairs <= 16) return run_mfma<128, 1, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s, counters);
   if (hd == 128 && pairs > 32 && pairs <= 48)  // one item instead of two that would each read K and V
     return run_mfma<128, 3, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
   if (hd == 128) return run_mfma<128, 2, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
-  if (hd == 64 && pairs <= 16) return run_mfma<64, 1, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (hd == 64 && pairs <= 16) return run_mfma<64, 1, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s, counters);
   if (hd == 64) return run_mfma<64, 2, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
   return hipErrorInvalidValue;
 }

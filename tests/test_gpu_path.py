@@ -305,3 +305,21 @@ def test_prompt_chunk_past_the_cache_end():
         eng.close()
     for a, b in zip(*caches):
         assert np.all(np.abs(a - b) <= 2e-3 * np.maximum(1, np.abs(b)))   # two roundings to half precision (2^-11 each) and chunk orders
+
+
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,gamma,n", [
+    (64, 16, 16, 2, 1, 300),     # 64 (head, row) pairs of a pass: the most whose key splits are merged in the attention launch
+    (64, 11, 11, 3, 1, 300),     # 66: the fewest that a launch of its own merges
+    (128, 4, 2, 1, 1, 700),      # two heads and two rows per item: each wave of the last workgroup merges one
+    (64, 4, 2, 1, 2, 700),       # six rows per item: a launch of its own
+    (64, 3, 3, 1, 3, 150),       # a cache that starts with few key splits and gains one on the way
+])
+def test_key_splits_of_few_rows(hd, heads, kv_heads, batch, gamma, n):
+    """Both ways the key splits of a pass of few rows are merged, every iteration against the oracle."""
+    ts = si.ModelShape(2, heads * hd, heads, kv_heads, hd, 352, 512, "bf16")
+    ds = si.ModelShape(1, 64, 1, 1, 64, 160, 512, "bf16")
+    wt, wd = _weights(ts, 31, "target", boost=2.0), _weights(ds, 31, "draft", boost=2.0)
+    prompt = np.random.default_rng(n).integers(0, ts.vocab, (batch, n)).astype(np.int32)
+    print(f"key splits hd {hd} heads {heads}/{kv_heads} batch {batch} gamma {gamma} n {n}", flush=True)
+    st = run_pair(ts, ds, wt, wd, prompt, 8, gamma=gamma, beam=2, mode="mtad", tau=0.0, seed=5, check_kv=True, fused_pass=0)
+    assert st["excused"] == 0 and all(e == gamma for e in st["eta"])
