@@ -708,14 +708,14 @@ hipError_t launch_accept_spd(TreeView tree, const float* logits, const float* ls
 // prefix whose cumulative probability exceeds top_p; normalised again), minus infinity outside the support, and the
 // row's logsumexp becomes 0, so that every consumer of (logits, lse) rows works on p~ unchanged.  Entries rank by value
 // descending, token id ascending; a NaN ranks last.
-//   1. every thread's best entry; top_k rounds of a workgroup-wide maximum over those give the top_k-th best of them, T
-//   2. the top_k entries of the row are among the entries that rank T or better, and those lie in the top_k threads whose best
-//      ranks T or better: they are listed in LDS (10 to 30 of them in a row of 32000 distinct logits, never more than
-//      top_k * V / 1024)
+//   1. every wave's best entry; T = the top_k-th best of those 16.  The top_k entries of the row rank T or better, and so do
+//      few others (10 to 60 in a row of logits in no order): they are listed in LDS.
+//   2. a row whose best entries share a few waves lists more than WARP_SHORT: T is then the top_k-th best of the threads' best
+//      entries, in top_k rounds of a workgroup-wide maximum, and at most top_k * V / 1024 rank T or better
 //   3. wave 0 takes the top_k best of the list and does the arithmetic, one token per lane, sums in descending order
-// A round costs one barrier and no look at the row (the owner of each winner searching its entries again, round by round,
-// was two thirds of 32 us per row).  The first 32768 entries of the row live in registers.
-constexpr int WARP_MAXK = 16, WARP_LIST = 2048;
+// Bound by its chain of steps, one compute unit per row; 32000 tokens, top_k 10: 15 us with T from the waves, 20 with T from
+// the threads' rounds for every row (a barrier each).  The first 32768 entries of the row live in registers.
+constexpr int WARP_MAXK = 16, WARP_LIST = 2048, WARP_SHORT = 512;
 __device__ __forceinline__ float lane_value(float v, int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); }  // i uniform
 __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ logits, float* __restrict__ lse, int V, int top_k, float top_p) {
   __shared__ uint64_t sh[2][16];
@@ -751,13 +751,8 @@ __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ log
   const bool held = V <= 1024 * PT;
   if (held)
     for (int v = t; v < V; v += 1024) row[v] = -INFINITY;
-  uint64_t T = 0, left = mine;
-  const int rounds = min(k, min(V, 1024));  // threads with an entry
-  for (int r = 0; r < rounds; ++r) {
-    T = block_max_rank(left, sh[r & 1]);  // (everybody has read the other buffer before this one's barrier)
-    if (left == T) left = 0;
-  }
-  if (mine >= T) {
+  auto list_from = [&](uint64_t T) {  // what ranks T or better
+    if (mine < T) return;
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
       const uint64_t r = rank_of(x[j], t + 1024 * j);
@@ -773,9 +768,33 @@ __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ log
         if (o < WARP_LIST) list[o] = r;
       }
     }
+  };
+  const uint64_t wave_best = wave_max_rank(mine);
+  if (lane == 0) sh[0][t >> 6] = wave_best;
+  __syncthreads();
+  {
+    const uint64_t w = sh[0][lane & 15];
+    int above = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) above += sh[0][i] > w;
+    list_from(~wave_max_rank(above < k ? ~w : 0));
   }
   __syncthreads();
   int n = count;
+  if (n > WARP_SHORT) {
+    __syncthreads();
+    if (t == 0) count = 0;
+    uint64_t T = 0, left = mine;
+    const int rounds = min(k, min(V, 1024));  // threads with an entry
+    for (int r = 0; r < rounds; ++r) {
+      T = block_max_rank(left, sh[r & 1]);  // (everybody has read the other buffer before this one's barrier)
+      if (left == T) left = 0;
+    }
+    __syncthreads();
+    list_from(T);
+    __syncthreads();
+    n = count;
+  }
   if (n > WARP_LIST) {  // only with more than 131072 tokens, and rows whose best entries share a few threads: one token a round
     uint64_t prev = ~0ull;
     for (int r = 0; r < k; ++r) {

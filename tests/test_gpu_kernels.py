@@ -249,7 +249,7 @@ def test_row_lse():
 
 
 @pytest.mark.parametrize("V,k,kind", [(1000, 10, "plain"), (7, 16, "plain"), (1024, 16, "same"), (32768, 10, "plain"), (32769, 16, "plain"), (33000, 10, "same"),
-                                      (40000, 16, "low"), (140000, 16, "stride"), (200000, 3, "plain"), (32000, 10, "zeros")])
+                                      (40000, 16, "low"), (140000, 16, "stride"), (200000, 3, "plain"), (32000, 10, "zeros"), (32000, 10, "waves")])
 def test_warp_rows_supports_of_every_layout(V, k, kind):
     """The support of the warped row is that of a stable descending sort: rows shorter and longer than the registers hold, one
     value everywhere, minus infinities, zeros of both signs, best entries that all fall to one thread (more than its list holds)."""
@@ -265,6 +265,8 @@ def test_warp_rows_supports_of_every_layout(V, k, kind):
         x[:, ::3] = 0.0
     elif kind == "stride":                                            # 137 entries per thread, the largest in threads 0 .. 15
         x[:, np.arange(V) % 1024 < 16] += 100.0
+    elif kind == "waves":                                             # 4000 entries of two waves above all others
+        x[:, np.arange(V) % 1024 < 128] += 100.0
     xd = torch.from_numpy(x).to(DEV)
     lse = torch.full((3,), 7.0, device=DEV)
     print(f"warp rows V={V} k={k} {kind}", flush=True)
