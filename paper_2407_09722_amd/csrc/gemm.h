@@ -51,8 +51,12 @@ struct GemmArgs {
 // *np (may be null): partial sums of squares per row an EPI_RESID product left in ssq_out
 hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, int* np = nullptr);
 // the same product for passes of many rows, fragments copied to LDS by the loads themselves (kernels_gemm_dma.hip); chosen by
-// launch_gemm_bf16
-hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* np);
+// launch_gemm_bf16.  tiles: instead of the planned ones (refused where they do not exist or fit)
+struct GemmTiles {
+  int strips, row_groups, tall, ranges;  // strips per wave, groups of 64 rows, wave groups side by side, ranges of the reduction
+};
+hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* np, const GemmTiles* tiles = nullptr);
+GemmTiles gemm_dma_tiles(const GemmArgs& a, int epi);  // the planned ones
 size_t gemm_dma_xfrag_elems(int R, int K);  // scratch a product of R rows on plane input wants
 size_t gemm_dma_split_floats();  // workspace its cut of the reduction dimension may take
 hipError_t launch_ssq_rows(const float* in, float* out, int R, int NP, hipStream_t s);  // out[m] = sum of in[m][0 .. NP)

@@ -625,6 +625,12 @@ struct Plan {
   bool tall;
 };
 constexpr int KS_MAX = 8;
+// partial sums per range must add up to the whole product, and what reads them (run_sum) knows neither row factors nor logsumexps
+bool can_cut(const GemmArgs& a, int epi) { return a.part && !(epi == EPI_STORE && (a.lse_part || a.ssq)); }
+bool cut_fits(const GemmArgs& a, int KS) {
+  const int KT = a.K >> 5, per = (KT + KS - 1) / KS;
+  return KS <= KS_MAX && per * (KS - 1) < KT /* no range is empty */ && (size_t)KS * a.R * a.N <= a.part_floats;
+}
 
 // Rows per workgroup (64 to 256), strips per workgroup (4 to 8, or 10 to 16 with the groups side by side where 129 rows and more
 // meet) and ranges of the reduction dimension: the cheapest by a count of clocks per compute unit.  A k tile lasts as long as its
@@ -634,14 +640,14 @@ constexpr int KS_MAX = 8;
 Plan plan_for(const GemmArgs& a, int epi) {
   Plan best{};
   const int NT = a.N >> 4, KT = a.K >> 5, cus = device_cus();
-  const bool can_cut = a.part && !(epi == EPI_STORE && (a.lse_part || a.ssq));
+  const bool cuts = can_cut(a, epi);
   double best_cost = 0;
   for (int B = 4; B >= 1; --B) {
     const int tm = (a.R + 64 * B - 1) / (64 * B);
     if (B > 1 && (a.R + 64 * (B - 1) - 1) / (64 * (B - 1)) == tm) continue;  // as many tiles of fewer rows
     for (int TS : {16, 14, 12, 10, 8, 7, 6, 5, 4}) {
       const bool tall = TS > 8;
-      if (tall && B < 3) continue;
+      if (tall ? B < 3 : TS == 4 && B > 1) continue;  // (4 strips meet more than 64 rows in no plan at 256 compute units)
       const int tn = (NT + TS - 1) / TS, frags = TS + 8 * B;
       const int mfma = 32 * TS * B, lds = 32 * (tall ? TS + 4 * B : TS + 2 * B) + 8 * frags, fill = 40 * frags, hbm = 98 * TS / tm;
       int interval = mfma;
@@ -650,8 +656,8 @@ Plan plan_for(const GemmArgs& a, int epi) {
       for (int KS = 1; KS <= KS_MAX; ++KS) {
         const int total = tn * tm * KS;
         if (KS > 1) {
-          if (!can_cut || total > cus || KT < 16 * KS || (size_t)KS * a.R * a.N > a.part_floats) break;
-          if (((KT + KS - 1) / KS) * (KS - 1) >= KT) continue;  // a range would be empty
+          if (!cuts || total > cus || KT < 16 * KS) break;
+          if (!cut_fits(a, KS)) continue;
         }
         const int rounds = (total + cus - 1) / cus;
         double cost = (double)rounds * (((KT + KS - 1) / KS) * (double)interval + 8000);
@@ -664,6 +670,11 @@ Plan plan_for(const GemmArgs& a, int epi) {
     }
   }
   return best;
+}
+
+Plan plan_of(const GemmArgs& a, const GemmTiles& t) {
+  const int TS = t.strips << t.tall, NT = a.N >> 4, rows = 64 * t.row_groups;
+  return Plan{t.strips, t.row_groups, t.ranges, (NT + TS - 1) / TS, (a.R + rows - 1) / rows, t.tall != 0};
 }
 
 template <int A, int B, bool TALL, int EPI>
@@ -685,6 +696,8 @@ template <int A, int EPI>
 hipError_t run_rows(const GemmArgs& a, const Plan& p, hipStream_t s) {
   switch (p.B) {
     case 1: return run_shape<A, 1, false, EPI>(a, p, s);
+  }
+  if constexpr (A > 4) switch (p.B) {
     case 2: return run_shape<A, 2, false, EPI>(a, p, s);
     case 3: return run_shape<A, 3, false, EPI>(a, p, s);
     case 4: return run_shape<A, 4, false, EPI>(a, p, s);
@@ -720,7 +733,7 @@ hipError_t run_sum(const GemmArgs& a, int KS, hipStream_t s) {
 }
 
 template <int EPI>
-hipError_t run_dma(GemmArgs a, hipStream_t s, int* np) {
+hipError_t run_dma(GemmArgs a, hipStream_t s, int* np, const GemmTiles* given) {
   if (!a.ncg) {  // planes: this product's activations in fragment order first
     a.ncg = (a.R + 7) / 8;
     const int64_t frags = (int64_t)(a.K >> 5) * a.ncg;
@@ -730,7 +743,7 @@ hipError_t run_dma(GemmArgs a, hipStream_t s, int* np) {
     if (e != hipSuccess) return e;
     a.X = a.xfrag;
   }
-  const Plan p = plan_for(a, EPI);
+  const Plan p = given ? plan_of(a, *given) : plan_for(a, EPI);
   hipError_t e = hipErrorInvalidValue;
   if (p.tall) switch (p.A) {
     case 5: e = run_tall<5, EPI>(a, p, s); break;
@@ -765,14 +778,42 @@ hipError_t launch_ssq_rows(const float* in, float* out, int R, int NP, hipStream
 
 bool gemm_dma_wide(int N) { return ((N >> 4) + 7) / 8 * 2 >= device_cus(); }
 
-hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* np) {
+GemmTiles gemm_dma_tiles(const GemmArgs& a, int epi) {
+  const Plan p = plan_for(a, epi);
+  return GemmTiles{p.A, p.B, p.tall, p.KS};
+}
+
+hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* np, const GemmTiles* t) {
+  if (t) {  // what plan_for and launch_gemm_bf16 see to for planned tiles
+    if (a.R <= ACT_COMPACT_ROWS || (a.N & 15) || (a.K & 31) || (epi == EPI_STORE && (a.ldy & 3))) return hipErrorInvalidValue;
+    if (t->ranges < 1 || (t->ranges > 1 && !(can_cut(a, epi) && cut_fits(a, t->ranges)))) return hipErrorInvalidValue;
+    if (t->tall < 0 || t->tall > 1 || t->strips < 4) return hipErrorInvalidValue;
+    if (t->tall ? t->strips < 5 || t->strips > 8 || t->row_groups < 3 || t->row_groups > 4
+                : t->strips > 8 || t->row_groups < 1 || t->row_groups > (t->strips == 4 ? 1 : 4))
+      return hipErrorInvalidValue;
+  }
   switch (epi) {
-    case EPI_STORE: return run_dma<EPI_STORE>(a, s, np);
-    case EPI_RESID: return run_dma<EPI_RESID>(a, s, np);
-    case EPI_SWIGLU: return run_dma<EPI_SWIGLU>(a, s, np);
-    case EPI_QKV: return run_dma<EPI_QKV>(a, s, np);
+    case EPI_STORE: return run_dma<EPI_STORE>(a, s, np, t);
+    case EPI_RESID: return run_dma<EPI_RESID>(a, s, np, t);
+    case EPI_SWIGLU: return run_dma<EPI_SWIGLU>(a, s, np, t);
+    case EPI_QKV: return run_dma<EPI_QKV>(a, s, np, t);
   }
   return hipErrorInvalidValue;
 }
 
 }  // namespace mtad
+
+// For the tests (and to time plans against each other): the many-row product with the epilogue and the tiles named, tiles[4] =
+// {strips per wave, row groups of 64, groups side by side, ranges}, or, with tiles[0] = 0, the planned tiles written there.  args: a
+// GemmArgs of `bytes` bytes.  Launches only with run != 0.  0, or -1 (sizes differ, or tiles that do not exist or fit) or -4.
+extern "C" int mtad_test_gemm_tiles(const void* args, size_t bytes, int epi, int* tiles, int run, void* stream) {
+  using namespace mtad;
+  if (!args || !tiles || bytes != sizeof(GemmArgs)) return -1;
+  const GemmArgs& a = *(const GemmArgs*)args;
+  GemmTiles t{tiles[0], tiles[1], tiles[2], tiles[3]};
+  if (!t.strips) t = gemm_dma_tiles(a, epi);
+  tiles[0] = t.strips; tiles[1] = t.row_groups; tiles[2] = t.tall; tiles[3] = t.ranges;
+  if (!run) return 0;
+  const hipError_t e = launch_gemm_bf16_dma(a, epi, (hipStream_t)stream, nullptr, &t);
+  return e == hipSuccess ? 0 : e == hipErrorInvalidValue ? -1 : -4;
+}

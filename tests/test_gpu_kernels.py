@@ -75,7 +75,7 @@ def _gemm_case(mb, R, N, K, dtype, seed, accumulate=False, ldy=None, ctx=None, x
                                    (5, 22016, 4096), (8, 8208, 160), (4, 8224, 96), (7, 8240, 1056), (6, 32000, 352),
                                    # 9 to 24 rows on the same kernel with two or three row groups
                                    (10, 12288, 4096), (16, 8208, 160), (9, 8224, 96), (13, 32000, 352), (17, 22016, 4096), (24, 8240, 96), (19, 8208, 1056),
-                                   # many rows: activations staged through LDS, 4 or 8 strips per workgroup, 8 / 16 / 24 column groups
+                                   # many rows and no context: the kernels above, 64 rows at a time
                                    (164, 16400, 256), (64, 16384, 160), (128, 16384, 96), (70, 16, 32), (190, 48, 1056), (77, 2000, 352), (25, 16400, 288), (32, 32000, 2048)])
 def test_gemm_bf16_matches_float64(R, N, K):
     mb = _mb()
@@ -85,8 +85,7 @@ def test_gemm_bf16_matches_float64(R, N, K):
 
 @pytest.mark.parametrize("R,N,K", [(17, 4096, 4096), (17, 4096, 11008), (64, 4096, 4096), (41, 5120, 5120), (9, 2064, 2048), (30, 4112, 2080),
                                    (164, 5120, 5120), (164, 16384, 2048), (100, 4112, 1056), (256, 4096, 1024),
-                                   # many rows (with a context's scratch): 4 or 8 strips per workgroup, 4 / 8 / 16 / 24 column
-                                   # groups, ragged strips, rows and k tiles
+                                   # many rows (with a context's scratch): the many-row kernel, ragged strips, rows and k tiles
                                    (164, 16400, 256), (64, 16384, 160), (128, 16384, 96), (70, 16, 32), (190, 48, 1056),
                                    (77, 2000, 352), (25, 16400, 288), (32, 32000, 2048), (100, 96, 160), (200, 32, 64)])
 def test_gemm_bf16_with_context_workspace(R, N, K):
@@ -129,9 +128,9 @@ def test_gemm_bf16_fragment_order_input(R, N, K):
                                    (65, 5120, 4096), (130, 2080, 8192), (200, 11264, 512), (250, 15360, 160), (164, 27648, 64),
                                    (222, 1664, 5728), (164, 12288, 4096), (250, 15360, 5120), (25, 15360, 5120), (58, 2576, 2048)])
 def test_gemm_bf16_many_rows(R, N, K):
-    """The many-row kernel at the edges of its tiles: 64, 128, 192 and 256 rows and one more or less, every count of strips per
-    workgroup with strips left over, one to many k tiles (fewer than the ring holds, odd counts), reductions cut into ranges;
-    stored and added."""
+    """The many-row kernel through the entry point, on the tiles planned for these shapes: 64, 128, 192 and 256 rows and one more
+    or less, strips left over, one to many k tiles, reductions cut into ranges; stored and added.  (Every tile shape with every
+    epilogue, planned here or not: test_gpu_tiles.py.)"""
     mb = _mb()
     shape = si.ModelShape(1, 8192, 64, 64, 128, 8192, 32000, "bf16")
     desc = mb.mtad_model(shape.n_layers, shape.d_model, shape.n_heads, shape.n_kv_heads, shape.head_dim, shape.d_ffn, shape.vocab, 1, shape.rms_eps,
@@ -147,8 +146,8 @@ def test_gemm_bf16_many_rows(R, N, K):
 
 def test_gemm_bf16_c5_gate_up_product_at_full_size():
     """The largest product of C5's target pass at its real size: 164 rows (4 trees of 41) x 27648 gate/up features x 5120,
-    activations in fragment order, on the kernel the pass takes for it (8 strips per workgroup, 24 column groups, 64 KiB
-    of LDS): every element against the float64 product."""
+    activations in fragment order, on the kernel the pass takes for it (the many-row kernel; at 256 compute units 14 strips x
+    192 rows per workgroup, the reduction cut in two): every element against the float64 product."""
     mb = _mb()
     w = si.WORKLOADS["C5"]
     desc = lambda s: mb.mtad_model(s.n_layers, s.d_model, s.n_heads, s.n_kv_heads, s.head_dim, s.d_ffn, s.vocab, 1, s.rms_eps, s.rope_theta, None)

@@ -269,7 +269,7 @@ def test_multi_token_joint_decoding_matches(kind, K, beam, sample):
     (64, 4, 4, 32, 150, 8),      # 32 sequences: several chunks of 64 rows each, the last one ragged
     (128, 4, 1, 3, 66, 32),      # one more token than a row mask holds
     (64, 2, 1, 1, 1301, 64),     # more than 1024 rows in one pass
-    (128, 16, 4, 1, 590, 64),    # wide products on row tiles of 192 and 256 rows, the groups of waves side by side
+    (128, 16, 4, 1, 590, 64),    # wide products on several tiles of 64 to 192 rows
     (64, 20, 5, 2, 333, 64),     # strip counts that leave a wave's last pair half empty, heads that end inside a workgroup
 ])
 def test_prompt_chunks_of_many_rows(hd, heads, kv_heads, batch, n, prefill_rows):
