@@ -53,7 +53,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, 
 // the same product for passes of many rows, fragments copied to LDS by the loads themselves (kernels_gemm_dma.hip); chosen by
 // launch_gemm_bf16.  tiles: instead of the planned ones (refused where they do not exist or fit)
 struct GemmTiles {
-  int strips, row_groups, tall, ranges;  // strips per wave, groups of 64 rows, wave groups side by side, ranges of the reduction
+  int strips, row_groups, tall, ranges;  // strips per wave, groups of 64 rows (0: one of 32), wave groups side by side, ranges of the reduction
 };
 hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* np, const GemmTiles* tiles = nullptr);
 GemmTiles gemm_dma_tiles(const GemmArgs& a, int epi);  // the planned ones

@@ -41,14 +41,28 @@ namespace {
 constexpr int NW = 8;                    // waves per workgroup: two groups of four
 constexpr int LDS_MOST = 160 * 1024 - 1536;  // of a compute unit, less the static arrays
 constexpr int PAIR = 2048;  // bytes of two activation fragments (16 rows)
+constexpr int NONTEMPORAL = 2;  // cache policy operand of global_load_lds
+// A wide output's weights that a single tile of rows reads (tiles of at most 64 rows, 7 or 8 strips) are requested as data that is
+// not read again.  HBM bounds these products: 32 rows, 32000 x 4096 49.7 -> 45.0 us (5.8 TB/s), 27648 x 5120 53.1 -> 48.0; 64 rows,
+// 32000 x 5120 68.7 -> 60.1, 27648 x 5120 60.2 -> 55.2.  Cut reductions of narrow outputs lose by it (5120 x 5120 at 48 rows
+// 19.1 -> 19.9 us), and so do tiles of 4 to 6 strips, which have fewer weights on their way (22016 x 4096, 32 rows: 35.5 -> 38.2).
+__host__ __device__ constexpr bool streams(int strips, int row_tiles) { return strips >= 1024 && row_tiles == 1; }
 
-// A strips per wave; TALL: the groups own A strips each and both take every k tile, else both own the same A strips
-template <int A, int B, bool TALL>
+// A strips per wave; TALL: the groups own A strips each and both take every k tile, else both own the same A strips.
+// B row groups of 64 rows, or B = 0: one of 32 rows (two of each group's waves hold rows, the others only bring fragments), for
+// passes of 25 to 32: half the activations on their way leave room for weights in the ring (13 slots of 8 strips instead of 9) and
+// among the requests.  With weights requested as above: 32000 x 4096 at 32 rows 52.1 us with a 64-row tile, 45.0 with this one.
+template <int A, int B_, bool TALL>
 struct DmaShape {
-  static constexpr int ROWS = 64 * B;                // rows per workgroup
+  static constexpr bool HALF_TILE = B_ == 0;
+  static constexpr int B = HALF_TILE ? 1 : B_;       // B operands per wave
+  static constexpr int XF = HALF_TILE ? 4 : 8 * B;   // activation fragments per k tile
+  static constexpr int ROWS = 8 * XF;                // rows per workgroup
   static constexpr int TS = TALL ? 2 * A : A;        // strips per workgroup
-  static constexpr int FRAGS = TS + 8 * B;           // KiB that one k tile brings: weight tiles, then 8 B activation fragments
+  static constexpr int FRAGS = TS + XF;              // KiB that one k tile brings: weight tiles, then activation fragments
   static constexpr int LPW = (FRAGS + NW - 1) / NW;  // of them per wave
+  static constexpr int FULL = FRAGS - (LPW - 1) * NW;  // waves that bring LPW; the others bring one less (HALF_TILE) or the last one again
+  static constexpr bool STREAM = B_ <= 1 && A >= 7;  // may request its weights as data that is not read again
   static constexpr int SLOT = FRAGS * 1024;
   static constexpr int D0 = LDS_MOST / SLOT;
   static constexpr int D = D0 > 16 ? 16 : D0;        // ring slots
@@ -219,16 +233,19 @@ struct PairEpilogue {
   }
 };
 
-template <int A, int B, bool TALL, int EPI>
+template <int A, int B_, bool TALL, int EPI>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_dma_kernel(GemmArgs a, int tiles_n, int tiles_m, int KS) {
-  using Sh = DmaShape<A, B, TALL>;
-  constexpr int LPW = Sh::LPW, D = Sh::D, SLOT = Sh::SLOT, TS = Sh::TS;
+  using Sh = DmaShape<A, B_, TALL>;
+  constexpr int B = Sh::B, LPW = Sh::LPW, D = Sh::D, SLOT = Sh::SLOT, TS = Sh::TS;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dma[];
   __shared__ float inv_s[Sh::ROWS];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave & 3, grp = wave >> 2;
+  const bool rowless = Sh::HALF_TILE && wr >= 2;  // waves that only bring fragments
+  const bool full = !Sh::HALF_TILE || wave < Sh::FULL;
+  const bool stream = Sh::STREAM && streams(a.N >> 4, tiles_m);
   const int c = lane & 15, kg = lane >> 4;
   const int KT_all = a.K >> 5, NT = a.N >> 4;
   // workgroups go to the 8 XCDs in turn: give each XCD a contiguous range of tiles, and within it blocks of up to four row tiles
@@ -245,9 +262,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int n_kt = min(KT_all, k_lo + per) - k_lo;  // the launcher leaves no range empty
 
   // What this wave requests per k tile: fragment f = i * 8 + wave is weight tile f, or activation fragment f - TS; those past
-  // the last one read it again, to the same place with the same contents.  (Weights on waves of their own, requested much
-  // earlier than the activations, were no faster: a compute unit's loads return in the order of their requests, so the
-  // activations behind them wait for HBM all the same, and the ring holds fewer of them.)
+  // the last one read it again, to the same place with the same contents (32-row tiles leave them out).  (Weights on waves of
+  // their own, requested much earlier than the activations, were no faster: a compute unit's loads return in the order of their
+  // requests, so the activations behind them wait for HBM all the same, and the ring holds fewer of them.)
   const char* src[LPW];
   size_t step[LPW];
   unsigned dst[LPW];
@@ -270,7 +287,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   auto request = [&](auto FROM, auto TO) {  // its share of a k tile, or part of it; the slot moves on with the last part
 #pragma unroll
     for (int i = FROM; i < TO; ++i) {
-      __builtin_amdgcn_global_load_lds((GlobalWords)(src[i] + (unsigned)lane * 16u), (LdsWords)(lds_dma + s_in + dst[i]), 16, 0, 0);
+      if (i == LPW - 1 && !full) break;
+      if (stream && i * NW + wave < TS)
+        __builtin_amdgcn_global_load_lds((GlobalWords)(src[i] + (unsigned)lane * 16u), (LdsWords)(lds_dma + s_in + dst[i]), 16, 0, NONTEMPORAL);
+      else
+        __builtin_amdgcn_global_load_lds((GlobalWords)(src[i] + (unsigned)lane * 16u), (LdsWords)(lds_dma + s_in + dst[i]), 16, 0, 0);
       src[i] += step[i];
     }
     if constexpr (TO == LPW) s_in = s_in + SLOT == D * SLOT ? 0 : s_in + SLOT;
@@ -293,7 +314,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int j = 0; j < B; ++j) acc[si][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   // lane (kg, row) of a B operand: fragment row / 8 of the pair, piece (kg, plane), row % 8
   const unsigned w_off = (unsigned)((TALL ? grp * A * 1024 : 0) + lane * 16);
-  const unsigned x_off = (unsigned)(TS * 1024 + wr * PAIR + (c >> 3) * 1024 + (kg * 16 + (c & 7)) * 16);
+  const unsigned x_off = (unsigned)(TS * 1024 + (Sh::HALF_TILE ? wr & 1 : wr) * PAIR + (c >> 3) * 1024 + (kg * 16 + (c & 7)) * 16);
   Frag fw[A], fx[B][2];
   constexpr int STRIDE = TALL ? SLOT : 2 * SLOT;
   int s_out = TALL ? 0 : grp * SLOT;  // ring slot of this group's next k tile
@@ -315,7 +336,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   auto interval_end = [&](bool steady) {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
-    if (steady) __builtin_amdgcn_s_waitcnt(wait_vm_lds((D - 2) * LPW));
+    if (steady && full) __builtin_amdgcn_s_waitcnt(wait_vm_lds((D - 2) * LPW));
+    else if (steady) __builtin_amdgcn_s_waitcnt(wait_vm_lds((D - 2) * (LPW - 1)));
     else __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -353,7 +375,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int t = 0; t < trips; ++t) {
       {  // memory interval: fragments of this group's k tile
         const bool more = i + ahead < n_kt;
-        fetch();
+        if (!rowless) fetch();
         if (more) request(NONE, ALL);
         interval_end(more);
         ++i;
@@ -362,7 +384,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const bool more = i + ahead < n_kt;
         if (more) request(NONE, ALL);
         __builtin_amdgcn_sched_barrier(0);
-        if (grp == 0 || 2 * t + 1 < n_kt) multiply();
+        if (!rowless && (grp == 0 || 2 * t + 1 < n_kt)) multiply();
         interval_end(more);
         ++i;
       }
@@ -433,7 +455,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   for (int p = 0; p < PAIRS; ++p) {
     constexpr int LAST = A - 1;
     const int nt = nt_wave + 2 * p;
-    if (!owns(p) || nt >= NT) continue;
+    if (!owns(p) || nt >= NT || rowless) continue;
     const bool have2 = 2 * p + 1 < A && nt + 1 < NT;
     if (KS > 1) {  // the launch after this one adds the ranges: part[range][row][packed feature]
 #pragma unroll
@@ -632,24 +654,26 @@ bool cut_fits(const GemmArgs& a, int KS) {
   return KS <= KS_MAX && per * (KS - 1) < KT /* no range is empty */ && (size_t)KS * a.R * a.N <= a.part_floats;
 }
 
-// Rows per workgroup (64 to 256), strips per workgroup (4 to 8, or 10 to 16 with the groups side by side where 129 rows and more
+// Rows per workgroup (32, or 64 to 256), strips per workgroup (4 to 8, or 10 to 16 with the groups side by side where 129 rows and more
 // meet) and ranges of the reduction dimension: the cheapest by a count of clocks per compute unit.  A k tile lasts as long as its
 // matrix instructions, its LDS traffic, its way to LDS (about 25 bytes per clock where weights from HBM and activations from L2
-// alternate) or its weights from HBM (10 bytes per clock and compute unit), plus the barriers.  A cut costs its partial
+// alternate) or its weights from HBM (10 to 11 bytes per clock and compute unit), plus the barriers.  A cut costs its partial
 // sums' way through memory and a launch.
 Plan plan_for(const GemmArgs& a, int epi) {
   Plan best{};
   const int NT = a.N >> 4, KT = a.K >> 5, cus = device_cus();
   const bool cuts = can_cut(a, epi);
   double best_cost = 0;
-  for (int B = 4; B >= 1; --B) {
-    const int tm = (a.R + 64 * B - 1) / (64 * B);
-    if (B > 1 && (a.R + 64 * (B - 1) - 1) / (64 * (B - 1)) == tm) continue;  // as many tiles of fewer rows
+  for (int B_ = 4; B_ >= 0; --B_) {
+    const int B = B_ ? B_ : 1, rows = B_ ? 64 * B_ : 32, tm = (a.R + rows - 1) / rows;
+    if (B_ == 0 ? tm > 1 : a.R <= 32) continue;                               // up to 32 rows: a tile of 32
+    if (B_ > 1 && (a.R + 64 * (B - 1) - 1) / (64 * (B - 1)) == tm) continue;  // as many tiles of fewer rows
     for (int TS : {16, 14, 12, 10, 8, 7, 6, 5, 4}) {
       const bool tall = TS > 8;
-      if (tall ? B < 3 : TS == 4 && B > 1) continue;  // (4 strips meet more than 64 rows in no plan at 256 compute units)
-      const int tn = (NT + TS - 1) / TS, frags = TS + 8 * B;
-      const int mfma = 32 * TS * B, lds = 32 * (tall ? TS + 4 * B : TS + 2 * B) + 8 * frags, fill = 40 * frags, hbm = 98 * TS / tm;
+      if (tall ? B_ < 3 : TS == 4 && B_ > 1) continue;  // (4 strips meet more than 64 rows in no plan at 256 compute units)
+      const int tn = (NT + TS - 1) / TS, frags = TS + rows / 8;
+      const int mfma = 32 * TS * B, lds = 32 * (tall ? TS + 4 * B : TS + 2 * B) + 8 * frags, fill = 40 * frags;
+      const int hbm = (B_ <= 1 && TS >= 7 && streams(NT, tm) ? 90 : 98) * TS / tm;
       int interval = mfma;
       for (int x : {lds, fill, hbm}) interval = x > interval ? x : interval;
       interval += tall ? 250 : 100;
@@ -664,7 +688,7 @@ Plan plan_for(const GemmArgs& a, int epi) {
         if (KS > 1) cost = 1.08 * (cost + 6000 + (double)(2 * KS) * a.R * a.N * 4 / 2000);  // worth it when clearly better
         if (best.A == 0 || cost < best_cost) {
           best_cost = cost;
-          best = Plan{tall ? TS / 2 : TS, B, KS, tn, tm, tall};
+          best = Plan{tall ? TS / 2 : TS, B_, KS, tn, tm, tall};
         }
       }
     }
@@ -673,7 +697,8 @@ Plan plan_for(const GemmArgs& a, int epi) {
 }
 
 Plan plan_of(const GemmArgs& a, const GemmTiles& t) {
-  const int TS = t.strips << t.tall, NT = a.N >> 4, rows = 64 * t.row_groups;
+  const int TS = t.strips << t.tall, NT = a.N >> 4;
+  const int rows = t.row_groups ? 64 * t.row_groups : 32;
   return Plan{t.strips, t.row_groups, t.ranges, (NT + TS - 1) / TS, (a.R + rows - 1) / rows, t.tall != 0};
 }
 
@@ -695,6 +720,7 @@ hipError_t run_shape(const GemmArgs& a, const Plan& p, hipStream_t s) {
 template <int A, int EPI>
 hipError_t run_rows(const GemmArgs& a, const Plan& p, hipStream_t s) {
   switch (p.B) {
+    case 0: return run_shape<A, 0, false, EPI>(a, p, s);
     case 1: return run_shape<A, 1, false, EPI>(a, p, s);
   }
   if constexpr (A > 4) switch (p.B) {
@@ -789,7 +815,7 @@ hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* 
     if (t->ranges < 1 || (t->ranges > 1 && !(can_cut(a, epi) && cut_fits(a, t->ranges)))) return hipErrorInvalidValue;
     if (t->tall < 0 || t->tall > 1 || t->strips < 4) return hipErrorInvalidValue;
     if (t->tall ? t->strips < 5 || t->strips > 8 || t->row_groups < 3 || t->row_groups > 4
-                : t->strips > 8 || t->row_groups < 1 || t->row_groups > (t->strips == 4 ? 1 : 4))
+                : t->strips > 8 || t->row_groups < 0 || t->row_groups > (t->strips == 4 ? 1 : 4))
       return hipErrorInvalidValue;
   }
   switch (epi) {
@@ -804,7 +830,7 @@ hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* 
 }  // namespace mtad
 
 // For the tests (and to time plans against each other): the many-row product with the epilogue and the tiles named, tiles[4] =
-// {strips per wave, row groups of 64, groups side by side, ranges}, or, with tiles[0] = 0, the planned tiles written there.  args: a
+// {strips per wave, row groups of 64 (0: one of 32), groups side by side, ranges}, or, with tiles[0] = 0, the planned tiles written there.  args: a
 // GemmArgs of `bytes` bytes.  Launches only with run != 0.  0, or -1 (sizes differ, or tiles that do not exist or fit) or -4.
 extern "C" int mtad_test_gemm_tiles(const void* args, size_t bytes, int epi, int* tiles, int run, void* stream) {
   using namespace mtad;

@@ -5,8 +5,8 @@ from paper_2407_09722_amd import binding as mb
 
 vp, i32, f32, size_t = C.c_void_p, C.c_int32, C.c_float, C.c_size_t
 STORE, RESID, SWIGLU, QKV = range(4)
-# (strips per wave, groups of 64 rows, wave groups side by side)
-TILES = [(A, B, 0) for A in (4, 5, 6, 7, 8) for B in (1, 2, 3, 4) if A > 4 or B < 2] + [(A, B, 1) for A in (5, 6, 7, 8) for B in (3, 4)]
+# (strips per wave, groups of 64 rows (0: one of 32), wave groups side by side)
+TILES = [(A, B, 0) for A in (4, 5, 6, 7, 8) for B in range(5) if A > 4 or B < 2] + [(A, B, 1) for A in (5, 6, 7, 8) for B in (3, 4)]
 
 
 class KvView(C.Structure):

@@ -195,7 +195,7 @@ def _qkv(R, NT, K, tile, ks, seed):
 @pytest.mark.parametrize("tile", T.TILES, ids=lambda t: f"{t[0]}x{t[1]}{'tall' if t[2] else ''}")
 def test_every_tile_with_every_epilogue(tile):
     A, B, tall = tile
-    rows, strips = 64 * B, A << tall
+    rows, strips = 64 * B or 32, A << tall
     for n, (R, NT, KT, ks) in enumerate([(max(25, rows - 5), strips + 3, 2, 1),         # one tile of rows, strips left over, fewer k tiles than the ring holds
                                          (rows + 27, strips * 2, 21, 1),                # a second tile of rows, an odd count of k tiles, more than the ring holds
                                          (rows, strips - 1, 18, 1),                     # full rows, one strip too few
@@ -206,13 +206,20 @@ def test_every_tile_with_every_epilogue(tile):
             check(R, nt, 32 * KT, tile, ks, seed=100 * A + 10 * B + n)
 
 
+@pytest.mark.parametrize("tile", [(7, 0, 0), (8, 0, 0), (7, 1, 0), (8, 1, 0)], ids=lambda t: f"{t[0]}x{t[1]}")
+@pytest.mark.parametrize("strips", [1023, 1026])   # the last width whose weights go through the caches, and one whose weights pass them by
+def test_wide_outputs(tile, strips):
+    print(f"tile {tile} strips={strips}", flush=True)
+    _store(32 - 3 * (tile[1] == 0) + 9 * tile[1], strips, 32 * 19, tile, 1, seed=strips)
+
+
 def test_tiles_that_do_not_exist_or_fit_are_refused():
     from paper_2407_09722_amd import binding as mb
     p = Product(40, 80, 96, 1, mb.MTAD_PACK_PLAIN)
     Y = torch.full((40, 80), KEPT, device=DEV)
     p.set(Y=Y)
     p.args.ldy = 80
-    for tile, ks in (((9, 1, 0), 1), ((3, 1, 0), 1), ((4, 2, 0), 1), ((8, 2, 1), 1), ((8, 5, 0), 1), ((8, 0, 0), 1), ((5, 3, 2), 1), ((8, 1, 0), 0), ((8, 1, 0), 4), ((8, 1, 0), 9)):
+    for tile, ks in (((9, 1, 0), 1), ((3, 1, 0), 1), ((4, 2, 0), 1), ((8, 2, 1), 1), ((8, 5, 0), 1), ((8, -1, 0), 1), ((8, 0, 1), 1), ((5, 3, 2), 1), ((8, 1, 0), 0), ((8, 1, 0), 4), ((8, 1, 0), 9)):
         assert T.launch(p.args, T.STORE, tile, ks) == -1, (tile, ks)
     p.args.part_floats = 2 * 40 * 80 - 1
     assert T.launch(p.args, T.STORE, (8, 1, 0), 2) == -1

@@ -14,3 +14,8 @@ def test_planned_tiles_are_tested_tiles():
                     assert 1 <= t[3] <= 8 and (part or t[3] == 1)
                     seen.add(t[:3])
     assert seen == tiles, f"never planned: {sorted(tiles - seen)}"
+
+
+def test_passes_of_up_to_32_rows_take_tiles_of_32():
+    for N, K in ((27648, 5120), (32000, 4096), (57344, 8192), (5120, 13824)):
+        assert all(T.planned(R, N, K)[1] == 0 for R in (25, 29, 32)) and T.planned(33, N, K)[1] == 1
