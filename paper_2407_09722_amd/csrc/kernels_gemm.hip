@@ -584,18 +584,41 @@ static hipError_t run_epi(GemmArgs a, int tag, hipStream_t s) {
   return hipSuccess;
 }
 
-// Passes of many rows take both operands through LDS (kernels_gemm_dma.hip).  Measured against the kernels above at the shapes of
-// the 7B-, 13B- and 1B-shaped models: it wins from 65 rows up everywhere (4096 x 4096 at 64 rows: 21.1 -> 15.2 us).  From 25 rows
-// up it wins where the output gives half of the compute units a workgroup of 8 strips (22016 x 4096 at 40 rows: 46.2 -> 38.8 us)
-// or the reduction is long enough to be worth cutting (2048 x 5632 at 32 rows 15.9 -> 12.7 us, 15360 x 5120 40.2 -> 35.8 us),
-// and for narrow outputs from 40 rows up at 4096 (14.9 -> 14.5 us, at 48 rows 16.6 -> 14.6) and from 57 at any length (2560 x 2048
-// at 64 rows 16.1 -> 11.5 us); 12288 x 4096 at 40 rows takes 24.4 us above and 27.8 us there.
+// Passes of many rows take both operands through LDS (kernels_gemm_dma.hip): from 65 rows up always (840 shapes of 1024 to 32000
+// features and 256 to 13824 terms), from 25 rows up where the output gives half of the compute units a workgroup of 8 strips, and for
+// narrower outputs where the reduction is long enough to be cut: from how many terms on depends on the rows, and on how even the
+// strips come out over the compute units in the kernels above.  us, above / there, on both sides of the lines:
+//   strips    rows     below the line               from the line on
+//   64        25       4096: 10.5 / 9.6             5120: 12.6 / 10.5
+//             40       3072: 9.6 / 9.7              4096: 12.1 / 10.0
+//             64       2048: 9.2 / 9.9              3072: 12.7 / 10.5
+//   256       32       5120: 15.0 / 16.0            8192: 22.8 / 22.7
+//             40       4096: 14.1 / 15.5            5120: 17.2 / 16.9
+//             64       3072: 14.3 / 15.0            4096: 18.6 / 16.5
+//   384       32       4096: 16.4 / 17.3            5120: 19.8 / 19.5
+//   512       32       8192: 31.2 / 34.1            11008: 42.0 / 41.0
+//   640       40       5120: 27.4 / 27.2 to 31      5632: 29.7 / 28.7
+//   768       48       5120: 30.5 / 32.4            8192: 46.4 / 45.5
+// One line for all of them (4096 terms from 40 rows on, 5120 below, none from 57) costs up to two thirds of a call: 1024 x 1024 at
+// 64 rows 9.6 us instead of 5.8, 12288 x 5120 at 25 rows 29.8 instead of 25.9.
+constexpr int NEVER = 0x7fffffff;
+static int dma_min_terms(int R, int NT) {
+  const int rows = R < 33 ? 0 : R < 40 ? 1 : R < 49 ? 2 : R < 57 ? 3 : 4, cus = device_cus();
+  const bool even = NT * 20 >= (NT + cus - 1) / cus * cus * 19;  // all compute units have the same count of strips, nearly
+  typedef int Terms[5];
+  constexpr Terms even_narrow{8192, 5120, 5120, 4096, 4096}, narrow{5120, 5120, 4096, 4096, 3072}, two_rounds{10240, 5120, 5120, 5120, 5120},
+      more{8192, 5632, 5632, 5120, 5120}, three_rounds{NEVER, 10240, 8192, 5120, 5120}, rest{5120, 5120, 5120, 5120, 5120};
+  if (NT <= SPLIT_MAX_STRIPS) return even ? even_narrow[rows] : narrow[rows];
+  if (NT <= 2 * cus) return even ? two_rounds[rows] : rest[rows];
+  if (NT <= 5 * cus / 2) return more[rows];
+  return NT <= 3 * cus ? three_rounds[rows] : rest[rows];
+}
+
 static bool use_dma(const GemmArgs& a) {
   if (!a.ncg && (!a.xfrag || a.xfrag_elems < gemm_dma_xfrag_elems(a.R, a.K))) return false;  // needs fragment order or its scratch
   if (a.R >= 65) return true;
   if (a.R < 25) return false;
-  const bool narrow = a.N / 16 <= SPLIT_MAX_STRIPS;
-  return gemm_dma_wide(a.N) || (a.part && (a.K >= 5120 || (narrow && (a.R >= 57 || (a.R >= 40 && a.K >= 4096)))));
+  return gemm_dma_wide(a.N) || (a.part && a.K >= dma_min_terms(a.R, a.N >> 4));
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, int* np) {
@@ -614,3 +637,8 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, 
 }
 
 }  // namespace mtad
+
+// For the tests: whether a product of bfloat16 weights goes to the many-row kernel.
+extern "C" int mtad_test_gemm_many_rows(const void* args, size_t bytes) {
+  return args && bytes == sizeof(mtad::GemmArgs) ? mtad::use_dma(*(const mtad::GemmArgs*)args) : -1;
+}

@@ -39,3 +39,11 @@ def planned(R, N, K, epi=STORE, part_floats=256 ** 3):
     status, t = _call(a, epi, (0, 0, 0, 0), 0, None)
     assert status == 0
     return t
+
+
+def many_rows(R, N, K, part_floats=256 ** 3):
+    """Whether a product with activations in fragment order goes to the many-row kernel."""
+    fn = mb.lib().mtad_test_gemm_many_rows
+    fn.argtypes, fn.restype = [vp, size_t], C.c_int
+    a = GemmArgs(R=R, N=N, K=K, ncg=(R + 7) // 8, part=vp(256) if part_floats else None, part_floats=part_floats)
+    return bool(fn(C.byref(a), C.sizeof(a)))
