@@ -21,9 +21,11 @@ struct mtad_ctx {
   int M;                      // rows per sequence of the target pass
   int Rmax;                   // most rows per sequence of any pass
   int draft_rows;             // rows per sequence of a draft step (max over steps)
-  int prompt_rows;            // most rows per sequence of a prompt chunk of a bf16 model
-  size_t ws_need;
+  int prompt_best;            // most rows per sequence of a prompt chunk of a bf16 model (0: both models are float32)
+  int prompt_rows;            // the same with the workspace that is bound
+  size_t ws_need;             // workspace for chunks of prompt_best rows
   char* ws;
+  size_t ws_bytes;
   // workspace carve-up
   float *h, *qkv, *dlogits, *lse, *partial, *part_key, *ssq, *lse_part;
   float* ssq_sum;    // [rows of a prompt chunk]
@@ -113,7 +115,10 @@ struct Carver {
   }
 };
 
-void carve(mtad_ctx* c, char* base) {
+// Lays the workspace out at `base` (null: only its size) for prompt chunks of prompt_rows rows per sequence; returns its bytes.
+// roomy: with room for the ranges of the many-row products' cut reductions and for 256 rows of mtad_k_gemm's plane input there.
+size_t carve(mtad_ctx* c, char* base, int prompt_rows, bool roomy) {
+  c->prompt_rows = prompt_rows;
   const mtad_model &t = c->tshape, &d = c->dshape;
   const size_t rows = (size_t)c->cfg.batch * c->Rmax;
   const size_t prompt = (size_t)c->cfg.batch * c->prompt_rows, wide = imax64(rows, prompt);  // rows of the largest pass
@@ -128,7 +133,7 @@ void carve(mtad_ctx* c, char* base) {
   c->xn = k.take<float>(rows8 * imax(imax(dmax, hhd), fmax));
   c->xg = k.take<float>(rows8 * dmax);
   c->ssq = k.take<float>(wide * (size_t)(dmax / 16 + 1));
-  c->ssq_sum = k.take<float>(prompt);
+  c->ssq_sum = k.take<float>(prompt > 256 ? prompt : 0);
   c->lse_part = k.take<float>(rows * (size_t)(imax(t.vocab, d.vocab) / 16 + 1) * 2);
   c->attn_cnt_n = (size_t)c->cfg.batch * imax(t.n_heads, d.n_heads) * (size_t)((c->Rmax + 7) / 8);
   c->attn_cnt = k.take<int>(c->attn_cnt_n);
@@ -143,13 +148,13 @@ void carve(mtad_ctx* c, char* base) {
         if (gemm_split_counters(N) > pc) pc = gemm_split_counters(N);
       }
     }
-    if (rows > 24 && (t.dtype == 1 || d.dtype == 1) && gemm_dma_split_floats() > pf) pf = gemm_dma_split_floats();
+    if (roomy && rows > 24 && (t.dtype == 1 || d.dtype == 1) && gemm_dma_split_floats() > pf) pf = gemm_dma_split_floats();
     c->gemm_part_n = pf + 64;
     c->gemm_part = k.take<float>(c->gemm_part_n);
     c->gemm_cnt_n = pc + 1;
     c->gemm_cnt = k.take<int>((size_t)c->gemm_cnt_n);
     // widest reduction dimension of any product: the model widths and FFN widths
-    c->gemm_xfrag_n = gemm_dma_xfrag_elems(imax((int)rows, 256), imax(imax(dmax, fmax), hhd));
+    c->gemm_xfrag_n = gemm_dma_xfrag_elems(roomy ? 256 : 192, imax(imax(dmax, fmax), hhd));
     c->gemm_xfrag = k.take<bf16_t>(c->gemm_xfrag_n);
   }
   {  // the one-launch pass: versions of what its steps hand on, sized for FLOW_MAX_ROWS rows of the larger need of the two models
@@ -193,7 +198,20 @@ void carve(mtad_ctx* c, char* base) {
   c->rd.nspec = k.take<int32_t>(c->cfg.batch);
   c->part_key = k.take<float>((size_t)c->cfg.batch * TOPB_BLOCKS * 8);
   c->part_idx = k.take<int>((size_t)c->cfg.batch * TOPB_BLOCKS * 8);
-  c->ws_need = k.off;
+  return k.off;
+}
+
+// The largest layout that fits `bytes`: prompt chunks of ever fewer rows, down to prefill_rows.  False: not even that fits.
+bool carve_within(mtad_ctx* c, char* base, size_t bytes) {
+  const int least = imin(c->prompt_best, c->cfg.prefill_rows);
+  for (int p = c->prompt_best;; p = imax(p / 2, least)) {
+    for (const bool roomy : {true, false})
+      if (carve(c, nullptr, p, roomy) <= bytes) {
+        carve(c, base, p, roomy);
+        return true;
+      }
+    if (p == least) return false;
+  }
 }
 
 int kv_ok(const mtad_kv* kv) {
@@ -525,10 +543,10 @@ int mtad_create(mtad_ctx** out, const mtad_config* cfg, const mtad_model* target
     delete c;
     return MTAD_ESHAPE;
   }
-  if (target->dtype == 1 || draft->dtype == 1) c->prompt_rows = imax(c->cfg.prefill_rows, imin(PROMPT_PASS_ROWS / cfg->batch, cfg->max_context));
+  if (target->dtype == 1 || draft->dtype == 1) c->prompt_best = imax(c->cfg.prefill_rows, imin(PROMPT_PASS_ROWS / cfg->batch, cfg->max_context));
   c->flow_on = 1;
   if (const char* e = getenv("MTAD_FUSED_PASS")) c->flow_on = atoi(e) < 0 ? 0 : (atoi(e) > 2 ? 2 : atoi(e));
-  carve(c, nullptr);
+  c->ws_need = carve(c, nullptr, c->prompt_best, true);
   *out = c;
   return MTAD_OK;
 }
@@ -540,9 +558,12 @@ size_t mtad_workspace_bytes(const mtad_ctx* c) { return c ? c->ws_need : 0; }
 int mtad_bind_workspace(mtad_ctx* c, void* buf, size_t bytes) {
   if (!c || !buf) return MTAD_EINVAL;
   if (((uintptr_t)buf) & 255) return MTAD_EINVAL;
-  if (bytes < c->ws_need) return MTAD_ECAP;
+  if (!carve_within(c, (char*)buf, bytes)) {  // (a workspace bound before stays bound)
+    if (c->ws) carve_within(c, c->ws, c->ws_bytes);
+    return MTAD_ECAP;
+  }
   c->ws = (char*)buf;
-  carve(c, c->ws);
+  c->ws_bytes = bytes;
   {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;

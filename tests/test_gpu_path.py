@@ -323,3 +323,47 @@ def test_key_splits_of_few_rows(hd, heads, kv_heads, batch, gamma, n):
     print(f"key splits hd {hd} heads {heads}/{kv_heads} batch {batch} gamma {gamma} n {n}", flush=True)
     st = run_pair(ts, ds, wt, wd, prompt, 8, gamma=gamma, beam=2, mode="mtad", tau=0.0, seed=5, check_kv=True, fused_pass=0)
     assert st["excused"] == 0 and all(e == gamma for e in st["eta"])
+
+
+@pytest.mark.parametrize("share", [0.0, 0.4, 0.9])
+def test_prompt_and_passes_on_a_smaller_workspace(share):
+    """Any buffer between what chunks of prefill_rows rows need and the best size is bound and used up to its end and no further:
+    the same caches (to the rounding of another chunking) and logits as with the best size."""
+    from paper_2407_09722_amd import binding as mb
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    ts = si.ModelShape(2, 512, 4, 2, 128, 1376, 512, "bf16")
+    m = DeviceModel(ts, _weights(ts, 41, "target", boost=2.0), DEV)
+    prompt = np.random.default_rng(8).integers(0, 512, (3, 401)).astype(np.int32)
+    results = []
+    for small in (False, True):
+        eng = Engine(m, m, batch=3, gamma=4, beam=3, mode="mmtad", max_context=512, prefill_rows=16)
+        if small:
+            def accepted(n):
+                try:
+                    mb.mtad_bind_workspace(eng.ctx, eng.workspace[:256 * n])
+                    return True
+                except mb.MtadError as e:
+                    assert e.status == mb.MTAD_ECAP
+                    return False
+            lo, best = 1, mb.mtad_workspace_bytes(eng.ctx) // 256
+            hi = best
+            while lo < hi:
+                mid = (lo + hi) // 2
+                lo, hi = (lo, mid) if accepted(mid) else (mid + 1, hi)
+            n = 256 * int(lo + share * (best - lo))
+            eng.workspace.fill_(0x5A)
+            mb.mtad_bind_workspace(eng.ctx, eng.workspace[:n])
+            print(f"workspace {n} of {256 * best}, least {256 * lo}", flush=True)
+            with pytest.raises(mb.MtadError):                      # refused, and the buffer bound before stays
+                mb.mtad_bind_workspace(eng.ctx, eng.workspace[:256 * (lo - 1)])
+        eng.prefill(prompt)
+        eng.iteration(0.0)
+        torch.cuda.synchronize()
+        assert mb.mtad_device_status(eng.ctx) == 0
+        if small:
+            assert bool((eng.workspace[n:] == 0x5A).all())
+        results.append([eng.tkv.gather(s, 400) for s in range(3)] + [[eng.logits.double().cpu().numpy()]])
+        eng.close()
+    for a, b in zip(*results):
+        for x, y in zip(a, b):
+            assert np.all(np.abs(x - y) <= 4e-3 * np.maximum(1, np.abs(y)))   # as for other chunk orders, one more layer and the head on top
