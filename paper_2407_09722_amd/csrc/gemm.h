@@ -54,6 +54,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tag, hipStream_t s, 
 // launch_gemm_bf16.  tiles: instead of the planned ones (refused where they do not exist or fit)
 struct GemmTiles {
   int strips, row_groups, tall, ranges;  // strips per wave, groups of 64 rows (0: one of 32), wave groups side by side, ranges of the reduction
+  int lds;  // bytes a compute unit is taken to have; 0: ask the device
 };
 hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* np, const GemmTiles* tiles = nullptr);
 GemmTiles gemm_dma_tiles(const GemmArgs& a, int epi);  // the planned ones

@@ -645,7 +645,15 @@ int device_cus() {
 struct Plan {
   int A, B, KS, tiles_n, tiles_m;
   bool tall;
+  int lds = 0;  // bytes a compute unit is taken to have; 0: ask the device
 };
+
+// LDS of one compute unit of the device (the most a workgroup can be given); 160 KiB on gfx950 if the query fails
+int device_lds_bytes(int dev) {
+  int v = 0;
+  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess) v = 0;
+  return v > 0 ? v : 160 * 1024;
+}
 constexpr int KS_MAX = 8;
 // partial sums per range must add up to the whole product, and what reads them (run_sum) knows neither row factors nor logsumexps
 bool can_cut(const GemmArgs& a, int epi) { return a.part && !(epi == EPI_STORE && (a.lse_part || a.ssq)); }
@@ -699,19 +707,25 @@ Plan plan_for(const GemmArgs& a, int epi) {
 Plan plan_of(const GemmArgs& a, const GemmTiles& t) {
   const int TS = t.strips << t.tall, NT = a.N >> 4;
   const int rows = t.row_groups ? 64 * t.row_groups : 32;
-  return Plan{t.strips, t.row_groups, t.ranges, (NT + TS - 1) / TS, (a.R + rows - 1) / rows, t.tall != 0};
+  return Plan{t.strips, t.row_groups, t.ranges, (NT + TS - 1) / TS, (a.R + rows - 1) / rows, t.tall != 0, t.lds};
 }
 
 template <int A, int B, bool TALL, int EPI>
 hipError_t run_shape(const GemmArgs& a, const Plan& p, hipStream_t s) {
   using Sh = DmaShape<A, B, TALL>;
   auto kern = gemm_bf16_dma_kernel<A, B, TALL, EPI>;
-  // more than 64 KiB of dynamic LDS needs the attribute; a success is remembered, a failure is reported and tried again
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set.load(std::memory_order_acquire)) {
+  // Once per device: its compute units hold the ring, and more than 64 KiB of dynamic LDS needs the attribute.  A success is
+  // remembered (bit d: device d; beyond 63 every launch asks), a failure is reported and tried again.
+  static std::atomic<uint64_t> ready{0};
+  int dev = 0;
+  if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
+  if (p.lds || !(ready.load(std::memory_order_acquire) & bit)) {
+    constexpr int STATIC = (int)sizeof(float) * Sh::ROWS;  // the kernel's own array
+    if (Sh::LDS + STATIC > (p.lds ? p.lds : device_lds_bytes(dev))) return hipErrorInvalidValue;
     const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Sh::LDS);
     if (e != hipSuccess) return e;
-    attr_set.store(true, std::memory_order_release);
+    ready.fetch_or(bit, std::memory_order_release);
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_n * p.tiles_m * p.KS)), dim3(NW * 64), Sh::LDS, s, a, p.tiles_n, p.tiles_m, p.KS);
   return hipGetLastError();
@@ -806,7 +820,7 @@ bool gemm_dma_wide(int N) { return ((N >> 4) + 7) / 8 * 2 >= device_cus(); }
 
 GemmTiles gemm_dma_tiles(const GemmArgs& a, int epi) {
   const Plan p = plan_for(a, epi);
-  return GemmTiles{p.A, p.B, p.tall, p.KS};
+  return GemmTiles{p.A, p.B, p.tall, p.KS, 0};
 }
 
 hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* np, const GemmTiles* t) {
@@ -830,13 +844,14 @@ hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* 
 }  // namespace mtad
 
 // For the tests (and to time plans against each other): the many-row product with the epilogue and the tiles named, tiles[4] =
-// {strips per wave, row groups of 64 (0: one of 32), groups side by side, ranges}, or, with tiles[0] = 0, the planned tiles written there.  args: a
-// GemmArgs of `bytes` bytes.  Launches only with run != 0.  0, or -1 (sizes differ, or tiles that do not exist or fit) or -4.
+// {strips per wave, row groups of 64 (0: one of 32), groups side by side, ranges}, or, with tiles[0] = 0, the planned tiles
+// written there.  args: a GemmArgs of `bytes` bytes.  run 0: no launch; above 1: on a device taken to have that many bytes of LDS
+// per compute unit.  0, or -1 (sizes differ, or tiles that do not exist or fit) or -4.
 extern "C" int mtad_test_gemm_tiles(const void* args, size_t bytes, int epi, int* tiles, int run, void* stream) {
   using namespace mtad;
   if (!args || !tiles || bytes != sizeof(GemmArgs)) return -1;
   const GemmArgs& a = *(const GemmArgs*)args;
-  GemmTiles t{tiles[0], tiles[1], tiles[2], tiles[3]};
+  GemmTiles t{tiles[0], tiles[1], tiles[2], tiles[3], run > 1 ? run : 0};
   if (!t.strips) t = gemm_dma_tiles(a, epi);
   tiles[0] = t.strips; tiles[1] = t.row_groups; tiles[2] = t.tall; tiles[3] = t.ranges;
   if (!run) return 0;

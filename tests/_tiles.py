@@ -28,9 +28,9 @@ def _call(args, epi, tile, run, stream):
     return fn(C.byref(args), C.sizeof(args), epi, C.byref(t), run, stream), tuple(t)
 
 
-def launch(args, epi, tile, ranges, stream=None):
-    """The product on the given tile; 0, or the entry point's error."""
-    return _call(args, epi, (*tile, ranges), 1, stream)[0]
+def launch(args, epi, tile, ranges, stream=None, lds=1):
+    """The product on the given tile (lds: on a device with that many bytes per compute unit); 0, or the entry point's error."""
+    return _call(args, epi, (*tile, ranges), lds, stream)[0]
 
 
 def planned(R, N, K, epi=STORE, part_floats=256 ** 3):

@@ -225,3 +225,21 @@ def test_tiles_that_do_not_exist_or_fit_are_refused():
     assert T.launch(p.args, T.STORE, (8, 1, 0), 2) == -1
     torch.cuda.synchronize()
     assert bool((Y == KEPT).all())
+
+
+def test_a_device_with_too_little_lds_is_refused():
+    """Checked on the host before the launch, also when the same kernel has run before."""
+    from paper_2407_09722_amd import binding as mb
+    p = Product(40, 80, 96, 1, mb.MTAD_PACK_PLAIN)
+    Y = torch.full((40, 80), KEPT, device=DEV)
+    p.set(Y=Y)
+    p.args.ldy = 80
+    for tile in ((8, 1, 0), (5, 4, 1)):
+        assert T.launch(p.args, T.STORE, tile, 1, lds=64 << 10) == -1
+        torch.cuda.synchronize()
+        assert bool((Y == KEPT).all())
+        assert T.launch(p.args, T.STORE, tile, 1, lds=160 << 10) == 0 and T.launch(p.args, T.STORE, tile, 1) == 0
+        torch.cuda.synchronize()
+        p.close(Y.cpu().numpy())
+        assert T.launch(p.args, T.STORE, tile, 1, lds=64 << 10) == -1
+        Y.fill_(KEPT)
