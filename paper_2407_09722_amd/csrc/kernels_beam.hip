@@ -503,8 +503,7 @@ __device__ __forceinline__ void accept_walk(AcceptWalk& w, const TreeView& tree,
     w.tok[t] = tree.tok[o];
     w.cond[t] = logp_cond[o];
   }
-  const bool q_in = gamma <= MTAD_MAX_ROWS;
-  if (q_in && t < gamma) w.qref[t] = tree.qref[s * gamma + t];
+  if (t < gamma) w.qref[t] = tree.qref[s * gamma + t];  // gamma < MTAD_MAX_ROWS: a context's passes hold gamma + 1 rows
   __syncthreads();
   if (t == 0) {
     // log p of every branch: conditionals summed from the first level down (parents precede children)
@@ -517,7 +516,7 @@ __device__ __forceinline__ void accept_walk(AcceptWalk& w, const TreeView& tree,
       w.joint[c] = jp;
       const int i = w.dep[c];
       if (i < 1 || i > gamma) continue;
-      const float diff = jp - (q_in ? w.qref[i - 1] : tree.qref[s * gamma + i - 1]);
+      const float diff = jp - w.qref[i - 1];
       if (mode == 0) {
         if (fminf(0.f, diff) > log_tau && i >= eta) { eta = i; node = c; }  // rows of a chain come in depth order
       } else {

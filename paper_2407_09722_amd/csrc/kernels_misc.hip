@@ -69,7 +69,8 @@ hipError_t launch_embed(int dtype, const void* E, const int32_t* tok, float* h, 
   return hipGetLastError();
 }
 
-// out[row][i] = h[row][i] / sqrt(mean(h[row]^2) + eps) * g[i]
+// out[row][i] = h[row][i] / sqrt(mean(h[row]^2) + eps) * g[i].  No pass runs it (the products normalise their input themselves): it is
+// the component entry point mtad_k_rmsnorm.
 template <typename T>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ h, const float* __restrict__ g, T* __restrict__ out,
                                                       int d, float eps) {

@@ -88,6 +88,7 @@ int shape_ok(const mtad_model* m) {
   return 1;
 }
 
+// key splits of a float32 model's attention
 int splits_for(const mtad_ctx* c, const mtad_model* m, int R) {
   const int chunks = (R + 15) / 16;
   const int blocks = c->cfg.batch * m->n_heads * chunks;
@@ -375,7 +376,6 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
   const int d = m->d_model, f = m->d_ffn, H = m->n_heads, hd = m->head_dim;
   const int qkvw = (H + 2 * m->n_kv_heads) * hd;
   const KvView kvv = view_of(kv, m);
-  const int n_splits = splits_for(c, m, R);
   const int tag = same_shape(m, &c->tshape) ? 1 : 0;
   const void* const* W = m->weights;
   const int tail = 1 + 6 * m->n_layers;
