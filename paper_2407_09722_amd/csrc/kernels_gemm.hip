@@ -23,6 +23,8 @@
 
 #include <stdlib.h>
 
+#include <type_traits>
+
 namespace mtad {
 
 // ---- packing ------------------------------------------------------------------------------------------
@@ -339,6 +341,11 @@ __global__ __launch_bounds__(GW * 64) void gemm_bf16_multi_kernel(GemmArgs a, in
 // up), RB rows at a time; plain FMA, sums over the wave.  These models are tiny and every kernel of a pass costs its launch:
 // normalisation (the row factor commutes with the product, as above), rotation with the cache write and the gating ride on
 // the products, five kernels a layer instead of nine (4 layers, d 256, 5 rows: 123 us a pass, 200 before).
+// Weights of less than 8 MB: the launch is one memory latency, the loads of RB rows go out together and those past the end are the
+// last one again.  From there on what is computed for rows that do not exist costs its share: 8192 x 4096, one row 35.9 us with RB =
+// 8, 21.6 with RB = 1 (6.2 TB/s); three rows 35.8, 25.6 with RB = 4; nine rows (8 and 1) 72.9, 57.7 without them.
+__host__ __device__ constexpr bool gemm_f32_small(const GemmF32Args& a) { return (int64_t)a.N * a.K < (2 << 20); }
+
 template <int RB, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   constexpr bool PAIR = EPI == EPI_SWIGLU || EPI == EPI_QKV;
@@ -359,34 +366,47 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   for (int r = 0; r < RB; ++r) acc[r] = acc2[r] = ss[r] = 0.f;
   const float *w1 = a.W + (int64_t)n * K, *w2 = a.W + (int64_t)n2 * K;
   const int rows = min(RB, a.R - r0);
+  auto products = [&](auto ALL, auto GAIN) {  // ALL: RB rows (past the end the last one again), else those there are
 #pragma unroll 2
-  for (int k = lane * 4; k < K; k += 256) {
-    const float4 w = *(const float4*)(w1 + k);
-    float4 v = w, g = make_float4(1.f, 1.f, 1.f, 1.f), x[RB];
-    if constexpr (PAIR) v = *(const float4*)(w2 + k);
-    if (a.gain) g = *(const float4*)(a.gain + k);
+    for (int k = lane * 4; k < K; k += 256) {
+      const float4 w = *(const float4*)(w1 + k);
+      float4 v = w, g = make_float4(1.f, 1.f, 1.f, 1.f), x[RB];
+      if constexpr (PAIR) v = *(const float4*)(w2 + k);
+      if constexpr (GAIN) g = *(const float4*)(a.gain + k);
 #pragma unroll
-    for (int r = 0; r < RB; ++r) x[r] = *(const float4*)(a.X + (int64_t)(r0 + min(r, rows - 1)) * K + k);  // rows past the end: the last one again
+      for (int r = 0; r < RB; ++r)
+        if (ALL || r < rows) x[r] = *(const float4*)(a.X + (int64_t)(r0 + (ALL ? min(r, rows - 1) : r)) * K + k);
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      if (a.gain) {
-        ss[r] = fmaf(x[r].x, x[r].x, ss[r]);
-        ss[r] = fmaf(x[r].y, x[r].y, ss[r]);
-        ss[r] = fmaf(x[r].z, x[r].z, ss[r]);
-        ss[r] = fmaf(x[r].w, x[r].w, ss[r]);
-        x[r].x *= g.x; x[r].y *= g.y; x[r].z *= g.z; x[r].w *= g.w;
-      }
-      acc[r] = fmaf(w.x, x[r].x, acc[r]);
-      acc[r] = fmaf(w.y, x[r].y, acc[r]);
-      acc[r] = fmaf(w.z, x[r].z, acc[r]);
-      acc[r] = fmaf(w.w, x[r].w, acc[r]);
-      if constexpr (PAIR) {
-        acc2[r] = fmaf(v.x, x[r].x, acc2[r]);
-        acc2[r] = fmaf(v.y, x[r].y, acc2[r]);
-        acc2[r] = fmaf(v.z, x[r].z, acc2[r]);
-        acc2[r] = fmaf(v.w, x[r].w, acc2[r]);
+      for (int r = 0; r < RB; ++r) {
+        if (!ALL && r >= rows) continue;
+        if constexpr (GAIN) {
+          ss[r] = fmaf(x[r].x, x[r].x, ss[r]);
+          ss[r] = fmaf(x[r].y, x[r].y, ss[r]);
+          ss[r] = fmaf(x[r].z, x[r].z, ss[r]);
+          ss[r] = fmaf(x[r].w, x[r].w, ss[r]);
+          x[r].x *= g.x; x[r].y *= g.y; x[r].z *= g.z; x[r].w *= g.w;
+        }
+        acc[r] = fmaf(w.x, x[r].x, acc[r]);
+        acc[r] = fmaf(w.y, x[r].y, acc[r]);
+        acc[r] = fmaf(w.z, x[r].z, acc[r]);
+        acc[r] = fmaf(w.w, x[r].w, acc[r]);
+        if constexpr (PAIR) {
+          acc2[r] = fmaf(v.x, x[r].x, acc2[r]);
+          acc2[r] = fmaf(v.y, x[r].y, acc2[r]);
+          acc2[r] = fmaf(v.z, x[r].z, acc2[r]);
+          acc2[r] = fmaf(v.w, x[r].w, acc2[r]);
+        }
       }
     }
+  };
+  constexpr std::true_type YES{};
+  constexpr std::false_type NO{};
+  if (RB == 1 || rows == RB || gemm_f32_small(a) || (K < 1024 && rows > RB / 2)) {  // (a short reduction is all latency, too)
+    if (a.gain) products(YES, YES);
+    else products(YES, NO);
+  } else {
+    if (a.gain) products(NO, YES);
+    else products(NO, NO);
   }
   // the sums of row r end in lane r (all rows' epilogues side by side)
   float y = 0.f, y2 = 0.f, q = 0.f;
@@ -442,10 +462,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   }
 }
 
-hipError_t launch_gemm_f32(const GemmF32Args& a, int epi, hipStream_t s) {
-  if (a.R <= 0) return hipSuccess;
-  if (a.K % 4) return hipErrorInvalidValue;
-  constexpr int RB = 8;
+template <int RB>
+static hipError_t run_f32(const GemmF32Args& a, int epi, hipStream_t s) {
   const int items = (epi == EPI_SWIGLU || epi == EPI_QKV) ? a.N / 2 : a.N;
   const dim3 grid((items + 3) / 4, (a.R + RB - 1) / RB), block(256);
   switch (epi) {
@@ -455,6 +473,13 @@ hipError_t launch_gemm_f32(const GemmF32Args& a, int epi, hipStream_t s) {
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_gemm_f32(const GemmF32Args& a, int epi, hipStream_t s) {
+  if (a.R <= 0) return hipSuccess;
+  if (a.K % 4) return hipErrorInvalidValue;
+  if (a.R > 4 || gemm_f32_small(a)) return run_f32<8>(a, epi, s);
+  return a.R == 1 ? run_f32<1>(a, epi, s) : run_f32<4>(a, epi, s);
 }
 
 template <int NG, int EPI, int TAG>

@@ -167,7 +167,10 @@ def test_gemm_accumulate_and_padded_rows():
     _gemm_case(mb, 7, 30, 44, 0, seed=3, accumulate=True, ldy=32)
 
 
-@pytest.mark.parametrize("R,N,K", [(1, 4, 4), (5, 1024, 256), (9, 688 * 2, 256), (5, 256, 688), (32, 37, 344), (64, 1024, 128)])
+@pytest.mark.parametrize("R,N,K", [(1, 4, 4), (5, 1024, 256), (9, 688 * 2, 256), (5, 256, 688), (32, 37, 344), (64, 1024, 128),
+                                   # weights of 8 MB and more: as many rows per wave as there are, and remainders of eight
+                                   (1, 2047, 1024), (1, 2048, 1024), (1, 2053, 1028), (3, 4097, 516), (4, 2048, 1024), (5, 2052, 1028), (5, 4100, 512),
+                                   (9, 2050, 1024), (15, 2053, 1028), (16, 2048, 1024)])
 def test_gemm_fp32_matches_float64(R, N, K):
     mb = _mb()
     _gemm_case(mb, R, N, K, 0, seed=R + N + K)

@@ -367,3 +367,20 @@ def test_prompt_and_passes_on_a_smaller_workspace(share):
     for a, b in zip(*results):
         for x, y in zip(a, b):
             assert np.all(np.abs(x - y) <= 4e-3 * np.maximum(1, np.abs(y)))   # as for other chunk orders, one more layer and the head on top
+
+
+@pytest.mark.parametrize("gamma", [1, 3, 4, 8])   # 2, 4, 5 and 9 rows; the draft's steps have 2 and 3
+def test_float32_pair_with_large_products(gamma):
+    """Products of 8 MB of weights and more with every fused step (normalisation, rotation and cache write, gating, lm_head)."""
+    ts, ds = si.ModelShape(1, 1024, 8, 4, 128, 2056, 2560, "fp32"), si.ModelShape(1, 128, 2, 1, 64, 172, 2560, "fp32")
+    wt, wd = _weights(ts, 47, "target", boost=2.0), _weights(ds, 47, "draft", boost=2.0)
+    prompt = np.random.default_rng(gamma).integers(0, 2560, (1, 21)).astype(np.int32)
+    print(f"float32 pair gamma {gamma}", flush=True)
+    st = run_pair(ts, ds, wt, wd, prompt, 6, gamma=gamma, beam=2, mode="mtad", tau=0.0, seed=7, check_kv=True)
+    assert st["excused"] == 0
+
+
+def test_float32_plain_decoding_with_large_products():
+    ts = si.ModelShape(1, 1024, 8, 4, 128, 2056, 2560, "fp32")
+    st = run_autoregressive(ts, _weights(ts, 47, "target", boost=2.0), np.random.default_rng(5).integers(0, 2560, (1, 9)).astype(np.int32), 6, sample=True, seed=6)
+    assert st["excused"] == 0
