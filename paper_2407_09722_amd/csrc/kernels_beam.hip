@@ -220,13 +220,14 @@ __device__ __forceinline__ uint64_t block_max_rank(uint64_t v, uint64_t* sh) {
 // list: TOP_LIST entries of the wave's own.
 constexpr uint64_t NO_RANK = ((uint64_t)0x007FFFFFu << 32) | 0x80000000u;  // rank_of(-infinity, 0x7FFFFFFF)
 constexpr int TOP_N = 16, TOP_LIST = MAXB * (TOP_N + 1);
-template <int N>
+template <int N, bool ONE = false>
 __device__ __forceinline__ uint64_t wave_top(const uint64_t (&e)[N], uint64_t kept, int b, uint64_t* list, int* count) {
   static_assert(N <= TOP_N, "list size");
   const int lane = threadIdx.x & 63;
   uint64_t mine = kept;
 #pragma unroll
   for (int j = 0; j < N; ++j) mine = e[j] > mine ? e[j] : mine;
+  if constexpr (ONE) return wave_max_rank(mine);  // b = 1: nothing to list
   uint64_t left = mine, T = 0;
   for (int r = 0; r < b; ++r) {
     T = wave_max_rank(left);
@@ -286,7 +287,8 @@ __device__ __forceinline__ float cand_score(const float* logits, const float* ls
   return cum[r] + (logits[(int64_t)row * V + v] - lse[row]);
 }
 
-// stage 1: grid (G, B); block g scans its slice of the n_live*V candidates
+// stage 1: grid (G, B); block g scans its slice of the n_live*V candidates, N per thread at a time.  ONE: one survivor.
+template <int N, bool ONE>
 __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restrict__ logits, const float* __restrict__ lse, BeamView hist,
                                                           const int32_t* __restrict__ cu_cnt, const int32_t* __restrict__ len, int step,
                                                           int R, int gamma, int beam, int V, int sample, uint64_t seed,
@@ -318,20 +320,20 @@ __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restric
       }
     }
   __syncthreads();
-  // sixteen candidates per thread at a time, their logits requested together
+  // N candidates per thread at a time, their logits requested together
   const int wave = threadIdx.x >> 6;
   uint64_t top = NO_RANK;
-  for (int cb = c0 + (int)threadIdx.x; cb - (int)threadIdx.x < c1; cb += 256 * TOP_N) {
-    uint64_t e[TOP_N];
-    float x[TOP_N];
+  for (int cb = c0 + (int)threadIdx.x; cb - (int)threadIdx.x < c1; cb += 256 * N) {
+    uint64_t e[N];
+    float x[N];
 #pragma unroll
-    for (int u = 0; u < TOP_N; ++u) {
+    for (int u = 0; u < N; ++u) {
       const int c = min(cb + 256 * u, c1 - 1), r = c / V;
       x[u] = logits[(int64_t)row0 * V + c];  // rows of the live beams follow each other
       x[u] = cum_s[r] + (x[u] - (lse_part ? lse_s[r] : lse[row0 + r]));
     }
 #pragma unroll
-    for (int u = 0; u < TOP_N; ++u) {
+    for (int u = 0; u < N; ++u) {
       const int c = cb + 256 * u;
       e[u] = NO_RANK;
       if (c < c1) {
@@ -339,7 +341,7 @@ __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restric
         e[u] = rank_of(x[u] == x[u] ? x[u] : -INFINITY, c);  // a NaN score never wins and never leaves an empty slot behind
       }
     }
-    top = wave_top(e, top, beam, sh.list[wave], &sh.count[wave]);
+    top = wave_top<N, ONE>(e, top, beam, sh.list[wave], &sh.count[wave]);
   }
   top = block_top(top, beam, sh);
   if ((int)threadIdx.x < beam) {
@@ -389,8 +391,21 @@ __global__ __launch_bounds__(256) void topb_stage2_kernel(const float* __restric
 hipError_t launch_topb(const float* logits, const float* lse, BeamView hist, const int32_t* cu_cnt, const int32_t* len, int step,
                        int B, int R, int gamma, int beam, int V, int sample, uint64_t seed, float* part_key, int* part_idx, int G,
                        hipStream_t s, const float* lse_part, int NP, float* lse_out) {
-  hipLaunchKernelGGL(topb_stage1_kernel, dim3(G, B), dim3(256), 0, s, logits, lse, hist, cu_cnt, len, step, R, gamma, beam, V, sample,
-                     seed, part_key, part_idx, (const float2*)lse_part, NP, lse_out);
+  // Sixteen candidates a thread keep the memory busy in a long slice; most of a short one's would be the last one again, and a single
+  // survivor needs no list.  With sixteen and the list / with four, and without it for one survivor, 64 workgroups a sequence: beam 1,
+  // 32000 tokens, 1, 16 and 64 sequences 8.0 / 5.9, 11.6 / 7.2 and 26.4 / 11.8 us; beam 4, 4096 tokens, one sequence 10.9 / 9.4.
+  const int per = ((step == 0 ? 1 : beam) * V + G - 1) / G;
+  auto stage1 = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(G, B), dim3(256), 0, s, logits, lse, hist, cu_cnt, len, step, R, gamma, beam, V, sample, seed, part_key, part_idx,
+                       (const float2*)lse_part, NP, lse_out);
+  };
+  if (per > 4 * 256) {
+    if (beam == 1) stage1(topb_stage1_kernel<TOP_N, true>);
+    else stage1(topb_stage1_kernel<TOP_N, false>);
+  } else {
+    if (beam == 1) stage1(topb_stage1_kernel<4, true>);
+    else stage1(topb_stage1_kernel<4, false>);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(topb_stage2_kernel, dim3(B), dim3(256), 0, s, logits, lse, hist, cu_cnt, step, R, gamma, beam, V, G, part_key,

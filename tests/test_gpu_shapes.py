@@ -275,6 +275,37 @@ def test_beam_topb_over_slices_of_several_trips(kind):
     eng.close()
 
 
+@pytest.mark.parametrize("V,beam,step", [(40, 1, 0), (1000, 1, 1), (65536, 1, 1), (65537, 1, 0), (300000, 1, 1), (16, 8, 1), (1000, 8, 0), (8192, 8, 1), (8193, 8, 1)])
+def test_beam_topb_over_short_slices_and_single_survivors(V, beam, step):
+    """Up to 1024 candidates in a workgroup's slice (65536 in all) take four a thread, longer ones sixteen; beam 1 takes no list.  The
+    edges of both, slices that are empty, equal keys, NaN and minus infinity."""
+    from paper_2407_09722_amd import binding as mb
+    B, gamma = 3, 2
+    eng = _engine(B, gamma, beam, "mtad", V)
+    g = np.random.default_rng(V + beam)
+    R = max(gamma + 1, beam)
+    logits = np.floor(4.0 * g.standard_normal((B, R, V))).astype(np.float32) if V > 100 else g.standard_normal((B, R, V)).astype(np.float32)
+    logits[1, :, ::2] = np.nan
+    logits[2] = -np.inf
+    logits[2, :, V - 3] = 1.0
+    lse = np.full((B, R), 9.0, np.float32)
+    prev = -np.abs(g.standard_normal((B, beam))).astype(np.float32)
+    eng.h_cum[:, 0].copy_(torch.from_numpy(prev).to(DEV))
+    print(f"beam top-b V {V} beam {beam} step {step}", flush=True)
+    mb.mtad_k_beam_topb(eng.ctx, torch.from_numpy(logits).to(DEV), torch.from_numpy(lse).to(DEV), eng.hist, step, torch.ones(B, dtype=torch.int32, device=DEV),
+                        torch.full((B,), 40, dtype=torch.int32, device=DEV), R, V, 0, 5)
+    torch.cuda.synchronize()
+    tok, par, cum = (x.cpu().numpy()[:, step] for x in (eng.h_tok, eng.h_parent, eng.h_cum))
+    for s in range(B):
+        live, rows = (np.zeros(1, np.float32), logits[s, :1]) if step == 0 else (prev[s], logits[s, :beam])
+        flat = (live[:, None] + (rows - np.float32(9.0))).astype(np.float32).ravel()
+        key = np.where(np.isnan(flat), -np.inf, flat.astype(np.float64))
+        sel = np.lexsort((np.arange(flat.size), -key))[:beam]
+        assert list(par[s] * V + tok[s]) == list(sel), s
+        assert np.array_equal(cum[s], flat[sel], equal_nan=True)
+    eng.close()
+
+
 def test_vocabulary_beyond_the_registers_of_the_row_logsumexp():
     """40000 tokens = 2500 strips of the lm_head: the row logsumexps of draft steps and target passes take the loop over memory."""
     t, d = si.ModelShape(1, 128, 2, 2, 64, 160, 40000, "bf16"), si.ModelShape(1, 64, 1, 1, 64, 96, 40000, "bf16")
