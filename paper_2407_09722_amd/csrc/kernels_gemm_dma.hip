@@ -42,16 +42,17 @@ constexpr int NW = 8;                    // waves per workgroup: two groups of f
 constexpr int LDS_MOST = 160 * 1024 - 1536;  // of a compute unit, less the static arrays
 constexpr int PAIR = 2048;  // bytes of two activation fragments (16 rows)
 constexpr int NONTEMPORAL = 2;  // cache policy operand of global_load_lds
-// A wide output's weights that a single tile of rows reads (tiles of at most 64 rows, 7 or 8 strips) are requested as data that is
-// not read again.  HBM bounds these products: 32 rows, 32000 x 4096 49.7 -> 45.0 us (5.8 TB/s), 27648 x 5120 53.1 -> 48.0; 64 rows,
-// 32000 x 5120 68.7 -> 60.1, 27648 x 5120 60.2 -> 55.2.  Cut reductions of narrow outputs lose by it (5120 x 5120 at 48 rows
-// 19.1 -> 19.9 us), and so do tiles of 4 to 6 strips, which have fewer weights on their way (22016 x 4096, 32 rows: 35.5 -> 38.2).
-__host__ __device__ constexpr bool streams(int strips, int row_tiles) { return strips >= 1024 && row_tiles == 1; }
+// Weights that a single tile of rows reads (tiles of at most 64 rows, 7 or 8 strips) and that the 256 MB of last-level cache cannot
+// hold from one pass to the next are requested as data that is not read again.  HBM bounds these products: 32 rows, 27648 x 5120
+// 53.1 -> 48.0 us (5.9 TB/s), 32000 x 5120 61.4 -> 53.4; 64 rows, 32000 x 5120 68.7 -> 60.1.  A smaller matrix read again and again
+// loses what the cache would bring (32000 x 2048 at 64 rows 24.3 -> 26.3, 57344 x 1280 32.1 -> 39.1); so do tiles of 4 to 6 strips,
+// which have fewer weights on their way (22016 x 4096, 32 rows: 35.5 -> 38.2).
+__host__ __device__ constexpr bool streams(int N, int K, int row_tiles) { return N >= 16384 && (int64_t)N * K >= (1 << 27) && row_tiles == 1; }
 
 // A strips per wave; TALL: the groups own A strips each and both take every k tile, else both own the same A strips.
 // B row groups of 64 rows, or B = 0: one of 32 rows (two of each group's waves hold rows, the others only bring fragments), for
 // passes of 25 to 32: half the activations on their way leave room for weights in the ring (13 slots of 8 strips instead of 9) and
-// among the requests.  With weights requested as above: 32000 x 4096 at 32 rows 52.1 us with a 64-row tile, 45.0 with this one.
+// among the requests.  With weights requested as above: 32000 x 5120 at 32 rows 59.1 us with a 64-row tile, 53.7 with this one.
 template <int A, int B_, bool TALL>
 struct DmaShape {
   static constexpr bool HALF_TILE = B_ == 0;
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int wr = wave & 3, grp = wave >> 2;
   const bool rowless = Sh::HALF_TILE && wr >= 2;  // waves that only bring fragments
   const bool full = !Sh::HALF_TILE || wave < Sh::FULL;
-  const bool stream = Sh::STREAM && streams(a.N >> 4, tiles_m);
+  const bool stream = Sh::STREAM && streams(a.N, a.K, tiles_m);
   const int c = lane & 15, kg = lane >> 4;
   const int KT_all = a.K >> 5, NT = a.N >> 4;
   // workgroups go to the 8 XCDs in turn: give each XCD a contiguous range of tiles, and within it blocks of up to four row tiles
@@ -681,7 +682,7 @@ Plan plan_for(const GemmArgs& a, int epi) {
       if (tall ? B_ < 3 : TS == 4 && B_ > 1) continue;  // (4 strips meet more than 64 rows in no plan at 256 compute units)
       const int tn = (NT + TS - 1) / TS, frags = TS + rows / 8;
       const int mfma = 32 * TS * B, lds = 32 * (tall ? TS + 4 * B : TS + 2 * B) + 8 * frags, fill = 40 * frags;
-      const int hbm = (B_ <= 1 && TS >= 7 && streams(NT, tm) ? 90 : 98) * TS / tm;
+      const int hbm = (B_ <= 1 && TS >= 7 && streams(a.N, a.K, tm) ? 90 : 98) * TS / tm;
       int interval = mfma;
       for (int x : {lds, fill, hbm}) interval = x > interval ? x : interval;
       interval += tall ? 250 : 100;

@@ -207,10 +207,27 @@ def test_every_tile_with_every_epilogue(tile):
 
 
 @pytest.mark.parametrize("tile", [(7, 0, 0), (8, 0, 0), (7, 1, 0), (8, 1, 0)], ids=lambda t: f"{t[0]}x{t[1]}")
-@pytest.mark.parametrize("strips", [1023, 1026])   # the last width whose weights go through the caches, and one whose weights pass them by
-def test_wide_outputs(tile, strips):
-    print(f"tile {tile} strips={strips}", flush=True)
-    _store(32 - 3 * (tile[1] == 0) + 9 * tile[1], strips, 32 * 19, tile, 1, seed=strips)
+@pytest.mark.parametrize("N", [16368, 16400])   # the last width at 8192 terms whose weights go through the caches, and one whose weights pass them by
+def test_weights_that_no_cache_holds(tile, N):
+    """Against the float64 product of the same operands on the device (the matrix is too large for the host)."""
+    from paper_2407_09722_amd import binding as mb
+    K, R = 8192, 29 if tile[1] == 0 else 41
+    print(f"tile {tile} N={N}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N)
+    W = torch.empty(N, K, dtype=torch.bfloat16, device=DEV).normal_(0, 0.05, generator=g)
+    X = torch.empty(R, K, device=DEV).normal_(generator=g)
+    hi = X.bfloat16()
+    lo = (X - hi.float()).bfloat16()
+    planes = torch.zeros(_frag_elems(R, K), dtype=torch.bfloat16, device=DEV)
+    planes[_dev(_offsets(R, K).ravel())] = torch.stack([hi, lo]).ravel()
+    packed, Y = torch.empty_like(W), torch.full((R + 1, N), KEPT, device=DEV)
+    mb.mtad_pack_matrix(mb.MTAD_PACK_PLAIN, W, packed, N, K, 0)
+    a = T.GemmArgs(W=packed.data_ptr(), X=planes.data_ptr(), R=R, N=N, K=K, ncg=(R + 7) // 8, Y=Y.data_ptr(), ldy=N)
+    assert T.launch(a, T.STORE, tile, 1) == 0
+    x, w = hi.double() + lo.double(), W.double()
+    want, scale = x @ w.T, x.abs() @ w.abs().T
+    torch.cuda.synchronize()
+    assert bool(((Y[:R].double() - want).abs() <= 2e-6 * scale + 1e-6).all()) and bool((Y[R] == KEPT).all())
 
 
 def test_tiles_that_do_not_exist_or_fit_are_refused():
