@@ -60,7 +60,6 @@ hipError_t launch_gemm_bf16_dma(const GemmArgs& a, int epi, hipStream_t s, int* 
 GemmTiles gemm_dma_tiles(const GemmArgs& a, int epi);  // the planned ones
 size_t gemm_dma_xfrag_elems(int R, int K);  // scratch a product of R rows on plane input wants
 size_t gemm_dma_split_floats();  // workspace its cut of the reduction dimension may take
-hipError_t launch_ssq_rows(const float* in, float* out, int R, int NP, hipStream_t s);  // out[m] = sum of in[m][0 .. NP)
 bool gemm_dma_wide(int N);       // enough strips to give half of the compute units a workgroup of 8
 // workspace a context should offer for the k split of a product with N outputs (0 if it would never be split)
 size_t gemm_split_floats(int N);

@@ -610,17 +610,6 @@ __global__ __launch_bounds__(256) void gemm_pairs_kernel(GemmArgs a) {
   }
 }
 
-// Sums of squares of a pass of many rows, [R][NP] -> [R]: every workgroup of the products that read them would otherwise reduce
-// its 256 rows again.
-__global__ __launch_bounds__(256) void ssq_rows_kernel(const float* __restrict__ in, float* __restrict__ out, int R, int NP) {
-  const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (m >= R) return;
-  float s = 0.f;
-  for (int p = lane; p < NP; p += 64) s += in[(int64_t)m * NP + p];
-  s = wave_sum(s);
-  if (lane == 0) out[m] = s;
-}
-
 // Activation planes [2][R][K] -> fragments (act_offset's order for more than 24 rows); rows past R are zeros.  One wave per
 // fragment.
 __global__ __launch_bounds__(256) void xfrag_kernel(const bf16_t* __restrict__ X, bf16_t* __restrict__ out, int R, int K, int ncg) {
@@ -811,11 +800,6 @@ size_t gemm_dma_xfrag_elems(int R, int K) { return (size_t)(K >> 5) * ((R + 7) /
 
 // floats of workspace the ranges of a cut reduction may take: at most one workgroup per compute unit, 256 rows x 16 strips each
 size_t gemm_dma_split_floats() { return (size_t)device_cus() * 256 * 256; }
-
-hipError_t launch_ssq_rows(const float* in, float* out, int R, int NP, hipStream_t s) {
-  hipLaunchKernelGGL(ssq_rows_kernel, dim3((unsigned)((R + 3) / 4)), dim3(256), 0, s, in, out, R, NP);
-  return hipGetLastError();
-}
 
 bool gemm_dma_wide(int N) { return ((N >> 4) + 7) / 8 * 2 >= device_cus(); }
 

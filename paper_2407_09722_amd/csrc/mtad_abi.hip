@@ -28,7 +28,6 @@ struct mtad_ctx {
   size_t ws_bytes;
   // workspace carve-up
   float *h, *qkv, *dlogits, *lse, *partial, *part_key, *ssq, *lse_part;
-  float* ssq_sum;    // [rows of a prompt chunk]
   size_t partial_n;  // floats
   float* qrows;  // [batch][gamma][draft vocab]: log q of every draft step's live row when the beam is one wide (mtad_accept_spd)
   void *xn, *xg;  // xn: attention output / FFN activation; xg: h*gain planes feeding the next normalised product
@@ -134,7 +133,6 @@ size_t carve(mtad_ctx* c, char* base, int prompt_rows, bool roomy) {
   c->xn = k.take<float>(rows8 * imax(imax(dmax, hhd), fmax));
   c->xg = k.take<float>(rows8 * dmax);
   c->ssq = k.take<float>(wide * (size_t)(dmax / 16 + 1));
-  c->ssq_sum = k.take<float>(prompt > 256 ? prompt : 0);
   c->lse_part = k.take<float>(rows * (size_t)(imax(t.vocab, d.vocab) / 16 + 1) * 2);
   c->attn_cnt_n = (size_t)c->cfg.batch * imax(t.n_heads, d.n_heads) * (size_t)((c->Rmax + 7) / 8);
   c->attn_cnt = k.take<int>(c->attn_cnt_n);
@@ -399,16 +397,6 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
   const bool prompt = R > c->Rmax;
   const int prompt_splits = prompt ? imax(1, (int)(c->partial_n / attention_partial_floats(B, R, H, hd, 1))) : 0;
   int np = 1;  // partial sums of squares per row currently at ssq
-  const float* ssq = c->ssq;
-  auto sum_ssq = [&]() -> int {
-    ssq = c->ssq;
-    if (prompt && np > 1 && rows > 256) {
-      HIP_TRY(c, launch_ssq_rows(c->ssq, c->ssq_sum, rows, np, s));
-      ssq = c->ssq_sum;
-      np = 1;
-    }
-    return MTAD_OK;
-  };
   for (int l = 0; l < m->n_layers; ++l) {
     const void* const* L = W + 1 + 6 * l;
     GemmArgs a;
@@ -424,7 +412,7 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
     a.xfrag_elems = c->gemm_xfrag_n;
     // qkv
     a.W = (const bf16_t*)L[1]; a.X = (const bf16_t*)c->xg; a.N = qkvw; a.K = d;
-    a.ssq = ssq; a.NP = np;
+    a.ssq = c->ssq; a.NP = np;
     a.q_out = c->qkv; a.rope = c->rope; a.slot = c->rd.slot; a.kv = kvv; a.layer = l; a.Rseq = R; a.n_heads = H; a.status = c->status;
     if (!logits && l + 1 == m->n_layers) {  // only the key and value heads, which follow the query heads in the packed matrix
       a.W += (size_t)H * hd * d;
@@ -444,10 +432,9 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
     a.ssq = nullptr; a.NP = 0;
     a.h = c->h; a.g_next = (const float*)L[3]; a.planes_out = (bf16_t*)c->xg; a.ssq_out = c->ssq;
     HIP_TRY(c, launch_gemm_bf16(a, EPI_RESID, tag, s, &np));
-    if (const int rc = sum_ssq()) return rc;
     // gate/up + SwiGLU
     a.W = (const bf16_t*)L[4]; a.X = (const bf16_t*)c->xg; a.N = 2 * f; a.K = d;
-    a.ssq = ssq; a.NP = np;
+    a.ssq = c->ssq; a.NP = np;
     a.act_out = (bf16_t*)c->xn;
     HIP_TRY(c, launch_gemm_bf16(a, EPI_SWIGLU, tag, s));
     // down projection + residual; prepares the next layer's (or the final) normalised input
@@ -455,7 +442,6 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
     a.ssq = nullptr; a.NP = 0;
     a.g_next = (const float*)(l + 1 < m->n_layers ? W[1 + 6 * (l + 1)] : W[tail]);
     HIP_TRY(c, launch_gemm_bf16(a, EPI_RESID, tag, s, &np));
-    if (const int rc = sum_ssq()) return rc;
   }
   c->pass_np = np;
   return logits ? lm_head(c, m, rows, logits, lse, s) : MTAD_OK;
