@@ -344,9 +344,8 @@ __global__ __launch_bounds__(GW * 64) void gemm_bf16_multi_kernel(GemmArgs a, in
 // Weights of less than 8 MB: the launch is one memory latency, the loads of RB rows go out together and those past the end are the
 // last one again.  From there on what is computed for rows that do not exist costs its share: 8192 x 4096, one row 35.9 us with RB =
 // 8, 21.6 with RB = 1 (6.2 TB/s); three rows 35.8, 25.6 with RB = 4; nine rows (8 and 1) 72.9, 57.7 without them.
-__host__ __device__ constexpr bool gemm_f32_small(const GemmF32Args& a) { return (int64_t)a.N * a.K < (2 << 20); }
-
-template <int RB, int EPI>
+// REST: the kernel that computes a remainder's rows alone.
+template <int RB, int EPI, bool REST>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   constexpr bool PAIR = EPI == EPI_SWIGLU || EPI == EPI_QKV;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -401,10 +400,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   };
   constexpr std::true_type YES{};
   constexpr std::false_type NO{};
-  if (RB == 1 || rows == RB || gemm_f32_small(a) || (K < 1024 && rows > RB / 2)) {  // (a short reduction is all latency, too)
+  const bool whole = !REST || rows == RB || (K < 1024 && rows > RB / 2);  // (a short reduction is all latency, too)
+  if (whole) {
     if (a.gain) products(YES, YES);
     else products(YES, NO);
-  } else {
+  } else if constexpr (REST) {
     if (a.gain) products(NO, YES);
     else products(NO, NO);
   }
@@ -462,14 +462,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   }
 }
 
-template <int RB>
+template <int RB, bool REST>
 static hipError_t run_f32(const GemmF32Args& a, int epi, hipStream_t s) {
   const int items = (epi == EPI_SWIGLU || epi == EPI_QKV) ? a.N / 2 : a.N;
   const dim3 grid((items + 3) / 4, (a.R + RB - 1) / RB), block(256);
   switch (epi) {
-    case EPI_STORE: hipLaunchKernelGGL((gemm_f32_kernel<RB, EPI_STORE>), grid, block, 0, s, a); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_f32_kernel<RB, EPI_SWIGLU>), grid, block, 0, s, a); break;
-    case EPI_QKV: hipLaunchKernelGGL((gemm_f32_kernel<RB, EPI_QKV>), grid, block, 0, s, a); break;
+    case EPI_STORE: hipLaunchKernelGGL((gemm_f32_kernel<RB, EPI_STORE, REST>), grid, block, 0, s, a); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_f32_kernel<RB, EPI_SWIGLU, REST>), grid, block, 0, s, a); break;
+    case EPI_QKV: hipLaunchKernelGGL((gemm_f32_kernel<RB, EPI_QKV, REST>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -478,8 +478,9 @@ static hipError_t run_f32(const GemmF32Args& a, int epi, hipStream_t s) {
 hipError_t launch_gemm_f32(const GemmF32Args& a, int epi, hipStream_t s) {
   if (a.R <= 0) return hipSuccess;
   if (a.K % 4) return hipErrorInvalidValue;
-  if (a.R > 4 || gemm_f32_small(a)) return run_f32<8>(a, epi, s);
-  return a.R == 1 ? run_f32<1>(a, epi, s) : run_f32<4>(a, epi, s);
+  if ((int64_t)a.N * a.K < (2 << 20)) return run_f32<8, false>(a, epi, s);
+  if (a.R == 1) return run_f32<1, false>(a, epi, s);
+  return a.R <= 4 ? run_f32<4, true>(a, epi, s) : run_f32<8, true>(a, epi, s);
 }
 
 template <int NG, int EPI, int TAG>
