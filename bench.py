@@ -151,8 +151,8 @@ def pass_kernel_name(w, one_launch):
         return "gemm_f32_kernel (+ attention kernels): one launch per product"
     if one_launch:
         return f"flow_pass_kernel<{w.target.head_dim}> (one launch = the whole target pass)"
-    return ("gemm_bf16_strips_kernel / gemm_bf16_kernel" if rows <= 8 else "gemm_bf16_multi_kernel / gemm_bf16_kernel" if rows < 65 else
-            "gemm_bf16_dma_kernel") + " (+ tree_attn_mfma_kernel): one launch per product"
+    return ("gemm_bf16_strips_kernel / gemm_bf16_kernel" if rows <= 8 else "gemm_bf16_multi_kernel / gemm_bf16_kernel" if rows < 25 else
+            "gemm_bf16_dma_kernel / gemm_bf16_multi_kernel" if rows < 65 else "gemm_bf16_dma_kernel") + " (+ tree_attn_mfma_kernel): one launch per product"
 
 
 def verify_block(eng, w, K, torch, stream):

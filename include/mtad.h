@@ -144,8 +144,8 @@ void mtad_destroy(mtad_ctx *ctx);
 /* Bytes of device workspace with which the context works best; bind exactly one buffer (256-byte aligned) before
  * any hot call.  The contents need no initialisation.  For bfloat16 models most of it serves prompt chunks of up to 2048 rows (a
  * 7B-shaped target: 338 MB with them, 94 MB without).  A smaller buffer is taken too, down to what chunks of prefill_rows rows
- * need: prompts then run in shorter chunks (2048 tokens of that target in chunks of 64 take five times as long) and products of
- * many rows cut their reductions less.  ECAP below that. */
+ * need: prompts then run in shorter chunks (2048 tokens of that target in chunks of 1024 take 2 % longer, in chunks of 64 three and a
+ * half times as long) and products of many rows cut their reductions less.  ECAP below that. */
 size_t mtad_workspace_bytes(const mtad_ctx *ctx);
 int mtad_bind_workspace(mtad_ctx *ctx, void *device_buf, size_t bytes);
 /* bf16 passes of at most 8 rows (all sequences together) can run every product and the attention of every layer as work

@@ -13,8 +13,9 @@
 //     tile and nothing spends issue slots on LDS writes.
 //   * 8 waves: wave r of either group owns row groups r, r + 4, ..; group 0 takes the even k tiles, group 1 the odd ones, and
 //     the groups run one barrier interval apart: on every SIMD one wave reads its fragments while the other issues its
-//     matrix instructions.  An interval is one k tile.  k tile j lies in ring slot j % D; it is read in interval j, its slot is refilled with k tile j + D in interval j + 1 (after the barrier
-//     that ends the reads), and every wave waits for its own share of k tile j + 1 before the barrier that ends interval j.
+//     matrix instructions.  An interval is one k tile.  k tile j lies in ring slot j % D; it is read in interval j, its slot is
+//     refilled with k tile j + D in interval j + 1 (after the barrier that ends the reads), and every wave waits for its own share
+//     of k tile j + 1 before the barrier that ends interval j.
 //   * an activation fragment holds 8 rows, hi and lo in alternate 128-byte pieces; a B operand takes every other piece of two
 //     fragments (shifting the second one by 128 bytes, so that an LDS beat touches other banks, measured the same).
 //   * TALL: with more rows than a workgroup takes (prompts) and for cut reductions the groups own strips of their own and both
@@ -22,11 +23,13 @@
 //     256.  What counts is bytes per instruction: a compute unit has about 64 KiB of requests outstanding and its loads
 //     return in the order they were made, so activations that lie in L2 wait behind weights that come from HBM, and the fill
 //     runs at 58 bytes per ns instead of the 140 that activations alone reach.
-// Measured (us per launch on the kernel before this one -> here): 27648 x 5120 at 164 rows 122 -> 104 and at 256 rows 193 -> 133
-// (1.09 PFLOP/s, hi and lo counted), 15360 x 5120 at 164 rows 90 -> 66 uncut and 58 cut in three, 5120 x 5120 51 -> 30, 5120 x
-// 13824 96 -> 61.  At 256 rows of the first shape the matrix instructions alone take 88 us, the activations' way to LDS 61, the
-// weights' 60, launch, epilogue and barriers 24.  At 2047 rows TALL runs at 1.5 PFLOP/s while all compute units have a tile (a
-// library product of 16384^3 reaches 1.58): 22016 x 4096 622 -> 537 us, 27648 x 5120 898 -> 811, 12288 x 4096 346 -> 329.
+// Measured, us with the sums of a cut: the planned tiles and, in brackets, the best uncut ones, each product with its own epilogue, at
+// 96 / 164 / 256 rows: gate/up 27648 x 5120 82 (82) / 110 (108) / 138 (136), QKV 15360 x 5120 54 (61) / 71 (80) / 85 (85), o 5120 x
+// 5120 26 (34) / 34 (35) / 41 (42), down 5120 x 13824 46 (81) / 62 (88) / 77 (100); no other tiles are more than 2 % faster.  The
+// kernel before this one took 122, 90, 51 and 96 at 164 rows (plain stores).  At 256 rows of the first shape (uncut, plain stores,
+// 125; 1.16 PFLOP/s, hi and lo counted) the matrix instructions alone take 88 us, the activations' way to LDS 61, the weights' 60,
+// launch, epilogue and barriers 24.  At 2047 rows TALL runs at 1.5 PFLOP/s while all compute units have a tile (a library product of
+// 16384^3 reaches 1.58): 22016 x 4096 622 -> 537 us, 27648 x 5120 898 -> 811, 12288 x 4096 346 -> 329.
 #include "common.h"
 #include "gemm.h"
 #include "gemm_device.h"

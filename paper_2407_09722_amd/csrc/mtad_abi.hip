@@ -98,9 +98,9 @@ int splits_for(const mtad_ctx* c, const mtad_model* m, int R) {
 
 // Rows of one prompt pass of a bf16 model, all sequences together.  From about 256 rows on a product is bound by the matrix
 // cores, no longer by its weights; 2048 rows fill the machine with 256-row tiles also where the output is narrow (4096
-// features: 256 workgroups), and cost a 13B-shaped model 270 MB of workspace.  Four 7B-shaped layers on 2047 tokens: 21.5 ms in
-// chunks of 64 rows, 5.25 ms in one pass; four 13B-shaped ones on 4 x 509: 13.4 -> 7.8 ms; the 22-layer draft on 4 x 1023:
-// 62.9 -> 21.3 ms (the last layer's share of these, 3 products and the attention that nothing reads, is left out in both models).
+// features: 256 workgroups), and cost a 13B-shaped model 260 MB of workspace (carve_within() makes do with less).  Four 7B-shaped
+// layers on 2047 tokens: 16.7 ms in chunks of 64 rows, 4.9 in chunks of 1024 or one pass; four 13B-shaped ones on 4 x 509, 4 x 64 rows
+// a chunk 9.7 -> 6.7 ms; the 22-layer draft on 4 x 1023 39.5 -> 17.2 (20.2 in chunks of half the size).
 constexpr int PROMPT_PASS_ROWS = 2048;
 
 struct Carver {
