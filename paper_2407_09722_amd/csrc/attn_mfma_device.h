@@ -4,19 +4,25 @@
 //
 // Work item = (key split, KV head, chunk of 16 or 32 (query head, row) pairs, sequence), run by AW waves of a workgroup
 // of NTH threads (waves beyond AW only take part in the barriers).  The query heads that share a KV head are rows of the
-// same item, so a grouped-query model reads K and V once for all of them.  The keys of the item are cut into 32-key tiles
-// dealt round-robin to the waves; every wave runs its own online softmax over its tiles, with the K and V of the next
-// tile (the next two with NSET = 2) in flight, and the waves merge through LDS at the end.
+// same item, so a grouped-query model reads K and V once for all of them.  The sequence's keys are cut into 32-key tiles
+// dealt round-robin to the waves of all its splits; every wave runs its own online softmax over its tiles, with the K and V of the
+// next tile (the next two with NSET = 2) in flight, and the waves merge through LDS at the end.  (More than 32 pairs on a KV head
+// and prompts: the kernel whose waves share their tiles, kernels_attn_mfma.hip.)
 //
 // Both products run on the matrix cores, transposed, so that every operand is cheap to fetch:
 //   S^T = K Q^T   A operand = 8 consecutive dims of one key per lane = 16 contiguous bytes of a cache row, loaded from
 //                 global memory straight into the operand registers; B operand = Q as two half terms (hi + lo, two
 //                 MFMAs: float32 accuracy) from LDS.  Lane (g, r) ends up with the scores of row r for 8 keys of
-//                 the tile: the per-row softmax needs two cross-lane steps and stays in that lane.
+//                 the tile: the per-row softmax stays in that lane, and exchanges only when a row's reference maximum moves.
 //   O^T = V^T P^T the probabilities a lane holds are exactly its B operand (the k index of the contraction is
 //                 assigned to keys in the order the score product left them), again as hi + lo halves; V^T fragments
-//                 are read transposed from a wave-private LDS copy of the V tile (padded rows: conflict free).
+//                 are read transposed from a wave-private LDS copy of the V tile (two transposing reads a fragment instead of
+//                 eight of two bytes; padded rows: conflict free).
 // The running output, maximum and sum of a row all live in the lanes of that row: no exchange inside the tile loop.
+// Bound by latency: launch, length, page, tile, arithmetic and merge are a chain.  us with the merge of the splits, before / with the
+// page and the queries requested before the length is known, a V tile's loads together instead of one after another's index,
+// transposing reads and the lazy reference: 17 rows x 32 heads x 128, 2064 keys 21.3 / 19.7; 8 x 5 rows x 32 heads, 700 keys 25.2 / 23.6;
+// 16 x 6 rows x 16 heads x 64, 300 keys 11.1 / 9.7; one row x 12 heads x 64, 256 keys 7.4 / 7.0.
 #pragma once
 #include "common.h"
 
@@ -25,8 +31,11 @@
 namespace mtad {
 
 constexpr int ATK = 32;  // keys per tile
+constexpr float ATTN_SLACK = 8.f;  // octaves a row's scores may outgrow the reference of its probabilities by (which then reach 256)
+constexpr float ATTN_LOG2E = 1.44269504f;  // scores are scaled to base 2: an exponential is one instruction and its scaling a fused multiply-add
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float attn_floatx4 __attribute__((ext_vector_type(4)));
 
 union KFrag {
@@ -36,15 +45,15 @@ union KFrag {
 
 template <int HD, int NRG, int AW, int DS = 1>
 struct MfmaAttnSmem {
-  static constexpr int VS = HD + 8;       // padded row of halves: 16-byte aligned, keys 4 apart land 16 banks apart
-  static constexpr int VSV = HD / DS + 8;  // the same for the part of a V row one wave holds
+  static constexpr int VS = HD + 8;         // padded query row of halves: 16-byte aligned
+  static constexpr int VSV = HD / DS + 16;  // row of a V tile (the part one wave holds): eight rows start 8 banks apart from each other
   union {
     struct {
       _Float16 v[AW * DS][ATK][VSV];  // V tile of each wave (its share of the dims)
       _Float16 q[2][NRG * 16][VS];    // query rows, hi and lo halves
     } a;
-    // per-wave outputs for the final merge, MRG row groups at a time (padded rows: the 16 rows of a store land in different banks)
-    float o[AW][(NRG <= 2 ? NRG : 1) * 16][HD + 4];
+    // per-wave outputs for the final merge (padded rows: the 16 rows of a store land in different banks)
+    float o[AW][NRG * 16][HD + 4];
   };
   float m[AW][NRG * 16], l[AW][NRG * 16];
 };
@@ -78,6 +87,13 @@ __device__ __forceinline__ float xsum(float v) {
   float a, b;
   lane_pair<OFF>(v, a, b);
   return a + b;
+}
+
+// Transposing read from LDS: each row of 16 lanes reads four rows of 16 halves, lane i at row i / 4, halves i % 4 * 4 .. + 3 (its
+// address); it gets the four rows' halves of column i.
+__device__ __forceinline__ half4 lds_columns(const _Float16* __restrict__ p) {
+  typedef short short4_t __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t*)p));
 }
 
 // physical token index (page * page_size + offset) of logical position pos; pages outside the pool read page 0
@@ -175,7 +191,7 @@ __device__ __forceinline__ void attn_merge_row(const float* __restrict__ pp, int
       const float mj = ml[j].x, lj = ml[j].y;
       if (s0 + j >= eff || mj == -INFINITY) continue;
       const float Mn = fmaxf(M, mj);
-      const float ws = (M == -INFINITY) ? 0.f : expf(M - Mn), wj = expf(mj - Mn);
+      const float ws = (M == -INFINITY) ? 0.f : exp2f(M - Mn), wj = exp2f(mj - Mn);
       L = L * ws + lj * wj;
 #pragma unroll
       for (int x = 0; x < DPL; ++x) o[x] = o[x] * ws + ov[j][x] * wj;
@@ -196,6 +212,76 @@ __device__ __forceinline__ void attn_merge_row(const float* __restrict__ pp, int
   attn_store<COH, DPL * 2>(out + act_offset(ncg, rows_all, K, 1, arow, ak), &lo);
 }
 
+// Visibility, running softmax per row and the probabilities as operands of the second product, for the scores s2 of NB * 16 keys from
+// key0 on: lane (sg4, row) holds keys blk * 16 + sg4 * 4 + i.  Keys below `all` are seen by every row of the wave; rmask: the
+// speculative keys (from len on) a row sees, CAUSAL: the first key it does not see.  m_run: the maximum a row's probabilities refer to,
+// the same in the row's four lanes; l_run: the sum of the lane's own probabilities.
+template <int RG, int NB, int DB, bool CAUSAL>
+__device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const unsigned long long (&rmask)[RG], float (&m_run)[RG], float (&l_run)[RG],
+                                             attn_floatx4 (&acc)[RG][DB], half8 (&ph)[RG][NB / 2], half8 (&pl)[RG][NB / 2], float scale, int key0, int len,
+                                             int all, int kend, int sg4) {
+  // keys inside the committed context (all but the last tile or two) are visible to every row: no mask
+  if (key0 + NB * 16 > all) {  // uniform over the wave
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg)
+#pragma unroll
+      for (int hb = 0; hb < NB / 2; ++hb) {
+        const int k0 = key0 + hb * 32, n = (CAUSAL ? min((int)rmask[rg], kend) : kend) - k0;
+        unsigned sees = n >= 32 ? ~0u : n > 0 ? (1u << n) - 1u : 0u;  // bit j: the row sees key k0 + j
+        if constexpr (!CAUSAL) {
+          const int spec = k0 - len;
+          sees &= spec >= 64 ? 0u : spec >= 0 ? (unsigned)(rmask[rg] >> spec) : spec <= -32 ? ~0u : ((unsigned)rmask[rg] << -spec) | ((1u << -spec) - 1u);
+        }
+        sees >>= sg4 * 4;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          s2[rg][hb * 2 + (e >> 2)][e & 3] = (sees >> ((e >> 2) * 16 + (e & 3))) & 1u ? s2[rg][hb * 2 + (e >> 2)][e & 3] : -INFINITY;
+        }
+      }
+  }
+  // The reference of a row follows its maximum only when some row's scores have outgrown theirs by ATTN_SLACK octaves: until then
+  // probabilities may be that much above 1, which costs no precision, nothing is rescaled and the row's lanes exchange nothing.
+  const float slack = ATTN_SLACK / scale;
+  float tmax[RG];
+  bool grown = false;
+#pragma unroll
+  for (int rg = 0; rg < RG; ++rg) {
+    tmax[rg] = s2[rg][0][0];
+#pragma unroll
+    for (int e = 1; e < NB * 4; ++e) tmax[rg] = fmaxf(tmax[rg], s2[rg][e >> 2][e & 3]);
+    grown |= tmax[rg] > m_run[rg] + slack;  // (from minus infinity: any key)
+  }
+  if (__any(grown)) {
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg) {
+      const float m_new = fmaxf(m_run[rg], xmax<32>(xmax<16>(tmax[rg])));
+      const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run[rg] - m_new) * scale);
+      m_run[rg] = m_new;
+      l_run[rg] *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[rg][db][i] *= alpha;
+    }
+  }
+#pragma unroll
+  for (int rg = 0; rg < RG; ++rg) {
+    const float mc = m_run[rg] == -INFINITY ? 0.f : m_run[rg] * scale;  // a row that has seen no key yet: all its probabilities are zero
+    typedef float floatx8_t __attribute__((ext_vector_type(8)));
+#pragma unroll
+    for (int hb = 0; hb < NB / 2; ++hb) {
+      floatx8_t pv;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        pv[e] = __builtin_amdgcn_exp2f(fmaf(s2[rg][hb * 2 + (e >> 2)][e & 3], scale, -mc));
+        l_run[rg] += pv[e];
+      }
+      ph[rg][hb] = __builtin_convertvector(pv, half8);
+      pl[rg][hb] = __builtin_convertvector(pv - __builtin_convertvector(ph[rg][hb], floatx8_t), half8);
+    }
+  }
+}
+
 // One work item.  All NTH threads of the workgroup call it with the same arguments (and their index t); threads of waves
 // beyond the item's only pass the barriers.  NSET register sets for K and V (1 or 2).  Returns the splits in use for the sequence (eff): with eff == 1
 // the item wrote the attention output itself, otherwise it left (max, sum, output) per row in
@@ -207,12 +293,10 @@ __device__ __forceinline__ void attn_merge_row(const float* __restrict__ pp, int
 // rows produce, i.e. the queries and the K / V of speculative positions.  K and V tiles that lie inside the committed
 // context are requested BEFORE it: a caller whose queries are still being computed has the cache reads of the context
 // in flight meanwhile.  (Items without work return before the call.)
-// CAUSAL: the rows are a chunk of a prompt, of any number: row r sees the committed context and rows 0 .. r, and an item
-// stops at the last key any of its rows sees; rd.mask is not read.
 struct AttnNoWait {
   __device__ __forceinline__ void operator()() const {}
 };
-template <int HD, int NRG, int AW, int NSET, int NTH, bool COH, int DS = 1, bool CAUSAL = false, typename WaitFn = AttnNoWait>
+template <int HD, int NRG, int AW, int NSET, int NTH, bool COH, int DS = 1, typename WaitFn = AttnNoWait>
 __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm, const float* __restrict__ q, int q_stride, const RowDesc& rd,
                                               const KvView& kv, int layer, int B, int R, int n_heads, int n_chunks, float scale,
                                               float* __restrict__ partial, int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg,
@@ -239,34 +323,46 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   const int pair0 = chunk * RBK, nrows = min(RBK, G * R - pair0);
   auto pair_head = [&](int r) { return g * G + (pair0 + r) / R; };  // query head and tree row of pair r of this item
   auto pair_row = [&](int r) { return (pair0 + r) % R; };
+  constexpr bool WAITS = !std::is_same<WaitFn, AttnNoWait>::value;
+  // What does not depend on the sequence's length is requested before it is known: the page of a wave's first tiles (tile t belongs to
+  // wave t % AW of split t / AW % splits) and, where they are there already, the queries, ahead of the tiles behind which
+  // they would otherwise queue.
+  const int tile0 = split * AW + wslot;
+  const int cap = kv_capacity(kv);
+  auto token_of = [&](int ti) -> int {
+    const int kj = ti * ATK + (lane & 31);
+    return kj < cap ? token_index(kv, seq, kj) : -1;
+  };
+  int tok0 = -1;
+  if (active) tok0 = token_of(tile0);
+  constexpr int QL = (RBK * (HD / 4) + NTH - 1) / NTH;  // float4s of the queries per thread
+  float4 qv[QL];
+  auto load_q = [&]() {
+#pragma unroll
+    for (int j = 0; j < QL; ++j) {
+      const int i = t + j * NTH, r = i / (HD / 4), d = (i % (HD / 4)) * 4;
+      qv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (r < nrows) qv[j] = *(const float4*)(q + (int64_t)(seq * R + pair_row(r)) * q_stride + (int64_t)pair_head(r) * HD + d);
+    }
+  };
+  if constexpr (!WAITS) load_q();
   const int len = kv.len[seq];
-  const int ktot = attn_keys(kv, rd, seq, CAUSAL);
+  const int ktot = attn_keys(kv, rd, seq);
   const int eff = attn_splits(ktot, n_splits, want_splits);  // splits actually used for this sequence
   if (split >= eff) return eff;
-  int per = (ktot + eff - 1) / eff;
-  per = ((per + ATK - 1) / ATK) * ATK;
-  const int kbeg = split * per;
-  int kend = min(ktot, kbeg + per), seen_by_all = len;  // keys below seen_by_all are visible to every row of the item
-  if constexpr (CAUSAL) {
-    const bool one_head = pair0 / R == (pair0 + nrows - 1) / R;  // else its rows wrap around: first and last row of the chunk are among them
-    kend = min(kend, len + 1 + (one_head ? pair_row(nrows - 1) : R - 1));
-    seen_by_all = len + 1 + (one_head ? pair_row(0) : 0);
-  }
-  const int n_tiles = (active && kend > kbeg) ? (kend - kbeg + ATK - 1) / ATK : 0;  // none for the waves that only pass barriers
+  const int n_tiles = active ? (ktot + ATK - 1) / ATK : 0;  // none for the waves that only pass barriers
+  const int TSTEP = eff * AW;  // tiles from one of a wave's to its next
   const int wv = active ? wave : 0;  // this wave's V tile in LDS
 
   const int srow = lane & 15, sg4 = lane >> 4;  // this lane's query row (within a row group) and key group
-  unsigned long long rmask[NRG];  // CAUSAL: the first key the row does not see
+  unsigned long long rmask[NRG];
 #pragma unroll
-  for (int rg = 0; rg < NRG; ++rg) {
-    if constexpr (CAUSAL) rmask[rg] = (rg * 16 + srow < nrows) ? (unsigned)(len + 1 + pair_row(rg * 16 + srow)) : 0u;
-    else rmask[rg] = (rg * 16 + srow < nrows) ? rd.mask[seq * R + pair_row(rg * 16 + srow)] : 0ull;
-  }
+  for (int rg = 0; rg < NRG; ++rg) rmask[rg] = (rg * 16 + srow < nrows) ? rd.mask[seq * R + pair_row(rg * 16 + srow)] : 0ull;
 
   // token index of key (tile start + lane % 32), looked up once per tile and handed round by shuffles
   auto lookup = [&](int ti) -> int {
-    const int kj = kbeg + ti * ATK + (lane & 31);
-    return (ti < n_tiles && kj < kend) ? token_index(kv, seq, kj) : -1;
+    const int kj = ti * ATK + (lane & 31);
+    return (ti < n_tiles && kj < ktot) ? token_index(kv, seq, kj) : -1;
   };
   const int64_t tok_stride = (int64_t)KVH * HD;  // elements per cached token
   const kv16_t* kbase = (const kv16_t*)kv.k + (int64_t)layer * kv.layer_stride + (int64_t)g * HD;
@@ -278,7 +374,6 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   // zeroed so that they contribute exact zeros.  The first tile is requested before the queries are staged.
   // With two sets a wave has two tiles in flight: with one set the requests of a tile go out only when the tile before
   // has arrived, so every tile of a wave pays a full memory latency.
-  constexpr int AHEAD = NSET * AW;
   constexpr std::integral_constant<int, 0> SET0{};
   constexpr std::integral_constant<int, NSET - 1> SET1{};
   KFrag kf[NSET][2][KS], vf[NSET][NV];
@@ -293,9 +388,8 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   auto load_v = [&](auto set, int tok32) {
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-      const int tk = __shfl(tok32, j * KPL + lane / CH, 64);
-      const uint4 v = *(const uint4*)(vbase + (int64_t)max(0, tk) * tok_stride + (lane % CH) * 8);
-      vf[set()][j].u = tk >= 0 ? v : make_uint4(0, 0, 0, 0);
+      const int tk = max(0, __shfl(tok32, j * KPL + lane / CH, 64));
+      vf[set()][j].u = *(const uint4*)(vbase + (int64_t)tk * tok_stride + (lane % CH) * 8);
     }
   };
   // The same for requests that go out before wait_for_rows: lanes without a committed key request nothing at all (token 0,
@@ -323,11 +417,9 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   // The first tile(s) of a wave go out BEFORE wait_for_rows: the page-table lookups of all their keys, and K and V of the
   // keys inside the committed context.  Keys at speculative positions (their K and V are being written by the caller's
   // own pass) are marked -(token + 2) by the early lookup, read as absent for now, and fetched lane by lane after the wait.
-  auto lookup_marked = [&](int ti) -> int {
-    const int kj = kbeg + ti * ATK + (lane & 31);
-    if (!(ti < n_tiles && kj < kend)) return -1;
-    const int tk = token_index(kv, seq, kj);
-    return kj < len ? tk : -(tk + 2);
+  auto mark = [&](int ti, int tk) -> int {
+    const int kj = ti * ATK + (lane & 31);
+    return kj >= ktot ? -1 : (!WAITS || kj < len) ? tk : -(tk + 2);
   };
   auto patch_k = [&](auto set, int tokm) {
 #pragma unroll
@@ -347,41 +439,53 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
     }
   };
   int tokm0 = -1, tokm1 = -1;
-  if (wslot < n_tiles) {
-    tokm0 = lookup_marked(wslot);
-    load_v_committed(SET0, tokm0);
-    load_k_committed(SET0, tokm0);
+  if (tile0 < n_tiles) {
+    tokm0 = mark(tile0, tok0);
+    if constexpr (WAITS) {
+      load_v_committed(SET0, tokm0);
+      load_k_committed(SET0, tokm0);
+    } else {
+      load_v(SET0, tokm0);
+      load_k(SET0, tokm0);
+    }
   }
-  if (NSET == 2 && wslot + AW < n_tiles) {
-    tokm1 = lookup_marked(wslot + AW);
-    load_v_committed(SET1, tokm1);
-    load_k_committed(SET1, tokm1);
+  if (NSET == 2 && tile0 + TSTEP < n_tiles) {
+    tokm1 = mark(tile0 + TSTEP, token_of(tile0 + TSTEP));
+    if constexpr (WAITS) {
+      load_v_committed(SET1, tokm1);
+      load_k_committed(SET1, tokm1);
+    } else {
+      load_v(SET1, tokm1);
+      load_k(SET1, tokm1);
+    }
   }
-  wait_for_rows();
-  if (__any(tokm0 <= -2)) {  // uniform over the wave
-    patch_v(SET0, tokm0);
-    patch_k(SET0, tokm0);
-  }
-  if (NSET == 2 && __any(tokm1 <= -2)) {
-    patch_v(SET1, tokm1);
-    patch_k(SET1, tokm1);
+  if constexpr (WAITS) {
+    wait_for_rows();
+    if (__any(tokm0 <= -2)) {  // uniform over the wave
+      patch_v(SET0, tokm0);
+      patch_k(SET0, tokm0);
+    }
+    if (NSET == 2 && __any(tokm1 <= -2)) {
+      patch_v(SET1, tokm1);
+      patch_k(SET1, tokm1);
+    }
+    load_q();
   }
 
   // queries of the item as half hi / lo terms in LDS (rows beyond the item are zero)
-  for (int i = t; i < RBK * (HD / 4); i += NTH) {
-    const int r = i / (HD / 4), d = (i % (HD / 4)) * 4;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (r < nrows) v = *(const float4*)(q + (int64_t)(seq * R + pair_row(r)) * q_stride + (int64_t)pair_head(r) * HD + d);
-    const float x[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const _Float16 hi = (_Float16)x[e];
-      sm.a.q[0][r][d + e] = hi;
-      sm.a.q[1][r][d + e] = (_Float16)(x[e] - (float)hi);
+  for (int j = 0; j < QL; ++j) {
+    const int i = t + j * NTH, r = i / (HD / 4), d = (i % (HD / 4)) * 4;
+    if (RBK * (HD / 4) % NTH == 0 || i < RBK * (HD / 4)) {
+      typedef float floatx4_t __attribute__((ext_vector_type(4)));
+      const floatx4_t x = floatx4_t{qv[j].x, qv[j].y, qv[j].z, qv[j].w};
+      const half4 hi = __builtin_convertvector(x, half4);
+      *(half4*)&sm.a.q[0][r][d] = hi;
+      *(half4*)&sm.a.q[1][r][d] = __builtin_convertvector(x - __builtin_convertvector(hi, floatx4_t), half4);
     }
   }
   __syncthreads();
-  float m_run[NRG], l_run[NRG];  // of row rg*16 + srow (replicated over the four key groups)
+  float m_run[NRG], l_run[NRG];  // of row rg*16 + srow: reference maximum (the same in the four key groups), sum over the lane's own keys
   attn_floatx4 acc[NRG][DB];     // O^T: dims db*16 + sg4*4 + i of row rg*16 + srow
 #pragma unroll
   for (int rg = 0; rg < NRG; ++rg) {
@@ -392,9 +496,18 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   }
 
   auto process = [&](auto set, int ti) {                    // tile ti, whose K and V are in (or on the way to) register set `set`
-    const bool more = ti + AHEAD < n_tiles;                 // uniform over the wave
-    const int tok_next = more ? lookup(ti + AHEAD) : -1;    // the page-table read of the set's next tile starts here
-    // V tile -> wave-private LDS copy
+    const int next = ti + NSET * TSTEP;
+    const bool more = next < n_tiles;                 // uniform over the wave
+    const int tok_next = more ? lookup(next) : -1;    // the page-table read of the set's next tile starts here
+    // V tile -> wave-private LDS copy; keys past the end as zeros
+    if ((ti + 1) * ATK > ktot) {  // uniform over the wave: the last tile
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        const unsigned keep = ti * ATK + j * KPL + lane / CH < ktot ? ~0u : 0u;
+        uint4& u = vf[set()][j].u;
+        u.x &= keep; u.y &= keep; u.z &= keep; u.w &= keep;
+      }
+    }
 #pragma unroll
     for (int j = 0; j < NV; ++j) *(uint4*)&sm.a.v[wv][j * KPL + lane / CH][(lane % CH) * 8] = vf[set()][j].u;
     if (more) load_v(set, tok_next);
@@ -423,77 +536,28 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
     // visibility, scale, running softmax per row; probabilities become the B operand of the second product
-    half8 ph[NRG], pl[NRG];
-    // a tile that lies inside the committed context (all but the last one or two) is visible to every row: no mask
-    const bool plain = kbeg + (ti + 1) * ATK <= min(seen_by_all, kend);  // uniform over the wave
-#pragma unroll
-    for (int rg = 0; rg < NRG; ++rg) {
-      float tmax = -INFINITY;
-      if (plain) {
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float sv = s2[rg][blk][i] * scale;
-            s2[rg][blk][i] = sv;
-            tmax = fmaxf(tmax, sv);
-          }
-      } else {
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int kj = kbeg + ti * ATK + blk * 16 + sg4 * 4 + i;
-            bool vis = kj < kend;
-            if constexpr (CAUSAL) vis = vis && kj < (int)rmask[rg];
-            else if (vis && kj >= len) vis = (rmask[rg] >> (kj - len)) & 1ull;
-            const float sv = vis ? s2[rg][blk][i] * scale : -INFINITY;
-            s2[rg][blk][i] = sv;
-            tmax = fmaxf(tmax, sv);
-          }
-      }
-      tmax = xmax<32>(xmax<16>(tmax));
-      const float m_new = fmaxf(m_run[rg], tmax);
-      const float alpha = (m_run[rg] == -INFINITY) ? 0.f : __expf(m_run[rg] - m_new);
-      float psum = 0.f;
-#pragma unroll
-      for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float pv = (s2[rg][blk][i] == -INFINITY) ? 0.f : __expf(s2[rg][blk][i] - m_new);
-          psum += pv;
-          const _Float16 hi = (_Float16)pv;
-          ph[rg][blk * 4 + i] = hi;
-          pl[rg][blk * 4 + i] = (_Float16)(pv - (float)hi);
-        }
-      psum = xsum<32>(xsum<16>(psum));
-      l_run[rg] = l_run[rg] * alpha + psum;
-      m_run[rg] = m_new;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[rg][db][i] *= alpha;
-    }
+    half8 ph[NRG][1], pl[NRG][1];
+    attn_softmax<NRG, 2, DB, false>(s2, rmask, m_run, l_run, acc, ph, pl, scale, ti * ATK, len, len, ktot, sg4);
 
     // O^T += V^T P^T: contraction slot e of key group sg4 is key (e/4)*16 + sg4*4 + e%4, as the scores came out
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
-      half8 vt;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vt[e] = sm.a.v[wv][(e >> 2) * 16 + sg4 * 4 + (e & 3)][db * 16 + srow];
+      const half4 v0 = lds_columns(&sm.a.v[wv][sg4 * 4 + (srow >> 2)][db * 16 + (srow & 3) * 4]);
+      const half4 v1 = lds_columns(&sm.a.v[wv][16 + sg4 * 4 + (srow >> 2)][db * 16 + (srow & 3) * 4]);
+      const half8 vt = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
       for (int rg = 0; rg < NRG; ++rg) {
-        acc[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, ph[rg], acc[rg][db], 0, 0, 0);
-        acc[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, pl[rg], acc[rg][db], 0, 0, 0);
+        acc[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, ph[rg][0], acc[rg][db], 0, 0, 0);
+        acc[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, pl[rg][0], acc[rg][db], 0, 0, 0);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();  // the V tile has been read before the next one overwrites it
   };
 #pragma unroll 1
-  for (int ti = wslot; ti < n_tiles; ti += AHEAD) {
+  for (int ti = tile0; ti < n_tiles; ti += NSET * TSTEP) {
     process(SET0, ti);
-    if (NSET == 2 && ti + AW < n_tiles) process(SET1, ti + AW);
+    if (NSET == 2 && ti + TSTEP < n_tiles) process(SET1, ti + TSTEP);
   }
   // ---- the waves meet in LDS (the buffer aliases the V tiles and the queries)
   const int mrow = t / TPR, md = (t % TPR) * DPT;  // merge role: row within a row group, first of DPT dims
@@ -515,55 +579,52 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   if (active && dpart == 0) {  // (the waves that share a tile hold the same statistics)
 #pragma unroll
     for (int rg = 0; rg < NRG; ++rg) {
+      l_run[rg] = xsum<32>(xsum<16>(l_run[rg]));
       if (sg4 == 0) {
-        sm.m[wslot][rg * 16 + srow] = m_run[rg];
+        sm.m[wslot][rg * 16 + srow] = m_run[rg] * scale;
         sm.l[wslot][rg * 16 + srow] = l_run[rg];
       }
     }
   }
-  constexpr int MRG = NRG <= 2 ? NRG : 1;  // row groups the merge buffer holds at a time
+  __syncthreads();  // everyone is done with the tiles
+  if (active) {
 #pragma unroll
-  for (int rg0 = 0; rg0 < NRG; rg0 += MRG) {
-    __syncthreads();  // everyone is done with the tiles (first pass) / with the previous row groups' buffer
-    if (active) {
+    for (int rm = 0; rm < NRG; ++rm)
 #pragma unroll
-      for (int rm = 0; rm < MRG; ++rm)
+      for (int db = 0; db < DB; ++db)
+        *(float4*)&sm.o[wslot][rm * 16 + srow][dpart * HV + db * 16 + sg4 * 4] =
+            make_float4(acc[rm][db][0], acc[rm][db][1], acc[rm][db][2], acc[rm][db][3]);
+  }
+  __syncthreads();
+  if (merger) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-          *(float4*)&sm.o[wslot][rm * 16 + srow][dpart * HV + db * 16 + sg4 * 4] =
-              make_float4(acc[rg0 + rm][db][0], acc[rg0 + rm][db][1], acc[rg0 + rm][db][2], acc[rg0 + rm][db][3]);
-    }
-    __syncthreads();
-    if (merger) {
+    for (int rm = 0; rm < NRG; ++rm) {
+      const int r = rm * 16 + mrow;
+      float M = -INFINITY;
 #pragma unroll
-      for (int rm = 0; rm < MRG; ++rm) {
-        const int r = (rg0 + rm) * 16 + mrow;
-        float M = -INFINITY;
+      for (int w2 = 0; w2 < AW; ++w2) M = fmaxf(M, sm.m[w2][r]);
+      float L = 0.f, o[DPT];
 #pragma unroll
-        for (int w2 = 0; w2 < AW; ++w2) M = fmaxf(M, sm.m[w2][r]);
-        float L = 0.f, o[DPT];
+      for (int x = 0; x < DPT; ++x) o[x] = 0.f;
 #pragma unroll
-        for (int x = 0; x < DPT; ++x) o[x] = 0.f;
+      for (int w2 = 0; w2 < AW; ++w2) {  // wave order (deterministic)
+        const float mw = sm.m[w2][r];
+        const float e = (mw == -INFINITY) ? 0.f : exp2f(mw - M);
+        L += sm.l[w2][r] * e;
 #pragma unroll
-        for (int w2 = 0; w2 < AW; ++w2) {  // wave order (deterministic)
-          const float mw = sm.m[w2][r];
-          const float e = (mw == -INFINITY) ? 0.f : expf(mw - M);
-          L += sm.l[w2][r] * e;
-#pragma unroll
-          for (int x4 = 0; x4 < DPT; x4 += 4) {
-            const float4 v = *(const float4*)&sm.o[w2][rm * 16 + mrow][md + x4];
-            o[x4] += v.x * e; o[x4 + 1] += v.y * e; o[x4 + 2] += v.z * e; o[x4 + 3] += v.w * e;
-          }
+        for (int x4 = 0; x4 < DPT; x4 += 4) {
+          const float4 v = *(const float4*)&sm.o[w2][rm * 16 + mrow][md + x4];
+          o[x4] += v.x * e; o[x4 + 1] += v.y * e; o[x4 + 2] += v.z * e; o[x4 + 3] += v.w * e;
         }
-        if (r < nrows) {
-          if (eff == 1) {  // nothing to exchange: this workgroup saw every key
-            store_out(r, o, L);
-          } else {  // partial[seq][head][row][split][HD+2] = (m, l, acc[HD]) for the merge
-            float* p = partial + ((((int64_t)seq * n_heads + pair_head(r)) * R + pair_row(r)) * n_splits + split) * (HD + 2);
+      }
+      if (r < nrows) {
+        if (eff == 1) {  // nothing to exchange: this workgroup saw every key
+          store_out(r, o, L);
+        } else {  // partial[seq][head][row][split][HD+2] = (m, l, acc[HD]) for the merge
+          float* p = partial + ((((int64_t)seq * n_heads + pair_head(r)) * R + pair_row(r)) * n_splits + split) * (HD + 2);
 #pragma unroll
-            for (int x = 0; x < DPT; x += 2) st8<COH>(p + 2 + md + x, make_uint2(__float_as_uint(o[x]), __float_as_uint(o[x + 1])));
-            if (t % TPR == 0) st8<COH>(p, make_uint2(__float_as_uint(M), __float_as_uint(L)));
-          }
+          for (int x = 0; x < DPT; x += 2) st8<COH>(p + 2 + md + x, make_uint2(__float_as_uint(o[x]), __float_as_uint(o[x + 1])));
+          if (t % TPR == 0) st8<COH>(p, make_uint2(__float_as_uint(M), __float_as_uint(L)));
         }
       }
     }

@@ -8,7 +8,8 @@
 // (at least one tile per wave each, at most as many as fill the machine once, or every resident slot where once is an
 // uneven fill); every split leaves (max, sum, output)
 // per row in global memory (same partial layout as the generic kernel) and a small second kernel, one wave per row,
-// merges them in split order.
+// merges them in split order.  More than 32 pairs on a KV head, and prompts of any number of rows, go to a kernel whose waves share
+// the tiles (tree_attn_rows_kernel).
 #include "attn_mfma_device.h"
 #include "common.h"
 
@@ -20,19 +21,17 @@ namespace {
 
 constexpr int FEW_ROWS = 64;  // (sequence, query head, row) triples of a pass that merges its key splits in the attention launch
 
-template <int HD, int NRG, int AW, bool CAUSAL>
+template <int HD, int NRG, int AW>
 __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(2))) void tree_attn_mfma_kernel(const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer,
                                                                int R, int n_heads, int n_chunks, float scale, float* __restrict__ partial,
                                                                int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg) {
   using Smem = MfmaAttnSmem<HD, NRG, AW>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];  // dynamic: an 8-wave variant needs more than 64 KiB
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   Smem& sm = *reinterpret_cast<Smem*>(smem_raw);
   // the kernels with registers to spare (head dim 64, or a single row group) hold two register sets for K and V
   constexpr int NSET = (HD == 64 || NRG == 1) ? 2 : 1;
-  // a chunk of a prompt: the items that see the most keys first
-  const int by = CAUSAL ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y;
-  const int g = CAUSAL ? by % (int)(gridDim.y / n_chunks) : by / n_chunks, chunk = CAUSAL ? by / (int)(gridDim.y / n_chunks) : by % n_chunks;
-  tree_attn_item<HD, NRG, AW, NSET, AW * 64, false, 1, CAUSAL>(sm, q, q_stride, rd, kv, layer, (int)gridDim.z, R, n_heads, n_chunks, scale, partial,
+  const int g = (int)blockIdx.y / n_chunks, chunk = (int)blockIdx.y % n_chunks;
+  tree_attn_item<HD, NRG, AW, NSET, AW * 64, false>(sm, q, q_stride, rd, kv, layer, (int)gridDim.z, R, n_heads, n_chunks, scale, partial,
                                                               n_splits, out, want_splits, ncg, (int)blockIdx.x, g, chunk, (int)blockIdx.z,
                                                               (int)threadIdx.x);
 }
@@ -70,6 +69,239 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) __attribute__((amdgpu_waves_per_eu
   }
 }
 
+// ---- items of many rows ---------------------------------------------------------------------------------------------
+// Work item = (key split, KV head, chunk of 16 RW (query head, row) pairs, sequence) = one workgroup of RW = 3 or 4 waves.  A wave owns
+// a row group of 16, its query fragments (hi and lo halves) in registers, and works on every tile of the item; K and V
+// tiles lie in two slots in LDS that all waves read, so that they come from memory once for 16 RW rows, and nothing has to be
+// merged between waves.  Tiles go from memory to LDS without passing registers (16 bytes per lane, four or eight cache rows an
+// instruction), the next one while this one is worked on; one barrier a tile: it ends the reads of the slot that is refilled and
+// says that every wave's share of the tile has arrived.
+// Where the 16-byte chunks of a row lie is turned by its key, so that 16 keys' chunk c (an operand of K) and the 32-byte pieces of
+// eight keys (a transposing read of V) fall into different banks.
+// What bounds it: a tile costs a wave as many clocks of LDS reads (K and V once per 16 rows) as of matrix instructions, and the
+// waves of a compute unit overlap the two only in part.  us with the merge of the splits, in items of 32 or 48 rows whose four
+// waves have tiles of their own (above) / here: prompts of 2047 rows x 32 heads x 128 146 / 90, 4 x 509 x 40 heads 96 / 48, 4 x 512 rows x
+// 32 heads on 4 x 64 48 / 25; trees: 4 x 41 rows x 40 heads x 128, 4100 keys 91 / 86 (3.9 TB/s; requests alone 63, arithmetic on
+// cached tiles alone 60), 8 heads on a key head 81 / 56; 4 x 8 rows x 32 heads on 4 x 64, 4100 keys 20.4 / 16.1; 40 rows x 32 heads x 64, 900
+// keys 16.0 / 11.3.  Up to 32 pairs a KV head (there / here with two waves): 17 rows x 32 heads x 128, 2064 keys 19.7 / 19.6; 8 x 30 rows x 16
+// heads, 700 keys 23.0 / 24.5; 4 x 20 rows x 32 heads x 64, 4000 keys 43.7 / 47.9: they stay above.
+// Measured and not better: two row groups a wave (prompt of 2047 rows 101, half the LDS reads but twice the work of the longest item);
+// three or four slots; tiles of 64 keys for head dim 128 (93) or of 32 for 64 (26 instead of 25).
+constexpr int ROWS_WAIT_ALL = 0x0070;  // s_waitcnt: no vector memory operation and no LDS operation outstanding
+constexpr int LOOK_KEYS = 512;  // keys whose places in the cache are looked up together
+
+template <int HD, int RW>
+struct RowsShape {
+  static constexpr int RTK = HD == 128 ? 32 : 64;     // keys per tile (8 KiB of K and of V)
+  static constexpr int TOK_TILES = LOOK_KEYS / RTK;  // tiles looked up together
+  static constexpr int CPR = HD / 8;          // 16-byte chunks of a cache row
+  static constexpr int KPI = 64 / CPR;        // keys one request covers
+  static constexpr int GROUPS = RTK / KPI;    // requests for K (and as many for V) per tile
+  static constexpr int TILE = RTK * HD * 2, SLOT = 2 * TILE;
+  static constexpr int LDS = 2 * SLOT + 2 * TOK_TILES * RTK * 4;
+  static constexpr int LOOK = (TOK_TILES * RTK + RW * 64 - 1) / (RW * 64);  // keys a thread looks up per block of tiles
+};
+
+template <int HD, int RW, bool CAUSAL>
+__global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(HD == 128 ? 3 : 4))) void tree_attn_rows_kernel(
+    const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int B, int R, int n_heads, int n_chunks, float scale,
+    float* __restrict__ partial, int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg, int splits) {
+  using Sh = RowsShape<HD, RW>;
+  constexpr int RG = 1;  // row groups per wave
+  constexpr int KS = HD / 32, DB = HD / 16, CPR = Sh::CPR, KPI = Sh::KPI, GROUPS = Sh::GROUPS, TILE = Sh::TILE, SLOT = Sh::SLOT, LOOK = Sh::LOOK, RTK = Sh::RTK, TOK_TILES = Sh::TOK_TILES, NB = RTK / 16;
+  extern __shared__ __attribute__((aligned(256))) unsigned char ring[];
+  int* const tokens = (int*)(ring + 2 * SLOT);  // [2][TOK_TILES][RTK]
+
+  const int t = threadIdx.x, lane = t & 63, srow = lane & 15, sg4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int split = blockIdx.x % splits, item = blockIdx.x / splits, KVH = kv.n_kv_heads, G = n_heads / KVH, g = item % KVH, seq = item / KVH % B;
+  const int rank = item / (KVH * B), chunk = CAUSAL ? n_chunks - 1 - rank : rank;  // a prompt's items that see the most keys first
+  const int pairs = G * R, pair0 = chunk * (RW * RG * 16), pair_end = min(pairs, pair0 + RW * RG * 16);  // pair p = query head p / R of the group, row p % R
+  const int wp0 = pair0 + wave * (RG * 16), wp_end = min(pair_end, wp0 + RG * 16);                      // this wave's
+  const bool rowless = wp0 >= pair_end;
+
+  const int len = kv.len[seq], ktot = attn_keys(kv, rd, seq, CAUSAL), eff = attn_splits(ktot, n_splits, want_splits);
+  if (split >= eff) return;
+  // keys the item sees, keys the wave sees, keys all the wave's rows see
+  auto last_row = [&](int p0, int p1) { return p0 / R == (p1 - 1) / R ? (p1 - 1) % R : R - 1; };
+  int kend = ktot, wend = ktot, all = len;
+  if constexpr (CAUSAL) {
+    kend = min(ktot, len + 1 + last_row(pair0, pair_end));
+    if (!rowless) {
+      wend = min(ktot, len + 1 + last_row(wp0, wp_end));
+      all = len + 1 + (wp0 / R == (wp_end - 1) / R ? wp0 % R : 0);
+    }
+  }
+  all = min(all, wend);
+  const int tiles = (kend + RTK - 1) / RTK, n_my = tiles > split ? (tiles - split + eff - 1) / eff : 0;  // tiles split, split + eff, ..
+
+  // keys of tiles block * TOK_TILES .. of this split, LOOK per thread; past the end the last key
+  auto key_of = [&](int block, int e) { return max(0, min((split + (block * TOK_TILES + e / RTK) * eff) * RTK + e % RTK, kend - 1)); };
+  int page[LOOK];
+  auto look_up = [&](int block) {
+#pragma unroll
+    for (int j = 0; j < LOOK; ++j) page[j] = kv.page_table[(int64_t)seq * kv.max_pages + key_of(block, t + j * (RW * 64)) / kv.page_size];
+  };
+  auto put = [&](int block) {
+#pragma unroll
+    for (int j = 0; j < LOOK; ++j) {
+      const int e = t + j * (RW * 64), pg = (page[j] < 0 || page[j] >= kv.n_pages) ? 0 : page[j];
+      if (e < TOK_TILES * RTK) tokens[(block & 1) * (TOK_TILES * RTK) + e] = pg * kv.page_size + key_of(block, e) % kv.page_size;
+    }
+  };
+  look_up(0);
+
+  // the wave's queries: lane (sg4, srow) of fragment ks holds dims ks * 32 + sg4 * 8 .. + 7 of row srow; rows that do not exist are zeros
+  half8 qh[RG][KS], ql[RG][KS];
+  unsigned long long rmask[RG];  // CAUSAL: the first key the row does not see
+#pragma unroll
+  for (int rg = 0; rg < RG; ++rg) {
+    const int p = wp0 + rg * 16 + srow;
+    const bool live = p < wp_end;
+    const int pc = live ? p : 0, row = pc % R;
+    const float* const qp = q + (int64_t)(seq * R + row) * q_stride + (int64_t)(g * G + pc / R) * HD + sg4 * 8;
+    if constexpr (CAUSAL) rmask[rg] = live ? (unsigned)(len + 1 + row) : 0u;
+    else rmask[rg] = live ? rd.mask[seq * R + row] : 0ull;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      typedef float floatx8_t __attribute__((ext_vector_type(8)));
+      const float4 a = *(const float4*)(qp + ks * 32), b = *(const float4*)(qp + ks * 32 + 4);
+      const floatx8_t x = live ? floatx8_t{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w} : floatx8_t{};
+      qh[rg][ks] = __builtin_convertvector(x, half8);
+      ql[rg][ks] = __builtin_convertvector(x - __builtin_convertvector(qh[rg][ks], floatx8_t), half8);
+    }
+  }
+  put(0);
+  __syncthreads();
+
+  typedef const __attribute__((address_space(1))) uint32_t* GlobalWords;
+  typedef __attribute__((address_space(3))) uint32_t* LdsWords;
+  const int64_t tok_stride = (int64_t)KVH * HD;
+  const kv16_t* const kbase = (const kv16_t*)kv.k + (int64_t)layer * kv.layer_stride + (int64_t)g * HD;
+  const kv16_t* const vbase = (const kv16_t*)kv.v + (int64_t)layer * kv.layer_stride + (int64_t)g * HD;
+  auto turn_k = [](int key) { return HD == 128 ? key & 15 : (key >> 1) & 7; };
+  auto turn_v = [](int key) { return HD == 128 ? 2 * (key & 7) : 2 * ((key >> 1) & 3); };
+  auto request = [&](int n) {  // this wave's share of tile n of the split
+    const int* const tt = tokens + (n / TOK_TILES & 1) * (TOK_TILES * RTK) + n % TOK_TILES * RTK;
+    unsigned char* const to = ring + (n & 1) * SLOT;
+#pragma unroll
+    for (int i = 0; i < (GROUPS + RW - 1) / RW; ++i) {
+      const int kg = wave + i * RW, key = kg * KPI + lane / CPR;
+      if (GROUPS % RW && kg >= GROUPS) break;  // uniform over the wave
+      const int64_t at = (int64_t)tt[key] * tok_stride;
+      __builtin_amdgcn_global_load_lds((GlobalWords)(kbase + at + ((lane % CPR) ^ turn_k(key)) * 8), (LdsWords)(to + kg * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((GlobalWords)(vbase + at + ((lane % CPR) ^ turn_v(key)) * 8), (LdsWords)(to + TILE + kg * 1024), 16, 0, 0);
+    }
+  };
+  if (n_my > 0) request(0);
+
+  float m_run[RG], l_run[RG];  // of row rg * 16 + srow: reference maximum (the same in the four key groups), sum over the lane's own keys
+  attn_floatx4 acc[RG][DB];    // O^T: dims db * 16 + sg4 * 4 + i of row rg * 16 + srow
+#pragma unroll
+  for (int rg = 0; rg < RG; ++rg) {
+    m_run[rg] = -INFINITY;
+    l_run[rg] = 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) acc[rg][db] = attn_floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  unsigned k_off[KS], v_off[DB];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) k_off[ks] = srow * (HD * 2) + ((ks * 4 + sg4) ^ turn_k(srow)) * 16;
+  {
+    const int key = sg4 * 4 + (srow >> 2);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) v_off[db] = TILE + key * (HD * 2) + ((2 * db + ((srow >> 1) & 1)) ^ turn_v(key)) * 16 + (srow & 1) * 8;
+  }
+
+#pragma unroll 1
+  for (int n = 0; n < n_my; ++n) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(ROWS_WAIT_ALL);  // this wave's share of the tile has arrived, its reads of the one before are done
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (n + 1 < n_my) request(n + 1);
+    // the next block of keys: looked up at the start of this one, in LDS two tiles later
+    const int blk_next = n / TOK_TILES + 1;
+    if (blk_next * TOK_TILES < n_my) {
+      if (n % TOK_TILES == 0) look_up(blk_next);
+      if (n % TOK_TILES == 2) put(blk_next);
+    }
+    const int key0 = (split + n * eff) * RTK;
+    const unsigned char* const sp = ring + (n & 1) * SLOT;
+    if (key0 + RTK > kend) {  // uniform over the workgroup: the last tile; V rows past the end become zeros
+      for (int i = t; i < RTK * CPR; i += RW * 64)
+        if (key0 + i / CPR >= kend) *(uint4*)(ring + (n & 1) * SLOT + TILE + i * 16) = make_uint4(0, 0, 0, 0);
+      __syncthreads();
+    }
+    if (rowless || key0 >= wend) continue;  // uniform over the wave
+
+    // S^T = K Q^T
+    attn_floatx4 s2[RG][NB];
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg)
+#pragma unroll
+      for (int blk = 0; blk < NB; ++blk) s2[rg][blk] = attn_floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int blk = 0; blk < NB; ++blk) {
+        const half8 kf = *(const half8*)(sp + k_off[ks] + blk * (16 * HD * 2));
+#pragma unroll
+        for (int rg = 0; rg < RG; ++rg) {
+          s2[rg][blk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qh[rg][ks], s2[rg][blk], 0, 0, 0);
+          s2[rg][blk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, ql[rg][ks], s2[rg][blk], 0, 0, 0);
+        }
+      }
+    half8 ph[RG][NB / 2], pl[RG][NB / 2];
+    attn_softmax<RG, NB, DB, CAUSAL>(s2, rmask, m_run, l_run, acc, ph, pl, scale, key0, len, all, kend, sg4);
+    // O^T += V^T P^T
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int hb = 0; hb < NB / 2; ++hb) {
+        const half4 v0 = lds_columns((const _Float16*)(sp + v_off[db] + hb * (32 * HD * 2))), v1 = lds_columns((const _Float16*)(sp + v_off[db] + hb * (32 * HD * 2) + 16 * HD * 2));
+        const half8 vt = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+        for (int rg = 0; rg < RG; ++rg) {
+          acc[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, ph[rg][hb], acc[rg][db], 0, 0, 0);
+          acc[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, pl[rg][hb], acc[rg][db], 0, 0, 0);
+        }
+      }
+  }
+  if (rowless) return;
+#pragma unroll
+  for (int rg = 0; rg < RG; ++rg) {
+    const int p = wp0 + rg * 16 + srow;
+    const bool live = p < wp_end;
+    const int pc = live ? p : wp0, row = pc % R, head = g * G + pc / R;
+    l_run[rg] = xsum<32>(xsum<16>(l_run[rg]));
+    if (eff == 1) {
+      const float inv = l_run[rg] > 0.f ? 1.0f / l_run[rg] : 0.f;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const float x[4] = {acc[rg][db][0] * inv, acc[rg][db][1] * inv, acc[rg][db][2] * inv, acc[rg][db][3] * inv};
+        uint2 hi, lo;
+        split_bf16_x4(x, hi, lo);
+        const int k = head * HD + db * 16 + sg4 * 4;
+        if (live) {
+          *(uint2*)(out + act_offset(ncg, B * R, n_heads * HD, 0, seq * R + row, k)) = hi;
+          *(uint2*)(out + act_offset(ncg, B * R, n_heads * HD, 1, seq * R + row, k)) = lo;
+        }
+      }
+    } else if (live) {
+      float* const pp = partial + ((((int64_t)seq * n_heads + head) * R + row) * n_splits + split) * (HD + 2);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        *(float2*)(pp + 2 + db * 16 + sg4 * 4) = make_float2(acc[rg][db][0], acc[rg][db][1]);
+        *(float2*)(pp + 2 + db * 16 + sg4 * 4 + 2) = make_float2(acc[rg][db][2], acc[rg][db][3]);
+      }
+      if (sg4 == 0) *(float2*)pp = make_float2(m_run[rg] * scale, l_run[rg]);
+    }
+  }
+}
+
 // Merge of the key splits, a kernel of its own: one wave per (sequence, query head, row).  As a separate launch it is
 // spread over the whole machine and costs about the same for any number of
 // splits, where the last workgroup of an item merging inside the attention kernel (the first design: 3.3 us of 13.1 at
@@ -87,40 +319,71 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(RowDesc rd, KvView kv, 
   attn_merge_row<HD, false>(pp, eff, out, ncg, B * R, n_heads * HD, seq * R + row, head, lane);
 }
 
-template <int HD, int NRG, int AW, bool CAUSAL = false>
-hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvView& kv, int layer, int B, int R, int n_heads, float* partial,
-                    int n_splits, void* out, int ncg, hipStream_t s, int* counters = nullptr) {
-  const int KVH = kv.n_kv_heads, G = n_heads / KVH;
-  const int n_chunks = (G * R + NRG * 16 - 1) / (NRG * 16);  // chunks of (query head, row) pairs per KV head
-  const float scale = 1.0f / sqrtf((float)HD);
-  auto kern = tree_attn_mfma_kernel<HD, NRG, AW, CAUSAL>;
-  constexpr size_t lds = sizeof(MfmaAttnSmem<HD, NRG, AW>);
-  static const hipError_t attr = lds > 64 * 1024 ? hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
-                                                 : hipSuccess;
-  if (attr != hipSuccess) return attr;
-  // splits: enough workgroups to fill the machine once (twice and four times over measured no faster at 512, 2048 and 4096
-  // keys when once is an even fill)
+int device_cus() {
   static const int n_cus = [] {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
     return cus > 0 ? cus : 256;
   }();
+  return n_cus;
+}
+
+// Key splits for `items` workgroups per split: enough workgroups to fill the machine once (twice and four times over measured no faster
+// at 512, 2048 and 4096 keys when once is an even fill).  An uneven fill (C5's target pass: 160 items x 2 splits on 256 compute
+// units) runs as long as the compute units that hold two workgroups; splits up to the number of resident slots shorten every workgroup
+// instead (41 rows x 40 heads x 4 sequences at 4096 keys: 99 -> 80 us with 3 splits).
+int splits_wanted(int items, int per_cu) {
+  const int n_cus = device_cus(), fill = items >= n_cus ? 1 : (n_cus + items - 1) / items;
+  const int more = (items * fill > n_cus && per_cu >= 2) ? (n_cus * per_cu) / items : 0;
+  return (fill < 255 ? fill : 255) | (more < 255 ? more : 255) << 8;
+}
+int widest_split(int n_splits, int want) {
+  const int widest = (want & 255) > (want >> 8) ? want & 255 : want >> 8;
+  return n_splits < widest ? n_splits : widest;
+}
+
+template <int HD>
+hipError_t run_merge(const RowDesc& rd, const KvView& kv, int B, int R, int n_heads, const float* partial, int n_splits, int want, void* out, int ncg, bool causal,
+                    hipStream_t s) {
+  hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3((B * n_heads * R + 3) / 4), dim3(256), 0, s, rd, kv, B, R, n_heads, partial, n_splits, want, (bf16_t*)out, ncg,
+                     causal);
+  return hipGetLastError();
+}
+
+template <int HD, int RW, bool CAUSAL>
+hipError_t run_rows(const float* q, int q_stride, const RowDesc& rd, const KvView& kv, int layer, int B, int R, int n_heads, float* partial, int n_splits,
+                    void* out, int ncg, hipStream_t s) {
+  using Sh = RowsShape<HD, RW>;
+  const int KVH = kv.n_kv_heads, G = n_heads / KVH, n_chunks = (G * R + RW * 16 - 1) / (RW * 16), items = KVH * n_chunks * B;
+  auto kern = tree_attn_rows_kernel<HD, RW, CAUSAL>;
+  static_assert(Sh::LDS <= 64 * 1024, "needs no attribute");
+  const int want = splits_wanted(items, 3), gx = widest_split(n_splits, want);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(gx * items)), dim3(RW * 64), Sh::LDS, s, q, q_stride, rd, kv, layer, B, R, n_heads, n_chunks,
+                     ATTN_LOG2E / sqrtf((float)HD), partial, n_splits, (bf16_t*)out, want, ncg, gx);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || gx == 1) return e;  // one split: every workgroup wrote its output
+  return run_merge<HD>(rd, kv, B, R, n_heads, partial, n_splits, want, out, ncg, CAUSAL, s);
+}
+
+template <int HD, int NRG, int AW>
+hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvView& kv, int layer, int B, int R, int n_heads, float* partial,
+                    int n_splits, void* out, int ncg, hipStream_t s, int* counters = nullptr) {
+  const int KVH = kv.n_kv_heads, G = n_heads / KVH;
+  const int n_chunks = (G * R + NRG * 16 - 1) / (NRG * 16);  // chunks of (query head, row) pairs per KV head
+  const float scale = ATTN_LOG2E / sqrtf((float)HD);
+  auto kern = tree_attn_mfma_kernel<HD, NRG, AW>;
+  constexpr size_t lds = sizeof(MfmaAttnSmem<HD, NRG, AW>);
+  static const hipError_t attr = lds > 64 * 1024 ? hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
+                                                 : hipSuccess;
+  if (attr != hipSuccess) return attr;
   const int items = KVH * n_chunks * B;
-  const int fill = items >= n_cus ? 1 : (n_cus + items - 1) / items;
-  // an uneven fill (C5's target pass: 160 items x 2 splits on 256 compute units) runs as long as the compute units that
-  // hold two workgroups; splits up to the number of resident slots shorten every workgroup instead (41 rows x 40 heads x
-  // 4 sequences at 4096 keys: 99 -> 80 us with 3 splits)
   static const int per_cu = [&] {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)kern, AW * 64, lds) != hipSuccess) n = 1;
     return n > 0 ? n : 1;
   }();
-  const int more = (items * fill > n_cus && per_cu >= 2) ? (n_cus * per_cu) / items : 0;
-  const int fill8 = fill < 255 ? fill : 255, more8 = more < 255 ? more : 255;
-  const int want = fill8 | (more8 << 8);
-  const int widest = fill8 > more8 ? fill8 : more8;
-  const int gx = n_splits < widest ? n_splits : widest;
-  if constexpr (NRG == 1 && !CAUSAL) {
+  const int want = splits_wanted(items, per_cu), gx = widest_split(n_splits, want);
+  if constexpr (NRG == 1) {
     // Six layers, us, two launches / one (rows = sequences x heads x rows each): 12 heads x 64, 12 rows, 256 / 2048 keys 164 / 153,
     // 179 / 171; 48 rows 170 / 159, 216 / 208; 32 heads x 64, 64 rows 218 / 198, 241 / 234.  Beyond, the last workgroups' merges
     // are no longer hidden: 96 rows, 2048 keys 252 / 261; 512 rows 292 / 315, 584 / 618.  Items of 8 rows (8 query heads on a key
@@ -135,27 +398,28 @@ hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvVie
                      partial, n_splits, (bf16_t*)out, want, ncg);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || gx == 1) return e;  // one split: every workgroup wrote its output
-  hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3((B * n_heads * R + 3) / 4), dim3(256), 0, s, rd, kv, B, R, n_heads, (const float*)partial,
-                     n_splits, want, (bf16_t*)out, ncg, CAUSAL);
-  return hipGetLastError();
+  return run_merge<HD>(rd, kv, B, R, n_heads, partial, n_splits, want, out, ncg, false, s);
 }
 
 }  // namespace
 
 
 // bf16 models: q float32 [B*R][q_stride], half-precision cache, output = bf16 hi / lo planes [2][B*R][n_heads*hd].
-// Passes of up to 16 rows per sequence use 16-row work items, larger ones 32-row items (K and V are read once per item).
+// Items of 16 or 32 (query head, row) pairs on a KV head with key tiles dealt to the waves; with more pairs the waves share the tiles
+// (both sides of the line: tree_attn_rows_kernel).
 hipError_t launch_attention_mfma(const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads,
                                  float* partial, int n_splits, void* out, int ncg, hipStream_t s, int* counters) {
   const int hd = kv.head_dim;
   if (kv.n_kv_heads < 1 || n_heads % kv.n_kv_heads) return hipErrorInvalidValue;
   const int pairs = n_heads / kv.n_kv_heads * R;  // (query head, row) pairs that share a KV head
   if (hd == 128 && pairs <= 16) return run_mfma<128, 1, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s, counters);
-  if (hd == 128 && pairs > 32 && pairs <= 48)  // one item instead of two that would each read K and V
-    return run_mfma<128, 3, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
-  if (hd == 128) return run_mfma<128, 2, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (hd == 128 && pairs <= 32) return run_mfma<128, 2, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (hd == 128 && pairs <= 48) return run_rows<128, 3, false>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (hd == 128) return run_rows<128, 4, false>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
   if (hd == 64 && pairs <= 16) return run_mfma<64, 1, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s, counters);
-  if (hd == 64) return run_mfma<64, 2, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (hd == 64 && pairs <= 32) return run_mfma<64, 2, 4>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (hd == 64 && pairs <= 48) return run_rows<64, 3, false>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (hd == 64) return run_rows<64, 4, false>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
   return hipErrorInvalidValue;
 }
 
@@ -163,8 +427,8 @@ hipError_t launch_attention_mfma(const float* q, int q_stride, const RowDesc& rd
 hipError_t launch_attention_prompt(const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads, float* partial,
                                    int n_splits, void* out, int ncg, hipStream_t s) {
   if (kv.n_kv_heads < 1 || n_heads % kv.n_kv_heads) return hipErrorInvalidValue;
-  if (kv.head_dim == 128) return run_mfma<128, 2, 4, true>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
-  if (kv.head_dim == 64) return run_mfma<64, 2, 4, true>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (kv.head_dim == 128) return run_rows<128, 4, true>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
+  if (kv.head_dim == 64) return run_rows<64, 4, true>(q, q_stride, rd, kv, layer, B, R, n_heads, partial, n_splits, out, ncg, s);
   return hipErrorInvalidValue;
 }
 

@@ -310,7 +310,7 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
       const KvView kv = ldc(&A->kv);
       const RowDesc rd = ldc(&A->rd);
       const int eff = tree_attn_item<HD, 1, ATTN_WAVES, 1, FT, true, HD == 128 ? 2 : 1>(sm.attn, A->q + (size_t)layer * A->q_stride, hhd, rd, kv, layer, B, Rseq, H,
-                                                                      n_chunks, 1.0f / sqrtf((float)HD), partial, n_splits, out, A->attn_want, ncg,
+                                                                      n_chunks, ATTN_LOG2E / sqrtf((float)HD), partial, n_splits, out, A->attn_want, ncg,
                                                                       split, kvh, chunk, seq, tid, [&]() {
                                                                         // K and V of the committed context are on their way; the
                                                                         // queries and the new rows' K / V need this layer's QKV product

@@ -325,6 +325,28 @@ def test_key_splits_of_few_rows(hd, heads, kv_heads, batch, gamma, n):
     assert st["excused"] == 0 and all(e == gamma for e in st["eta"])
 
 
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,gamma,beam,n,page_size", [
+    (64, 2, 2, 1, 4, 8, 1000, 16),     # 33 pairs a KV head: the fewest of a workgroup of three waves, the last of which holds one row
+    (128, 2, 2, 1, 4, 8, 1000, 3),     # the same for head dim 128, pages that no tile boundary meets
+    (64, 6, 2, 2, 3, 5, 95, 16),       # 48 pairs: the most of three waves; one key split, keys that end a tile of 32 less one
+    (128, 3, 1, 2, 3, 5, 127, 1),      # 48 pairs, pages of one token
+    (64, 7, 1, 1, 6, 1, 600, 5),       # 49 pairs: the fewest of four waves, 16 of whose rows do not exist
+    (128, 4, 1, 3, 3, 5, 640, 16),     # 64 pairs: four full waves
+    (64, 13, 1, 2, 4, 1, 700, 16),     # 65 pairs: a second workgroup that holds one row
+    (128, 8, 1, 1, 5, 8, 2500, 16),    # 328 pairs: six workgroups a KV head
+])
+def test_attention_items_of_many_rows(hd, heads, kv_heads, batch, gamma, beam, n, page_size):
+    """More than 32 (query head, row) pairs on a KV head: the kernel whose waves share their tiles, at the edges of its workgroups, tiles
+    and key blocks, every iteration against the oracle."""
+    ts = si.ModelShape(1, 256, heads, kv_heads, hd, 352, 512, "bf16")
+    ds = si.ModelShape(1, 64, 1, 1, 64, 160, 512, "bf16")
+    wt, wd = _weights(ts, 37, "target", boost=2.0), _weights(ds, 37, "draft", boost=2.0)
+    prompt = np.random.default_rng(n).integers(0, ts.vocab, (batch, n)).astype(np.int32)
+    print(f"items of many rows hd {hd} heads {heads}/{kv_heads} batch {batch} rows {1 + gamma * beam} n {n} pages {page_size}", flush=True)
+    st = run_pair(ts, ds, wt, wd, prompt, 2 * gamma + 2, gamma=gamma, beam=beam, mode="mmtad" if beam > 1 else "mtad", tau=0.0, seed=5, check_kv=True, page_size=page_size)
+    assert st["excused"] == 0 and all(e == gamma for e in st["eta"])
+
+
 @pytest.mark.parametrize("share", [0.0, 0.4, 0.9])
 def test_prompt_and_passes_on_a_smaller_workspace(share):
     """Any buffer between what chunks of prefill_rows rows need and the best size is bound and used up to its end and no further:
