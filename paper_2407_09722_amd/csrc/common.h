@@ -206,7 +206,7 @@ hipError_t launch_embed(int dtype, const void* E, const int32_t* tok, float* h, 
                         void* planes, float* ssq, const int32_t* pos, float2* table, int head_dim, float theta, int ncg, hipStream_t s);
 // out = rmsnorm(h) * g, written as hi/lo bf16 planes [2][rows][d] (dtype 1) or f32 [rows][d] (dtype 0)
 hipError_t launch_rmsnorm(int dtype, const float* h, const float* g, void* out, int rows, int d, float eps, hipStream_t s);
-// q: [rows][q_stride] float32 with head h at column h*head_dim; counters: zeroed ints [B][n_heads][ceil(R/16)], used by
+// q: [rows][q_stride] float32 with head h at column h*head_dim; counters: zeroed ints [B][n_heads][ceil(R/8)], used by
 // the last workgroup of an item, which merges the key splits (bf16 models: in passes of few rows, else a kernel of its own does)
 hipError_t launch_attention(int dtype, const float* q, int q_stride, const RowDesc& rd, KvView kv, int layer, int B, int R, int n_heads,
                             float* partial, int n_splits, int* counters, void* out, int ncg, hipStream_t s);

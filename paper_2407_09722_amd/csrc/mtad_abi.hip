@@ -87,12 +87,12 @@ int shape_ok(const mtad_model* m) {
   return 1;
 }
 
-// key splits of a float32 model's attention
+// most key splits of a float32 model's attention (the kernel takes one per 256 keys there are)
 int splits_for(const mtad_ctx* c, const mtad_model* m, int R) {
-  const int chunks = (R + 15) / 16;
+  const int chunks = (R + 7) / 8;
   const int blocks = c->cfg.batch * m->n_heads * chunks;
   int s = (1024 + blocks - 1) / blocks;
-  s = imin(s, (c->cfg.max_context + 127) / 128);
+  s = imin(s, (c->cfg.max_context + 255) / 256);
   return imax(1, imin(32, s));
 }
 

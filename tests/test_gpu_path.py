@@ -347,6 +347,25 @@ def test_attention_items_of_many_rows(hd, heads, kv_heads, batch, gamma, beam, n
     assert st["excused"] == 0 and all(e == gamma for e in st["eta"])
 
 
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,gamma,beam,n,page_size", [
+    (64, 3, 1, 1, 1, 1, 59, 16),      # 2 rows: one for each wave of a pair; keys that come to end a block of 64
+    (128, 2, 2, 2, 2, 1, 60, 3),      # 3 rows, pages of three
+    (64, 2, 2, 1, 7, 1, 244, 16),     # 8 rows: a whole chunk; 256 keys and more on the way: a second key split
+    (128, 2, 1, 1, 4, 2, 250, 1),     # 9 rows: a second chunk of one row
+    (64, 4, 2, 1, 5, 8, 1100, 16),    # 41 rows, several splits of several blocks
+    (128, 1, 1, 3, 4, 8, 600, 5),     # 33 rows
+])
+def test_float32_attention_blocks_and_splits(hd, heads, kv_heads, batch, gamma, beam, n, page_size):
+    """float32 attention at the edges of its row chunks, key blocks and splits, every iteration against the oracle."""
+    ts = si.ModelShape(2, 192, heads, kv_heads, hd, 256, 512, "fp32")
+    ds = si.ModelShape(1, 64, 1, 1, 64, 160, 512, "fp32")
+    wt, wd = _weights(ts, 41, "target", boost=2.0), _weights(ds, 41, "draft", boost=2.0)
+    prompt = np.random.default_rng(n).integers(0, ts.vocab, (batch, n)).astype(np.int32)
+    print(f"float32 attention hd {hd} heads {heads}/{kv_heads} batch {batch} rows {1 + gamma * beam} n {n} pages {page_size}", flush=True)
+    st = run_pair(ts, ds, wt, wd, prompt, 3 * gamma + 3, gamma=gamma, beam=beam, mode="mmtad" if beam > 1 else "mtad", tau=0.0, seed=5, check_kv=True, page_size=page_size)
+    assert st["excused"] == 0 and all(e == gamma for e in st["eta"]) and st["max_logit_err"] < 1e-4
+
+
 @pytest.mark.parametrize("share", [0.0, 0.4, 0.9])
 def test_prompt_and_passes_on_a_smaller_workspace(share):
     """Any buffer between what chunks of prefill_rows rows need and the best size is bound and used up to its end and no further:
