@@ -22,7 +22,8 @@
 // Bound by latency: launch, length, page, tile, arithmetic and merge are a chain.  us with the merge of the splits, before / with the
 // page and the queries requested before the length is known, a V tile's loads together instead of one after another's index,
 // transposing reads and the lazy reference: 17 rows x 32 heads x 128, 2064 keys 21.3 / 19.7; 8 x 5 rows x 32 heads, 700 keys 25.2 / 23.6;
-// 16 x 6 rows x 16 heads x 64, 300 keys 11.1 / 9.7; one row x 12 heads x 64, 256 keys 7.4 / 7.0.
+// 16 x 6 rows x 16 heads x 64, 300 keys 11.1 / 9.8; then, with the kernel arguments in one fetch and LDS accesses of 16 bytes (the struct
+// below is aligned for them), one row x 32 heads x 128, 4000 keys 22.7 / 20.9, one row x 12 heads x 64, 256 keys 7.4 / 7.0 / 5.8.
 #pragma once
 #include "common.h"
 
@@ -44,7 +45,7 @@ union KFrag {
 };
 
 template <int HD, int NRG, int AW, int DS = 1>
-struct MfmaAttnSmem {
+struct alignas(16) MfmaAttnSmem {
   static constexpr int VS = HD + 8;         // padded query row of halves: 16-byte aligned
   static constexpr int VSV = HD / DS + 16;  // row of a V tile (the part one wave holds): eight rows start 8 banks apart from each other
   union {
@@ -327,14 +328,15 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   // What does not depend on the sequence's length is requested before it is known: the page of a wave's first tiles (tile t belongs to
   // wave t % AW of split t / AW % splits) and, where they are there already, the queries, ahead of the tiles behind which
   // they would otherwise queue.
+  // (All kernel arguments are loaded at once here; left to itself the compiler fetches them in rounds, each a trip to memory.)
+  if constexpr (!WAITS)
+    asm volatile("" ::"s"(q), "s"(q_stride), "s"(rd.nspec), "s"(rd.mask), "s"(kv.k), "s"(kv.v), "s"(kv.page_table), "s"(kv.len), "s"(kv.page_size),
+                 "s"(kv.max_pages), "s"(kv.n_pages), "s"(kv.n_kv_heads), "s"(kv.layer_stride), "s"(layer), "s"(R), "s"(n_heads), "s"(n_splits), "s"(want_splits));
   const int tile0 = split * AW + wslot;
   const int cap = kv_capacity(kv);
-  auto token_of = [&](int ti) -> int {
-    const int kj = ti * ATK + (lane & 31);
-    return kj < cap ? token_index(kv, seq, kj) : -1;
-  };
-  int tok0 = -1;
-  if (active) tok0 = token_of(tile0);
+  auto key_of = [&](int ti) { return min(ti * ATK + (lane & 31), cap - 1); };
+  const int page0 = kv.page_table[(int64_t)seq * kv.max_pages + key_of(tile0) / kv.page_size];
+  auto token_in = [&](int ti, int page) { return ((page < 0 || page >= kv.n_pages) ? 0 : page) * kv.page_size + key_of(ti) % kv.page_size; };
   constexpr int QL = (RBK * (HD / 4) + NTH - 1) / NTH;  // float4s of the queries per thread
   float4 qv[QL];
   auto load_q = [&]() {
@@ -440,7 +442,7 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
   };
   int tokm0 = -1, tokm1 = -1;
   if (tile0 < n_tiles) {
-    tokm0 = mark(tile0, tok0);
+    tokm0 = mark(tile0, token_in(tile0, page0));
     if constexpr (WAITS) {
       load_v_committed(SET0, tokm0);
       load_k_committed(SET0, tokm0);
@@ -450,7 +452,7 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
     }
   }
   if (NSET == 2 && tile0 + TSTEP < n_tiles) {
-    tokm1 = mark(tile0 + TSTEP, token_of(tile0 + TSTEP));
+    tokm1 = mark(tile0 + TSTEP, token_index(kv, seq, key_of(tile0 + TSTEP)));
     if constexpr (WAITS) {
       load_v_committed(SET1, tokm1);
       load_k_committed(SET1, tokm1);

@@ -68,7 +68,8 @@ __global__ __launch_bounds__(F32_THREADS) __attribute__((amdgpu_waves_per_eu(2))
     const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int R, int n_heads, int n_chunks, float scale, float* __restrict__ partial,
     int n_splits, int* __restrict__ counters, float* __restrict__ out) {
   constexpr int E = HD / 64;  // float4s per lane of a key or a query
-  __shared__ float o_s[F32_BLOCKS][F32_ROWS][HD], m_s[F32_BLOCKS][F32_ROWS], l_s[F32_BLOCKS][F32_ROWS];
+  __shared__ __attribute__((aligned(16))) float o_s[F32_BLOCKS][F32_ROWS][HD];
+  __shared__ float m_s[F32_BLOCKS][F32_ROWS], l_s[F32_BLOCKS][F32_ROWS];
   __shared__ int last_s;
   const int t = threadIdx.x, lane = t & 63, c = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), kb = wave >> 1;
@@ -79,12 +80,12 @@ __global__ __launch_bounds__(F32_THREADS) __attribute__((amdgpu_waves_per_eu(2))
   const int cap = kv_capacity(kv);
 
   // what does not depend on the length first: the place of this lane's key of the first block, the queries
-  auto token_of = [&](int block) {
-    const int key = block * F32_BLOCK + 4 * c + g;
-    return key < cap ? token_index(kv, seq, key) : 0;
-  };
+  // (all kernel arguments at once; left to itself the compiler fetches them in rounds, each a trip to memory)
+  asm volatile("" ::"s"(q), "s"(q_stride), "s"(rd.nspec), "s"(rd.mask), "s"(kv.k), "s"(kv.v), "s"(kv.page_table), "s"(kv.len), "s"(kv.page_size), "s"(kv.max_pages),
+               "s"(kv.n_pages), "s"(kv.n_kv_heads), "s"(kv.layer_stride), "s"(layer), "s"(R), "s"(n_heads), "s"(n_splits), "s"(n_chunks), "s"(out));
+  auto key_of = [&](int block) { return min(block * F32_BLOCK + 4 * c + g, cap - 1); };
   const int block0 = split * F32_BLOCKS + kb;
-  int tok = token_of(block0);
+  const int page0 = kv.page_table[(int64_t)seq * kv.max_pages + key_of(block0) / kv.page_size];
   float4 qv[HALF_ROWS][E];
   unsigned long long mask[HALF_ROWS];
 #pragma unroll
@@ -94,6 +95,7 @@ __global__ __launch_bounds__(F32_THREADS) __attribute__((amdgpu_waves_per_eu(2))
 #pragma unroll
     for (int e = 0; e < E; ++e) qv[r][e] = *(const float4*)(q + (int64_t)row * q_stride + head * HD + e * 64 + 4 * c);
   }
+  int tok = ((page0 < 0 || page0 >= kv.n_pages) ? 0 : page0) * kv.page_size + key_of(block0) % kv.page_size;
   const int len = kv.len[seq], ktot = attn_keys(kv, rd, seq), eff = f32_splits(ktot, n_splits);
   if (split >= eff) return;
   const int blocks = nr > 0 ? (ktot + F32_BLOCK - 1) / F32_BLOCK : 0;
@@ -125,7 +127,7 @@ __global__ __launch_bounds__(F32_THREADS) __attribute__((amdgpu_waves_per_eu(2))
     request(kf, kbase);
     if constexpr (E == 1) request(vf, vbase);  // (two float4s per key and lane: no room for V beside K)
     const int next = b + eff * F32_BLOCKS;
-    if (next < blocks) tok = token_of(next);
+    if (next < blocks) tok = token_index(kv, seq, key_of(next));
     const int key = b * F32_BLOCK + 4 * c + g;
     float p[HALF_ROWS];
 #pragma unroll

@@ -114,6 +114,9 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(HD == 1
 
   const int t = threadIdx.x, lane = t & 63, srow = lane & 15, sg4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  // (all kernel arguments at once; left to itself the compiler fetches them in rounds, each a trip to memory)
+  asm volatile("" ::"s"(q), "s"(q_stride), "s"(rd.nspec), "s"(rd.mask), "s"(kv.k), "s"(kv.v), "s"(kv.page_table), "s"(kv.len), "s"(kv.page_size), "s"(kv.max_pages),
+               "s"(kv.n_pages), "s"(kv.n_kv_heads), "s"(kv.layer_stride), "s"(layer), "s"(R), "s"(n_heads), "s"(n_splits), "s"(n_chunks), "s"(splits));
   const int split = blockIdx.x % splits, item = blockIdx.x / splits, KVH = kv.n_kv_heads, G = n_heads / KVH, g = item % KVH, seq = item / KVH % B;
   const int rank = item / (KVH * B), chunk = CAUSAL ? n_chunks - 1 - rank : rank;  // a prompt's items that see the most keys first
   const int pairs = G * R, pair0 = chunk * (RW * RG * 16), pair_end = min(pairs, pair0 + RW * RG * 16);  // pair p = query head p / R of the group, row p % R
