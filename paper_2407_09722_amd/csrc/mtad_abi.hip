@@ -97,11 +97,11 @@ int splits_for(const mtad_ctx* c, const mtad_model* m, int R) {
 }
 
 // Rows of one prompt pass of a bf16 model, all sequences together.  From about 256 rows on a product is bound by the matrix
-// cores, no longer by its weights; 2048 rows fill the machine with 256-row tiles also where the output is narrow (4096
-// features: 256 workgroups), and cost a 13B-shaped model 260 MB of workspace (carve_within() makes do with less).  Four 7B-shaped
+// cores, no longer by its weights; 2048 rows fill the machine with 256-row tiles where the output is 4096 features wide (256
+// workgroups), 4096 rows where it is 2048, and cost a 13B-shaped model 520 MB of workspace (carve_within() makes do with less).  Four 7B-shaped
 // layers on 2047 tokens: 16.7 ms in chunks of 64 rows, 4.9 in chunks of 1024 or one pass; four 13B-shaped ones on 4 x 509, 4 x 64 rows
-// a chunk 9.7 -> 6.7 ms; the 22-layer draft on 4 x 1023 39.5 -> 17.2 (20.2 in chunks of half the size).
-constexpr int PROMPT_PASS_ROWS = 2048;
+// a chunk 9.7 -> 6.7 ms; the 22-layer draft of 2048 features on 4 x 1023 tokens 39.5 ms in chunks of 256 rows in all, 15.6 in two of 2048, 14.9 in one pass.
+constexpr int PROMPT_PASS_ROWS = 4096;
 
 struct Carver {
   size_t off = 0;
