@@ -41,13 +41,13 @@ hipError_t launch_accept_spd(TreeView tree, const float* logits, const float* ls
 // multi-token joint decoding: the chain in `tree` as an accept record (all gamma tokens emitted)
 hipError_t launch_accept_chain(TreeView tree, int B, int gamma, AcceptView out, hipStream_t s);
 // lse_part (launch_topb): the logits' logsumexps are finished from (max, sum exp) partials [rows][NP] and written to lse_out = lse;
-// part (launch_accept): ACCEPT_PARTS 8-byte words per sequence, or null
+// part, counters (launch_accept): ACCEPT_PARTS 8-byte words and one zeroed word, left zeroed, per sequence, or null
 constexpr int ACCEPT_PARTS = 16;
 // rows of logits -> rows of log p~ (top_k, then top_p prefix; 1 <= top_k <= 16), lse -> 0; in place
 hipError_t launch_warp_rows(float* logits, float* lse, int rows, int V, int top_k, float top_p, hipStream_t s);
 hipError_t launch_gather_logp(const float* logits, const float* lse, TreeView tree, int B, int V, float* logp_cond, hipStream_t s);
 hipError_t launch_accept(TreeView tree, const float* logp_cond, const float* logits, int V, const int32_t* len, float log_tau, int mode,
-                         int B, int gamma, int sample, uint64_t seed, AcceptView out, void* part, hipStream_t s);
+                         int B, int gamma, int sample, uint64_t seed, AcceptView out, void* part, int* counters, hipStream_t s);
 hipError_t launch_kv_gather(int dtype, KvView kv, int n_layers, int B, const int32_t* eta, const int32_t* path, const int32_t* src_beam,
                             const int32_t* cu_cnt, int M, int gamma, int beam, int is_draft, hipStream_t s);
 hipError_t launch_commit_state(int32_t* tlen, int32_t* dlen, TreeView tree, AcceptView acc, int32_t* root_tok, int32_t* cu_tok,

@@ -320,7 +320,15 @@ __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restric
       }
     }
   __syncthreads();
-  // N candidates per thread at a time, their logits requested together
+  // N candidates per thread at a time, their logits requested together.  A slice lies in at most two rows (a workgroup has 1/G of at
+  // most MAXB of them, and G >= MAXB): their likelihoods and logsumexps are looked up once, not per candidate behind a division.
+  const int ra = min(c0 / V, n_live - 1), rb = min(ra + 1, n_live - 1), rb_at = (ra + 1) * V;
+  const float cum_a = cum_s[ra], cum_b = cum_s[rb];
+  float lse_a = 0.f, lse_b = 0.f;
+  if (c0 < c1) {
+    lse_a = lse_part ? lse_s[ra] : lse[row0 + ra];
+    if (c1 > rb_at) lse_b = lse_part ? lse_s[rb] : lse[row0 + rb];
+  }
   const int wave = threadIdx.x >> 6;
   uint64_t top = NO_RANK;
   for (int cb = c0 + (int)threadIdx.x; cb - (int)threadIdx.x < c1; cb += 256 * N) {
@@ -328,9 +336,9 @@ __global__ __launch_bounds__(256) void topb_stage1_kernel(const float* __restric
     float x[N];
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-      const int c = min(cb + 256 * u, c1 - 1), r = c / V;
+      const int c = min(cb + 256 * u, c1 - 1);
       x[u] = logits[(int64_t)row0 * V + c];  // rows of the live beams follow each other
-      x[u] = cum_s[r] + (x[u] - (lse_part ? lse_s[r] : lse[row0 + r]));
+      x[u] = (c >= rb_at ? cum_b : cum_a) + (x[u] - (c >= rb_at ? lse_b : lse_a));
     }
 #pragma unroll
     for (int u = 0; u < N; ++u) {
@@ -577,11 +585,11 @@ __device__ __forceinline__ uint64_t best_of_row(const float* __restrict__ row, i
 }
 
 // Acceptance and bonus token by one workgroup per sequence (part == null), or, with 2 x gridDim.x words of workspace per
-// sequence at `part`, the bonus token's argmax by gridDim.x workgroups, which leave their best entries to accept_finish_kernel:
-// 32000 Gumbel keys are 11 us of one compute unit's arithmetic and 1 us of sixteen's.
+// sequence at `part`, the bonus token's argmax by gridDim.x workgroups: 32000 Gumbel keys are 11 us of one compute unit's arithmetic and
+// 1 us of sixteen's.  counters: a zeroed word per sequence, left zeroed, or null (a launch of its own then takes the best of all).
 __global__ __launch_bounds__(1024) void accept_kernel(TreeView tree, const float* __restrict__ logp_cond, const float* __restrict__ logits,
                                                      int V, const int32_t* __restrict__ len, float log_tau, int mode, int gamma,
-                                                     int sample, uint64_t seed, AcceptView out, uint64_t* __restrict__ part) {
+                                                     int sample, uint64_t seed, AcceptView out, uint64_t* __restrict__ part, int* __restrict__ counters) {
   __shared__ AcceptWalk w;
   __shared__ uint64_t sh[16];
   const int s = blockIdx.y, M = tree.M;
@@ -589,17 +597,32 @@ __global__ __launch_bounds__(1024) void accept_kernel(TreeView tree, const float
   if (blockIdx.x == 0 && threadIdx.x == 0) accept_store(w, out, s, M, gamma);
   const float* row = logits + ((int64_t)s * M + w.node) * V;
   const uint64_t nk = noise_key(seed, s * STREAMS_PER_SEQ + STREAM_BONUS, len[s] + 1 + w.eta);
-  const uint64_t best = block_max_rank(best_of_row(row, V, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, sample, nk), sh);
-  if (threadIdx.x != 0) return;
+  uint64_t best = block_max_rank(best_of_row(row, V, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, sample, nk), sh);
+  if (threadIdx.x >= 64) return;
   if (part) {
-    part[s * gridDim.x + blockIdx.x] = best;
-    return;
+    const int G = gridDim.x;
+    if (!counters) {  // accept_finish_kernel takes the best of all
+      if (threadIdx.x == 0) part[s * G + blockIdx.x] = best;
+      return;
+    }
+    // wave 0 of the workgroup that arrives last takes it
+    int prev = 0;
+    if (threadIdx.x == 0) {
+      __hip_atomic_store((unsigned long long*)part + s * G + blockIdx.x, (unsigned long long)best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_s_waitcnt(0);  // acknowledged
+      prev = __hip_atomic_fetch_add(counters + s, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane(prev) != G - 1) return;
+    if (threadIdx.x == 0) __hip_atomic_store(counters + s, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // clean for the next launch
+    best = row_max(__hip_atomic_load((unsigned long long*)part + s * G + min((int)(threadIdx.x & 15), G - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));  // G <= 16
   }
+  if (threadIdx.x != 0) return;
   int bi = rank_idx(best);
   if (bi < 0 || bi >= V) bi = 0;  // only reachable with non-finite logits: stay in the vocabulary
   out.bonus_tok[s] = bi;
   out.out_tok[s * (gamma + 1) + w.eta] = bi;
 }
+
 __global__ __launch_bounds__(64) void accept_finish_kernel(const uint64_t* __restrict__ part, int G, int V, int gamma, AcceptView out) {
   const int s = blockIdx.x;
   const uint64_t best = row_max(part[s * G + min((int)(threadIdx.x & 15), G - 1)]);  // G <= 16
@@ -611,20 +634,22 @@ __global__ __launch_bounds__(64) void accept_finish_kernel(const uint64_t* __res
 }
 
 hipError_t launch_accept(TreeView tree, const float* logp_cond, const float* logits, int V, const int32_t* len, float log_tau, int mode,
-                         int B, int gamma, int sample, uint64_t seed, AcceptView out, void* part, hipStream_t s) {
+                         int B, int gamma, int sample, uint64_t seed, AcceptView out, void* part, int* counters, hipStream_t s) {
   // Sixteen workgroups of 256 threads where their partial results have a place and there is noise to compute.  One workgroup / sixteen,
   // us: 1 sequence of 17 rows, 4096, 6144, 8192 and 32000 tokens 7.7 / 7.8, 8.6 / 7.8, 9.2 / 7.9, 19.0 / 8.8; 64 sequences of 2
   // rows 5.4 / 6.4, 6.1 / 6.7, 6.8 / 6.8, 16.8 / 9.2.
   const bool wide = part && sample && V >= 8192;
   if (!wide) {
     hipLaunchKernelGGL(accept_kernel, dim3(1, B), dim3(1024), 0, s, tree, logp_cond, logits, V, len, log_tau, mode, gamma, sample, seed, out,
-                       (uint64_t*)nullptr);
+                       (uint64_t*)nullptr, (int*)nullptr);
     return hipGetLastError();
   }
+  // Two launches / one: 32000 tokens, 1, 4, 16 and 64 sequences 8.8 / 8.4, 13.9 / 13.0, 7.1 / 8.6 and 9.0 / 11.4 us (17, 41, 4 and 2 rows each).
+  const bool one_launch = counters && B <= 8;
   hipLaunchKernelGGL(accept_kernel, dim3(ACCEPT_PARTS, B), dim3(256), 0, s, tree, logp_cond, logits, V, len, log_tau, mode, gamma, sample, seed, out,
-                     (uint64_t*)part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+                     (uint64_t*)part, one_launch ? counters : nullptr);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || one_launch) return e;
   hipLaunchKernelGGL(accept_finish_kernel, dim3(B), dim3(64), 0, s, (const uint64_t*)part, ACCEPT_PARTS, V, gamma, out);
   return hipGetLastError();
 }
@@ -724,20 +749,23 @@ hipError_t launch_accept_spd(TreeView tree, const float* logits, const float* ls
 // prefix whose cumulative probability exceeds top_p; normalised again), minus infinity outside the support, and the
 // row's logsumexp becomes 0, so that every consumer of (logits, lse) rows works on p~ unchanged.  Entries rank by value
 // descending, token id ascending; a NaN ranks last.
-//   1. every wave's best entry; T = the top_k-th best of those 16.  The top_k entries of the row rank T or better, and so do
-//      few others (10 to 60 in a row of logits in no order): they are listed in LDS.
-//   2. a row whose best entries share a few waves lists more than WARP_SHORT: T is then the top_k-th best of the threads' best
-//      entries, in top_k rounds of a workgroup-wide maximum, and at most top_k * V / 1024 rank T or better
-//   3. wave 0 takes the top_k best of the list and does the arithmetic, one token per lane, sums in descending order
-// Bound by its chain of steps, one compute unit per row; 32000 tokens, top_k 10: 15 us with T from the waves, 20 with T from
-// the threads' rounds for every row (a barrier each).  The first 32768 entries of the row live in registers.
-// WARP_SHORT 128 / 512 / 2048, 4 rows with their copy, us: 1000 tokens in two waves, top_k 10 21.5 / 15.1 / 15.1; 4096 of one value,
+//   1. every wave's largest value; t = the top_k-th largest of those 16.  The top_k entries of the row reach t, and so do few
+//      others (10 to 60 in a row of logits in no order): they are listed in LDS.
+//   2. a row whose largest values share a few waves, or that repeats one value, lists more than WARP_SHORT or has no such t: a
+//      threshold of value and id is then the top_k-th best of the threads' best entries, in top_k rounds of a workgroup-wide maximum, and
+//      at most top_k * V / 1024 entries reach it
+//   3. wave 0 orders the list (up to 64 entries: every lane counts the entries before its own) and does the arithmetic, one token per
+//      lane, sums in descending order
+// Bound by its chain of steps, one compute unit per row; 32000 tokens, top_k 10: 15.2 us with the threshold, the list and the order
+// taken on 64-bit (value, id) ranks, 10.7 on values, ranks only in the list.  The first 32768 entries of the row live in registers.
+// WARP_SHORT 128 / 512 / 2048, 4 rows with their copy, us (ranks): 1000 tokens in two waves, top_k 10 21.5 / 15.1 / 15.1; 4096 of one value,
 // top_k 16 28.5 / 28.5 / 42.3; 8192 with the best 1024 in two waves 22.7 / 22.7 / 31.6; 151936 sorted 105 / 105 / 89.
 constexpr int WARP_MAXK = 16, WARP_LIST = 2048, WARP_SHORT = 512;
 __device__ __forceinline__ float lane_value(float v, int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); }  // i uniform
 __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ logits, float* __restrict__ lse, int V, int top_k, float top_p) {
   __shared__ uint64_t sh[2][16];
   __shared__ uint64_t list[WARP_LIST];
+  __shared__ float best_s[16];
   __shared__ int count;
   __shared__ float tv[WARP_MAXK];
   __shared__ int ti[WARP_MAXK], keep_s;
@@ -746,70 +774,95 @@ __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ log
   constexpr int PT = 32;
   float x[PT];
 #pragma unroll
-  for (int j = 0; j < PT; ++j) {
-    const float v = row[min(t + 1024 * j, V - 1)];
-    x[j] = (v == v) ? v : -INFINITY;
-  }
+  for (int j = 0; j < PT; ++j) x[j] = row[min(t + 1024 * j, V - 1)];
   auto at = [&](int v) {  // entries beyond the registers
     const float y = row[v];
     return (y == y) ? y : -INFINITY;
   };
   if (t == 0) count = 0;
-  uint64_t mine = rank_of(-INFINITY, 0x7FFFFFFF);
+  float mine = -INFINITY;
 #pragma unroll
   for (int j = 0; j < PT; ++j) {
-    const uint64_t r = rank_of(x[j], t + 1024 * j);
-    if (t + 1024 * j < V && r > mine) mine = r;
+    x[j] = (x[j] == x[j] && t + 1024 * j < V) ? x[j] : -INFINITY;
+    mine = fmaxf(mine, x[j]);
   }
-  for (int v = t + 1024 * PT; v < V; v += 1024) {
-    const uint64_t r = rank_of(at(v), v);
-    if (r > mine) mine = r;
-  }
-  // a row that lies in registers whole is overwritten now, while the rounds run
+  for (int v = t + 1024 * PT; v < V; v += 1024) mine = fmaxf(mine, at(v));
+  // a row that lies in registers whole is overwritten now, while the rest runs
   const bool held = V <= 1024 * PT;
   if (held)
     for (int v = t; v < V; v += 1024) row[v] = -INFINITY;
-  auto list_from = [&](uint64_t T) {  // what ranks T or better
-    if (mine < T) return;
-#pragma unroll
-    for (int j = 0; j < PT; ++j) {
-      const uint64_t r = rank_of(x[j], t + 1024 * j);
-      if (t + 1024 * j < V && r >= T) {
-        const int o = atomicAdd(&count, 1);
-        if (o < WARP_LIST) list[o] = r;
-      }
-    }
-    for (int v = t + 1024 * PT; v < V; v += 1024) {
-      const uint64_t r = rank_of(at(v), v);
-      if (r >= T) {
-        const int o = atomicAdd(&count, 1);
-        if (o < WARP_LIST) list[o] = r;
-      }
-    }
-  };
-  const uint64_t wave_best = wave_max_rank(mine);
-  if (lane == 0) sh[0][t >> 6] = wave_best;
+  const float wave_best = wave_max(mine);
+  if (lane == 0) best_s[t >> 6] = wave_best;
   __syncthreads();
+  float T;
   {
-    const uint64_t w = sh[0][lane & 15];
+    const float w = best_s[lane & 15];
     int above = 0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) above += sh[0][i] > w;
-    list_from(~wave_max_rank(above < k ? ~w : 0));
+    for (int i = 0; i < 16; ++i) above += best_s[i] > w;
+    T = -wave_max(above < k ? -w : -INFINITY);
+  }
+  const bool sparse = T > -INFINITY;  // uniform over the workgroup
+  if (sparse && wave_best >= T) {     // uniform over the wave
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+      const uint64_t hits = __ballot(x[j] >= T);
+      if (hits) {
+        int at0 = 0;
+        if (lane == 0) at0 = atomicAdd(&count, __popcll(hits));
+        at0 = __builtin_amdgcn_readfirstlane(at0);
+        if (at0 > WARP_SHORT) break;  // too long already
+        const int o = at0 + __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0));
+        if (x[j] >= T && o < WARP_LIST) list[o] = rank_of(x[j], t + 1024 * j);
+      }
+    }
+    for (int v = t + 1024 * PT; v < V && *(volatile int*)&count <= WARP_SHORT; v += 1024) {
+      const float y = at(v);
+      if (y >= T) {
+        const int o = atomicAdd(&count, 1);
+        if (o < WARP_LIST) list[o] = rank_of(y, v);
+      }
+    }
   }
   __syncthreads();
   int n = count;
-  if (n > WARP_SHORT) {
+  if (n > WARP_SHORT || !sparse) {
     __syncthreads();
     if (t == 0) count = 0;
-    uint64_t T = 0, left = mine;
+    uint64_t best = rank_of(-INFINITY, 0x7FFFFFFF);
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+      const uint64_t r = rank_of(x[j], t + 1024 * j);
+      if (t + 1024 * j < V && r > best) best = r;
+    }
+    for (int v = t + 1024 * PT; v < V; v += 1024) {
+      const uint64_t r = rank_of(at(v), v);
+      if (r > best) best = r;
+    }
+    uint64_t R = 0, left = best;
     const int rounds = min(k, min(V, 1024));  // threads with an entry
     for (int r = 0; r < rounds; ++r) {
-      T = block_max_rank(left, sh[r & 1]);  // (everybody has read the other buffer before this one's barrier)
-      if (left == T) left = 0;
+      R = block_max_rank(left, sh[r & 1]);  // (everybody has read the other buffer before this one's barrier)
+      if (left == R) left = 0;
     }
     __syncthreads();
-    list_from(T);
+    if (best >= R) {
+#pragma unroll
+      for (int j = 0; j < PT; ++j) {
+        const uint64_t r = rank_of(x[j], t + 1024 * j);
+        if (t + 1024 * j < V && r >= R) {
+          const int o = atomicAdd(&count, 1);
+          if (o < WARP_LIST) list[o] = r;
+        }
+      }
+      for (int v = t + 1024 * PT; v < V; v += 1024) {
+        const uint64_t r = rank_of(at(v), v);
+        if (r >= R) {
+          const int o = atomicAdd(&count, 1);
+          if (o < WARP_LIST) list[o] = r;
+        }
+      }
+    }
     __syncthreads();
     n = count;
   }
@@ -828,19 +881,34 @@ __global__ __launch_bounds__(1024) void warp_rows_kernel(float* __restrict__ log
     __syncthreads();
   }
   if (t < 64) {
-    auto lane_best = [&]() {
-      uint64_t b = 0;
-      for (int o = lane; o < n; o += 64) b = list[o] > b ? list[o] : b;
-      return b;
-    };
-    uint64_t b = lane_best(), own = 0;  // own: lane i keeps the i-th best
-    for (int r = 0; r < k; ++r) {
-      const uint64_t w = wave_max_rank(b);
-      if (lane == r) own = w;
-      if (b == w) {
-        for (int o = lane; o < n; o += 64)
-          if (list[o] == w) list[o] = 0;
-        b = lane_best();
+    uint64_t own = 0;  // lane i keeps the i-th best
+    if (n <= 64) {
+      const uint64_t e = lane < n ? list[lane] : 0;
+      const int lo = (int)(uint32_t)e, hi = (int)(e >> 32);
+      int before = 0;
+      for (int i = 0; i < n; ++i) {
+        const uint64_t o = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32) | (uint32_t)__builtin_amdgcn_readlane(lo, i);
+        before += o > e;
+      }
+      if (lane < n && before < k) sh[0][before] = e;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (lane < k) own = ((volatile uint64_t*)sh[0])[lane];
+    } else {
+      auto lane_best = [&]() {
+        uint64_t b = 0;
+        for (int o = lane; o < n; o += 64) b = list[o] > b ? list[o] : b;
+        return b;
+      };
+      uint64_t b = lane_best();
+      for (int r = 0; r < k; ++r) {
+        const uint64_t w = wave_max_rank(b);
+        if (lane == r) own = w;
+        if (b == w) {
+          for (int o = lane; o < n; o += 64)
+            if (list[o] == w) list[o] = 0;
+          b = lane_best();
+        }
       }
     }
     const bool in = lane < k;

@@ -678,7 +678,7 @@ int mtad_accept(mtad_ctx* c, const mtad_tree* tree, const float* logp_cond, cons
   const float log_tau = (tau > 0.f) ? (float)log((double)tau) : -INFINITY;
   const AcceptView av{out->eta, out->path, out->bonus_row, out->bonus_tok, out->out_tok, out->out_cnt};
   HIP_TRY(c, launch_accept(tview(tree), logp_cond, logits, vocab, tkv->len, log_tau, mode, c->cfg.batch, c->cfg.gamma,
-                           sample_bonus ? 1 : 0, seed, av, c->ws ? c->part_key : nullptr, (hipStream_t)stream));
+                           sample_bonus ? 1 : 0, seed, av, c->ws ? c->part_key : nullptr, c->ws ? c->attn_cnt : nullptr, (hipStream_t)stream));
   return MTAD_OK;
 }
 

@@ -251,7 +251,8 @@ def test_row_lse():
 
 
 @pytest.mark.parametrize("V,k,kind", [(1000, 10, "plain"), (7, 16, "plain"), (1024, 16, "same"), (32768, 10, "plain"), (32769, 16, "plain"), (33000, 10, "same"),
-                                      (40000, 16, "low"), (140000, 16, "stride"), (200000, 3, "plain"), (32000, 10, "zeros"), (32000, 10, "waves")])
+                                      (40000, 16, "low"), (140000, 16, "stride"), (200000, 3, "plain"), (32000, 10, "zeros"), (32000, 10, "waves"),
+                                      (32000, 10, "plateau64"), (32000, 10, "plateau65"), (32000, 16, "plateau512"), (32000, 10, "plateau513"), (5000, 10, "nan")])
 def test_warp_rows_supports_of_every_layout(V, k, kind):
     """The support of the warped row is that of a stable descending sort: rows shorter and longer than the registers hold, one
     value everywhere, minus infinities, zeros of both signs, best entries that all fall to one thread (more than its list holds)."""
@@ -267,6 +268,12 @@ def test_warp_rows_supports_of_every_layout(V, k, kind):
         x[:, ::3] = 0.0
     elif kind == "stride":                                            # 137 entries per thread, the largest in threads 0 .. 15
         x[:, np.arange(V) % 1024 < 16] += 100.0
+    elif kind.startswith("plateau"):                                  # so many entries, over all waves, share the largest value: the list's lengths
+        x[:, :int(kind[7:]) * 61:61] = 9.0
+    elif kind == "nan":
+        x[:, np.arange(V) % 7 != 3] = np.nan
+        x[1] = np.nan                                                 # (a row of nothing else)
+        x[1, 4321] = 1.0
     elif kind == "waves":                                             # 4000 entries of two waves above all others
         x[:, np.arange(V) % 1024 < 128] += 100.0
     xd = torch.from_numpy(x).to(DEV)
@@ -276,7 +283,7 @@ def test_warp_rows_supports_of_every_layout(V, k, kind):
     torch.cuda.synchronize()
     got = xd.cpu().numpy()
     for r in range(3):
-        order = np.lexsort((np.arange(V), -(x[r].astype(np.float64))))[:min(k, V)]
+        order = np.lexsort((np.arange(V), -np.where(np.isnan(x[r]), -np.inf, x[r]).astype(np.float64)))[:min(k, V)]
         keep = order[np.isfinite(x[r][order])]
         assert np.array_equal(np.sort(np.flatnonzero(np.isfinite(got[r]))), np.sort(keep))
         e = np.exp(x[r][keep].astype(np.float64) - x[r][keep[0]])
