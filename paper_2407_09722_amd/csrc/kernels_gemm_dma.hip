@@ -487,43 +487,48 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 }
 
-// After a product whose reduction dimension was cut into KS ranges: one workgroup per row adds the ranges in order.
-//   RESID  the residual epilogue over the whole row: h += sum, the next norm's input h * gain as hi / lo terms, and the row's
-//          sum of squares as ONE value, so that the products that read it have nothing left to reduce
-//   STORE  the row of Y
-constexpr int RT = 1024;  // threads
+// After a product whose reduction dimension was cut into KS ranges: grid (pieces of ROW_PIECE features, rows), every workgroup adds the
+// ranges of its piece in order.
+//   RESID  the residual epilogue: h += sum, the next norm's input h * gain as hi / lo terms, and the sum of squares of the piece, so
+//          that the products that read them have a handful of values per row left to add
+//   STORE  the piece of Y
+// Bound by the ranges' way from memory; a workgroup per row (164 rows x 5120, 8 ranges, 27 MB: 11.9 us) left compute units idle, 10.7; 40 rows x 4096 (21 MB) 6.2, 5.0.
+constexpr int RT = 256, ROW_PIECE = RT * 4;
 template <int KS, int EPI>
 __global__ __launch_bounds__(RT) void gemm_rows_kernel(GemmArgs a) {
   __shared__ float sh[RT / 64];
-  const int m = blockIdx.x, N = a.N;
+  const int m = blockIdx.y, N = a.N, n = blockIdx.x * ROW_PIECE + (int)threadIdx.x * 4;
   const size_t range = (size_t)a.R * N;
   float q = 0.f;
-  for (int n = (int)threadIdx.x * 4; n < N; n += RT * 4) {
+  if (n < N) {
     const float* const p = a.part + (size_t)m * N + n;
     float4 t[KS];
 #pragma unroll
     for (int k = 0; k < KS; ++k) t[k] = *(const float4*)(p + k * range);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f), gn = o;
+    if constexpr (EPI == EPI_RESID) {
+      o = *(const float4*)(a.h + (int64_t)m * N + n);
+      gn = *(const float4*)(a.g_next + n);
+    }
     float4 s = t[0];
 #pragma unroll
     for (int k = 1; k < KS; ++k) { s.x += t[k].x; s.y += t[k].y; s.z += t[k].z; s.w += t[k].w; }
     if constexpr (EPI == EPI_STORE) {
       float4* const y = (float4*)(a.Y + (int64_t)m * a.ldy + n);
       if (a.accumulate) {
-        const float4 o = *y;
+        o = *y;
         s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
       }
       *y = s;
     } else {
-      float4* const hp = (float4*)(a.h + (int64_t)m * N + n);
-      const float4 o = *hp, gn = *(const float4*)(a.g_next + n);
       s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
-      *hp = s;
+      *(float4*)(a.h + (int64_t)m * N + n) = s;
       const float x[4] = {s.x * gn.x, s.y * gn.y, s.z * gn.z, s.w * gn.w};
       uint2 hi, lo;
       split_bf16_x4(x, hi, lo);
       *(uint2*)(a.planes_out + act_offset(a.ncg, a.R, N, 0, m, n)) = hi;
       *(uint2*)(a.planes_out + act_offset(a.ncg, a.R, N, 1, m, n)) = lo;
-      q += s.x * s.x + s.y * s.y + s.z * s.z + s.w * s.w;
+      q = s.x * s.x + s.y * s.y + s.z * s.z + s.w * s.w;
     }
   }
   if constexpr (EPI == EPI_RESID) {
@@ -532,7 +537,7 @@ __global__ __launch_bounds__(RT) void gemm_rows_kernel(GemmArgs a) {
     __syncthreads();
     if (threadIdx.x == 0) {
       for (int w = 1; w < RT / 64; ++w) q += sh[w];
-      a.ssq_out[m] = q;
+      a.ssq_out[(int64_t)m * gridDim.x + blockIdx.x] = q;
     }
   }
 }
@@ -743,12 +748,14 @@ hipError_t run_tall(const GemmArgs& a, const Plan& p, hipStream_t s) {
   return p.B == 4 ? run_shape<A, 4, true, EPI>(a, p, s) : run_shape<A, 3, true, EPI>(a, p, s);
 }
 
+int row_pieces(int N) { return (N + ROW_PIECE - 1) / ROW_PIECE; }  // never more than there are strips
+
 template <int KS, int EPI>
 hipError_t run_sum_ks(const GemmArgs& a, hipStream_t s) {
   if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV)
     hipLaunchKernelGGL((gemm_pairs_kernel<KS, EPI>), dim3((unsigned)((a.N / 8 + 255) / 256), (unsigned)a.R), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((gemm_rows_kernel<KS, EPI>), dim3((unsigned)a.R), dim3(RT), 0, s, a);
+    hipLaunchKernelGGL((gemm_rows_kernel<KS, EPI>), dim3((unsigned)row_pieces(a.N), (unsigned)a.R), dim3(RT), 0, s, a);
   return hipGetLastError();
 }
 template <int EPI>
@@ -793,7 +800,7 @@ hipError_t run_dma(GemmArgs a, hipStream_t s, int* np, const GemmTiles* given) {
   }
   if (e != hipSuccess) return e;
   if (p.KS > 1) e = run_sum<EPI>(a, p.KS, s);
-  if (np) *np = p.KS > 1 ? 1 : a.N >> 4;
+  if (np) *np = p.KS > 1 ? row_pieces(a.N) : a.N >> 4;
   return e;
 }
 
