@@ -337,10 +337,44 @@ __global__ __launch_bounds__(GW * 64) void gemm_bf16_multi_kernel(GemmArgs a, in
   }
 }
 
+// Sums of RB values over the wave, row_of_lane(lane) in each lane: the first exchanges halve the number of values instead of
+// repeating each of them in both halves (the additions and their order are wave_sum's): 14 additions instead of 48 for RB = 8.
+template <int RB>
+__device__ __forceinline__ int row_of_lane(int lane) {
+  return RB == 8 ? 2 * (lane >> 4) + (lane & 1) : RB == 4 ? lane >> 4 : 0;
+}
+template <int RB>
+__device__ __forceinline__ float wave_sums(const float (&v)[RB], int lane) {
+  static_assert(RB == 1 || RB == 4 || RB == 8, "");
+  if constexpr (RB == 1) {
+    return wave_sum(v[0]);
+  } else {
+    float c[RB / 2], d[RB / 4];
+#pragma unroll
+    for (int j = 0; j < RB / 2; ++j) {
+      const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[j]), __float_as_uint(v[j + RB / 2]), false, false);
+      c[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int j = 0; j < RB / 4; ++j) {
+      const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(c[j]), __float_as_uint(c[j + RB / 4]), false, false);
+      float t = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+      t += row_turn<8>(t);
+      t += row_turn<4>(t);
+      t += row_turn<2>(t);
+      t += row_turn<1>(t);
+      d[j] = t;
+    }
+    if constexpr (RB == 8) return lane & 1 ? d[1] : d[0];
+    return d[0];
+  }
+}
 // float32 models: one wave per output feature, or per pair of features that an element-wise step joins (rotary partners, gate and
 // up), RB rows at a time; plain FMA, sums over the wave.  These models are tiny and every kernel of a pass costs its launch:
 // normalisation (the row factor commutes with the product, as above), rotation with the cache write and the gating ride on
-// the products, five kernels a layer instead of nine (4 layers, d 256, 5 rows: 123 us a pass, 200 before).
+// the products, five kernels a layer instead of nine (4 layers, d 256, 5 rows: 123 us a pass, 200 before).  What the epilogue reads
+// (rotary values, cache slot, the value to add to) is requested ahead of the products and the page while the sums run; with
+// wave_sums this took 98.6 instead of 105 us of that pass, 354 instead of 412 of a 256-row prompt (d 256, 4 layers).
 // Weights of less than 8 MB: the launch is one memory latency, the loads of RB rows go out together and those past the end are the
 // last one again.  From there on what is computed for rows that do not exist costs its share: 8192 x 4096, one row 35.9 us with RB =
 // 8, 21.6 with RB = 1 (6.2 TB/s); three rows 35.8, 25.6 with RB = 4; nine rows (8 and 1) 72.9, 57.7 without them.
@@ -365,6 +399,21 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   for (int r = 0; r < RB; ++r) acc[r] = acc2[r] = ss[r] = 0.f;
   const float *w1 = a.W + (int64_t)n * K, *w2 = a.W + (int64_t)n2 * K;
   const int rows = min(RB, a.R - r0);
+  // the lane that ends with the sums of a row requests what its epilogue reads ahead of the products
+  const int row = row_of_lane<RB>(lane), m = r0 + min(row, rows - 1);
+  const bool ends = (lane & 15) < (RB == 8 ? 2 : 1) && (RB > 1 || lane == 0) && row < rows;
+  float before = 0.f;
+  float2 cs = make_float2(1.f, 0.f);
+  int slot = -1;
+  if (ends) {
+    if constexpr (EPI == EPI_STORE) {
+      if (a.accumulate) before = a.Y[(int64_t)m * a.ldy + n];
+    }
+    if constexpr (EPI == EPI_QKV) {
+      if (head < a.n_heads + a.kv.n_kv_heads) cs = a.rope[(int64_t)m * (a.kv.head_dim >> 1) + i];
+      if (head >= a.n_heads) slot = a.slot[m];
+    }
+  }
   auto products = [&](auto ALL, auto GAIN) {  // ALL: RB rows (past the end the last one again), else those there are
 #pragma unroll 2
     for (int k = lane * 4; k < K; k += 256) {
@@ -408,23 +457,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
     if (a.gain) products(NO, YES);
     else products(NO, NO);
   }
-  // the sums of row r end in lane r (all rows' epilogues side by side)
-  float y = 0.f, y2 = 0.f, q = 0.f;
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    const float t = wave_sum(acc[r]);
-    y = lane == r ? t : y;
-    if constexpr (PAIR) {
-      const float t2 = wave_sum(acc2[r]);
-      y2 = lane == r ? t2 : y2;
-    }
-    if (a.gain) {
-      const float t3 = wave_sum(ss[r]);
-      q = lane == r ? t3 : q;
-    }
+  int64_t token = 0;
+  if constexpr (EPI == EPI_QKV) {
+    if (slot >= 0 && slot < kv_capacity(a.kv)) token = kv_token_offset(a.kv, m / a.Rseq, slot);
   }
-  if (lane >= rows) return;
-  const int m = r0 + lane;
+  // (all rows' epilogues side by side)
+  float y = wave_sums(acc, lane), y2 = 0.f, q = 0.f;
+  if constexpr (PAIR) y2 = wave_sums(acc2, lane);
+  if (a.gain) q = wave_sums(ss, lane);
+  if (!ends) return;
   if (a.gain) {
     const float inv = 1.0f / sqrtf(q / (float)K + a.eps);
     y *= inv;
@@ -435,9 +476,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   } else if constexpr (EPI == EPI_QKV) {
     const int hd = a.kv.head_dim, KVH = a.kv.n_kv_heads, H = a.n_heads;
     if (head < H + KVH) {  // q and k heads are rotated
-      const float2 cs = a.rope[(int64_t)m * (hd >> 1) + i];
-      const float t = y * cs.x - y2 * cs.y;
-      y2 = y2 * cs.x + y * cs.y;
+      const float t = fmaf(y, cs.x, -(y2 * cs.y));
+      y2 = fmaf(y2, cs.x, y * cs.y);
       y = t;
     }
     if (head < H) {
@@ -445,20 +485,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
       a.Y[(int64_t)m * a.ldy + n2] = y2;
       return;
     }
-    const int slot = a.slot[m];
     if (slot < 0) return;
     if (slot >= kv_capacity(a.kv)) {
       atomicOr(a.status, (uint32_t)ST_KV_CAP);
       return;
     }
     const bool is_k = head < H + KVH;
-    float* const dst = (float*)(is_k ? a.kv.k : a.kv.v) + (int64_t)a.layer * a.kv.layer_stride + kv_token_offset(a.kv, m / a.Rseq, slot) +
+    float* const dst = (float*)(is_k ? a.kv.k : a.kv.v) + (int64_t)a.layer * a.kv.layer_stride + token +
                        (int64_t)(head - (is_k ? H : H + KVH)) * hd + i;
     dst[0] = y;
     dst[hd >> 1] = y2;
   } else {
-    float* const out = a.Y + (int64_t)m * a.ldy + n;
-    *out = a.accumulate ? (*out + y) : y;
+    a.Y[(int64_t)m * a.ldy + n] = a.accumulate ? before + y : y;
   }
 }
 

@@ -176,6 +176,13 @@ def test_gemm_fp32_matches_float64(R, N, K):
     _gemm_case(mb, R, N, K, 0, seed=R + N + K)
 
 
+@pytest.mark.parametrize("R,N,K,ldy", [(1, 5, 8, 7), (3, 33, 260, 33), (8, 64, 256, 64), (11, 30, 44, 32),      # eight rows per wave
+                                       (1, 2049, 1028, 2050), (3, 4097, 516, 4097), (13, 2050, 1024, 2052)])      # one, four, eight and a remainder
+def test_gemm_fp32_accumulates(R, N, K, ldy):
+    """Each row's sum has to meet its own old value in the lane that ends with it."""
+    _gemm_case(_mb(), R, N, K, 0, seed=R * 7 + N, accumulate=True, ldy=ldy)
+
+
 @pytest.mark.parametrize("rows,V,top_k,top_p", [(37, 32000, 10, 0.9), (5, 1000, 10, 0.9), (3, 7, 10, 0.9), (9, 4099, 16, 0.5), (4, 32000, 1, 0.9), (3, 40001, 10, 0.9),
                                                 (6, 2048, 10, 1.0)])
 def test_warp_rows_matches_oracle(rows, V, top_k, top_p):
