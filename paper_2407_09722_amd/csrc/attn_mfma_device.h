@@ -213,10 +213,15 @@ __device__ __forceinline__ void attn_merge_row(const float* __restrict__ pp, int
   attn_store<COH, DPL * 2>(out + act_offset(ncg, rows_all, K, 1, arow, ak), &lo);
 }
 
+// m * scale, rounded: never part of a fused multiply-add, so that everybody who uses it uses the same number
+__device__ __forceinline__ float attn_scaled(float m, float scale) {
+#pragma clang fp contract(off)
+  return m * scale;
+}
 // Visibility, running softmax per row and the probabilities as operands of the second product, for the scores s2 of NB * 16 keys from
 // key0 on: lane (sg4, row) holds keys blk * 16 + sg4 * 4 + i.  Keys below `all` are seen by every row of the wave; rmask: the
-// speculative keys (from len on) a row sees, CAUSAL: the first key it does not see.  m_run: the maximum a row's probabilities refer to,
-// the same in the row's four lanes; l_run: the sum of the lane's own probabilities.
+// speculative keys (from len on) a row sees, CAUSAL: the first key it does not see.  m_run: the scaled maximum a row's probabilities
+// refer to, the same in the row's four lanes; l_run: the sum of the lane's own probabilities.
 template <int RG, int NB, int DB, bool CAUSAL>
 __device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const unsigned long long (&rmask)[RG], float (&m_run)[RG], float (&l_run)[RG],
                                              attn_floatx4 (&acc)[RG][DB], half8 (&ph)[RG][NB / 2], half8 (&pl)[RG][NB / 2], float scale, int key0, int len,
@@ -242,7 +247,6 @@ __device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const u
   }
   // The reference of a row follows its maximum only when some row's scores have outgrown theirs by ATTN_SLACK octaves: until then
   // probabilities may be that much above 1, which costs no precision, nothing is rescaled and the row's lanes exchange nothing.
-  const float slack = ATTN_SLACK / scale;
   float tmax[RG];
   bool grown = false;
 #pragma unroll
@@ -250,13 +254,13 @@ __device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const u
     tmax[rg] = s2[rg][0][0];
 #pragma unroll
     for (int e = 1; e < NB * 4; ++e) tmax[rg] = fmaxf(tmax[rg], s2[rg][e >> 2][e & 3]);
-    grown |= tmax[rg] > m_run[rg] + slack;  // (from minus infinity: any key)
+    grown |= fmaf(tmax[rg], scale, -m_run[rg]) > ATTN_SLACK;  // (from minus infinity: any key)
   }
   if (__any(grown)) {
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
-      const float m_new = fmaxf(m_run[rg], xmax<32>(xmax<16>(tmax[rg])));
-      const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run[rg] - m_new) * scale);
+      const float m_new = fmaxf(m_run[rg], attn_scaled(xmax<32>(xmax<16>(tmax[rg])), scale));
+      const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run[rg] - m_new);  // of the references the probabilities were formed with
       m_run[rg] = m_new;
       l_run[rg] *= alpha;
 #pragma unroll
@@ -267,7 +271,7 @@ __device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const u
   }
 #pragma unroll
   for (int rg = 0; rg < RG; ++rg) {
-    const float mc = m_run[rg] == -INFINITY ? 0.f : m_run[rg] * scale;  // a row that has seen no key yet: all its probabilities are zero
+    const float mc = m_run[rg] == -INFINITY ? 0.f : m_run[rg];  // a row that has seen no key yet: all its probabilities are zero
     typedef float floatx8_t __attribute__((ext_vector_type(8)));
 #pragma unroll
     for (int hb = 0; hb < NB / 2; ++hb) {
@@ -487,7 +491,7 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
     }
   }
   __syncthreads();
-  float m_run[NRG], l_run[NRG];  // of row rg*16 + srow: reference maximum (the same in the four key groups), sum over the lane's own keys
+  float m_run[NRG], l_run[NRG];  // of row rg*16 + srow: scaled reference maximum (the same in the four key groups), sum over the lane's own keys
   attn_floatx4 acc[NRG][DB];     // O^T: dims db*16 + sg4*4 + i of row rg*16 + srow
 #pragma unroll
   for (int rg = 0; rg < NRG; ++rg) {
@@ -583,7 +587,7 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
     for (int rg = 0; rg < NRG; ++rg) {
       l_run[rg] = xsum<32>(xsum<16>(l_run[rg]));
       if (sg4 == 0) {
-        sm.m[wslot][rg * 16 + srow] = m_run[rg] * scale;
+        sm.m[wslot][rg * 16 + srow] = m_run[rg];
         sm.l[wslot][rg * 16 + srow] = l_run[rg];
       }
     }

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(HD == 1
   };
   if (n_my > 0) request(0);
 
-  float m_run[RG], l_run[RG];  // of row rg * 16 + srow: reference maximum (the same in the four key groups), sum over the lane's own keys
+  float m_run[RG], l_run[RG];  // of row rg * 16 + srow: scaled reference maximum (the same in the four key groups), sum over the lane's own keys
   attn_floatx4 acc[RG][DB];    // O^T: dims db * 16 + sg4 * 4 + i of row rg * 16 + srow
 #pragma unroll
   for (int rg = 0; rg < RG; ++rg) {
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(HD == 1
         *(float2*)(pp + 2 + db * 16 + sg4 * 4) = make_float2(acc[rg][db][0], acc[rg][db][1]);
         *(float2*)(pp + 2 + db * 16 + sg4 * 4 + 2) = make_float2(acc[rg][db][2], acc[rg][db][3]);
       }
-      if (sg4 == 0) *(float2*)pp = make_float2(m_run[rg] * scale, l_run[rg]);
+      if (sg4 == 0) *(float2*)pp = make_float2(m_run[rg], l_run[rg]);
     }
   }
 }

@@ -1,0 +1,99 @@
+"""Attention of bf16 models on its own: a model of one layer whose logits are the attention output, over a cache that the test writes."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+QUERY = 2048                       # the large component of every query; the other one is 1
+
+
+def _model(heads, kv_heads, hd):
+    """Every query is (.., 1, 2048, 0 ..): the two components turn by less than 1e-20 at any position.  New tokens' keys and values are zero; the
+    attention output is added to a hidden state of ones and read through a unit matrix."""
+    d = heads * hd
+    shape = si.ModelShape(1, d, heads, kv_heads, hd, 32, d, "bf16", rms_eps=0.0, rope_theta=1e30)
+    zero = lambda *n: np.zeros(n, np.float32)
+    qkv, eye = zero(shape.qkv_rows, d), np.eye(d, dtype=np.float32)
+    half = hd // 2
+    for h in range(heads):
+        qkv[h * hd + half - 1, 0], qkv[h * hd + half - 2, 0] = QUERY, 1
+    w = {"embed": np.ones((d, d), np.float32), "L0.w_qkv": qkv, "L0.w_o": eye, "L0.w_gu": zero(64, d), "L0.w_d": zero(d, 32), "unembed": eye}
+    w = {k: si.f32_to_bf16_bits(v) for k, v in w.items()}
+    w.update({k: np.ones(d, np.float32) for k in ("L0.g_attn", "L0.g_ffn", "g_final")})
+    return shape, w
+
+
+def _run(heads, kv_heads, hd, batch, gamma, beam, lens, keys, values, fused_pass):
+    """Logits [batch][rows][heads * hd] over a cache of lens[s] tokens, keys / values [batch][n][kv_heads][hd]; every row sees itself alone
+    beside them."""
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    shape, w = _model(heads, kv_heads, hd)
+    m = DeviceModel(shape, w, DEV)
+    n = keys.shape[1]
+    eng = Engine(m, m, batch=batch, gamma=gamma, beam=beam, mode="mmtad", max_context=n + 64, prefill_rows=1, fused_pass=fused_pass)
+    at = eng.tkv.page_table.cpu().numpy()[:, np.arange(n) // 16] * 16 + np.arange(n) % 16
+    for to, x in ((eng.tkv.k, keys), (eng.tkv.v, values)):
+        flat = to.view(-1, kv_heads, hd)
+        flat[torch.from_numpy(at.astype(np.int64)).to(DEV)] = torch.from_numpy(x.astype(np.float16)).to(DEV)
+    eng.tkv.len.copy_(torch.tensor(lens, dtype=torch.int32))
+    M = eng.M
+    eng.t_parent.fill_(0)
+    eng.t_depth.fill_(1)
+    eng.t_mask.copy_(torch.from_numpy(np.left_shift(np.uint64(1), np.arange(M, dtype=np.uint64)).astype(np.int64)).expand(batch, M))
+    eng.verify_phase()
+    torch.cuda.synchronize()
+    out = eng.logits.cpu().numpy().astype(np.float64)
+    eng.close()
+    return out
+
+
+def _expected(heads, kv_heads, hd, lens, keys, values, rows):
+    out = []
+    for s, n in enumerate(lens):
+        k, v = keys[s, :n].astype(np.float64), values[s, :n].astype(np.float64)
+        score = (k[:, :, hd // 2 - 1] * QUERY + k[:, :, hd // 2 - 2]) / np.sqrt(hd)                  # [n][kv_heads]
+        score = np.concatenate([score, np.zeros((1, kv_heads))])                                     # the row itself: key and value zero
+        p = np.exp(score - score.max(0))
+        o = np.einsum("nh,nhd->hd", p[:-1], v) / p.sum(0)[:, None]
+        h = 1 + np.repeat(o, heads // kv_heads, 0).reshape(-1)
+        out.append(np.tile(h / np.sqrt((h * h).mean()), (rows, 1)))
+    return np.stack(out)
+
+
+# the attention output is kept as two bfloat16 terms, 2^-17 of it (it lies within the values, 4.5 at most); the sums in float32 add less than a tenth of that
+TOLERANCE = 4.5 * 2**-17
+
+
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,gamma,beam,n,fused_pass", [
+    (64, 4, 4, 1, 1, 1, 9000, 0),      # key splits merged in the attention launch
+    (64, 8, 8, 32, 3, 2, 2000, 0),     # one row group
+    (128, 8, 8, 32, 3, 2, 2000, 0),
+    (64, 16, 8, 16, 4, 3, 2000, 0),    # 26 (query head, row) pairs a KV head: two row groups
+    (128, 16, 8, 16, 4, 3, 2000, 0),
+    (64, 8, 2, 2, 4, 4, 2000, 0),      # 68: waves that share their tiles
+    (128, 6, 2, 2, 4, 3, 2000, 0),     # 39
+    (64, 4, 4, 1, 3, 2, 9000, 2),      # the one-launch pass
+    (128, 4, 4, 2, 3, 1, 9000, 2),
+])
+def test_scores_in_the_hundred_thousands(hd, heads, kv_heads, batch, gamma, beam, n, fused_pass):
+    """The maximum a row's probabilities refer to moves while keys of hundreds of thousands of octaves are added up: what was added before has
+    to be scaled by the very difference of the two references.  (Scores are whole numbers below 2^24, exact in float32.)"""
+    print(f"scores hd {hd} heads {heads}/{kv_heads} batch {batch} rows {1 + gamma * beam} n {n} fused {fused_pass}", flush=True)
+    rows = 1 + gamma * beam
+    r = np.random.default_rng(hd + heads + rows)
+    keys, values = np.zeros((batch, n, kv_heads, hd)), r.standard_normal((batch, n, kv_heads, hd)).astype(np.float16)
+    half, place = hd // 2, np.arange(n)[None, :, None]
+    step = int(np.ceil(8.5 * np.log(2) * np.sqrt(hd)))                                               # a little more than eight octaves
+    rises = (place > 0.6 * n) & (r.random((batch, n, kv_heads)) < 1 / 48)
+    again = (place > 0.85 * n) & (r.random((batch, n, kv_heads)) < 1 / 96)
+    keys[..., half - 1] = 2000 + r.integers(0, 2, (batch, 1, kv_heads))
+    keys[..., half - 2] = r.integers(0, 4, (batch, n, kv_heads)) + step * (rises * 1 + again * 1)
+    lens = [n - 7 * s for s in range(batch)]
+    got = _run(heads, kv_heads, hd, batch, gamma, beam, lens, keys, values, fused_pass)
+    want = _expected(heads, kv_heads, hd, lens, keys, values, rows)
+    err = np.abs(got - want).max()
+    print(f"largest error {err:.2e}", flush=True)
+    assert err < TOLERANCE
