@@ -221,9 +221,9 @@ __device__ __forceinline__ float attn_scaled(float m, float scale) {
 // Visibility, running softmax per row and the probabilities as operands of the second product, for the scores s2 of NB * 16 keys from
 // key0 on: lane (sg4, row) holds keys blk * 16 + sg4 * 4 + i.  Keys below `all` are seen by every row of the wave; rmask: the
 // speculative keys (from len on) a row sees, CAUSAL: the first key it does not see.  m_run: the scaled maximum a row's probabilities
-// refer to, the same in the row's four lanes; l_run: the sum of the lane's own probabilities.
+// refer to, m_top: the score up to which it stays, the same in the row's four lanes; l_run: the sum of the lane's own probabilities.
 template <int RG, int NB, int DB, bool CAUSAL>
-__device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const unsigned long long (&rmask)[RG], float (&m_run)[RG], float (&l_run)[RG],
+__device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const unsigned long long (&rmask)[RG], float (&m_run)[RG], float (&m_top)[RG], float (&l_run)[RG],
                                              attn_floatx4 (&acc)[RG][DB], half8 (&ph)[RG][NB / 2], half8 (&pl)[RG][NB / 2], float scale, int key0, int len,
                                              int all, int kend, int sg4) {
   // keys inside the committed context (all but the last tile or two) are visible to every row: no mask
@@ -247,6 +247,7 @@ __device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const u
   }
   // The reference of a row follows its maximum only when some row's scores have outgrown theirs by ATTN_SLACK octaves: until then
   // probabilities may be that much above 1, which costs no precision, nothing is rescaled and the row's lanes exchange nothing.
+  const float slack = ATTN_SLACK / scale;
   float tmax[RG];
   bool grown = false;
 #pragma unroll
@@ -254,14 +255,15 @@ __device__ __forceinline__ void attn_softmax(attn_floatx4 (&s2)[RG][NB], const u
     tmax[rg] = s2[rg][0][0];
 #pragma unroll
     for (int e = 1; e < NB * 4; ++e) tmax[rg] = fmaxf(tmax[rg], s2[rg][e >> 2][e & 3]);
-    grown |= fmaf(tmax[rg], scale, -m_run[rg]) > ATTN_SLACK;  // (from minus infinity: any key)
+    grown |= tmax[rg] > m_top[rg];  // (from minus infinity: any key)
   }
   if (__any(grown)) {
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
-      const float m_new = fmaxf(m_run[rg], attn_scaled(xmax<32>(xmax<16>(tmax[rg])), scale));
+      const float m_tile = xmax<32>(xmax<16>(tmax[rg])), m_new = fmaxf(m_run[rg], attn_scaled(m_tile, scale));
       const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run[rg] - m_new);  // of the references the probabilities were formed with
       m_run[rg] = m_new;
+      m_top[rg] = fmaxf(m_top[rg], m_tile + slack);
       l_run[rg] *= alpha;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -491,11 +493,11 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
     }
   }
   __syncthreads();
-  float m_run[NRG], l_run[NRG];  // of row rg*16 + srow: scaled reference maximum (the same in the four key groups), sum over the lane's own keys
+  float m_run[NRG], m_top[NRG], l_run[NRG];  // of row rg*16 + srow: scaled reference maximum, score up to which it stays (the same in the four key groups), sum over the lane's own keys
   attn_floatx4 acc[NRG][DB];     // O^T: dims db*16 + sg4*4 + i of row rg*16 + srow
 #pragma unroll
   for (int rg = 0; rg < NRG; ++rg) {
-    m_run[rg] = -INFINITY;
+    m_run[rg] = m_top[rg] = -INFINITY;
     l_run[rg] = 0.f;
 #pragma unroll
     for (int db = 0; db < DB; ++db) acc[rg][db] = attn_floatx4{0.f, 0.f, 0.f, 0.f};
@@ -543,7 +545,7 @@ __device__ __forceinline__ int tree_attn_item(MfmaAttnSmem<HD, NRG, AW, DS>& sm,
 
     // visibility, scale, running softmax per row; probabilities become the B operand of the second product
     half8 ph[NRG][1], pl[NRG][1];
-    attn_softmax<NRG, 2, DB, false>(s2, rmask, m_run, l_run, acc, ph, pl, scale, ti * ATK, len, len, ktot, sg4);
+    attn_softmax<NRG, 2, DB, false>(s2, rmask, m_run, m_top, l_run, acc, ph, pl, scale, ti * ATK, len, len, ktot, sg4);
 
     // O^T += V^T P^T: contraction slot e of key group sg4 is key (e/4)*16 + sg4*4 + e%4, as the scores came out
 #pragma unroll

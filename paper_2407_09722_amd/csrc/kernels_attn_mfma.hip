@@ -198,11 +198,11 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(HD == 1
   };
   if (n_my > 0) request(0);
 
-  float m_run[RG], l_run[RG];  // of row rg * 16 + srow: scaled reference maximum (the same in the four key groups), sum over the lane's own keys
+  float m_run[RG], m_top[RG], l_run[RG];  // of row rg * 16 + srow: scaled reference maximum, score up to which it stays (the same in the four key groups), sum over the lane's own keys
   attn_floatx4 acc[RG][DB];    // O^T: dims db * 16 + sg4 * 4 + i of row rg * 16 + srow
 #pragma unroll
   for (int rg = 0; rg < RG; ++rg) {
-    m_run[rg] = -INFINITY;
+    m_run[rg] = m_top[rg] = -INFINITY;
     l_run[rg] = 0.f;
 #pragma unroll
     for (int db = 0; db < DB; ++db) acc[rg][db] = attn_floatx4{0.f, 0.f, 0.f, 0.f};
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(HD == 1
         }
       }
     half8 ph[RG][NB / 2], pl[RG][NB / 2];
-    attn_softmax<RG, NB, DB, CAUSAL>(s2, rmask, m_run, l_run, acc, ph, pl, scale, key0, len, all, kend, sg4);
+    attn_softmax<RG, NB, DB, CAUSAL>(s2, rmask, m_run, m_top, l_run, acc, ph, pl, scale, key0, len, all, kend, sg4);
     // O^T += V^T P^T
 #pragma unroll
     for (int db = 0; db < DB; ++db)
