@@ -21,19 +21,52 @@ namespace {
 
 constexpr int FEW_ROWS = 64;  // (sequence, query head, row) triples of a pass that merges its key splits in the attention launch
 
+int device_cus() {
+  static const int n_cus = [] {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
+    return cus > 0 ? cus : 256;
+  }();
+  return n_cus;
+}
+
+// A workgroup's place among key splits, KV heads, sequences (and chunks of rows, the slowest).  Workgroups go to the XCDs in turn, and a sequence
+// may use only the first few of the splits a launch offers.  Where the launch offers no more than one workgroup a compute unit, the splits
+// of an item are neighbours.  Where it offers more (spread), those in use would crowd on some XCDs (offered 8, in use 4: on half of them), so
+// the splits run slowest, and the KV heads are turned by sequence and split: a head's rows lie at a fixed place in every token of the cache, and
+// an XCD that reads all heads in turn is the faster one.  (With one workgroup a compute unit and one split that writes its output itself,
+// turned heads were slower, 32 x 5 rows x 64 heads on 8 x 128, 60 keys 217 / 224.  With few items their chunks, which
+// share keys, would go to different XCDs: 33 rows x 16 heads on 2 x 64, 4100 keys 168 / 176.)
+// us of a pass of four narrow layers, splits fastest / slowest / slowest and heads turned: 8 x one row x 12 heads x 64, 2064 keys 163 / 141 / 141;
+// 4 x one row x 40 heads x 64, 1100 keys 163 / 146 / 144, 2064 keys 211 / 197 / 186; 4 x 33 rows x 40 heads x 128, 300 keys 275 / 263 / 262; 8 x one
+// row x 40 heads x 128, 2064 keys 432 / - / 410.
+struct AttnPlace {
+  int split, g, seq, chunk;
+};
+__host__ __device__ constexpr AttnPlace attn_place(bool spread, int KVH, int x, int y, int z) {  // grid: attn_grid()
+  const int split = spread ? z : x, head = spread ? x : y, seq = spread ? y : z;
+  return {split, spread ? (head + seq + split) % KVH : head, seq, 0};
+}
+bool spread_splits(int offered, int items) { return 4 * items > device_cus() && offered * items > device_cus(); }
+dim3 attn_grid(bool spread, int gx, int KVH, int B) { return spread ? dim3(KVH, B, gx) : dim3(gx, KVH, B); }
+__host__ __device__ constexpr AttnPlace rows_place(int splits, int KVH, int B, int x, int y) {  // splits: 0 if spread; grid: rows_grid()
+  const int split = splits ? x % splits : y, item = splits ? x / splits : x, seq = item / KVH % B;
+  return {split, (splits ? item : item + seq + split) % KVH, seq, item / (KVH * B)};
+}
+dim3 rows_grid(bool spread, int gx, int items) { return spread ? dim3(items, gx) : dim3(items * gx); }
+
 template <int HD, int NRG, int AW>
 __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(2))) void tree_attn_mfma_kernel(const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer,
-                                                               int R, int n_heads, int n_chunks, float scale, float* __restrict__ partial,
-                                                               int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg) {
+                                                               int B, int R, int n_heads, float scale, float* __restrict__ partial,
+                                                               int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg, bool spread) {
   using Smem = MfmaAttnSmem<HD, NRG, AW>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   Smem& sm = *reinterpret_cast<Smem*>(smem_raw);
   // the kernels with registers to spare (head dim 64, or a single row group) hold two register sets for K and V
   constexpr int NSET = (HD == 64 || NRG == 1) ? 2 : 1;
-  const int g = (int)blockIdx.y / n_chunks, chunk = (int)blockIdx.y % n_chunks;
-  tree_attn_item<HD, NRG, AW, NSET, AW * 64, false>(sm, q, q_stride, rd, kv, layer, (int)gridDim.z, R, n_heads, n_chunks, scale, partial,
-                                                              n_splits, out, want_splits, ncg, (int)blockIdx.x, g, chunk, (int)blockIdx.z,
-                                                              (int)threadIdx.x);
+  const AttnPlace at = attn_place(spread, kv.n_kv_heads, blockIdx.x, blockIdx.y, blockIdx.z);
+  tree_attn_item<HD, NRG, AW, NSET, AW * 64, false>(sm, q, q_stride, rd, kv, layer, B, R, n_heads, 1, scale, partial, n_splits, out, want_splits, ncg, at.split,
+                                                    at.g, 0, at.seq, (int)threadIdx.x);
 }
 
 // The same item for passes of few rows in all (small models): the key split that arrives last for an item merges its rows,
@@ -42,18 +75,19 @@ __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // counters: one zeroed word per item, left zeroed.  At most ATTN_WAVES rows an item.
 template <int HD>
 __global__ __launch_bounds__(ATTN_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2))) void tree_attn_few_kernel(
-    const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int R, int n_heads, float scale, float* __restrict__ partial, int n_splits,
-    bf16_t* __restrict__ out, int want_splits, int ncg, int* __restrict__ counters) {
+    const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int B, int R, int n_heads, float scale, float* __restrict__ partial, int n_splits,
+    bf16_t* __restrict__ out, int want_splits, int ncg, bool spread, int* __restrict__ counters) {
   __shared__ MfmaAttnSmem<HD, 1, ATTN_WAVES> sm;
   __shared__ int last_s;
-  const int B = gridDim.z, split = blockIdx.x, g = blockIdx.y, seq = blockIdx.z, t = threadIdx.x;
+  const AttnPlace at = attn_place(spread, kv.n_kv_heads, blockIdx.x, blockIdx.y, blockIdx.z);
+  const int split = at.split, g = at.g, seq = at.seq, t = threadIdx.x;
   const int eff = tree_attn_item<HD, 1, ATTN_WAVES, 2, ATTN_WAVES * 64, true>(sm, q, q_stride, rd, kv, layer, B, R, n_heads, 1, scale, partial, n_splits, out,
                                                                             want_splits, ncg, split, g, 0, seq, t);
   if (eff == 1 || split >= eff) return;  // uniform: the item wrote its output itself, or there was no such split
   __builtin_amdgcn_s_waitcnt(0);  // the partial results have been acknowledged
   __syncthreads();
   if (t == 0) {
-    int* const c = counters + seq * gridDim.y + g;
+    int* const c = counters + seq * kv.n_kv_heads + g;
     const int prev = __hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     last_s = prev == eff - 1;
     if (prev == eff - 1) __hip_atomic_store(c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // clean for the next launch
@@ -117,8 +151,9 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(HD == 1
   // (all kernel arguments at once; left to itself the compiler fetches them in rounds, each a trip to memory)
   asm volatile("" ::"s"(q), "s"(q_stride), "s"(rd.nspec), "s"(rd.mask), "s"(kv.k), "s"(kv.v), "s"(kv.page_table), "s"(kv.len), "s"(kv.page_size), "s"(kv.max_pages),
                "s"(kv.n_pages), "s"(kv.n_kv_heads), "s"(kv.layer_stride), "s"(layer), "s"(R), "s"(n_heads), "s"(n_splits), "s"(n_chunks), "s"(splits));
-  const int split = blockIdx.x % splits, item = blockIdx.x / splits, KVH = kv.n_kv_heads, G = n_heads / KVH, g = item % KVH, seq = item / KVH % B;
-  const int rank = item / (KVH * B), chunk = CAUSAL ? n_chunks - 1 - rank : rank;  // a prompt's items that see the most keys first
+  const int KVH = kv.n_kv_heads, G = n_heads / KVH;
+  const AttnPlace at = rows_place(splits, KVH, B, blockIdx.x, blockIdx.y);
+  const int split = at.split, g = at.g, seq = at.seq, chunk = CAUSAL ? n_chunks - 1 - at.chunk : at.chunk;  // a prompt's items that see the most keys first
   const int pairs = G * R, pair0 = chunk * (RW * RG * 16), pair_end = min(pairs, pair0 + RW * RG * 16);  // pair p = query head p / R of the group, row p % R
   const int wp0 = pair0 + wave * (RG * 16), wp_end = min(pair_end, wp0 + RG * 16);                      // this wave's
   const bool rowless = wp0 >= pair_end;
@@ -322,15 +357,6 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(RowDesc rd, KvView kv, 
   attn_merge_row<HD, false>(pp, eff, out, ncg, B * R, n_heads * HD, seq * R + row, head, lane);
 }
 
-int device_cus() {
-  static const int n_cus = [] {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
-    return cus > 0 ? cus : 256;
-  }();
-  return n_cus;
-}
-
 // Key splits for `items` workgroups per split: enough workgroups to fill the machine once (twice and four times over measured no faster
 // at 512, 2048 and 4096 keys when once is an even fill).  An uneven fill (C5's target pass: 160 items x 2 splits on 256 compute
 // units) runs as long as the compute units that hold two workgroups; splits up to the number of resident slots shorten every workgroup
@@ -361,8 +387,9 @@ hipError_t run_rows(const float* q, int q_stride, const RowDesc& rd, const KvVie
   auto kern = tree_attn_rows_kernel<HD, RW, CAUSAL>;
   static_assert(Sh::LDS <= 64 * 1024, "needs no attribute");
   const int want = splits_wanted(items, 3), gx = widest_split(n_splits, want);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(gx * items)), dim3(RW * 64), Sh::LDS, s, q, q_stride, rd, kv, layer, B, R, n_heads, n_chunks,
-                     ATTN_LOG2E / sqrtf((float)HD), partial, n_splits, (bf16_t*)out, want, ncg, gx);
+  const bool spread = spread_splits(gx, items);
+  hipLaunchKernelGGL(kern, rows_grid(spread, gx, items), dim3(RW * 64), Sh::LDS, s, q, q_stride, rd, kv, layer, B, R, n_heads, n_chunks,
+                     ATTN_LOG2E / sqrtf((float)HD), partial, n_splits, (bf16_t*)out, want, ncg, spread ? 0 : gx);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || gx == 1) return e;  // one split: every workgroup wrote its output
   return run_merge<HD>(rd, kv, B, R, n_heads, partial, n_splits, want, out, ncg, CAUSAL, s);
@@ -372,33 +399,34 @@ template <int HD, int NRG, int AW>
 hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvView& kv, int layer, int B, int R, int n_heads, float* partial,
                     int n_splits, void* out, int ncg, hipStream_t s, int* counters = nullptr) {
   const int KVH = kv.n_kv_heads, G = n_heads / KVH;
-  const int n_chunks = (G * R + NRG * 16 - 1) / (NRG * 16);  // chunks of (query head, row) pairs per KV head
+  if (G * R > NRG * 16) return hipErrorInvalidValue;  // one item a KV head
   const float scale = ATTN_LOG2E / sqrtf((float)HD);
   auto kern = tree_attn_mfma_kernel<HD, NRG, AW>;
   constexpr size_t lds = sizeof(MfmaAttnSmem<HD, NRG, AW>);
   static const hipError_t attr = lds > 64 * 1024 ? hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
                                                  : hipSuccess;
   if (attr != hipSuccess) return attr;
-  const int items = KVH * n_chunks * B;
+  const int items = KVH * B;
   static const int per_cu = [&] {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)kern, AW * 64, lds) != hipSuccess) n = 1;
     return n > 0 ? n : 1;
   }();
   const int want = splits_wanted(items, per_cu), gx = widest_split(n_splits, want);
+  const bool spread = spread_splits(gx, items);
   if constexpr (NRG == 1) {
     // Six layers, us, two launches / one (rows = sequences x heads x rows each): 12 heads x 64, 12 rows, 256 / 2048 keys 164 / 153,
     // 179 / 171; 48 rows 170 / 159, 216 / 208; 32 heads x 64, 64 rows 218 / 198, 241 / 234.  Beyond, the last workgroups' merges
     // are no longer hidden: 96 rows, 2048 keys 252 / 261; 512 rows 292 / 315, 584 / 618.  Items of 8 rows (8 query heads on a key
     // head), two to a wave and few items to split the keys over: 2048 keys 204 / 211.
     if (counters && gx > 1 && B * n_heads * R <= FEW_ROWS && G * R <= ATTN_WAVES) {
-      hipLaunchKernelGGL((tree_attn_few_kernel<HD>), dim3(gx, KVH, B), dim3(AW * 64), 0, s, q, q_stride, rd, kv, layer, R, n_heads, scale, partial, n_splits,
-                         (bf16_t*)out, want, ncg, counters);
+      hipLaunchKernelGGL((tree_attn_few_kernel<HD>), attn_grid(spread, gx, KVH, B), dim3(AW * 64), 0, s, q, q_stride, rd, kv, layer, B, R, n_heads, scale,
+                         partial, n_splits, (bf16_t*)out, want, ncg, spread, counters);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL(kern, dim3(gx, KVH * n_chunks, B), dim3(AW * 64), lds, s, q, q_stride, rd, kv, layer, R, n_heads, n_chunks, scale,
-                     partial, n_splits, (bf16_t*)out, want, ncg);
+  hipLaunchKernelGGL(kern, attn_grid(spread, gx, KVH, B), dim3(AW * 64), lds, s, q, q_stride, rd, kv, layer, B, R, n_heads, scale, partial, n_splits,
+                     (bf16_t*)out, want, ncg, spread);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || gx == 1) return e;  // one split: every workgroup wrote its output
   return run_merge<HD>(rd, kv, B, R, n_heads, partial, n_splits, want, out, ncg, false, s);
@@ -436,3 +464,17 @@ hipError_t launch_attention_prompt(const float* q, int q_stride, const RowDesc& 
 }
 
 }  // namespace mtad
+
+// Host side only, for the tests: the (split, KV head, sequence, chunk of rows) of every workgroup of an attention launch, in the order they are
+// dispatched; at: 4 ints each.
+extern "C" void mtad_test_attention_places(int rows, int n_kv_heads, int chunks, int batch, int offered, int spread, int* at) {
+  using namespace mtad;
+  const int items = n_kv_heads * batch * chunks;
+  const dim3 g = rows ? rows_grid(spread != 0, offered, items) : attn_grid(spread != 0, offered, n_kv_heads, batch);
+  for (unsigned z = 0; z < g.z; ++z)
+    for (unsigned y = 0; y < g.y; ++y)
+      for (unsigned x = 0; x < g.x; ++x, at += 4) {
+        const AttnPlace p = rows ? rows_place(spread ? 0 : offered, n_kv_heads, batch, x, y) : attn_place(spread != 0, n_kv_heads, x, y, z);
+        at[0] = p.split, at[1] = p.g, at[2] = p.seq, at[3] = p.chunk;
+      }
+}
