@@ -133,11 +133,12 @@ struct RowsShape {
   static constexpr int GROUPS = RTK / KPI;    // requests for K (and as many for V) per tile
   static constexpr int TILE = RTK * HD * 2, SLOT = 2 * TILE;
   static constexpr int LDS = 2 * SLOT + 2 * TOK_TILES * RTK * 4;
+  static constexpr int WAVES = HD == 128 ? 3 : 4;  // per SIMD
   static constexpr int LOOK = (TOK_TILES * RTK + RW * 64 - 1) / (RW * 64);  // keys a thread looks up per block of tiles
 };
 
 template <int HD, int RW, bool CAUSAL>
-__global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(HD == 128 ? 3 : 4))) void tree_attn_rows_kernel(
+__global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(RowsShape<HD, RW>::WAVES))) void tree_attn_rows_kernel(
     const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int B, int R, int n_heads, int n_chunks, float scale,
     float* __restrict__ partial, int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg, int splits) {
   using Sh = RowsShape<HD, RW>;
@@ -358,14 +359,28 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(RowDesc rd, KvView kv, 
 }
 
 // Key splits for `items` workgroups per split: enough workgroups to fill the machine once (twice and four times over measured no faster
-// at 512, 2048 and 4096 keys when once is an even fill).  An uneven fill (C5's target pass: 160 items x 2 splits on 256 compute
-// units) runs as long as the compute units that hold two workgroups; splits up to the number of resident slots shorten every workgroup
-// instead (41 rows x 40 heads x 4 sequences at 4096 keys: 99 -> 80 us with 3 splits).
+// at 512, 2048 and 4096 keys when once is an even fill).  An uneven fill (160 items x 2 splits on 256 compute units) runs as long as the
+// compute units that hold two workgroups: then the splits with which a compute unit of n = 2 .. per_cu workgroups holds the least of an item,
+// n / splits; two workgroups get a tenth more done together than three or four.  us of a pass of four narrow layers (4 sequences) with the
+// splits of 2 / 3 / 4 workgroups: 40 heads x 41 rows x 128 (160 items) 3 / 4 splits, 2064 keys 381 / 398, 4100 keys 517 / 531; 48 heads x 33 rows x
+// 128 2 / 4 / 5 splits, 4100 keys 587 / 567 / 583; 24 heads x 57 rows x 128 5 / 8, 4100 keys 403 / 426; one row x 40 heads x 64, 2 sequences, 6 / 9 / 12,
+// 4100 keys 179 / 185 / 182, 8 sequences 1 / 2 / 3, 2064 keys 286 / 267 / 256.
 int splits_wanted(int items, int per_cu) {
   const int n_cus = device_cus(), fill = items >= n_cus ? 1 : (n_cus + items - 1) / items;
-  const int more = (items * fill > n_cus && per_cu >= 2) ? (n_cus * per_cu) / items : 0;
+  int more = 0;
+  float least = INFINITY;
+  for (int n = 2; items * fill > n_cus && n <= per_cu; ++n) {
+    const int splits = n_cus * n / items;
+    const float share = (n == 2 ? 0.9f : 1.f) * n / splits;
+    if (splits > 0 && share < least) least = share, more = splits;
+  }
   return (fill < 255 ? fill : 255) | (more < 255 ? more : 255) << 8;
 }
+// Most workgroups a compute unit.  Items of one or two row groups: those that are resident, but 4 for head dim 64 and one row group (3
+// resident; 8 sequences above).  Items of many rows: 3; up to 5 are resident, and no faster (5 x 41 rows x 40 heads x 128, 2064 keys, 2 / 3 / 4
+// workgroups 422 / 424 / 453; 4 x 33 rows x 48 heads x 64, 4100 keys 405 / 374 / 386).
+constexpr int item_per_cu(int hd, int nrg) { return hd == 64 && nrg == 1 ? 4 : 2; }
+constexpr int ROWS_PER_CU = 3;
 int widest_split(int n_splits, int want) {
   const int widest = (want & 255) > (want >> 8) ? want & 255 : want >> 8;
   return n_splits < widest ? n_splits : widest;
@@ -386,7 +401,7 @@ hipError_t run_rows(const float* q, int q_stride, const RowDesc& rd, const KvVie
   const int KVH = kv.n_kv_heads, G = n_heads / KVH, n_chunks = (G * R + RW * 16 - 1) / (RW * 16), items = KVH * n_chunks * B;
   auto kern = tree_attn_rows_kernel<HD, RW, CAUSAL>;
   static_assert(Sh::LDS <= 64 * 1024, "needs no attribute");
-  const int want = splits_wanted(items, 3), gx = widest_split(n_splits, want);
+  const int want = splits_wanted(items, ROWS_PER_CU), gx = widest_split(n_splits, want);
   const bool spread = spread_splits(gx, items);
   hipLaunchKernelGGL(kern, rows_grid(spread, gx, items), dim3(RW * 64), Sh::LDS, s, q, q_stride, rd, kv, layer, B, R, n_heads, n_chunks,
                      ATTN_LOG2E / sqrtf((float)HD), partial, n_splits, (bf16_t*)out, want, ncg, spread ? 0 : gx);
@@ -407,12 +422,7 @@ hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvVie
                                                  : hipSuccess;
   if (attr != hipSuccess) return attr;
   const int items = KVH * B;
-  static const int per_cu = [&] {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)kern, AW * 64, lds) != hipSuccess) n = 1;
-    return n > 0 ? n : 1;
-  }();
-  const int want = splits_wanted(items, per_cu), gx = widest_split(n_splits, want);
+  const int want = splits_wanted(items, item_per_cu(HD, NRG)), gx = widest_split(n_splits, want);
   const bool spread = spread_splits(gx, items);
   if constexpr (NRG == 1) {
     // Six layers, us, two launches / one (rows = sequences x heads x rows each): 12 heads x 64, 12 rows, 256 / 2048 keys 164 / 153,
@@ -477,4 +487,12 @@ extern "C" void mtad_test_attention_places(int rows, int n_kv_heads, int chunks,
         const AttnPlace p = rows ? rows_place(spread ? 0 : offered, n_kv_heads, batch, x, y) : attn_place(spread != 0, n_kv_heads, x, y, z);
         at[0] = p.split, at[1] = p.g, at[2] = p.seq, at[3] = p.chunk;
       }
+}
+// Host side only, for the tests: the key splits a launch offers and its items, for `pairs` (query head, row) pairs on a KV head.  They hold
+// for 256 compute units where there is no device.
+extern "C" int mtad_test_attention_splits(int head_dim, int pairs, int n_kv_heads, int batch, int causal, int n_splits, int* items) {
+  using namespace mtad;
+  const bool rows = causal || pairs > 32, four = causal || pairs > 48;
+  *items = n_kv_heads * batch * (rows ? (pairs + (four ? 63 : 47)) / (four ? 64 : 48) : 1);
+  return widest_split(n_splits, splits_wanted(*items, rows ? ROWS_PER_CU : item_per_cu(head_dim, pairs > 16 ? 2 : 1)));
 }

@@ -29,3 +29,30 @@ def test_every_item_has_its_workgroups_and_the_xcds_share_them(rows, chunks, kv_
         for used in range(1, offered + 1):                               # the splits that sequences of one length make use of
             share = np.bincount(np.flatnonzero(at[:, 0] < used) % XCDS, minlength=XCDS)
             assert share.max() <= -(-items * used // XCDS)
+
+
+def _splits(hd, pairs, kv_heads, batch, causal=0, n_splits=32):
+    items = C.c_int()
+    return mb.lib().mtad_test_attention_splits(hd, pairs, kv_heads, batch, causal, n_splits, C.byref(items)), items.value
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("pairs", [1, 16, 17, 33, 49, 64, 130])
+def test_an_uneven_fill_is_split_evenly(hd, pairs):
+    """The compute unit with the most work holds at most a tenth and a rounding more of an item than with the best number of splits."""
+    most = 2 if pairs == 17 or pairs <= 16 and hd == 128 else 4 if pairs <= 16 else 3
+    for batch in (1, 2, 3, 4, 5, 8, 16):
+        for kv_heads in (1, 2, 4, 5, 8, 12, 20, 24, 32, 40, 48, 64):
+            splits, items = _splits(hd, pairs, kv_heads, batch)
+            assert 1 <= splits <= 32
+            if items * -(-CUS // items) == CUS or items < 16:
+                continue
+            load = lambda s: -(-items * s // CUS) / s
+            assert load(splits) <= 1.12 * min(load(s) for s in range(1, max(1, CUS * most // items) + 1)), (batch, kv_heads, splits, items)
+
+
+@pytest.mark.parametrize("hd,pairs,kv_heads,batch,splits", [(128, 41, 40, 4, 3), (64, 41, 40, 4, 3), (128, 41, 40, 5, 2), (128, 33, 48, 4, 4), (128, 57, 24, 4, 5), (64, 1, 40, 2, 6),
+                                                            (64, 1, 40, 8, 3), (64, 9, 12, 8, 5), (128, 5, 32, 4, 2), (128, 5, 32, 8, 1)])
+def test_measured_numbers_of_splits(hd, pairs, kv_heads, batch, splits):
+    assert _splits(hd, pairs, kv_heads, batch)[0] == splits
+    assert _splits(hd, pairs, kv_heads, batch, n_splits=2)[0] == min(2, splits)
