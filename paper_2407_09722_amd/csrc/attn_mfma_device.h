@@ -109,18 +109,19 @@ __device__ __forceinline__ int token_index(const KvView& kv, int seq, int pos) {
 // exchange only if it gives every wave a tile (measured at 512 and 2048 keys).  want_splits = fill_splits +
 // (more_splits << 8): fill_splits give every compute unit a workgroup; more_splits, offered when that leaves some
 // compute units with two workgroups and the rest with one, fill every resident slot and are taken only where every
-// wave still gets four tiles.
+// wave still gets four tiles.  Bits 16 on: the tiles below which a sequence is not split at all.
 constexpr int ATTN_WAVES = 4;
 __device__ __forceinline__ int attn_keys(const KvView& kv, const RowDesc& rd, int seq, bool causal = false) {
   const int nspec = max(0, causal ? rd.nspec[seq] : min(rd.nspec[seq], 64));
   return min(kv.len[seq] + nspec, kv_capacity(kv));
 }
-__device__ __forceinline__ int attn_splits(int ktot, int n_splits, int want_splits) {
+__host__ __device__ __forceinline__ int attn_splits(int ktot, int n_splits, int want_splits) {
   // from two splits on, one more for a remainder: it keeps every wave at one tile (516 keys: 5 splits of 4 tiles
   // instead of 4 splits of 5, whose first wave runs a second tile after the first)
   constexpr int WK = ATTN_WAVES * ATK;
+  if (ktot < (want_splits >> 16) * ATK) return 1;
   const int fill = min(want_splits & 255, ktot < 2 * WK ? 1 : (ktot + WK - 1) / WK);
-  const int more = min(want_splits >> 8, ktot / (4 * ATTN_WAVES * ATK));
+  const int more = min(want_splits >> 8 & 255, ktot / (4 * ATTN_WAVES * ATK));
   return max(1, min(n_splits, max(fill, more)));
 }
 

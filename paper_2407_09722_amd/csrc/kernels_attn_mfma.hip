@@ -365,7 +365,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(RowDesc rd, KvView kv, 
 // splits of 2 / 3 / 4 workgroups: 40 heads x 41 rows x 128 (160 items) 3 / 4 splits, 2064 keys 381 / 398, 4100 keys 517 / 531; 48 heads x 33 rows x
 // 128 2 / 4 / 5 splits, 4100 keys 587 / 567 / 583; 24 heads x 57 rows x 128 5 / 8, 4100 keys 403 / 426; one row x 40 heads x 64, 2 sequences, 6 / 9 / 12,
 // 4100 keys 179 / 185 / 182, 8 sequences 1 / 2 / 3, 2064 keys 286 / 267 / 256.
-int splits_wanted(int items, int per_cu) {
+// least_keys: from how many keys on a sequence is split.
+int splits_wanted(int items, int per_cu, int least_keys) {
   const int n_cus = device_cus(), fill = items >= n_cus ? 1 : (n_cus + items - 1) / items;
   int more = 0;
   float least = INFINITY;
@@ -374,15 +375,20 @@ int splits_wanted(int items, int per_cu) {
     const float share = (n == 2 ? 0.9f : 1.f) * n / splits;
     if (splits > 0 && share < least) least = share, more = splits;
   }
-  return (fill < 255 ? fill : 255) | (more < 255 ? more : 255) << 8;
+  return (fill < 255 ? fill : 255) | (more < 255 ? more : 255) << 8 | least_keys / ATK << 16;
 }
 // Most workgroups a compute unit.  Items of one or two row groups: those that are resident, but 4 for head dim 64 and one row group (3
 // resident; 8 sequences above).  Items of many rows: 3; up to 5 are resident, and no faster (5 x 41 rows x 40 heads x 128, 2064 keys, 2 / 3 / 4
 // workgroups 422 / 424 / 453; 4 x 33 rows x 48 heads x 64, 4100 keys 405 / 374 / 386).
 constexpr int item_per_cu(int hd, int nrg) { return hd == 64 && nrg == 1 ? 4 : 2; }
 constexpr int ROWS_PER_CU = 3;
+// Keys from which on items of many rows are split where they give at least every other compute unit a workgroup: below, the merge's launch
+// costs more than the tiles it saves a workgroup (14 of 32 keys, 10 of 64).  us of a pass of four narrow layers, split / whole: 32 x 8 rows x 32 heads on 4 x 128,
+// 300, 400, 516 keys 255 / 235, 250 / 243, 255 / 266; 4 x 33 rows x 40 heads x 128, 300, 400, 516 keys 262 / 262, 267 / 272, 276 / 293; 8 x 29 rows x 32
+// heads on 8 x 64, 300, 516 keys 227 / 212, 233 / 228; 4 x 33 rows x 32 heads x 64, 700 keys 230 / 243; prompts of 300 tokens x 32 heads x 128 226 / 217.
+int rows_least_keys(int hd, int items) { return 2 * items < device_cus() ? 0 : hd == 128 ? 448 : 640; }
 int widest_split(int n_splits, int want) {
-  const int widest = (want & 255) > (want >> 8) ? want & 255 : want >> 8;
+  const int fill = want & 255, more = want >> 8 & 255, widest = fill > more ? fill : more;
   return n_splits < widest ? n_splits : widest;
 }
 
@@ -401,7 +407,7 @@ hipError_t run_rows(const float* q, int q_stride, const RowDesc& rd, const KvVie
   const int KVH = kv.n_kv_heads, G = n_heads / KVH, n_chunks = (G * R + RW * 16 - 1) / (RW * 16), items = KVH * n_chunks * B;
   auto kern = tree_attn_rows_kernel<HD, RW, CAUSAL>;
   static_assert(Sh::LDS <= 64 * 1024, "needs no attribute");
-  const int want = splits_wanted(items, ROWS_PER_CU), gx = widest_split(n_splits, want);
+  const int want = splits_wanted(items, ROWS_PER_CU, rows_least_keys(HD, items)), gx = widest_split(n_splits, want);
   const bool spread = spread_splits(gx, items);
   hipLaunchKernelGGL(kern, rows_grid(spread, gx, items), dim3(RW * 64), Sh::LDS, s, q, q_stride, rd, kv, layer, B, R, n_heads, n_chunks,
                      ATTN_LOG2E / sqrtf((float)HD), partial, n_splits, (bf16_t*)out, want, ncg, spread ? 0 : gx);
@@ -422,7 +428,7 @@ hipError_t run_mfma(const float* q, int q_stride, const RowDesc& rd, const KvVie
                                                  : hipSuccess;
   if (attr != hipSuccess) return attr;
   const int items = KVH * B;
-  const int want = splits_wanted(items, item_per_cu(HD, NRG)), gx = widest_split(n_splits, want);
+  const int want = splits_wanted(items, item_per_cu(HD, NRG), 0), gx = widest_split(n_splits, want);
   const bool spread = spread_splits(gx, items);
   if constexpr (NRG == 1) {
     // Six layers, us, two launches / one (rows = sequences x heads x rows each): 12 heads x 64, 12 rows, 256 / 2048 keys 164 / 153,
@@ -488,11 +494,14 @@ extern "C" void mtad_test_attention_places(int rows, int n_kv_heads, int chunks,
         at[0] = p.split, at[1] = p.g, at[2] = p.seq, at[3] = p.chunk;
       }
 }
-// Host side only, for the tests: the key splits a launch offers and its items, for `pairs` (query head, row) pairs on a KV head.  They hold
-// for 256 compute units where there is no device.
-extern "C" int mtad_test_attention_splits(int head_dim, int pairs, int n_kv_heads, int batch, int causal, int n_splits, int* items) {
+// Host side only, for the tests: the key splits a launch offers (out[0]) and a sequence of `keys` keys uses (out[1]), and the launch's items
+// (out[2]), for `pairs` (query head, row) pairs on a KV head.  They hold for 256 compute units where there is no device.
+extern "C" void mtad_test_attention_splits(int head_dim, int pairs, int n_kv_heads, int batch, int causal, int n_splits, int keys, int* out) {
   using namespace mtad;
   const bool rows = causal || pairs > 32, four = causal || pairs > 48;
-  *items = n_kv_heads * batch * (rows ? (pairs + (four ? 63 : 47)) / (four ? 64 : 48) : 1);
-  return widest_split(n_splits, splits_wanted(*items, rows ? ROWS_PER_CU : item_per_cu(head_dim, pairs > 16 ? 2 : 1)));
+  const int items = n_kv_heads * batch * (rows ? (pairs + (four ? 63 : 47)) / (four ? 64 : 48) : 1);
+  const int want = rows ? splits_wanted(items, ROWS_PER_CU, rows_least_keys(head_dim, items)) : splits_wanted(items, item_per_cu(head_dim, pairs > 16 ? 2 : 1), 0);
+  out[0] = widest_split(n_splits, want);
+  out[1] = attn_splits(keys, out[0], want);
+  out[2] = items;
 }

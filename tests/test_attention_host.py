@@ -31,9 +31,11 @@ def test_every_item_has_its_workgroups_and_the_xcds_share_them(rows, chunks, kv_
             assert share.max() <= -(-items * used // XCDS)
 
 
-def _splits(hd, pairs, kv_heads, batch, causal=0, n_splits=32):
-    items = C.c_int()
-    return mb.lib().mtad_test_attention_splits(hd, pairs, kv_heads, batch, causal, n_splits, C.byref(items)), items.value
+def _splits(hd, pairs, kv_heads, batch, causal=0, n_splits=32, keys=4096):
+    """Splits offered, splits that so many keys use, items."""
+    out = (C.c_int * 3)()
+    mb.lib().mtad_test_attention_splits(hd, pairs, kv_heads, batch, causal, n_splits, keys, out)
+    return tuple(out)
 
 
 @pytest.mark.parametrize("hd", [64, 128])
@@ -43,7 +45,7 @@ def test_an_uneven_fill_is_split_evenly(hd, pairs):
     most = 2 if pairs == 17 or pairs <= 16 and hd == 128 else 4 if pairs <= 16 else 3
     for batch in (1, 2, 3, 4, 5, 8, 16):
         for kv_heads in (1, 2, 4, 5, 8, 12, 20, 24, 32, 40, 48, 64):
-            splits, items = _splits(hd, pairs, kv_heads, batch)
+            splits, _, items = _splits(hd, pairs, kv_heads, batch)
             assert 1 <= splits <= 32
             if items * -(-CUS // items) == CUS or items < 16:
                 continue
@@ -56,3 +58,12 @@ def test_an_uneven_fill_is_split_evenly(hd, pairs):
 def test_measured_numbers_of_splits(hd, pairs, kv_heads, batch, splits):
     assert _splits(hd, pairs, kv_heads, batch)[0] == splits
     assert _splits(hd, pairs, kv_heads, batch, n_splits=2)[0] == min(2, splits)
+
+
+@pytest.mark.parametrize("hd,pairs,kv_heads,batch,causal,least", [(128, 64, 4, 32, 0, 448), (128, 128, 4, 16, 0, 448), (64, 116, 8, 8, 0, 640), (128, 300, 32, 1, 1, 448),
+                                                                  (64, 8 * 300, 4, 1, 1, 640), (64, 33, 32, 4, 0, 640), (128, 41, 40, 4, 0, 448),
+                                                                  (128, 64, 4, 31, 0, 256), (64, 57, 8, 4, 0, 256), (128, 5, 32, 4, 0, 256), (64, 1, 40, 4, 0, 256)])
+def test_short_contexts_are_not_split(hd, pairs, kv_heads, batch, causal, least):
+    """Items of many rows that give every other compute unit a workgroup are split later than others."""
+    used = lambda keys: _splits(hd, pairs, kv_heads, batch, causal, keys=keys)[1]
+    assert used(1) == used(least - 1) == 1 < used(least)
