@@ -97,3 +97,23 @@ def test_scores_in_the_hundred_thousands(hd, heads, kv_heads, batch, gamma, beam
     err = np.abs(got - want).max()
     print(f"largest error {err:.2e}", flush=True)
     assert err < TOLERANCE
+
+
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,gamma,beam,n", [
+    (64, 40, 40, 4, 4, 1, 2100),       # 160 items of one row group: the splits run slowest, the heads are turned
+    (64, 12, 12, 8, 4, 3, 2100),       # 96
+    (128, 24, 24, 4, 4, 5, 1300),      # 96 of two row groups
+    (64, 24, 24, 4, 5, 8, 1700),       # 96 of many rows
+    (64, 40, 8, 5, 5, 8, 1100),        # 160: four chunks of rows a head
+    (128, 16, 8, 8, 7, 4, 900),        # 64: the splits of an item side by side
+    (128, 64, 8, 8, 4, 4, 600),        # 192, some sequences split, some whole
+])
+def test_grids_of_sequences_of_different_lengths(hd, heads, kv_heads, batch, gamma, beam, n):
+    """More and fewer workgroups than compute units, sequences that use all, some or one of the splits a launch offers."""
+    print(f"grid hd {hd} heads {heads}/{kv_heads} batch {batch} rows {1 + gamma * beam} n {n}", flush=True)
+    r = np.random.default_rng(heads + n)
+    keys, values = np.zeros((batch, n, kv_heads, hd)), r.standard_normal((batch, n, kv_heads, hd)).astype(np.float16)
+    keys[..., hd // 2 - 2] = r.integers(-16, 17, (batch, n, kv_heads))
+    lens = [n, 1, n // 2, 130, n // 4, n - 1, 449, 300][:batch]
+    got = _run(heads, kv_heads, hd, batch, gamma, beam, lens, keys, values, 0)
+    assert np.abs(got - _expected(heads, kv_heads, hd, lens, keys, values, 1 + gamma * beam)).max() < TOLERANCE
