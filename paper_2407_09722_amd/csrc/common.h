@@ -226,6 +226,8 @@ hipError_t launch_lse_gather(const float* lse_part, float* lse, int B, int M, in
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t s);
 hipError_t launch_row_lse(const float* logits, float* lse, int rows, int vocab, hipStream_t s);
 
+// most key splits of a float32 model's attention in a context of that many keys
+int f32_attention_splits(int B, int n_heads, int R, int max_context);
 size_t attention_partial_floats(int B, int R, int n_heads, int head_dim, int n_splits);
 
 }  // namespace mtad

@@ -13,6 +13,12 @@
 // Bound by latency: a launch, the length, the page, the block and its arithmetic are a chain.  us, tiles staged in LDS and a thread per
 // (key, rows) before / here: 5 rows x 4 heads x 64, 82 keys 9.2 / 6.3 (in a pass 11.1 / 6.5); one row x 8 heads, 300 keys 12.1 / 6.7; 5 rows x
 // 4 heads x 128, 4096 keys 52.7 / 20.7; 3 x 57 rows x 8 heads x 64, 900 keys (arithmetic) 38.5 / 38.6.
+// A compute unit holds one workgroup (212 registers, eight waves), and a wave's next block costs less than a workgroup's start and a share of the
+// merge: no more splits than give every compute unit one.  us of a pass of four narrow layers, splits for four workgroups a compute unit / two / one / half
+// of them: 16 x 9 rows x 8 heads x 64, 700 keys 290 / 255 / 212 / 212; 16 x 5 rows, 1500 keys 256 / 248 / 215 / 265; 4 x 25 rows, 1500 keys 242 / 228 / 207 / 244; one
+// sequence of 57 rows, 1500 keys 172 / 171 / 147 / 170; 5 rows, 700 keys (32 workgroups a split) alike.  (At one a compute unit, chunks and query
+// heads that share keys are KV heads apart in the grid, so that they mostly are on one XCD and its cache has the keys once: 2 x 57 rows x 8 heads x 128,
+// 8100 keys 817 / 595, 8 x 9 rows, 4100 keys 562 / 488, 700 keys 224 / 208.)
 #include "attn_mfma_device.h"
 #include "common.h"
 
@@ -65,15 +71,16 @@ __device__ __forceinline__ void each16(F f) {
 
 template <int HD>
 __global__ __launch_bounds__(F32_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void tree_attn_f32_kernel(
-    const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int R, int n_heads, int n_chunks, float scale, float* __restrict__ partial,
-    int n_splits, int* __restrict__ counters, float* __restrict__ out) {
+    const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int R, int n_heads, int group, int n_chunks, float scale,
+    float* __restrict__ partial, int n_splits, int* __restrict__ counters, float* __restrict__ out) {
   constexpr int E = HD / 64;  // float4s per lane of a key or a query
   __shared__ __attribute__((aligned(16))) float o_s[F32_BLOCKS][F32_ROWS][HD];
   __shared__ float m_s[F32_BLOCKS][F32_ROWS], l_s[F32_BLOCKS][F32_ROWS];
   __shared__ int last_s;
   const int t = threadIdx.x, lane = t & 63, c = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), kb = wave >> 1;
-  const int split = blockIdx.x, head = blockIdx.y / n_chunks, chunk = blockIdx.y % n_chunks, seq = blockIdx.z;
+  const int KVH = kv.n_kv_heads, kv_head = blockIdx.y % KVH, rest = blockIdx.y / KVH;
+  const int split = blockIdx.x, head = kv_head * group + rest % group, chunk = rest / group, seq = blockIdx.z;
   const int nrows = min(F32_ROWS, R - chunk * F32_ROWS), half = (nrows + 1) >> 1;
   const int r0 = (wave & 1) * half, nr = (wave & 1) ? nrows - half : half;  // this wave's rows of the chunk
   const int row0 = seq * R + chunk * F32_ROWS + r0;
@@ -82,7 +89,7 @@ __global__ __launch_bounds__(F32_THREADS) __attribute__((amdgpu_waves_per_eu(2))
   // what does not depend on the length first: the place of this lane's key of the first block, the queries
   // (all kernel arguments at once; left to itself the compiler fetches them in rounds, each a trip to memory)
   asm volatile("" ::"s"(q), "s"(q_stride), "s"(rd.nspec), "s"(rd.mask), "s"(kv.k), "s"(kv.v), "s"(kv.page_table), "s"(kv.len), "s"(kv.page_size), "s"(kv.max_pages),
-               "s"(kv.n_pages), "s"(kv.n_kv_heads), "s"(kv.layer_stride), "s"(layer), "s"(R), "s"(n_heads), "s"(n_splits), "s"(n_chunks), "s"(out));
+               "s"(kv.n_pages), "s"(kv.n_kv_heads), "s"(kv.layer_stride), "s"(layer), "s"(R), "s"(n_heads), "s"(n_splits), "s"(n_chunks), "s"(group), "s"(out));
   auto key_of = [&](int block) { return min(block * F32_BLOCK + 4 * c + g, cap - 1); };
   const int block0 = split * F32_BLOCKS + kb;
   const int page0 = kv.page_table[(int64_t)seq * kv.max_pages + key_of(block0) / kv.page_size];
@@ -101,7 +108,7 @@ __global__ __launch_bounds__(F32_THREADS) __attribute__((amdgpu_waves_per_eu(2))
   const int blocks = nr > 0 ? (ktot + F32_BLOCK - 1) / F32_BLOCK : 0;
 
   const int64_t tok_stride = (int64_t)kv.n_kv_heads * HD;
-  const int64_t at = (int64_t)layer * kv.layer_stride + (int64_t)(head * kv.n_kv_heads / n_heads) * HD + 4 * c;
+  const int64_t at = (int64_t)layer * kv.layer_stride + (int64_t)kv_head * HD + 4 * c;
   const float *const kbase = (const float*)kv.k + at, *const vbase = (const float*)kv.v + at;
   float m_run[HALF_ROWS], l_run[HALF_ROWS];
   float4 acc[HALF_ROWS][E];
@@ -274,12 +281,18 @@ template <int HD>
 hipError_t run_f32(const float* q, int q_stride, const RowDesc& rd, const KvView& kv, int layer, int B, int R, int n_heads, float* partial, int n_splits,
                    int* counters, void* out, hipStream_t s) {
   const int n_chunks = (R + F32_ROWS - 1) / F32_ROWS;
-  hipLaunchKernelGGL((tree_attn_f32_kernel<HD>), dim3(n_splits, n_heads * n_chunks, B), dim3(F32_THREADS), 0, s, q, q_stride, rd, kv, layer, R, n_heads, n_chunks,
-                     1.0f / sqrtf((float)HD), partial, n_splits, counters, (float*)out);
+  hipLaunchKernelGGL((tree_attn_f32_kernel<HD>), dim3(n_splits, n_heads * n_chunks, B), dim3(F32_THREADS), 0, s, q, q_stride, rd, kv, layer, R, n_heads, n_heads / kv.n_kv_heads,
+                     n_chunks, 1.0f / sqrtf((float)HD), partial, n_splits, counters, (float*)out);
   return hipGetLastError();
 }
 
 }  // namespace
+
+int f32_attention_splits(int B, int n_heads, int R, int max_context) {
+  const int items = B * n_heads * ((R + F32_ROWS - 1) / F32_ROWS), fill = (256 + items - 1) / items, most = (max_context + F32_BLOCKS * F32_BLOCK - 1) / (F32_BLOCKS * F32_BLOCK);
+  const int s = fill < most ? fill : most;
+  return s < 1 ? 1 : s > 32 ? 32 : s;  // (32: what the exchange buffer is made for)
+}
 
 size_t attention_partial_floats(int B, int R, int n_heads, int head_dim, int n_splits) {
   return (size_t)B * R * n_heads * n_splits * (head_dim + 2);
@@ -296,3 +309,8 @@ hipError_t launch_attention(int dtype, const float* q, int q_stride, const RowDe
 }
 
 }  // namespace mtad
+
+// Host side only, for the tests.
+extern "C" int mtad_test_f32_attention_splits(int batch, int n_heads, int rows, int max_context) {
+  return mtad::f32_attention_splits(batch, n_heads, rows, max_context);
+}

@@ -87,15 +87,6 @@ int shape_ok(const mtad_model* m) {
   return 1;
 }
 
-// most key splits of a float32 model's attention (the kernel takes one per 256 keys there are)
-int splits_for(const mtad_ctx* c, const mtad_model* m, int R) {
-  const int chunks = (R + 7) / 8;
-  const int blocks = c->cfg.batch * m->n_heads * chunks;
-  int s = (1024 + blocks - 1) / blocks;
-  s = imin(s, (c->cfg.max_context + 255) / 256);
-  return imax(1, imin(32, s));
-}
-
 // Rows of one prompt pass of a bf16 model, all sequences together.  From about 256 rows on a product is bound by the matrix
 // cores, no longer by its weights; 2048 rows fill the machine with 256-row tiles where the output is 4096 features wide (256
 // workgroups), 4096 rows where it is 2048, and cost a 13B-shaped model 520 MB of workspace (carve_within() makes do with less).  Four 7B-shaped
@@ -270,7 +261,7 @@ int decoder_pass_f32(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R,
   const int d = m->d_model, f = m->d_ffn, H = m->n_heads, hd = m->head_dim;
   const int qkvw = (H + 2 * m->n_kv_heads) * hd;
   const KvView kvv = view_of(kv, m);
-  const int n_splits = splits_for(c, m, R);
+  const int n_splits = f32_attention_splits(B, H, R, c->cfg.max_context);
   const void* const* W = m->weights;
   HIP_TRY(c, launch_embed(0, W[0], c->rd.tok, c->h, rows, d, m->vocab, nullptr, nullptr, nullptr, c->rd.pos, c->rope, hd, m->rope_theta, 0, s));
   GemmF32Args a;

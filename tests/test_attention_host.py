@@ -67,3 +67,13 @@ def test_short_contexts_are_not_split(hd, pairs, kv_heads, batch, causal, least)
     """Items of many rows that give every other compute unit a workgroup are split later than others."""
     used = lambda keys: _splits(hd, pairs, kv_heads, batch, causal, keys=keys)[1]
     assert used(1) == used(least - 1) == 1 < used(least)
+
+
+def test_float32_splits_fill_the_machine_once():
+    for batch in (1, 2, 4, 8, 16):
+        for heads in (1, 2, 4, 8, 16):
+            for rows in (1, 5, 8, 9, 25, 57):
+                for keys in (1, 256, 257, 700, 4100, 12000):
+                    s, items = mb.lib().mtad_test_f32_attention_splits(batch, heads, rows, keys), batch * heads * -(-rows // 8)
+                    assert s == 1 or (s - 1) * items < CUS and (s - 1) * 256 < keys and s <= 32
+                    assert s in (32, -(-keys // 256)) or s * items >= CUS

@@ -1,4 +1,4 @@
-"""Attention of bf16 models on its own: a model of one layer whose logits are the attention output, over a cache that the test writes."""
+"""Attention on its own: a model of one layer whose logits are the attention output, over a cache that the test writes."""
 import numpy as np
 import pytest
 import torch
@@ -10,34 +10,35 @@ DEV = "cuda:0"
 QUERY = 2048                       # the large component of every query; the other one is 1
 
 
-def _model(heads, kv_heads, hd):
+def _model(heads, kv_heads, hd, dtype="bf16"):
     """Every query is (.., 1, 2048, 0 ..): the two components turn by less than 1e-20 at any position.  New tokens' keys and values are zero; the
     attention output is added to a hidden state of ones and read through a unit matrix."""
     d = heads * hd
-    shape = si.ModelShape(1, d, heads, kv_heads, hd, 32, d, "bf16", rms_eps=0.0, rope_theta=1e30)
+    shape = si.ModelShape(1, d, heads, kv_heads, hd, 32, d, dtype, rms_eps=0.0, rope_theta=1e30)
     zero = lambda *n: np.zeros(n, np.float32)
     qkv, eye = zero(shape.qkv_rows, d), np.eye(d, dtype=np.float32)
     half = hd // 2
     for h in range(heads):
         qkv[h * hd + half - 1, 0], qkv[h * hd + half - 2, 0] = QUERY, 1
     w = {"embed": np.ones((d, d), np.float32), "L0.w_qkv": qkv, "L0.w_o": eye, "L0.w_gu": zero(64, d), "L0.w_d": zero(d, 32), "unembed": eye}
-    w = {k: si.f32_to_bf16_bits(v) for k, v in w.items()}
+    if dtype == "bf16":
+        w = {k: si.f32_to_bf16_bits(v) for k, v in w.items()}
     w.update({k: np.ones(d, np.float32) for k in ("L0.g_attn", "L0.g_ffn", "g_final")})
     return shape, w
 
 
-def _run(heads, kv_heads, hd, batch, gamma, beam, lens, keys, values, fused_pass):
+def _run(heads, kv_heads, hd, batch, gamma, beam, lens, keys, values, fused_pass=0, dtype="bf16"):
     """Logits [batch][rows][heads * hd] over a cache of lens[s] tokens, keys / values [batch][n][kv_heads][hd]; every row sees itself alone
     beside them."""
     from paper_2407_09722_amd.engine import DeviceModel, Engine
-    shape, w = _model(heads, kv_heads, hd)
+    shape, w = _model(heads, kv_heads, hd, dtype)
     m = DeviceModel(shape, w, DEV)
     n = keys.shape[1]
     eng = Engine(m, m, batch=batch, gamma=gamma, beam=beam, mode="mmtad", max_context=n + 64, prefill_rows=1, fused_pass=fused_pass)
     at = eng.tkv.page_table.cpu().numpy()[:, np.arange(n) // 16] * 16 + np.arange(n) % 16
     for to, x in ((eng.tkv.k, keys), (eng.tkv.v, values)):
         flat = to.view(-1, kv_heads, hd)
-        flat[torch.from_numpy(at.astype(np.int64)).to(DEV)] = torch.from_numpy(x.astype(np.float16)).to(DEV)
+        flat[torch.from_numpy(at.astype(np.int64)).to(DEV)] = torch.from_numpy(x).to(DEV, to.dtype)
     eng.tkv.len.copy_(torch.tensor(lens, dtype=torch.int32))
     M = eng.M
     eng.t_parent.fill_(0)
@@ -117,3 +118,23 @@ def test_grids_of_sequences_of_different_lengths(hd, heads, kv_heads, batch, gam
     lens = [n, 1, n // 2, 130, n // 4, n - 1, 449, 300][:batch]
     got = _run(heads, kv_heads, hd, batch, gamma, beam, lens, keys, values, 0)
     assert np.abs(got - _expected(heads, kv_heads, hd, lens, keys, values, 1 + gamma * beam)).max() < TOLERANCE
+
+
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,gamma,beam,n", [
+    (64, 8, 8, 16, 8, 1, 1300),        # 9 rows: one key split, five or six rounds of blocks, the last of 20 keys
+    (128, 8, 8, 8, 4, 3, 1100),        # 13 rows, two splits of two or three rounds
+    (64, 16, 4, 3, 3, 5, 900),         # three splits
+    (128, 8, 2, 4, 7, 8, 700),         # 57 rows: one split
+    (64, 2, 2, 1, 4, 1, 9000),         # 32 splits, some with a second round
+])
+def test_float32_waves_of_several_blocks(hd, heads, kv_heads, batch, gamma, beam, n):
+    """The float32 kernel's key loop: running maxima that move from block to block, the next block's places, a last block that is cut."""
+    print(f"float32 hd {hd} heads {heads}/{kv_heads} batch {batch} rows {1 + gamma * beam} n {n}", flush=True)
+    r = np.random.default_rng(heads + n)
+    keys, values = np.zeros((batch, n, kv_heads, hd), np.float32), r.standard_normal((batch, n, kv_heads, hd)).astype(np.float32)
+    keys[..., hd // 2 - 2] = r.standard_normal((batch, n, kv_heads)) * 12 + np.arange(n)[None, :, None] * (40 / n) * r.choice([-1, 0, 1], (batch, 1, kv_heads))
+    lens = [n - (97 * s) % (n // 2) for s in range(batch)]
+    got = _run(heads, kv_heads, hd, batch, gamma, beam, lens, keys, values, dtype="fp32")
+    err = np.abs(got - _expected(heads, kv_heads, hd, lens, keys, values, 1 + gamma * beam)).max()
+    print(f"largest error {err:.2e}", flush=True)
+    assert err < 1e-5  # of values up to 4.5 with weights from scores up to 10: a few units in the last place of each
