@@ -130,7 +130,7 @@ typedef struct {
   int32_t batch, gamma, beam;
   int32_t mode;         /* MTAD_MODE_* : fixes the rows of the target pass (1+gamma or 1+beam*gamma) */
   int32_t prefill_rows; /* rows per sequence in one prefill chunk, 1..64; a bfloat16 model takes a longer prompt in larger chunks
-                           (up to 2048 rows of all sequences together) if the workspace bound is large enough for them */
+                           (up to 4096 rows of all sequences together) if the workspace bound is large enough for them */
   int32_t max_context;  /* upper bound on committed + speculative tokens per sequence */
 } mtad_config;
 
@@ -142,10 +142,10 @@ typedef struct {
 int mtad_create(mtad_ctx **ctx, const mtad_config *cfg, const mtad_model *target, const mtad_model *draft);
 void mtad_destroy(mtad_ctx *ctx);
 /* Bytes of device workspace with which the context works best; bind exactly one buffer (256-byte aligned) before
- * any hot call.  The contents need no initialisation.  For bfloat16 models most of it serves prompt chunks of up to 2048 rows (a
- * 7B-shaped target: 338 MB with them, 94 MB without).  A smaller buffer is taken too, down to what chunks of prefill_rows rows
- * need: prompts then run in shorter chunks (2048 tokens of that target in chunks of 1024 take 2 % longer, in chunks of 64 three and a
- * half times as long) and products of many rows cut their reductions less.  ECAP below that. */
+ * any hot call.  The contents need no initialisation.  For bfloat16 models most of it serves prompt chunks of up to 4096 rows (a
+ * 7B-shaped target: 532 MB with them, 94 MB without).  A smaller buffer is taken too, down to what chunks of prefill_rows rows
+ * need: prompts then run in shorter chunks (4096 tokens of that target in chunks of 2048 take 7 % longer, 2048 tokens in chunks of 1024
+ * another 2 %, in chunks of 64 three and a half times as long) and products of many rows cut their reductions less.  ECAP below that. */
 size_t mtad_workspace_bytes(const mtad_ctx *ctx);
 int mtad_bind_workspace(mtad_ctx *ctx, void *device_buf, size_t bytes);
 /* bf16 passes of at most 8 rows (all sequences together) can run every product and the attention of every layer as work

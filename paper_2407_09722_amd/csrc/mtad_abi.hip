@@ -89,9 +89,12 @@ int shape_ok(const mtad_model* m) {
 
 // Rows of one prompt pass of a bf16 model, all sequences together.  From about 256 rows on a product is bound by the matrix
 // cores, no longer by its weights; 2048 rows fill the machine with 256-row tiles where the output is 4096 features wide (256
-// workgroups), 4096 rows where it is 2048, and cost a 13B-shaped model 520 MB of workspace (carve_within() makes do with less).  Four 7B-shaped
-// layers on 2047 tokens: 16.7 ms in chunks of 64 rows, 4.9 in chunks of 1024 or one pass; four 13B-shaped ones on 4 x 509, 4 x 64 rows
-// a chunk 9.7 -> 6.7 ms; the 22-layer draft of 2048 features on 4 x 1023 tokens 39.5 ms in chunks of 256 rows in all, 15.6 in two of 2048, 14.9 in one pass.
+// workgroups), 4096 rows where it is 2048, and wider models still gain (fewer last waves of tiles).  They cost a 13B-shaped model 520 MB of
+// workspace (carve_within() makes do with less).  Four 7B-shaped layers on 2047 tokens: 16.7 ms in chunks of 64 rows, 4.9 in chunks of 1024 or one pass;
+// the 22-layer draft of 2048 features on 4 x 1023 tokens 39.5 ms in chunks of 256 rows in all, 15.6 in two of 2048, 14.9 in one pass.  Passes of
+// 2048 / 4096 / 8192 rows, us: 4090 tokens, three layers of 5120 features 9301 / 9067 / 9054, of 4096 6238 / 5819 / 5821, four of 3072 5670 / 5177 / 5216, six of
+// 2048 4534 / 4083 / 4110, of 768 1640 / 1192 / 1190; 6000 tokens 14408 / 14222 / 14224, 9683 / 9429 / 9171, 8805 / 8439 / 8259, 7212 / 6999 / 6213, 2668 / 2171 / 1768: 8192 rows
+// would double the workspace for prompts longer than 4096 tokens.
 constexpr int PROMPT_PASS_ROWS = 4096;
 
 struct Carver {
