@@ -104,8 +104,8 @@ def test_attention_items_of_c4_32_rows_per_item_8_key_splits_over_2048_keys():
 
 def test_attention_items_of_c5_48_rows_per_item_3_key_splits_over_4096_keys():
     """The attention launch of C5's verify step: 40 KV heads of 128 x 4 sequences = 160 work items of 41 rows (three
-    16-row groups per item), a context of more than 4096 keys in 3 splits (480 workgroups: every resident slot of 256
-    compute units at two per unit).  The four sequences carry one prompt and the run is deterministic, so one oracle run
+    16-row groups per item), a context of more than 4096 keys in 3 splits (480 workgroups: two per compute unit at most, which
+    leaves the fullest of 256 units less of an item than any other number).  The four sequences carry one prompt and the run is deterministic, so one oracle run
     (float64 attention over 4100 x 4100 scores per head) serves all four: sequence 0 is compared with the oracle,
     the other three with sequence 0."""
     t = si.ModelShape(1, 256, 40, 40, 128, 256, 1024, "bf16")
@@ -123,20 +123,25 @@ def test_attention_items_of_c5_48_rows_per_item_3_key_splits_over_4096_keys():
 
 # ---- decision kernels on the oracle's float32 inputs: integers must be identical -------------------------------------
 
-def _engine(B, gamma, beam, mode, V):
+def _engine(B, gamma, beam, mode, V, max_context=256):
     from paper_2407_09722_amd.engine import DeviceModel, Engine
     shape = si.ModelShape(1, 64, 1, 1, 64, 96, V, "fp32")
     w = si.make_weights(shape, 1, "target", threads=1)
     m = DeviceModel(shape, w, DEV)
-    return Engine(m, m, batch=B, gamma=gamma, beam=beam, mode=mode, max_context=256, device=DEV)
+    return Engine(m, m, batch=B, gamma=gamma, beam=beam, mode=mode, max_context=max_context, prefill_rows=min(64, 256 // B), device=DEV)
 
 
-@pytest.mark.parametrize("V,trials", [(1024, 40), (8191, 16), (8192, 16), (32000, 16)])  # from 8192 tokens on a sampled row goes to 16 workgroups
+# from 8192 tokens on a sampled row goes to 16 workgroups, the last of which finishes up to 8 sequences; a second launch finishes more
+@pytest.mark.parametrize("V,trials,B", [(1024, 40, 3), (8191, 16, 3), (8192, 16, 3), (32000, 16, 3), (8192, 16, 8), (8192, 16, 9), (32000, 16, 9)])
 @pytest.mark.parametrize("mode", ["mtad", "mmtad"])
-def test_accept_kernel_bit_exact_on_oracle_inputs(mode, V, trials):
+def test_accept_kernel_bit_exact_on_oracle_inputs(mode, V, trials, B):
     from paper_2407_09722_amd import binding as mb
-    B, gamma, beam = 3, 4, 3
-    eng = _engine(B, gamma, beam, mode, V)
+    gamma, beam = 4, 3
+    eng = _engine(B, gamma, beam, mode, V, max_context=600)
+    before = [x.clone() for x in (eng.t_tok, eng.t_parent, eng.t_depth)]
+    eng.tkv.len.fill_(520)
+    eng.verify_phase()               # three key splits: attention's arrival words, which the acceptance uses too
+    passed = eng.logits.clone()
     g = np.random.default_rng(7)
     M = eng.M
     for trial in range(trials):
@@ -186,6 +191,11 @@ def test_accept_kernel_bit_exact_on_oracle_inputs(mode, V, trials):
                 t, gap = mtad.bonus_token(logits[s, node], sample=sample, seed=trial, seq_index=s, position=17 + trial + 1 + e,
                                           dt=np.float32)
             assert tok[s] == t or (sample and gap < 1e-5), (trial, s, gap)
+    for x, y in zip((eng.t_tok, eng.t_parent, eng.t_depth), before):
+        x.copy_(y)
+    eng.tkv.len.fill_(520)
+    eng.verify_phase()
+    assert torch.equal(eng.logits, passed)
     eng.close()
 
 
