@@ -142,7 +142,6 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(RowsSha
     const float* __restrict__ q, int q_stride, RowDesc rd, KvView kv, int layer, int B, int R, int n_heads, int n_chunks, float scale,
     float* __restrict__ partial, int n_splits, bf16_t* __restrict__ out, int want_splits, int ncg, int splits) {
   using Sh = RowsShape<HD, RW>;
-  constexpr int RG = 1;  // row groups per wave
   constexpr int KS = HD / 32, DB = HD / 16, CPR = Sh::CPR, KPI = Sh::KPI, GROUPS = Sh::GROUPS, TILE = Sh::TILE, SLOT = Sh::SLOT, LOOK = Sh::LOOK, RTK = Sh::RTK, TOK_TILES = Sh::TOK_TILES, NB = RTK / 16;
   extern __shared__ __attribute__((aligned(256))) unsigned char ring[];
   int* const tokens = (int*)(ring + 2 * SLOT);  // [2][TOK_TILES][RTK]
@@ -155,8 +154,8 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(RowsSha
   const int KVH = kv.n_kv_heads, G = n_heads / KVH;
   const AttnPlace at = rows_place(splits, KVH, B, blockIdx.x, blockIdx.y);
   const int split = at.split, g = at.g, seq = at.seq, chunk = CAUSAL ? n_chunks - 1 - at.chunk : at.chunk;  // a prompt's items that see the most keys first
-  const int pairs = G * R, pair0 = chunk * (RW * RG * 16), pair_end = min(pairs, pair0 + RW * RG * 16);  // pair p = query head p / R of the group, row p % R
-  const int wp0 = pair0 + wave * (RG * 16), wp_end = min(pair_end, wp0 + RG * 16);                      // this wave's
+  const int pairs = G * R, pair0 = chunk * (RW * 16), pair_end = min(pairs, pair0 + RW * 16);  // pair p = query head p / R of the group, row p % R
+  const int wp0 = pair0 + wave * 16, wp_end = min(pair_end, wp0 + 16);                      // this wave's
   const bool rowless = wp0 >= pair_end;
 
   const int len = kv.len[seq], ktot = attn_keys(kv, rd, seq, CAUSAL), eff = attn_splits(ktot, n_splits, want_splits);
@@ -191,23 +190,22 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(RowsSha
   look_up(0);
 
   // the wave's queries: lane (sg4, srow) of fragment ks holds dims ks * 32 + sg4 * 8 .. + 7 of row srow; rows that do not exist are zeros
-  half8 qh[RG][KS], ql[RG][KS];
-  unsigned long long rmask[RG];  // CAUSAL: the first key the row does not see
-#pragma unroll
-  for (int rg = 0; rg < RG; ++rg) {
-    const int p = wp0 + rg * 16 + srow;
+  half8 qh[1][KS], ql[1][KS];
+  unsigned long long rmask[1];  // CAUSAL: the first key the row does not see
+  {
+    const int p = wp0 + srow;
     const bool live = p < wp_end;
     const int pc = live ? p : 0, row = pc % R;
     const float* const qp = q + (int64_t)(seq * R + row) * q_stride + (int64_t)(g * G + pc / R) * HD + sg4 * 8;
-    if constexpr (CAUSAL) rmask[rg] = live ? (unsigned)(len + 1 + row) : 0u;
-    else rmask[rg] = live ? rd.mask[seq * R + row] : 0ull;
+    if constexpr (CAUSAL) rmask[0] = live ? (unsigned)(len + 1 + row) : 0u;
+    else rmask[0] = live ? rd.mask[seq * R + row] : 0ull;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       typedef float floatx8_t __attribute__((ext_vector_type(8)));
       const float4 a = *(const float4*)(qp + ks * 32), b = *(const float4*)(qp + ks * 32 + 4);
       const floatx8_t x = live ? floatx8_t{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w} : floatx8_t{};
-      qh[rg][ks] = __builtin_convertvector(x, half8);
-      ql[rg][ks] = __builtin_convertvector(x - __builtin_convertvector(qh[rg][ks], floatx8_t), half8);
+      qh[0][ks] = __builtin_convertvector(x, half8);
+      ql[0][ks] = __builtin_convertvector(x - __builtin_convertvector(qh[0][ks], floatx8_t), half8);
     }
   }
   put(0);
@@ -234,15 +232,12 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(RowsSha
   };
   if (n_my > 0) request(0);
 
-  float m_run[RG], m_top[RG], l_run[RG];  // of row rg * 16 + srow: scaled reference maximum, score up to which it stays (the same in the four key groups), sum over the lane's own keys
-  attn_floatx4 acc[RG][DB];    // O^T: dims db * 16 + sg4 * 4 + i of row rg * 16 + srow
+  float m_run[1], m_top[1], l_run[1];  // of row srow: scaled reference maximum, score up to which it stays (the same in the four key groups), sum over the lane's own keys
+  attn_floatx4 acc[1][DB];    // O^T: dims db * 16 + sg4 * 4 + i of row srow
+  m_run[0] = m_top[0] = -INFINITY;
+  l_run[0] = 0.f;
 #pragma unroll
-  for (int rg = 0; rg < RG; ++rg) {
-    m_run[rg] = m_top[rg] = -INFINITY;
-    l_run[rg] = 0.f;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) acc[rg][db] = attn_floatx4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int db = 0; db < DB; ++db) acc[0][db] = attn_floatx4{0.f, 0.f, 0.f, 0.f};
   unsigned k_off[KS], v_off[DB];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) k_off[ks] = srow * (HD * 2) + ((ks * 4 + sg4) ^ turn_k(srow)) * 16;
@@ -277,24 +272,19 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(RowsSha
     if (rowless || key0 >= wend) continue;  // uniform over the wave
 
     // S^T = K Q^T
-    attn_floatx4 s2[RG][NB];
+    attn_floatx4 s2[1][NB];
 #pragma unroll
-    for (int rg = 0; rg < RG; ++rg)
-#pragma unroll
-      for (int blk = 0; blk < NB; ++blk) s2[rg][blk] = attn_floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int blk = 0; blk < NB; ++blk) s2[0][blk] = attn_floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int blk = 0; blk < NB; ++blk) {
         const half8 kf = *(const half8*)(sp + k_off[ks] + blk * (16 * HD * 2));
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) {
-          s2[rg][blk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qh[rg][ks], s2[rg][blk], 0, 0, 0);
-          s2[rg][blk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, ql[rg][ks], s2[rg][blk], 0, 0, 0);
-        }
+        s2[0][blk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qh[0][ks], s2[0][blk], 0, 0, 0);
+        s2[0][blk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, ql[0][ks], s2[0][blk], 0, 0, 0);
       }
-    half8 ph[RG][NB / 2], pl[RG][NB / 2];
-    attn_softmax<RG, NB, DB, CAUSAL>(s2, rmask, m_run, m_top, l_run, acc, ph, pl, scale, key0, len, all, kend, sg4);
+    half8 ph[1][NB / 2], pl[1][NB / 2];
+    attn_softmax<1, NB, DB, CAUSAL>(s2, rmask, m_run, m_top, l_run, acc, ph, pl, scale, key0, len, all, kend, sg4);
     // O^T += V^T P^T
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -302,42 +292,36 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(RowsSha
       for (int hb = 0; hb < NB / 2; ++hb) {
         const half4 v0 = lds_columns((const _Float16*)(sp + v_off[db] + hb * (32 * HD * 2))), v1 = lds_columns((const _Float16*)(sp + v_off[db] + hb * (32 * HD * 2) + 16 * HD * 2));
         const half8 vt = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) {
-          acc[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, ph[rg][hb], acc[rg][db], 0, 0, 0);
-          acc[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, pl[rg][hb], acc[rg][db], 0, 0, 0);
-        }
+        acc[0][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, ph[0][hb], acc[0][db], 0, 0, 0);
+        acc[0][db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vt, pl[0][hb], acc[0][db], 0, 0, 0);
       }
   }
   if (rowless) return;
+  const int p = wp0 + srow;
+  const bool live = p < wp_end;
+  const int pc = live ? p : wp0, row = pc % R, head = g * G + pc / R;
+  l_run[0] = xsum<32>(xsum<16>(l_run[0]));
+  if (eff == 1) {
+    const float inv = l_run[0] > 0.f ? 1.0f / l_run[0] : 0.f;
 #pragma unroll
-  for (int rg = 0; rg < RG; ++rg) {
-    const int p = wp0 + rg * 16 + srow;
-    const bool live = p < wp_end;
-    const int pc = live ? p : wp0, row = pc % R, head = g * G + pc / R;
-    l_run[rg] = xsum<32>(xsum<16>(l_run[rg]));
-    if (eff == 1) {
-      const float inv = l_run[rg] > 0.f ? 1.0f / l_run[rg] : 0.f;
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        const float x[4] = {acc[rg][db][0] * inv, acc[rg][db][1] * inv, acc[rg][db][2] * inv, acc[rg][db][3] * inv};
-        uint2 hi, lo;
-        split_bf16_x4(x, hi, lo);
-        const int k = head * HD + db * 16 + sg4 * 4;
-        if (live) {
-          *(uint2*)(out + act_offset(ncg, B * R, n_heads * HD, 0, seq * R + row, k)) = hi;
-          *(uint2*)(out + act_offset(ncg, B * R, n_heads * HD, 1, seq * R + row, k)) = lo;
-        }
+    for (int db = 0; db < DB; ++db) {
+      const float x[4] = {acc[0][db][0] * inv, acc[0][db][1] * inv, acc[0][db][2] * inv, acc[0][db][3] * inv};
+      uint2 hi, lo;
+      split_bf16_x4(x, hi, lo);
+      const int k = head * HD + db * 16 + sg4 * 4;
+      if (live) {
+        *(uint2*)(out + act_offset(ncg, B * R, n_heads * HD, 0, seq * R + row, k)) = hi;
+        *(uint2*)(out + act_offset(ncg, B * R, n_heads * HD, 1, seq * R + row, k)) = lo;
       }
-    } else if (live) {
-      float* const pp = partial + ((((int64_t)seq * n_heads + head) * R + row) * n_splits + split) * (HD + 2);
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        *(float2*)(pp + 2 + db * 16 + sg4 * 4) = make_float2(acc[rg][db][0], acc[rg][db][1]);
-        *(float2*)(pp + 2 + db * 16 + sg4 * 4 + 2) = make_float2(acc[rg][db][2], acc[rg][db][3]);
-      }
-      if (sg4 == 0) *(float2*)pp = make_float2(m_run[rg], l_run[rg]);
     }
+  } else if (live) {
+    float* const pp = partial + ((((int64_t)seq * n_heads + head) * R + row) * n_splits + split) * (HD + 2);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      *(float2*)(pp + 2 + db * 16 + sg4 * 4) = make_float2(acc[0][db][0], acc[0][db][1]);
+      *(float2*)(pp + 2 + db * 16 + sg4 * 4 + 2) = make_float2(acc[0][db][2], acc[0][db][3]);
+    }
+    if (sg4 == 0) *(float2*)pp = make_float2(m_run[0], l_run[0]);
   }
 }
 
