@@ -370,7 +370,9 @@ constexpr int ROWS_PER_CU = 3;
 // costs more than the tiles it saves a workgroup (14 of 32 keys, 10 of 64).  us of a pass of four narrow layers, split / whole: 32 x 8 rows x 32 heads on 4 x 128,
 // 300, 400, 516 keys 255 / 235, 250 / 243, 255 / 266; 4 x 33 rows x 40 heads x 128, 300, 400, 516 keys 262 / 262, 267 / 272, 276 / 293; 8 x 29 rows x 32
 // heads on 8 x 64, 300, 516 keys 227 / 212, 233 / 228; 4 x 33 rows x 32 heads x 64, 700 keys 230 / 243; prompts of 300 tokens x 32 heads x 128 226 / 217.
-int rows_least_keys(int hd, int items) { return 2 * items < device_cus() ? 0 : hd == 128 ? 448 : 640; }
+// A prompt's rows see half of its keys on average and are many to merge (split / whole in a launch that offers splits): 31 heads x 128, 479 tokens 261 / 240,
+// 20 heads 220 / 215, 16 heads, 600 tokens 222 / 229; 12 heads x 64, 700 tokens 193 / 189, 8 heads, 1000 tokens 189 / 192.
+int rows_least_keys(int hd, int items, bool causal) { return 2 * items < device_cus() ? 0 : hd == 128 ? (causal ? 544 : 448) : (causal ? 960 : 640); }
 int widest_split(int n_splits, int want) {
   const int fill = want & 255, more = want >> 8 & 255, widest = fill > more ? fill : more;
   return n_splits < widest ? n_splits : widest;
@@ -391,7 +393,7 @@ hipError_t run_rows(const float* q, int q_stride, const RowDesc& rd, const KvVie
   const int KVH = kv.n_kv_heads, G = n_heads / KVH, n_chunks = (G * R + RW * 16 - 1) / (RW * 16), items = KVH * n_chunks * B;
   auto kern = tree_attn_rows_kernel<HD, RW, CAUSAL>;
   static_assert(Sh::LDS <= 64 * 1024, "needs no attribute");
-  const int want = splits_wanted(items, ROWS_PER_CU, rows_least_keys(HD, items)), gx = widest_split(n_splits, want);
+  const int want = splits_wanted(items, ROWS_PER_CU, rows_least_keys(HD, items, CAUSAL)), gx = widest_split(n_splits, want);
   const bool spread = spread_splits(gx, items);
   hipLaunchKernelGGL(kern, rows_grid(spread, gx, items), dim3(RW * 64), Sh::LDS, s, q, q_stride, rd, kv, layer, B, R, n_heads, n_chunks,
                      ATTN_LOG2E / sqrtf((float)HD), partial, n_splits, (bf16_t*)out, want, ncg, spread ? 0 : gx);
@@ -484,7 +486,7 @@ extern "C" void mtad_test_attention_splits(int head_dim, int pairs, int n_kv_hea
   using namespace mtad;
   const bool rows = causal || pairs > 32, four = causal || pairs > 48;
   const int items = n_kv_heads * batch * (rows ? (pairs + (four ? 63 : 47)) / (four ? 64 : 48) : 1);
-  const int want = rows ? splits_wanted(items, ROWS_PER_CU, rows_least_keys(head_dim, items)) : splits_wanted(items, item_per_cu(head_dim, pairs > 16 ? 2 : 1), 0);
+  const int want = rows ? splits_wanted(items, ROWS_PER_CU, rows_least_keys(head_dim, items, causal != 0)) : splits_wanted(items, item_per_cu(head_dim, pairs > 16 ? 2 : 1), 0);
   out[0] = widest_split(n_splits, want);
   out[1] = attn_splits(keys, out[0], want);
   out[2] = items;

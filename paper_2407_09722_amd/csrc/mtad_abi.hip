@@ -386,10 +386,13 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
   c->pass_ncg = ncg;
   HIP_TRY(c, launch_embed(1, W[0], c->rd.tok, c->h, rows, d, m->vocab, (const float*)W[1], c->xg, c->ssq, c->rd.pos, c->rope, hd, m->rope_theta,
                           ncg, s));
-  // a prompt chunk of more rows than a row mask and the attention's exchange buffer are made for; its key splits are as many as
-  // that buffer takes (a chunk that needs them to fill the machine is small enough for several)
+  // A prompt chunk of more rows than a row mask and the attention's exchange buffer are made for; its key splits are as many as that
+  // buffer or the products', whichever is the larger, takes.  One split (the attention's buffer alone, from 1024 rows on) left few heads
+  // a chain of all keys in the last rows' workgroups: four narrow layers, 1842 tokens x 6 heads x 128 342 us, with splits 279; 2047 x 4 329, 276.
   const bool prompt = R > c->Rmax;
-  const int prompt_splits = prompt ? imax(1, (int)(c->partial_n / attention_partial_floats(B, R, H, hd, 1))) : 0;
+  const bool wide = prompt && c->gemm_part_n > c->partial_n;  // (no product runs beside attention)
+  float* const exchange = wide ? c->gemm_part : c->partial;
+  const int prompt_splits = prompt ? imax(1, imin(8, (int)((wide ? c->gemm_part_n : c->partial_n) / attention_partial_floats(B, R, H, hd, 1)))) : 0;
   int np = 1;  // partial sums of squares per row currently at ssq
   for (int l = 0; l < m->n_layers; ++l) {
     const void* const* L = W + 1 + 6 * l;
@@ -417,7 +420,7 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
     }
     HIP_TRY(c, launch_gemm_bf16(a, EPI_QKV, tag, s));
     if (prompt)
-      HIP_TRY(c, launch_attention_prompt(c->qkv, H * hd, c->rd, kvv, l, B, R, H, c->partial, prompt_splits, c->xn, ncg, s));
+      HIP_TRY(c, launch_attention_prompt(c->qkv, H * hd, c->rd, kvv, l, B, R, H, exchange, prompt_splits, c->xn, ncg, s));
     else
       HIP_TRY(c, launch_attention(1, c->qkv, H * hd, c->rd, kvv, l, B, R, H, c->partial, imin(32, (c->cfg.max_context + 127) / 128), c->attn_cnt,
                                   c->xn, ncg, s));

@@ -60,8 +60,8 @@ def test_measured_numbers_of_splits(hd, pairs, kv_heads, batch, splits):
     assert _splits(hd, pairs, kv_heads, batch, n_splits=2)[0] == min(2, splits)
 
 
-@pytest.mark.parametrize("hd,pairs,kv_heads,batch,causal,least", [(128, 64, 4, 32, 0, 448), (128, 128, 4, 16, 0, 448), (64, 116, 8, 8, 0, 640), (128, 300, 32, 1, 1, 448),
-                                                                  (64, 8 * 300, 4, 1, 1, 640), (64, 33, 32, 4, 0, 640), (128, 41, 40, 4, 0, 448),
+@pytest.mark.parametrize("hd,pairs,kv_heads,batch,causal,least", [(128, 64, 4, 32, 0, 448), (128, 128, 4, 16, 0, 448), (64, 116, 8, 8, 0, 640), (128, 300, 32, 1, 1, 544),
+                                                                  (64, 8 * 300, 4, 1, 1, 960), (64, 33, 32, 4, 0, 640), (128, 41, 40, 4, 0, 448),
                                                                   (128, 64, 4, 31, 0, 256), (64, 57, 8, 4, 0, 256), (128, 5, 32, 4, 0, 256), (64, 1, 40, 4, 0, 256)])
 def test_short_contexts_are_not_split(hd, pairs, kv_heads, batch, causal, least):
     """Items of many rows that give every other compute unit a workgroup are split later than others."""

@@ -284,6 +284,40 @@ def test_prompt_chunks_of_many_rows(hd, heads, kv_heads, batch, n, prefill_rows)
     assert st["excused"] == 0 and all(e == 2 for e in st["eta"])
 
 
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,n", [
+    (128, 3, 3, 1, 1300),      # 63 items, up to five splits, partial results in the products' buffer
+    (64, 8, 2, 1, 1290),       # 162 items of four query heads
+])
+def test_prompt_key_splits(hd, heads, kv_heads, batch, n):
+    """Prompts of few heads cut their keys: the caches against chunks of 16 rows, whose attention is the trees'."""
+    from paper_2407_09722_amd import binding as mb
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    ts = si.ModelShape(3, heads * hd, heads, kv_heads, hd, 352, 512, "bf16")
+    m = DeviceModel(ts, _weights(ts, 43, "target", boost=2.0), DEV)
+    prompt = np.random.default_rng(n).integers(0, ts.vocab, (batch, n + 1)).astype(np.int32)
+    print(f"prompt splits hd {hd} heads {heads}/{kv_heads} batch {batch} n {n}", flush=True)
+    caches = []
+    for least in (True, False):
+        eng = Engine(m, m, batch=batch, gamma=2, beam=2, mode="mtad", max_context=n + 64, prefill_rows=16)
+        if least:
+            lo, hi = 0, eng.workspace.numel() // 256
+            while hi - lo > 1:
+                mid = (lo + hi) // 2
+                try:
+                    mb.mtad_bind_workspace(eng.ctx, eng.workspace[:256 * mid])
+                    hi = mid
+                except mb.MtadError:
+                    lo = mid
+            mb.mtad_bind_workspace(eng.ctx, eng.workspace[:256 * hi])
+        eng.prefill(prompt)
+        torch.cuda.synchronize()
+        caches.append([eng.tkv.gather(s, n) for s in range(batch)])
+        eng.close()
+    for old, new in zip(*caches):
+        for a, b in zip(old, new):
+            assert np.all(np.abs(a - b) <= 2e-3 * np.maximum(1, np.abs(b)))   # two roundings to half precision (2^-11 each) and chunk orders
+
+
 def test_prompt_chunk_past_the_cache_end():
     """Tokens that do not fit are not stored: the status bit is set, the length stops at the capacity, and what fits is what a
     prompt of just those tokens leaves."""
