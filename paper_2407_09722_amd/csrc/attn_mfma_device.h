@@ -107,9 +107,9 @@ __device__ __forceinline__ int token_index(const KvView& kv, int seq, int pos) {
 // Keys of sequence seq (committed + speculative) and the key splits used for it.  Every workgroup that works on the
 // sequence derives the same numbers: as many splits as the launch offers, but a split is worth its
 // exchange only if it gives every wave a tile (measured at 512 and 2048 keys).  want_splits = fill_splits +
-// (more_splits << 8): fill_splits give every compute unit a workgroup; more_splits, offered when that leaves some
-// compute units with two workgroups and the rest with one, fill every resident slot and are taken only where every
-// wave still gets four tiles.  Bits 16 on: the tiles below which a sequence is not split at all.
+// (more_splits << 8) + (least_tiles << 16): fill_splits give every compute unit a workgroup; more_splits, offered when that leaves
+// some compute units with two workgroups and the rest with one, fill them more evenly and are taken only where every
+// wave still gets four tiles; a sequence of less than least_tiles tiles is not split at all.
 constexpr int ATTN_WAVES = 4;
 __device__ __forceinline__ int attn_keys(const KvView& kv, const RowDesc& rd, int seq, bool causal = false) {
   const int nspec = max(0, causal ? rd.nspec[seq] : min(rd.nspec[seq], 64));
