@@ -23,9 +23,9 @@ struct AcceptView {
 };
 
 hipError_t launch_draft_rows(const RowDesc& rd, const int32_t* len, BeamView hist, const int32_t* cu_tok, const int32_t* cu_cnt,
-                             int step, int B, int R, int gamma, int beam, int cap, uint32_t* status, hipStream_t s);
+                             int step, int B, int R, int gamma, int beam, int cap, uint32_t* status, uint32_t* epoch, hipStream_t s);
 hipError_t launch_verify_rows(const RowDesc& rd, const int32_t* len, const int32_t* root_tok, TreeView tree, int B, int cap,
-                              uint32_t* status, hipStream_t s);
+                              uint32_t* status, uint32_t* epoch, hipStream_t s);
 hipError_t launch_prefill_rows(const RowDesc& rd, const int32_t* len, const int32_t* tokens, int n, int c0, int B, int R, int cap,
                                uint32_t* status, hipStream_t s);
 hipError_t launch_advance_len(int32_t* len, const int32_t* nspec, int B, int cap, hipStream_t s);

@@ -37,8 +37,9 @@ __device__ __forceinline__ uint64_t chain_bits(int r) { return (r >= 63) ? ~0ull
 
 __global__ void draft_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, BeamView hist, const int32_t* __restrict__ cu_tok,
                                   const int32_t* __restrict__ cu_cnt, int step, int B, int R, int gamma, int beam, int cap,
-                                  uint32_t* __restrict__ status) {
+                                  uint32_t* __restrict__ status, uint32_t* __restrict__ epoch) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx == 0 && epoch) *epoch += 1;  // the pass's number
   if (idx >= B * R) return;
   const int s = idx / R, r = idx % R;
   int cnt = cu_cnt[s];
@@ -85,16 +86,17 @@ __global__ void draft_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, B
 }
 
 hipError_t launch_draft_rows(const RowDesc& rd, const int32_t* len, BeamView hist, const int32_t* cu_tok, const int32_t* cu_cnt,
-                             int step, int B, int R, int gamma, int beam, int cap, uint32_t* status, hipStream_t s) {
+                             int step, int B, int R, int gamma, int beam, int cap, uint32_t* status, uint32_t* epoch, hipStream_t s) {
   hipLaunchKernelGGL(draft_rows_kernel, dim3((B * R + 63) / 64), dim3(64), 0, s, rd, len, hist, cu_tok, cu_cnt, step, B, R, gamma,
-                     beam, cap, status);
+                     beam, cap, status, epoch);
   return hipGetLastError();
 }
 
 __global__ void verify_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, const int32_t* __restrict__ root_tok, TreeView tree,
-                                   int B, int cap, uint32_t* __restrict__ status) {
+                                   int B, int cap, uint32_t* __restrict__ status, uint32_t* __restrict__ epoch) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int M = tree.M;
+  if (idx == 0 && epoch) *epoch += 1;  // the pass's number
   if (idx >= B * M) return;
   const int s = idx / M, r = idx % M;
   const int n = len[s];
@@ -111,8 +113,8 @@ __global__ void verify_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, 
 }
 
 hipError_t launch_verify_rows(const RowDesc& rd, const int32_t* len, const int32_t* root_tok, TreeView tree, int B, int cap,
-                              uint32_t* status, hipStream_t s) {
-  hipLaunchKernelGGL(verify_rows_kernel, dim3((B * tree.M + 63) / 64), dim3(64), 0, s, rd, len, root_tok, tree, B, cap, status);
+                              uint32_t* status, uint32_t* epoch, hipStream_t s) {
+  hipLaunchKernelGGL(verify_rows_kernel, dim3((B * tree.M + 63) / 64), dim3(64), 0, s, rd, len, root_tok, tree, B, cap, status, epoch);
   return hipGetLastError();
 }
 

@@ -6,6 +6,7 @@
 #include "common.h"
 #include "gemm.h"
 #include "flow.h"
+#include "relay.h"
 
 #include <math.h>
 #include <mutex>
@@ -48,8 +49,9 @@ struct mtad_ctx {
   RowDesc rd;
   uint32_t* status;
   int n_cus;                // compute units of the device
-  // one-launch pass (kernels_flow.hip) for bf16 passes of at most FLOW_MAX_ROWS rows: 0 never, 1 where a layer's
-  // weights are large enough for the stream to matter (the default), 2 always
+  // passes of at most 8 rows in one launch: 0 never; 1 (the default) small models' where that is the faster (kernels_relay.hip), and bf16
+  // passes where a layer's weights are large enough for the stream to matter (kernels_flow.hip); 2 bf16 passes
+  // always, that way
   int flow_on;
   bf16_t *flow_xg, *flow_xattn, *flow_xffn;  // per-step versions of the activation terms (see flow.h)
   float *flow_ssq, *flow_q;
@@ -59,6 +61,11 @@ struct mtad_ctx {
 #ifdef MTAD_FLOW_PROFILE
   unsigned long long* flow_prof;
 #endif
+  uint64_t* relay_mail;  // one-launch pass of small models (relay.h); null: the workspace has no room for it
+  size_t relay_mail_n;
+  uint32_t* relay_sync;
+  unsigned relay_patience;  // ticks of the 100 MHz clock after which its workgroups count out those that have not started
+  int relay_absent;         // (tests: so many of its workgroups never start)
   // set by mtad_verify_tree around its pass: the logsumexp kernel of a bf16 pass then also gathers logp_cond
   const mtad_tree* gather_tree;
   float* gather_out;
@@ -97,6 +104,16 @@ int shape_ok(const mtad_model* m) {
 // would double the workspace for prompts longer than 4096 tokens.
 constexpr int PROMPT_PASS_ROWS = 4096;
 
+// The one-launch pass of small models, B sequences of R rows: fills in what depends on shapes alone and returns its workgroups, 0 where
+// the steps are launched one by one.
+int relay_shape(RelayArgs& a, const mtad_model* m, int B, int R, int max_context) {
+  memset(&a, 0, sizeof(a));
+  a.n_layers = m->n_layers; a.d = m->d_model; a.f = m->d_ffn; a.H = m->n_heads; a.KVH = m->n_kv_heads; a.vocab = m->vocab;
+  a.eps = m->rms_eps;
+  a.rows = B * R; a.Rseq = R; a.B = B;
+  return relay_plan(a, m->dtype, m->head_dim, max_context);
+}
+
 struct Carver {
   size_t off = 0;
   char* base;
@@ -110,8 +127,8 @@ struct Carver {
 };
 
 // Lays the workspace out at `base` (null: only its size) for prompt chunks of prompt_rows rows per sequence; returns its bytes.
-// roomy: with room for the ranges of the many-row products' cut reductions and for 256 rows of mtad_k_gemm's plane input there.
-size_t carve(mtad_ctx* c, char* base, int prompt_rows, bool roomy) {
+// relay: with what the one-launch pass of small models hands on.  roomy: with room for the ranges of the many-row products' cut reductions and for 256 rows of mtad_k_gemm's plane input there.
+size_t carve(mtad_ctx* c, char* base, int prompt_rows, bool roomy, bool relay) {
   c->prompt_rows = prompt_rows;
   const mtad_model &t = c->tshape, &d = c->dshape;
   const size_t rows = (size_t)c->cfg.batch * c->Rmax;
@@ -175,6 +192,21 @@ size_t carve(mtad_ctx* c, char* base, int prompt_rows, bool roomy) {
     c->flow_prof = k.take<unsigned long long>((size_t)4 * 100000);
 #endif
   }
+  c->relay_mail = nullptr;
+  c->relay_sync = nullptr;
+  c->relay_mail_n = 0;
+  if (relay) {  // both models' words at the most rows that a pass in one launch has; two layers in turn, and once more for a pass that starts over
+    for (const mtad_model* m : {&t, &d})
+      for (int R = 1; R <= c->Rmax && c->cfg.batch * R <= RELAY_MAX_ROWS; ++R) {
+        RelayArgs a;
+        if (relay_shape(a, m, c->cfg.batch, R, c->cfg.max_context) < 1) continue;
+        c->relay_mail_n = imax64(c->relay_mail_n, (size_t)4 * relay_mail_words(a.rows, a.d, a.f, a.H, a.KVH, m->head_dim, a.splits, nullptr));
+      }
+    if (c->relay_mail_n) {
+      c->relay_mail = k.take<uint64_t>(c->relay_mail_n);
+      c->relay_sync = k.take<uint32_t>(RELAY_SYNC_WORDS);
+    }
+  }
   c->qkv = k.take<float>(imax64(rows * qkv, prompt * hhd));  // float32 models: q, k and v; bf16 models: q
   c->dlogits = k.take<float>((size_t)c->cfg.batch * c->draft_rows * d.vocab);
   c->qrows = k.take<float>(c->cfg.beam == 1 ? (size_t)c->cfg.batch * c->cfg.gamma * d.vocab : 1);
@@ -198,9 +230,9 @@ size_t carve(mtad_ctx* c, char* base, int prompt_rows, bool roomy) {
 bool carve_within(mtad_ctx* c, char* base, size_t bytes) {
   const int least = imin(c->prompt_best, c->cfg.prefill_rows);
   for (int p = c->prompt_best;; p = imax(p / 2, least)) {
-    for (const bool roomy : {true, false})
-      if (carve(c, nullptr, p, roomy) <= bytes) {
-        carve(c, base, p, roomy);
+    for (const int kind : {3, 2, 0})  // (bit 1: roomy, bit 0: relay)
+      if (carve(c, nullptr, p, kind & 2, kind & 1) <= bytes) {
+        carve(c, base, p, kind & 2, kind & 1);
         return true;
       }
     if (p == least) return false;
@@ -444,8 +476,34 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
   return logits ? lm_head(c, m, rows, logits, lse, s) : MTAD_OK;
 }
 
+// The whole pass of a small model in one launch; the row inputs (rd) and its number (relay_sync[0]) are there.
+int relay_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, RelayArgs& a, int groups, hipStream_t s) {
+  memcpy(a.w, m->weights, sizeof(void*) * (size_t)(3 + 6 * m->n_layers));
+  for (int i = 0; i < m->head_dim / 2; ++i) a.inv_freq[i] = pow((double)m->rope_theta, -(double)i / (double)(m->head_dim / 2));
+  a.ncg = c->pass_ncg = a.rows < 2 ? 0 : 1;
+  a.kv = view_of(kv, m);
+  a.rd = c->rd;
+  a.mail.words = c->relay_mail;
+  relay_mail_words(a.rows, a.d, a.f, a.H, a.KVH, m->head_dim, a.splits, &a.mail);
+  a.sync = c->relay_sync; a.status = c->status;
+  a.h = c->h; a.xg = (bf16_t*)c->xg; a.ssq = c->ssq;
+  a.patience = c->relay_patience;
+  a.present = imax(1, groups - c->relay_absent);
+  c->pass_np = m->d_model / 16;
+  HIP_TRY(c, launch_relay(a, m->dtype, m->head_dim, groups, s));
+  return MTAD_OK;
+}
+
 // The pass, followed by final norm + lm_head + row logsumexp when `logits` is given.
 int decoder_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStream_t s, float* logits, float* lse) {
+  if (logits && c->flow_on == 1 && c->relay_mail) {
+    RelayArgs a;
+    const int groups = relay_shape(a, m, c->cfg.batch, R, c->cfg.max_context);
+    if (groups > 0 && (size_t)4 * relay_mail_words(a.rows, a.d, a.f, a.H, a.KVH, m->head_dim, a.splits, nullptr) <= c->relay_mail_n) {
+      const int rc = relay_pass(c, m, kv, a, groups, s);
+      return rc ? rc : lm_head(c, m, a.rows, logits, lse, s);
+    }
+  }
   if (m->dtype == 1) return decoder_pass_bf16(c, m, kv, R, s, logits, lse);
   int rc = decoder_pass_f32(c, m, kv, R, s, !logits);
   if (rc || !logits) return rc;
@@ -527,9 +585,10 @@ int mtad_create(mtad_ctx** out, const mtad_config* cfg, const mtad_model* target
     return MTAD_ESHAPE;
   }
   if (target->dtype == 1 || draft->dtype == 1) c->prompt_best = imax(c->cfg.prefill_rows, imin(PROMPT_PASS_ROWS / cfg->batch, cfg->max_context));
+  c->relay_patience = 20000;  // 0.2 ms: all of them have been seen at work after one or two layers
   c->flow_on = 1;
   if (const char* e = getenv("MTAD_FUSED_PASS")) c->flow_on = atoi(e) < 0 ? 0 : (atoi(e) > 2 ? 2 : atoi(e));
-  c->ws_need = carve(c, nullptr, c->prompt_best, true);
+  c->ws_need = carve(c, nullptr, c->prompt_best, true, true);
   *out = c;
   return MTAD_OK;
 }
@@ -555,6 +614,8 @@ int mtad_bind_workspace(mtad_ctx* c, void* buf, size_t bytes) {
   hipError_t e = hipMemset(c->status, 0, 256);
   if (e == hipSuccess) e = hipMemset(c->attn_cnt, 0, sizeof(int) * c->attn_cnt_n);
   if (e == hipSuccess) e = hipMemset(c->gemm_cnt, 0, sizeof(int) * (size_t)c->gemm_cnt_n);
+  if (e == hipSuccess && c->relay_mail) e = hipMemset(c->relay_mail, 0, sizeof(uint64_t) * c->relay_mail_n);
+  if (e == hipSuccess && c->relay_sync) e = hipMemset(c->relay_sync, 0, sizeof(uint32_t) * RELAY_SYNC_WORDS);
   if (e != hipSuccess) {
     c->last_hip = (int)e;
     return MTAD_EHIP;
@@ -618,7 +679,7 @@ int mtad_draft_beam_step(mtad_ctx* c, const mtad_model* draft, mtad_kv* dkv, mta
   const int R = (step == 0) ? gamma + 1 : beam;
   const BeamView hv{hist->tok, hist->parent, hist->cum_logq};
   HIP_TRY(c, launch_draft_rows(c->rd, dkv->len, hv, st->catchup_tok, st->catchup_cnt, step, B, R, gamma, beam,
-                               dkv->page_size * dkv->max_pages, c->status, s));
+                               dkv->page_size * dkv->max_pages, c->status, c->relay_sync, s));
   c->lse_later = draft->dtype == 1 && c->warp_k == 0 && beam > 1;  // (warping and a saved row of log q read them first)
   const bool lse_later = c->lse_later;
   int rc = decoder_pass(c, draft, dkv, R, s, c->dlogits, c->lse);
@@ -651,7 +712,7 @@ int mtad_verify_tree(mtad_ctx* c, const mtad_model* target, mtad_kv* tkv, const 
   if (tree->M < 1 || tree->M > c->Rmax) return MTAD_ESHAPE;
   hipStream_t s = (hipStream_t)stream;
   const int B = c->cfg.batch, M = tree->M;
-  HIP_TRY(c, launch_verify_rows(c->rd, tkv->len, root_tok, tview(tree), B, tkv->page_size * tkv->max_pages, c->status, s));
+  HIP_TRY(c, launch_verify_rows(c->rd, tkv->len, root_tok, tview(tree), B, tkv->page_size * tkv->max_pages, c->status, c->relay_sync, s));
   c->gather_tree = c->warp_k > 0 ? nullptr : tree;  // warped rows are gathered after the warp
   c->gather_out = c->warp_k > 0 ? nullptr : logp_cond;
   int rc = decoder_pass(c, target, tkv, M, s, logits, row_lse);
@@ -722,6 +783,16 @@ int mtad_kv_commit(mtad_ctx* c, mtad_kv* tkv, mtad_kv* dkv, const mtad_tree* tre
 }
 
 // ---- component entry points (include/mtad_kernels.h) ------------------------------------------------------------
+
+// For the tests of the small models' one-launch pass: the workgroups that a pass of R rows a sequence of the target (draft: 1) takes, 0 where
+// it is not of that kind.  From now on `absent` of them never start, and the others count them out after `patience` ticks of 10 ns (0: as before).
+extern "C" int mtad_test_relay(mtad_ctx* c, int draft, int R, int absent, unsigned patience) {
+  if (!c || R < 1 || absent < 0) return MTAD_EINVAL;
+  c->relay_absent = absent;
+  if (patience) c->relay_patience = patience;
+  RelayArgs a;
+  return relay_shape(a, draft ? &c->dshape : &c->tshape, c->cfg.batch, R, c->cfg.max_context);
+}
 
 #ifdef MTAD_FLOW_PROFILE
 extern "C" void* mtad_flow_profile(mtad_ctx* c) { return c ? c->flow_prof : nullptr; }

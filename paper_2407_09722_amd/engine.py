@@ -103,7 +103,7 @@ class Engine:
         self.ctx = mb.mtad_create(cfg, target.desc, draft.desc)
         self.workspace = torch.empty(mb.mtad_workspace_bytes(self.ctx), dtype=torch.uint8, device=device)
         mb.mtad_bind_workspace(self.ctx, self.workspace)
-        if fused_pass is not None:                          # 0 / False: one kernel per step; 1: one launch for large models; 2: always
+        if fused_pass is not None:                          # 0 / False: one kernel per step; 1: one launch where it is the faster; 2: bf16 always
             mb.mtad_set_fused_pass(self.ctx, int(fused_pass))
         if warp is not None:                                # (top_k, top_p): both models' distributions are warped
             mb.mtad_set_warp(self.ctx, warp[0], warp[1])

@@ -1,0 +1,177 @@
+"""The decoder pass of a small model in one launch, at the edges of its units, splits and waits."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+from tests._parity import run_pair
+from tests.test_gpu_attention import TOLERANCE, _expected, _run
+from tests.test_gpu_path import _weights
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _relay(eng, draft, rows, absent=0, patience=0):
+    """Workgroups of such a pass (0: a launch a step); absent ones never start, and are counted out after patience * 10 ns."""
+    from paper_2407_09722_amd import binding as mb
+    return mb.lib().mtad_test_relay(eng.ctx, draft, rows, absent, C.c_uint(patience))
+
+
+@pytest.mark.parametrize("dtype,heads,kv_heads,hd,ffn,layers,batch,gamma,beam,n", [
+    ("fp32", 1, 1, 64, 8, 1, 1, 1, 1, 1),        # one layer, a reduction of 8 terms, an empty cache
+    ("fp32", 2, 1, 64, 1032, 3, 1, 6, 1, 40),    # 129 strips of gate and up: the last unit has one of two
+    ("fp32", 6, 2, 64, 344, 2, 1, 7, 1, 40),     # 8 rows, 24 pairs a KV head
+    ("fp32", 3, 3, 128, 200, 2, 4, 1, 1, 70),    # 4 sequences of 2 rows
+    ("fp32", 2, 1, 128, 344, 2, 1, 5, 2, 520),   # draft steps of two beams; a second split of the keys
+    ("bf16", 1, 1, 64, 32, 1, 1, 1, 1, 1),
+    ("bf16", 6, 2, 64, 1056, 3, 1, 7, 1, 40),    # 132 strips of gate and up; 33 k tiles of down over 8 waves
+    ("bf16", 12, 12, 64, 160, 2, 8, 1, 1, 30),   # 144 strips of q, k and v; draft steps of 8 sequences
+    ("bf16", 5, 1, 128, 352, 2, 2, 3, 2, 270),   # 20 pairs a KV head: three units of 8, 8 and 4; a second split
+    ("bf16", 2, 2, 128, 96, 40, 1, 4, 3, 20),    # many layers
+])
+def test_pass_against_the_oracle(dtype, heads, kv_heads, hd, ffn, layers, batch, gamma, beam, n):
+    """Every iteration, logits and cache, of a target whose passes are of that kind; the draft's beam steps likewise."""
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    ts = si.ModelShape(layers, heads * hd, heads, kv_heads, hd, ffn, 512, dtype)
+    ds = si.ModelShape(1, 64, 1, 1, 64, 160, 512, dtype)
+    wt, wd = _weights(ts, 61, "target", boost=2.0), _weights(ds, 61, "draft", boost=2.0)
+    prompt = np.random.default_rng(n).integers(0, ts.vocab, (batch, n)).astype(np.int32)
+    print(f"one launch {dtype} {heads}/{kv_heads} x {hd} ffn {ffn} layers {layers} batch {batch} gamma {gamma} beam {beam} n {n}", flush=True)
+    tm, dm = DeviceModel(ts, wt, DEV), DeviceModel(ds, wd, DEV)
+    eng = Engine(tm, dm, batch=batch, gamma=gamma, beam=beam, mode="mtad", max_context=n + 64, prefill_rows=16, device=DEV)
+    assert _relay(eng, 0, 1 + gamma) > 0 or (1 + gamma) * batch > 8
+    assert _relay(eng, 1, beam) > 0 or beam * batch > 8
+    eng.close()
+    st = run_pair(ts, ds, wt, wd, prompt, 2 * gamma + 2, gamma=gamma, beam=beam, mode="mtad", tau=0.0, seed=5, check_kv=True, prefill_rows=16, fused_pass=1,
+                  device_models=(tm, dm))
+    assert st["excused"] == 0 and all(e == gamma for e in st["eta"])
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("hd,heads,kv_heads,batch,gamma,beam,n", [
+    (64, 4, 4, 1, 1, 1, 9000),       # eight splits of several rounds of blocks
+    (128, 2, 2, 1, 3, 2, 4100),      # 7 rows
+    (64, 4, 2, 2, 3, 1, 1025),       # a split of one key
+    (128, 6, 2, 4, 1, 1, 257),       # empty and nearly empty caches beside a second split
+])
+def test_long_caches(dtype, hd, heads, kv_heads, batch, gamma, beam, n):
+    """Splits of the keys, their merge, running maxima that move from block to block, sequences shorter than a split."""
+    print(f"long {dtype} hd {hd} heads {heads}/{kv_heads} batch {batch} rows {1 + gamma * beam} n {n}", flush=True)
+    r = np.random.default_rng(heads + n)
+    keys, values = np.zeros((batch, n, kv_heads, hd), np.float32), r.standard_normal((batch, n, kv_heads, hd)).astype(np.float16).astype(np.float32)
+    if dtype == "fp32":
+        keys[..., hd // 2 - 2] = r.standard_normal((batch, n, kv_heads)) * 12 + np.arange(n)[None, :, None] * (40 / n) * r.choice([-1, 0, 1], (batch, 1, kv_heads))
+    else:  # whole numbers, exact in the cache: two octaves' worth of steps up and down
+        keys[..., hd // 2 - 1] = 1000
+        keys[..., hd // 2 - 2] = r.integers(0, 4, (batch, n, kv_heads)) + np.round(np.arange(n)[None, :, None] * (40 / n) * r.choice([-1, 0, 1], (batch, 1, kv_heads)))
+    lens = [n, 0, 1, n - 64][:batch]
+    got = _run(heads, kv_heads, hd, batch, gamma, beam, lens, keys, values, 1, dtype)
+    err = np.abs(got - _expected(heads, kv_heads, hd, lens, keys, values, 1 + gamma * beam)).max()
+    print(f"largest error {err:.2e}", flush=True)
+    assert err < (1e-5 if dtype == "fp32" else TOLERANCE)
+
+
+def _engine(dtype, hd=64, rows=4):
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    shape = si.ModelShape(3, 4 * hd, 4, 2, hd, 352, 512, dtype)
+    m = DeviceModel(shape, _weights(shape, 7, "target", boost=2.0), DEV)
+    eng = Engine(m, m, batch=1, gamma=rows - 1, beam=1, mode="mtad", max_context=700, device=DEV, fused_pass=1)
+    eng.prefill(np.random.default_rng(2).integers(0, 512, (1, 600)).astype(np.int32))
+    eng.draft_phase()
+    eng.verify_phase()
+    torch.cuda.synchronize()
+    return eng
+
+
+def _verify(eng, absent=0, patience=20000):
+    """A pass over other tokens, with all workgroups (what it leaves behind is wrong for the one that is looked at), then that one."""
+    _relay(eng, 0, 4, 0, 20000)
+    eng.t_tok.bitwise_xor_(1)
+    eng.verify_phase()
+    other = eng.logits.clone()
+    eng.t_tok.bitwise_xor_(1)
+    _relay(eng, 0, 4, absent, patience)
+    eng.verify_phase()
+    assert not torch.equal(other, eng.logits)
+    torch.cuda.synchronize()
+    return eng.logits.cpu(), eng.tkv.k.cpu(), eng.tkv.v.cpu()
+
+
+@pytest.mark.parametrize("dtype,hd", [("fp32", 64), ("fp32", 128), ("bf16", 64), ("bf16", 128)])
+def test_workgroups_that_do_not_start(dtype, hd):
+    """Those that are there count the others out and do all units themselves, bit for bit the same; one is enough; then all are back."""
+    from paper_2407_09722_amd import binding as mb
+    eng = _engine(dtype, hd)
+    want = _verify(eng)
+    n = _relay(eng, 0, 4)
+    assert n > 8
+    for absent in (1, n // 2, n - 1, 0, n - 3):
+        print(f"{dtype} {hd}: {absent} of {n} absent", flush=True)
+        got = _verify(eng, absent, 300)                 # 3 us
+        assert mb.mtad_device_status(eng.ctx) == 0
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), absent
+    for patience in (1, 30, 1000, 3000):                # all there, but some have waited too long for others at some place of the pass
+        for _ in range(20):
+            got = _verify(eng, 0, patience)
+            assert torch.equal(got[0], want[0]), patience
+    assert mb.mtad_device_status(eng.ctx) == 0
+    eng.close()
+
+
+def test_a_pass_that_is_given_up():
+    """A workgroup missing and nobody allowed to count it out: the pass ends all the same, the status says so, and the next one is right."""
+    from paper_2407_09722_amd import binding as mb
+    eng = _engine("bf16")
+    want = _verify(eng)
+    _relay(eng, 0, 4, 1, 0xFFFFFFFF)
+    eng.verify_phase()
+    bits = C.c_uint32()
+    mb.lib().mtad_device_status(eng.ctx, C.byref(bits), None)
+    assert bits.value == 8
+    assert all(torch.equal(a, b) for a, b in zip(_verify(eng), want))
+    eng.close()
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_captured_iterations(dtype):
+    """Iterations replayed from a graph, with eager work between, and two engines on streams of their own at the same time."""
+    from paper_2407_09722_amd import binding as mb
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    shape = si.ModelShape(2, 256, 4, 2, 64, 352, 512, dtype)
+    draft = si.ModelShape(1, 64, 1, 1, 64, 160, 512, dtype)
+    tm, dm = DeviceModel(shape, _weights(shape, 9, "target"), DEV), DeviceModel(draft, _weights(draft, 9, "draft"), DEV)
+    prompt = np.random.default_rng(4).integers(0, 512, (2, 33)).astype(np.int32)
+
+    def engine():
+        e = Engine(tm, dm, batch=2, gamma=3, beam=3, mode="mtad", max_context=128, device=DEV, fused_pass=1)
+        e.prefill(prompt)
+        torch.cuda.synchronize()
+        return e
+
+    eager, want = engine(), []
+    assert _relay(eager, 0, 4) > 0 and _relay(eager, 1, 3) > 0
+    for _ in range(6):
+        eager.iteration(0.3, sample_beam=True, seed=9)
+        torch.cuda.synchronize()
+        want.append((eager.emitted(), eager.logits.cpu()))
+    rep = engine()
+    graph = rep.capture_iteration(0.3, sample_beam=True, seed=9)
+    scratch = torch.zeros(1 << 16, device=DEV)
+    for i in range(6):
+        graph.replay()
+        scratch.add_(1.0)
+        torch.cuda.synchronize()
+        assert rep.emitted() == want[i][0] and torch.equal(rep.logits.cpu(), want[i][1]), i
+    pair = [(engine(), torch.cuda.Stream()) for _ in range(2)]
+    for i in range(6):
+        for e, s in pair:
+            e.iteration(0.3, sample_beam=True, seed=9, stream=s)
+        torch.cuda.synchronize()
+        for e, _ in pair:
+            assert e.emitted() == want[i][0] and torch.equal(e.logits.cpu(), want[i][1]), i
+    for e in (eager, rep, pair[0][0], pair[1][0]):
+        assert mb.mtad_device_status(e.ctx) == 0
+        e.close()
