@@ -150,7 +150,7 @@ size_t mtad_workspace_bytes(const mtad_ctx *ctx);
 int mtad_bind_workspace(mtad_ctx *ctx, void *device_buf, size_t bytes);
 /* Passes of at most 8 rows (all sequences together) can run every product and the attention of every layer in ONE kernel
  * launch instead of one per step (same arithmetic; the form every larger pass takes).  on = 0: never; 1 (the default): where it is the
- * faster form, for models of small layers (float32 and bf16) and for bf16 passes whose layers hold at least 64 MiB of
+ * faster form, for models of small layers (float32 and bf16) and for bf16 passes of 4 rows and more whose layers hold at least 64 MiB of
  * weights; 2: for every bf16 pass, as the latter.  Waits inside a one-launch pass are bounded: one that gives up sets status
  * bit 3 and the pass runs to its end.  The environment variable MTAD_FUSED_PASS=0|1|2 sets the same at context creation. */
 int mtad_set_fused_pass(mtad_ctx *ctx, int32_t on);

@@ -50,7 +50,7 @@ struct mtad_ctx {
   uint32_t* status;
   int n_cus;                // compute units of the device
   // passes of at most 8 rows in one launch: 0 never; 1 (the default) small models' where that is the faster (kernels_relay.hip), and bf16
-  // passes where a layer's weights are large enough for the stream to matter (kernels_flow.hip); 2 bf16 passes
+  // passes of 4 rows and more where a layer's weights are large enough for the stream to matter (kernels_flow.hip); 2 bf16 passes
   // always, that way
   int flow_on;
   bf16_t *flow_xg, *flow_xattn, *flow_xffn;  // per-step versions of the activation terms (see flow.h)
@@ -404,11 +404,16 @@ int decoder_pass_bf16(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R
   const void* const* W = m->weights;
   const int tail = 1 + 6 * m->n_layers;
   if (c->flow_on && rows <= FLOW_MAX_ROWS && R <= c->Rmax && m->n_layers <= FLOW_MAX_LAYERS) {
-    // Steps hand over through counters and flags in memory, about as dear as a kernel boundary each; what the one launch
-    // gains is the weights requested across those handovers, which counts where a layer streams tens of megabytes
-    // (7B-shaped target, 405 MB per layer: pass 2.78 -> 2.61 ms) and not for small models (two 14 MB layers: 95 -> 106 us).
+    // Steps hand over through counters and flags in memory, about as dear as a kernel boundary each; what the one launch gains is
+    // the weights requested across those handovers, which counts where a layer streams tens of megabytes and its steps' kernels
+    // have more to do than to stream them.  us, a launch a step / one launch, 500 tokens: 16 layers of 32 heads x 128, ffn 11008
+    // (405 MB a layer) one row 1276 / 1377, 3 rows 1308 / 1418, 5 rows 1338 / 1296, 8 rows 1385 / 1338, 4 x 2 rows 1470 / 1387; 24 of 20 x 128, 6912
+    // (159 MB) 1113 / 1176, 1144 / 1220, 1294 / 1211, 1364 / 1263, 1450 / 1331; 24 of 16 x 128, 4096 (84 MB) 819 / 861, 843 / 892, 917 / 905, 963 / 933,
+    // 1017 / 953.  With attention between two launches a layer it loses: 24 of 32 on 4 x 64, 5632, 3 rows 905 / 1067, 5 rows 963 / 1005, 16 of 32 on
+    // 8 x 128, 11008, 5 rows 1264 / 1295.  (That is more than 16 query heads x rows a KV head.)
     const size_t layer_bytes = 2 * ((size_t)qkvw * d + (size_t)d * H * hd + (size_t)3 * d * f);
-    if (c->flow_on >= 2 || layer_bytes >= ((size_t)64 << 20)) return flow_pass(c, m, kv, R, s, logits, lse);
+    const bool streams = rows >= 4 && H / m->n_kv_heads * R <= 16 && layer_bytes >= ((size_t)64 << 20);
+    if (c->flow_on >= 2 || streams) return flow_pass(c, m, kv, R, s, logits, lse);
   }
   // one kernel per step, 2 rows or more: activations in operand-fragment order (act_offset), whole cache lines per
   // fragment, without the unused row slots up to 24 rows (C3 verify, 5 rows: 3.20 ms on planes, 3.14 ms with 8-row

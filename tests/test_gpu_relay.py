@@ -175,3 +175,26 @@ def test_captured_iterations(dtype):
     for e in (eager, rep, pair[0][0], pair[1][0]):
         assert mb.mtad_device_status(e.ctx) == 0
         e.close()
+
+
+@pytest.mark.parametrize("heads,kv_heads,rows,batch", [(16, 16, 3, 1), (16, 16, 4, 1), (16, 16, 2, 2), (16, 4, 4, 1), (16, 4, 5, 1), (16, 2, 2, 1)])
+def test_large_layers(heads, kv_heads, rows, batch):
+    """Layers of 64 MiB and more: 4 rows or more with at most 16 query heads x rows a KV head take the other one-launch pass, the rest the
+    steps; either side of both lines is what both forms give."""
+    from paper_2407_09722_amd import binding as mb
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    shape = si.ModelShape(1, 2048, heads, kv_heads, 128, 4608, 512, "bf16")
+    m = DeviceModel(shape, si.make_weights(shape, 5, "target", threads=8), DEV)
+    eng = Engine(m, m, batch=batch, gamma=rows - 1, beam=1, mode="mtad", max_context=300, device=DEV)
+    eng.prefill(np.random.default_rng(2).integers(0, 512, (batch, 200)).astype(np.int32))
+    eng.draft_phase()
+    got = []
+    for on in (0, 1, 2):
+        mb.mtad_set_fused_pass(eng.ctx, on)
+        eng.verify_phase()
+        torch.cuda.synchronize()
+        got.append(eng.logits.cpu().double())
+    for other in (got[0], got[2]):  # operands of two bf16 terms, 2^-17, through two products a row
+        assert (got[1] - other).norm() <= 2**-15 * other.norm()
+    assert mb.mtad_device_status(eng.ctx) == 0
+    eng.close()
