@@ -30,6 +30,10 @@
 // 125; 1.16 PFLOP/s, hi and lo counted) the matrix instructions alone take 88 us, the activations' way to LDS 61, the weights' 60,
 // launch, epilogue and barriers 24.  At 2047 rows TALL runs at 1.5 PFLOP/s while all compute units have a tile (a library product of
 // 16384^3 reaches 1.58): 22016 x 4096 622 -> 537 us, 27648 x 5120 898 -> 811, 12288 x 4096 346 -> 329.
+//   * MANY: side-by-side tiles of more than one a compute unit are taken by workgroups that stay (a tile's requests before the results of the
+//     one before have left; the launch's arguments, row factors and ring filled once).  A workgroup a tile / workgroups that stay, us:
+//     4092 rows, 11264 x 2048 309 / 287; 2047 rows, 22016 x 4096 537 / 524, 12288 x 4096 308 / 304; 2036 rows, 27648 x 5120 811 / 803, 15360 x
+//     5120 451 / 450.  Of one tile a compute unit the same code is 2 % slower (2048 x 2048 71 / 72, 2048 x 5632 156 / 162): it keeps its own.
 #include "common.h"
 #include "gemm.h"
 #include "gemm_device.h"
@@ -237,12 +241,20 @@ struct PairEpilogue {
   }
 };
 
-template <int A, int B_, bool TALL, int EPI>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_dma_kernel(GemmArgs a, int tiles_n, int tiles_m, int KS) {
+// the kernel's first argument, to be read from memory again
+__device__ __forceinline__ const GemmArgs& fresh_args() {
+  const __attribute__((address_space(4))) GemmArgs* p = (const __attribute__((address_space(4))) GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const GemmArgs*)p;
+}
+
+template <int A, int B_, bool TALL, bool MANY, int EPI>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_dma_kernel(GemmArgs args, int tiles_n, int tiles_m, int KS) {
   using Sh = DmaShape<A, B_, TALL>;
   constexpr int B = Sh::B, LPW = Sh::LPW, D = Sh::D, SLOT = Sh::SLOT, TS = Sh::TS;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dma[];
   __shared__ float inv_s[Sh::ROWS];
+  const GemmArgs& a = args;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -254,16 +266,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int KT_all = a.K >> 5, NT = a.N >> 4;
   // workgroups go to the 8 XCDs in turn: give each XCD a contiguous range of tiles, and within it blocks of up to four row tiles
   // by a few feature tiles, so that its L2 serves a weight tile to four workgroups and an activation fragment to several
-  const int total = (int)gridDim.x, id = (int)blockIdx.x, xcd = id & 7;
-  int l = xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
-  const int tiles = tiles_n * tiles_m, ks = l / tiles;
-  l -= ks * tiles;
-  const int per_group = 4 * tiles_n, mg = l / per_group, lg = l - mg * per_group;
-  const int gm = min(4, tiles_m - mg * 4);
-  const int tm = mg * 4 + lg % gm, tn = lg / gm;
-  const int nt0 = tn * TS, row0 = tm * Sh::ROWS;
-  const int per = (KT_all + KS - 1) / KS, k_lo = ks * per;
-  const int n_kt = min(KT_all, k_lo + per) - k_lo;  // the launcher leaves no range empty
+  const int tiles = tiles_n * tiles_m, total = tiles * KS, per = (KT_all + KS - 1) / KS;
+  struct Tile {
+    int nt0, row0, ks, k_lo, n_kt;
+  };
+  auto place = [&](int id) {
+    const int xcd = id & 7;
+    int l = xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
+    const int ks = l / tiles;
+    l -= ks * tiles;
+    const int per_group = 4 * tiles_n, mg = l / per_group, lg = l - mg * per_group;
+    const int gm = min(4, tiles_m - mg * 4);
+    const int tm = mg * 4 + lg % gm, tn = lg / gm;
+    const int k_lo = ks * per;
+    return Tile{tn * TS, tm * Sh::ROWS, ks, k_lo, min(KT_all, k_lo + per) - k_lo};  // the launcher leaves no range empty
+  };
 
   // What this wave requests per k tile: fragment f = i * 8 + wave is weight tile f, or activation fragment f - TS; those past
   // the last one read it again, to the same place with the same contents (32-row tiles leave them out).  (Weights on waves of
@@ -272,22 +289,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const char* src[LPW];
   size_t step[LPW];
   unsigned dst[LPW];
-  const int cg0 = row0 >> 3, cg_last = a.ncg - 1;
-#pragma unroll
-  for (int i = 0; i < LPW; ++i) {
-    const int f = min(i * NW + wave, Sh::FRAGS - 1);
-    if (f < TS) {
-      src[i] = (const char*)a.W + (((size_t)min(nt0 + f, NT - 1) * KT_all + k_lo) << 10);
-      step[i] = 1024;
-      dst[i] = (unsigned)f * 1024u;
-    } else {
-      const int x = f - TS;
-      src[i] = (const char*)a.X + (((size_t)k_lo * a.ncg + min(cg0 + x, cg_last)) << 10);
-      step[i] = (size_t)a.ncg << 10;
-      dst[i] = (unsigned)f * 1024u;
-    }
-  }
   int s_in = 0;  // ring slot of the next request, in bytes
+  auto aim = [&](const Tile& at) {
+    const int cg0 = at.row0 >> 3, cg_last = a.ncg - 1;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const int f = min(i * NW + wave, Sh::FRAGS - 1);
+      if (f < TS) {
+        src[i] = (const char*)a.W + (((size_t)min(at.nt0 + f, NT - 1) * KT_all + at.k_lo) << 10);
+        step[i] = 1024;
+        dst[i] = (unsigned)f * 1024u;
+      } else {
+        const int x = f - TS;
+        src[i] = (const char*)a.X + (((size_t)at.k_lo * a.ncg + min(cg0 + x, cg_last)) << 10);
+        step[i] = (size_t)a.ncg << 10;
+        dst[i] = (unsigned)f * 1024u;
+      }
+    }
+    s_in = 0;
+  };
   auto request = [&](auto FROM, auto TO) {  // its share of a k tile, or part of it; the slot moves on with the last part
 #pragma unroll
     for (int i = FROM; i < TO; ++i) {
@@ -304,24 +324,24 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr std::integral_constant<int, LPW / 2> HALF{};
   constexpr std::integral_constant<int, LPW> ALL{};
   constexpr int ahead = D - 1;
-  for (int j = 0; j < ahead && j < n_kt; ++j) request(NONE, ALL);
-  {
-    GemmArgs ar = a;
+  auto row_factors = [&](int row0) {
+    GemmArgs ar = MANY ? fresh_args() : a;
     ar.row0 = row0;
     gemm_row_factors<false, 8>(ar, inv_s, min(Sh::ROWS, a.R - row0), wave, lane, NW);
-  }
+  };
+  int id = (int)blockIdx.x;
+  Tile at = place(id);
+  aim(at);
+  for (int j = 0; j < ahead && j < at.n_kt; ++j) request(NONE, ALL);
+  row_factors(at.row0);
 
   floatx4 acc[A][B];
-#pragma unroll
-  for (int si = 0; si < A; ++si)
-#pragma unroll
-    for (int j = 0; j < B; ++j) acc[si][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   // lane (kg, row) of a B operand: fragment row / 8 of the pair, piece (kg, plane), row % 8
   const unsigned w_off = (unsigned)((TALL ? grp * A * 1024 : 0) + lane * 16);
   const unsigned x_off = (unsigned)(TS * 1024 + (Sh::HALF_TILE ? wr & 1 : wr) * PAIR + (c >> 3) * 1024 + (kg * 16 + (c & 7)) * 16);
   Frag fw[A], fx[B][2];
   constexpr int STRIDE = TALL ? SLOT : 2 * SLOT;
-  int s_out = TALL ? 0 : grp * SLOT;  // ring slot of this group's next k tile
+  int s_out;  // ring slot of this group's next k tile
   auto fetch = [&]() {
     const unsigned char *const wp = lds_dma + s_out + w_off, *const xp = lds_dma + s_out + x_off;
 #pragma unroll
@@ -365,125 +385,155 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int si = 0; si < A; ++si) acc[si][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[si].v, fx[j][p].v, acc[si][j], 0, 0, 0);
   };
 
-  interval_end(n_kt >= ahead);  // k tile 0 is there (and the row factors)
-  if constexpr (!TALL) {
-    int i = 0;  // interval: k tile i + ahead is requested in it
-    if (grp == 1) {
-      const bool more = i + ahead < n_kt;
-      if (more) request(NONE, ALL);
-      interval_end(more);
-      ++i;
-    }
-    const int trips = (n_kt + 1) >> 1;
+  // MANY: the launch has one workgroup a compute unit, which works on tiles id, id + workgroups, .. (the count is a multiple of 8, so it stays in
+  // its XCD's range).  The ring is free after a tile's last barrier: the next tile's first k tiles arrive while this one's results
+  // leave, and workgroups drift apart, so that one's results leave under another's matrix instructions.
 #pragma unroll 1
-    for (int t = 0; t < trips; ++t) {
-      {  // memory interval: fragments of this group's k tile
+  for (bool first = true;; first = false) {
+    const int n_kt = at.n_kt, nt0 = at.nt0, row0 = at.row0;
+    s_out = TALL ? 0 : grp * SLOT;
+#pragma unroll
+    for (int si = 0; si < A; ++si)
+#pragma unroll
+      for (int j = 0; j < B; ++j) acc[si][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    interval_end(first && n_kt >= ahead);  // k tile 0 is there (and the row factors); later ones: all requested, whatever the results' stores count
+    if constexpr (!TALL) {
+      int i = 0;  // interval: k tile i + ahead is requested in it
+      if (grp == 1) {
         const bool more = i + ahead < n_kt;
-        if (!rowless) fetch();
         if (more) request(NONE, ALL);
         interval_end(more);
         ++i;
       }
-      {  // compute interval
-        const bool more = i + ahead < n_kt;
-        if (more) request(NONE, ALL);
-        __builtin_amdgcn_sched_barrier(0);
-        if (!rowless && (grp == 0 || 2 * t + 1 < n_kt)) multiply();
-        interval_end(more);
-        ++i;
-      }
-    }
-    if (grp == 0) interval_end(false);
-  } else {
-    // two intervals per k tile: group 0 reads k tile j in interval 2j and multiplies in 2j + 1, group 1 one interval later; k tile
-    // j + ahead goes out in halves in the same two intervals (its slot was last read in interval 2j - 1), and k tile j + 1 has
-    // arrived at the end of 2j + 1
-    if (grp == 0) {
+      const int trips = (n_kt + 1) >> 1;
 #pragma unroll 1
-      for (int j = 0; j < n_kt; ++j) {
-        const bool more = j + ahead < n_kt;
-        fetch();
-        if (more) request(NONE, HALF);
-        barrier();
-        if (more) request(HALF, ALL);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply();
-        interval_end(more);
+      for (int t = 0; t < trips; ++t) {
+        {  // memory interval: fragments of this group's k tile
+          const bool more = i + ahead < n_kt;
+          if (!rowless) fetch();
+          if (more) request(NONE, ALL);
+          interval_end(more);
+          ++i;
+        }
+        {  // compute interval
+          const bool more = i + ahead < n_kt;
+          if (more) request(NONE, ALL);
+          __builtin_amdgcn_sched_barrier(0);
+          if (!rowless && (grp == 0 || 2 * t + 1 < n_kt)) multiply();
+          interval_end(more);
+          ++i;
+        }
       }
-      barrier();
+      if (grp == 0) interval_end(false);
     } else {
-      if (ahead < n_kt) request(NONE, HALF);
-      barrier();
+      // two intervals per k tile: group 0 reads k tile j in interval 2j and multiplies in 2j + 1, group 1 one interval later; k tile
+      // j + ahead goes out in halves in the same two intervals (its slot was last read in interval 2j - 1), and k tile j + 1 has
+      // arrived at the end of 2j + 1
+      if (grp == 0) {
 #pragma unroll 1
-      for (int j = 0; j < n_kt; ++j) {
-        const bool more = j + ahead < n_kt;
-        fetch();
-        if (more) request(HALF, ALL);
-        interval_end(more);
-        if (j + 1 + ahead < n_kt) request(NONE, HALF);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply();
+        for (int j = 0; j < n_kt; ++j) {
+          const bool more = j + ahead < n_kt;
+          fetch();
+          if (more) request(NONE, HALF);
+          barrier();
+          if (more) request(HALF, ALL);
+          __builtin_amdgcn_sched_barrier(0);
+          multiply();
+          interval_end(more);
+        }
         barrier();
+      } else {
+        if (ahead < n_kt) request(NONE, HALF);
+        barrier();
+#pragma unroll 1
+        for (int j = 0; j < n_kt; ++j) {
+          const bool more = j + ahead < n_kt;
+          fetch();
+          if (more) request(HALF, ALL);
+          interval_end(more);
+          if (j + 1 + ahead < n_kt) request(NONE, HALF);
+          __builtin_amdgcn_sched_barrier(0);
+          multiply();
+          barrier();
+        }
       }
     }
-  }
 
-  // not TALL: the groups' sums meet in LDS; group 0 finishes the first half of the pairs of strips, group 1 the others
-  constexpr int PAIRS = (A + 1) / 2, PH = (PAIRS + 1) / 2;
-  floatx4* const red = reinterpret_cast<floatx4*>(lds_dma);  // [4 waves][A][B][64]
-  auto owns = [&](int p) { return TALL || (p < PH) == (grp == 0); };
-  if constexpr (!TALL) {
+    // (the arguments that the results' way out reads; held across the tiles they cost 30 more scalar spills)
+    const GemmArgs& a = MANY ? fresh_args() : args;
+    const int next_id = id + (int)gridDim.x;
+    const bool again = MANY && next_id < total;
+    Tile next = at;
+    if (again) {
+      next = place(next_id);
+      aim(next);
+      for (int j = 0; j < ahead && j < next.n_kt; ++j) request(NONE, ALL);
+    }
+
+    // not TALL: the groups' sums meet in LDS; group 0 finishes the first half of the pairs of strips, group 1 the others
+    constexpr int PAIRS = (A + 1) / 2, PH = (PAIRS + 1) / 2;
+    floatx4* const red = reinterpret_cast<floatx4*>(lds_dma);  // [4 waves][A][B][64]
+    auto owns = [&](int p) { return TALL || (p < PH) == (grp == 0); };
+    if constexpr (!TALL) {
 #pragma unroll
-    for (int si = 0; si < A; ++si)
-      if (!owns(si >> 1)) {
+      for (int si = 0; si < A; ++si)
+        if (!owns(si >> 1)) {
 #pragma unroll
-        for (int j = 0; j < B; ++j) red[((wr * A + si) * B + j) * 64 + lane] = acc[si][j];
-      }
-    __syncthreads();
-#pragma unroll
-    for (int si = 0; si < A; ++si)
-      if (owns(si >> 1)) {
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-          const floatx4 o = red[((wr * A + si) * B + j) * 64 + lane];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[si][j][e] += o[e];
+          for (int j = 0; j < B; ++j) red[((wr * A + si) * B + j) * 64 + lane] = acc[si][j];
         }
-      }
-  }
-  const int rows_here = min(Sh::ROWS, a.R - row0);
-  const int nt_wave = nt0 + (TALL ? grp * A : 0);
-  const bool need_kv = EPI == EPI_QKV && KS == 1 && (nt_wave + A) * 16 > a.n_heads * a.kv.head_dim;
-  const PairEpilogue<EPI, B> fin(a, row0, wr, c, kg, rows_here, inv_s, need_kv);
+      __syncthreads();
 #pragma unroll
-  for (int p = 0; p < PAIRS; ++p) {
-    constexpr int LAST = A - 1;
-    const int nt = nt_wave + 2 * p;
-    if (!owns(p) || nt >= NT || rowless) continue;
-    const bool have2 = 2 * p + 1 < A && nt + 1 < NT;
-    if (KS > 1) {  // the launch after this one adds the ranges: part[range][row][packed feature]
+      for (int si = 0; si < A; ++si)
+        if (owns(si >> 1)) {
 #pragma unroll
-      for (int o = 0; o < 2; ++o)
-        if (o == 0 || have2) {
+          for (int j = 0; j < B; ++j) {
+            const floatx4 o = red[((wr * A + si) * B + j) * 64 + lane];
 #pragma unroll
-          for (int j = 0; j < B; ++j)
-            if (fin.live[j]) *(floatx4*)(a.part + ((size_t)ks * a.R + fin.m[j]) * a.N + (nt + o) * 16 + kg * 4) = acc[2 * p + o < A ? 2 * p + o : LAST][j];
-        }
-    } else if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
-      fin.paired(nt, acc[2 * p], acc[2 * p + 1 < A ? 2 * p + 1 : LAST], have2);
-    } else {
-#pragma unroll
-      for (int o = 0; o < 2; ++o)
-        if (o == 0 || have2) {
-          floatx4 (&s)[B] = acc[2 * p + o < A ? 2 * p + o : LAST];
-          if constexpr (EPI == EPI_RESID) {
-            fin.resid(nt + o, s);
-          } else {
-#pragma unroll
-            for (int j = 0; j < B; ++j) gemm_epilogue<EPI>(a, nt + o, s[j], fin.m[j], fin.live[j], fin.inv[j], kg);
+            for (int e = 0; e < 4; ++e) acc[si][j][e] += o[e];
           }
         }
     }
+    const int rows_here = min(Sh::ROWS, a.R - row0);
+    const int nt_wave = nt0 + (TALL ? grp * A : 0);
+    const bool need_kv = EPI == EPI_QKV && KS == 1 && (nt_wave + A) * 16 > a.n_heads * a.kv.head_dim;
+    const PairEpilogue<EPI, B> fin(a, row0, wr, c, kg, rows_here, inv_s, need_kv);
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p) {
+      constexpr int LAST = A - 1;
+      const int nt = nt_wave + 2 * p;
+      if (!owns(p) || nt >= NT || rowless) continue;
+      const bool have2 = 2 * p + 1 < A && nt + 1 < NT;
+      if (KS > 1) {  // the launch after this one adds the ranges: part[range][row][packed feature]
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+          if (o == 0 || have2) {
+#pragma unroll
+            for (int j = 0; j < B; ++j)
+              if (fin.live[j]) *(floatx4*)(a.part + ((size_t)at.ks * a.R + fin.m[j]) * a.N + (nt + o) * 16 + kg * 4) = acc[2 * p + o < A ? 2 * p + o : LAST][j];
+          }
+      } else if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
+        fin.paired(nt, acc[2 * p], acc[2 * p + 1 < A ? 2 * p + 1 : LAST], have2);
+      } else {
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+          if (o == 0 || have2) {
+            floatx4 (&s)[B] = acc[2 * p + o < A ? 2 * p + o : LAST];
+            if constexpr (EPI == EPI_RESID) {
+              fin.resid(nt + o, s);
+            } else {
+#pragma unroll
+              for (int j = 0; j < B; ++j) gemm_epilogue<EPI>(a, nt + o, s[j], fin.m[j], fin.live[j], fin.inv[j], kg);
+            }
+          }
+      }
+    }
+    if (!again) break;
+    if (next.row0 != row0) {
+      __syncthreads();  // the factors of this tile have been read
+      row_factors(next.row0);
+    }
+    id = next_id;
+    at = next;
   }
 }
 
@@ -640,6 +690,9 @@ int device_cus() {
   return n_cus;
 }
 
+// workgroups of a launch whose workgroups take several tiles each: one a compute unit, as many on every XCD
+int resident_groups() { return device_cus() & ~7; }
+
 struct Plan {
   int A, B, KS, tiles_n, tiles_m;
   bool tall;
@@ -708,10 +761,10 @@ Plan plan_of(const GemmArgs& a, const GemmTiles& t) {
   return Plan{t.strips, t.row_groups, t.ranges, (NT + TS - 1) / TS, (a.R + rows - 1) / rows, t.tall != 0, t.lds};
 }
 
-template <int A, int B, bool TALL, int EPI>
-hipError_t run_shape(const GemmArgs& a, const Plan& p, hipStream_t s) {
+template <int A, int B, bool TALL, bool MANY, int EPI>
+hipError_t run_launch(const GemmArgs& a, const Plan& p, hipStream_t s) {
   using Sh = DmaShape<A, B, TALL>;
-  auto kern = gemm_bf16_dma_kernel<A, B, TALL, EPI>;
+  auto kern = gemm_bf16_dma_kernel<A, B, TALL, MANY, EPI>;
   // Once per device: its compute units hold the ring, and more than 64 KiB of dynamic LDS needs the attribute.  A success is
   // remembered (bit d: device d; beyond 63 every launch asks), a failure is reported and tried again.
   static std::atomic<uint64_t> ready{0};
@@ -725,8 +778,16 @@ hipError_t run_shape(const GemmArgs& a, const Plan& p, hipStream_t s) {
     if (e != hipSuccess) return e;
     ready.fetch_or(bit, std::memory_order_release);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_n * p.tiles_m * p.KS)), dim3(NW * 64), Sh::LDS, s, a, p.tiles_n, p.tiles_m, p.KS);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(MANY ? resident_groups() : p.tiles_n * p.tiles_m * p.KS)), dim3(NW * 64), Sh::LDS, s, a, p.tiles_n, p.tiles_m, p.KS);
   return hipGetLastError();
+}
+
+template <int A, int B, bool TALL, int EPI>
+hipError_t run_shape(const GemmArgs& a, const Plan& p, hipStream_t s) {
+  if constexpr (TALL) {
+    if (resident_groups() && p.tiles_n * p.tiles_m * p.KS > resident_groups()) return run_launch<A, B, TALL, true, EPI>(a, p, s);
+  }
+  return run_launch<A, B, TALL, false, EPI>(a, p, s);
 }
 
 template <int A, int EPI>

@@ -206,6 +206,18 @@ def test_every_tile_with_every_epilogue(tile):
             check(R, nt, 32 * KT, tile, ks, seed=100 * A + 10 * B + n)
 
 
+@pytest.mark.parametrize("tile,KT", [((5, 3, 1), 2), ((5, 3, 1), 9), ((7, 4, 1), 5)], ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else str(x))
+def test_more_tiles_than_compute_units(tile, KT):
+    """Workgroups that take a second tile, of the same rows or of others, with fewer and more k tiles than the ring holds; rows and strips left over."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    A, B, _ = tile
+    R, NT = 4 * 64 * B + 27, 2 * A * (cus // 5 + 2) + 4                # five tiles of rows, the last one apart from the four that share weights
+    assert 5 * ((NT + 2 * A - 1) // (2 * A)) > cus
+    for epi, check in enumerate((_store, _resid, _swiglu, _qkv)):
+        print(f"tile {tile} R={R} strips={NT} k tiles={KT} epilogue={epi}", flush=True)
+        check(R, NT // 8 * 8 if epi == T.QKV else NT, 32 * KT, tile, 1, seed=KT)
+
+
 @pytest.mark.parametrize("tile", [(7, 0, 0), (8, 0, 0), (7, 1, 0), (8, 1, 0)], ids=lambda t: f"{t[0]}x{t[1]}")
 @pytest.mark.parametrize("N", [16368, 16400])   # the last width at 8192 terms whose weights go through the caches, and one whose weights pass them by
 def test_weights_that_no_cache_holds(tile, N):
