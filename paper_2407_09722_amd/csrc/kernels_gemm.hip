@@ -212,15 +212,17 @@ __global__ __launch_bounds__(GW * 64) __attribute__((amdgpu_waves_per_eu((S + NG
 // Several strips per workgroup, for passes of more than 8 rows.  With NG row groups a weight tile needs NG activation
 // fragments of its own size from L2; a workgroup that works on S strips at once loads the fragments of a k tile
 // once and uses them for S weight tiles, so the L2 -> compute-unit traffic per weight byte drops from 1 + NG to
-// 1 + NG/S.  Same wave layout as above with one k tile per batch and wave; the S strips are reduced and finished one
+// 1 + NG/S.  Same wave layout as above with U k tiles per batch and wave; the S strips are reduced and finished one
 // after the other through the same LDS buffer.  A product with about one strip per compute unit or fewer would leave
 // most units idle at S > 1: its reduction dimension is then also cut into KS ranges (grid.y); every workgroup leaves
 // its sums in global memory (device-scope write-through stores) and the one that arrives last for a group of strips
 // adds the KS partial sums in range order and runs the epilogues (deterministic, same protocol as the attention splits).  S * NG <= 12 (16 for 48 and 64 rows) bounds the accumulator registers.
-template <int NG, int EPI>
+// U = 2 for two strips (9 to 24 rows, two ranges): 32 KiB of weights are on their way to a compute unit with one tile a batch, less than HBM's
+// latency times its share of the rate.  4096 x 11008 at 17 rows 24.6 -> 23.6 us (3.8 TB/s); four tiles a batch 24.2, four ranges 26.1.
+template <int NG, int EPI, int U>
 __global__ __launch_bounds__(GW * 64) void gemm_bf16_multi_kernel(GemmArgs a, int S) {
   __shared__ int last_s;
-  constexpr int SM = NG <= 4 ? 12 / NG : (NG <= 6 ? 3 : 4);  // most strips per workgroup
+  constexpr int SM = U > 1 ? 2 : NG <= 4 ? 12 / NG : (NG <= 6 ? 3 : 4);  // most strips per workgroup
   __shared__ floatx4 red[GW * NG * 64];
   __shared__ float inv_s[NG * 8];
   const int lane = threadIdx.x & 63;
@@ -240,16 +242,20 @@ __global__ __launch_bounds__(GW * 64) void gemm_bf16_multi_kernel(GemmArgs a, in
   const unsigned voff = (unsigned)lane * 16u;
   const ActAddr xa = act_addr(a, lane);
 
-  Frag w[2][SM], b[2][1][NG];
-  auto load_w = [&](Frag (&ws)[SM], int kt) {
+  constexpr int span = U * GW;
+  Frag w[2][U][SM], b[2][U][NG];
+  auto load_w = [&](Frag (&ws)[U][SM], int kt) {
 #pragma unroll
-    for (int s2 = 0; s2 < SM; ++s2)
-      if (s2 < ns && kt < KT) ws[s2].n = __builtin_nontemporal_load((const uintx4*)(strip0 + s2 * strip_bytes + ((size_t)kt << 10) + voff));
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s2 = 0; s2 < SM; ++s2)
+        if (s2 < ns && kt + u * GW < KT)
+          ws[u][s2].n = __builtin_nontemporal_load((const uintx4*)(strip0 + s2 * strip_bytes + ((size_t)(kt + u * GW) << 10) + voff));
   };
-  gemm_load_b<NG, 1>(b[0], xa.X, xa.xoff, xa.kstride, xa.gstride, KT, k_lo + wave, rows_here, c);
+  gemm_load_b<NG, U>(b[0], xa.X, xa.xoff, xa.kstride, xa.gstride, KT, k_lo + wave, rows_here, c);
   load_w(w[0], k_lo + wave);
-  gemm_load_b<NG, 1>(b[1], xa.X, xa.xoff, xa.kstride, xa.gstride, KT, k_lo + wave + GW, rows_here, c);
-  load_w(w[1], k_lo + wave + GW);
+  gemm_load_b<NG, U>(b[1], xa.X, xa.xoff, xa.kstride, xa.gstride, KT, k_lo + wave + span, rows_here, c);
+  load_w(w[1], k_lo + wave + span);
 
   floatx4 acc[SM][NG];
 #pragma unroll
@@ -257,21 +263,23 @@ __global__ __launch_bounds__(GW * 64) void gemm_bf16_multi_kernel(GemmArgs a, in
 #pragma unroll
     for (int g = 0; g < NG; ++g) acc[s2][g] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  for (int kt = k_lo + wave; kt < KT; kt += 2 * GW) {
+  for (int kt = k_lo + wave; kt < KT; kt += 2 * span) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int k0 = kt + h * GW;
-      if (k0 < KT) {
+      const int k0 = kt + h * span;
 #pragma unroll
-        for (int s2 = 0; s2 < SM; ++s2)
-          if (s2 < ns) {
+      for (int u = 0; u < U; ++u)
+        if (k0 + u * GW < KT) {
 #pragma unroll
-            for (int g = 0; g < NG; ++g) acc[s2][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[h][s2].v, b[h][0][g].v, acc[s2][g], 0, 0, 0);
-          }
-      }
-      if (k0 + 2 * GW < KT) {
-        gemm_load_b<NG, 1>(b[h], xa.X, xa.xoff, xa.kstride, xa.gstride, KT, k0 + 2 * GW, rows_here, c);
-        load_w(w[h], k0 + 2 * GW);
+          for (int s2 = 0; s2 < SM; ++s2)
+            if (s2 < ns) {
+#pragma unroll
+              for (int g = 0; g < NG; ++g) acc[s2][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[h][u][s2].v, b[h][u][g].v, acc[s2][g], 0, 0, 0);
+            }
+        }
+      if (k0 + 2 * span < KT) {
+        gemm_load_b<NG, U>(b[h], xa.X, xa.xoff, xa.kstride, xa.gstride, KT, k0 + 2 * span, rows_here, c);
+        load_w(w[h], k0 + 2 * span);
       }
     }
   }
@@ -546,10 +554,10 @@ static hipError_t run_strips(const GemmArgs& a, int tag, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int NG, int EPI>
+template <int NG, int EPI, int U = 1>
 static hipError_t run_multi(const GemmArgs& a, int S, int KS, hipStream_t s) {
   const int NT = a.N / 16;
-  hipLaunchKernelGGL((gemm_bf16_multi_kernel<NG, EPI>), dim3((NT + S - 1) / S, KS), dim3(GW * 64), 0, s, a, S);
+  hipLaunchKernelGGL((gemm_bf16_multi_kernel<NG, EPI, U>), dim3((NT + S - 1) / S, KS), dim3(GW * 64), 0, s, a, S);
   return hipGetLastError();
 }
 
@@ -624,7 +632,8 @@ static hipError_t run_epi(GemmArgs a, int tag, hipStream_t s) {
       continue;
     }
     if (S > 1) {
-      if (ng <= 2) e = run_multi<2, EPI>(a, S, KS, s);
+      if (KS == 2) e = ng <= 2 ? run_multi<2, EPI, 2>(a, S, KS, s) : run_multi<3, EPI, 2>(a, S, KS, s);  // (two strips: registers for two tiles a batch)
+      else if (ng <= 2) e = run_multi<2, EPI>(a, S, KS, s);
       else if (ng <= 3) e = run_multi<3, EPI>(a, S, KS, s);
       else if (ng <= 4) e = run_multi<4, EPI>(a, S, KS, s);
       else if (ng <= 6) e = run_multi<6, EPI>(a, S, KS, s);

@@ -105,6 +105,23 @@ def test_gemm_bf16_with_context_workspace(R, N, K):
     mb.mtad_destroy(ctx)
 
 
+@pytest.mark.parametrize("R,N,K", [(9, 16, 8192), (16, 80, 8224), (17, 112, 8704), (24, 4112, 8288), (10, 6144, 13824)])
+def test_gemm_bf16_two_ranges(R, N, K):
+    """9 to 24 rows of long reductions: two ranges, two k tiles a batch.  Ranges that fill the waves' batches, or leave some waves or one of
+    a batch's tiles without work; a last group of one strip.  Twice: the arrival counters return to zero."""
+    mb = _mb()
+    shape = si.ModelShape(1, 4096, 32, 32, 128, 11008, 32000, "bf16")
+    draft = si.ModelShape(1, 6144, 48, 48, 128, 8192, 32000, "bf16")
+    desc = lambda s: mb.mtad_model(s.n_layers, s.d_model, s.n_heads, s.n_kv_heads, s.head_dim, s.d_ffn, s.vocab, 1, s.rms_eps, s.rope_theta, None)
+    ctx = mb.mtad_create(mb.mtad_config(1, 4, 4, 1, 64, 256), desc(shape), desc(draft))
+    ws = torch.empty(mb.mtad_workspace_bytes(ctx), dtype=torch.uint8, device=DEV)
+    mb.mtad_bind_workspace(ctx, ws)
+    for acc, order in ((False, mb.MTAD_X_FRAGMENTS), (True, mb.MTAD_X_PLANES)):
+        print(f"gemm bf16 two ranges R={R} N={N} K={K} accumulate={acc}", flush=True)
+        _gemm_case(mb, R, N, K, 1, seed=R + K, ctx=ctx, accumulate=acc, x_order=order)
+    mb.mtad_destroy(ctx)
+
+
 @pytest.mark.parametrize("R,N,K", [(1, 64, 96), (2, 8208, 160), (5, 12288, 4096), (5, 4096, 11008), (8, 22016, 256), (7, 48, 1056),
                                    (9, 4096, 4096), (17, 12288, 4096), (24, 4112, 64), (41, 8192, 96), (64, 4096, 1024),
                                    (25, 16400, 288), (100, 4112, 1056), (164, 5120, 5120), (190, 48, 1056)])
