@@ -255,6 +255,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_dma[];
   __shared__ float inv_s[Sh::ROWS];
   const GemmArgs& a = args;
+  // (what the first requests need of the arguments at once; left to itself the compiler fetches it in three rounds, each a trip to memory)
+  asm volatile("" ::"s"(a.W), "s"(a.X), "s"(a.R), "s"(a.N), "s"(a.K), "s"(a.ncg), "s"(a.ssq), "s"(a.NP), "s"(tiles_n), "s"(tiles_m), "s"(KS));
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
