@@ -461,7 +461,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
     }
 
-    // (the arguments that the results' way out reads; held across the tiles they cost 30 more scalar spills)
+    // (the arguments that the results' way out reads; held across the tiles they cost 20 to 70 more scalar spills)
     const GemmArgs& a = MANY ? fresh_args() : args;
     const int next_id = id + (int)gridDim.x;
     const bool again = MANY && next_id < total;
