@@ -658,7 +658,7 @@ __device__ __forceinline__ bool relay_product(RelaySmem& sm, unsigned char* x, R
 
 // The waves' results [wave][pair][dim] and the own rows, added in order, and handed on; splits other than the first hand on theirs to the first.
 template <bool BF, int HD, int PC>
-__device__ __forceinline__ bool relay_merge(RelaySmem& sm, const float* o_s, int o_stride, const float* vn, RelayPtr A, const Watch& watch, const Step& at, int split, int eff, int used,
+__device__ __forceinline__ void relay_merge(RelaySmem& sm, const float* o_s, int o_stride, const float* vn, RelayPtr A, const Watch& watch, const Step& at, int split, int eff, int used,
                                             int seq, int kvh, int p0, int np, int wave, int lane) {
   auto exponential = [](float v) { return BF ? __builtin_amdgcn_exp2f(v) : expf(v); };
   const int H = A->H, KVH = A->KVH, Rseq = A->Rseq, G = H / KVH, P = G * Rseq, splits = A->splits;
@@ -734,9 +734,10 @@ __device__ __forceinline__ bool relay_merge(RelaySmem& sm, const float* o_s, int
     else if (eff > 1) gather(std::integral_constant<int, 1>{});
     if (stay) put(at.words + A->mail.att + (size_t)(seq * Rseq + p % Rseq) * (H * HD) + (kvh * G + p / Rseq) * HD + dim, at.tag, sum > 0.f ? o / sum : 0.f);
   }
+  // Read between the next unit's barriers, or at the end of the run: a wave that read it here could do so after a faster one has failed the
+  // next unit's wait, and the two would be at different barriers from then on.
   if (!stay) sm.leave = 1;
   __syncthreads();  // what was staged is free again
-  return !sm.leave;
 }
 
 // One unit of attention: (split, group of pairs, key head, sequence), at most PC (query head, row) pairs; the split that merges is the last
@@ -962,7 +963,8 @@ __device__ __forceinline__ bool relay_attend_f32(RelaySmem& sm, unsigned char* x
     if (c16 == 0) sm.own[key_row][key_pair] = key_seen ? y * scale : -INFINITY;
   }
   __syncthreads();
-  return relay_merge<false, HD, PC>(sm, o_s, PC * HD, vn, A, watch, at, split, eff, min(RWAVES, blocks - split * RWAVES), seq, kvh, p0, np, wave, lane);
+  relay_merge<false, HD, PC>(sm, o_s, PC * HD, vn, A, watch, at, split, eff, min(RWAVES, blocks - split * RWAVES), seq, kvh, p0, np, wave, lane);
+  return true;
 }
 
 // bf16 models: scores and outputs of the cached keys on the matrix cores, S = K Q^T and O^T = V^T P, at most 8 pairs.  The columns of a
@@ -1216,7 +1218,8 @@ __device__ __forceinline__ bool relay_attend_bf16(RelaySmem& sm, unsigned char* 
     }
   }
   __syncthreads();
-  return relay_merge<true, HD, PC>(sm, (const float*)(qh + 2 * PC * S::QS), S::VB / 4, vn, A, watch, at, split, eff, min(RWAVES, blocks - split * RWAVES), seq, kvh, p0, np, wave, lane);
+  relay_merge<true, HD, PC>(sm, (const float*)(qh + 2 * PC * S::QS), S::VB / 4, vn, A, watch, at, split, eff, min(RWAVES, blocks - split * RWAVES), seq, kvh, p0, np, wave, lane);
+  return true;
 }
 
 // All units of workgroup `rank` of `groups`.  False: the pass goes on without what this one would have done (leave).

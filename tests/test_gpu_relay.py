@@ -74,12 +74,12 @@ def test_long_caches(dtype, hd, heads, kv_heads, batch, gamma, beam, n):
     assert err < (1e-5 if dtype == "fp32" else TOLERANCE)
 
 
-def _engine(dtype, hd=64, rows=4):
+def _engine(dtype, hd=64, rows=4, n=600):
     from paper_2407_09722_amd.engine import DeviceModel, Engine
     shape = si.ModelShape(3, 4 * hd, 4, 2, hd, 352, 512, dtype)
     m = DeviceModel(shape, _weights(shape, 7, "target", boost=2.0), DEV)
-    eng = Engine(m, m, batch=1, gamma=rows - 1, beam=1, mode="mtad", max_context=700, device=DEV, fused_pass=1)
-    eng.prefill(np.random.default_rng(2).integers(0, 512, (1, 600)).astype(np.int32))
+    eng = Engine(m, m, batch=1, gamma=rows - 1, beam=1, mode="mtad", max_context=n + 100, device=DEV, fused_pass=1)
+    eng.prefill(np.random.default_rng(2).integers(0, 512, (1, n)).astype(np.int32))
     eng.draft_phase()
     eng.verify_phase()
     torch.cuda.synchronize()
@@ -118,6 +118,23 @@ def test_workgroups_that_do_not_start(dtype, hd):
             got = _verify(eng, 0, patience)
             assert torch.equal(got[0], want[0]), patience
     assert mb.mtad_device_status(eng.ctx) == 0
+    eng.close()
+
+
+@pytest.mark.parametrize("dtype,hd", [("fp32", 64), ("bf16", 128)])
+def test_waits_that_fail_in_a_merge(dtype, hd):
+    """Few workgroups, several attention units each, some of which merge the splits of others: they leave from a merge's wait or from that of
+    the unit after it, and whoever takes part again gives the same bits."""
+    from paper_2407_09722_amd import binding as mb
+    eng = _engine(dtype, hd, n=2040)
+    want = _verify(eng)
+    n = _relay(eng, 0, 4)
+    for absent in (n - 2, n - 3, n - 5, n - 7):
+        for patience in (1, 300):
+            print(f"{dtype} {hd}: {absent} of {n} absent, patience {patience}", flush=True)
+            got = _verify(eng, absent, patience)
+            assert mb.mtad_device_status(eng.ctx) == 0
+            assert all(torch.equal(a, b) for a, b in zip(got, want)), (absent, patience)
     eng.close()
 
 
