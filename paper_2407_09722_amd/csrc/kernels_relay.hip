@@ -13,9 +13,10 @@
 //   * Every result of a step depends on all results of the step before, so nobody can be more than a step ahead of anybody's reads,
 //     and two layers' words alternate.
 //   * All units of a layer must run before the next can: the workgroups have to be on the machine at the same time.  Where another
-//     launch holds the compute units that some of them need, whoever has waited too long counts out those that have not started,
-//     and the others share all units among themselves from the first layer on, with words of their own (nothing they write differs
-//     from what was there).  Every wait ends, at the latest after 0.2 s with the status bit of a pass that was given up.
+//     launch holds the compute units that some of them need, whoever has waited too long in layer 0 counts those that have started.  If some
+//     have not, the others share all units among themselves from the first layer on, with words of their own (nothing they write differs
+//     from what was there); if all have, or one has been past layer 0 and so has seen a result of everybody, the pass goes on and nobody
+//     counts again.  Every wait ends, at the latest after 0.2 s with the status bit of a pass that was given up.
 #include "attn_mfma_device.h"
 #include "gemm.h"
 #include "gemm_device.h"
@@ -62,6 +63,7 @@ struct RelaySmem {
   int rope_unit[ROPE_SLOTS];
   float m[RWAVES][PAIR_CHUNK], l[RWAVES][PAIR_CHUNK], own[RELAY_MAX_ROWS][PAIR_CHUNK];  // attention: of a wave's keys; scores of the own rows
   int leave;
+  uint32_t verdict;
 };
 
 // What a wait has to know besides its words
@@ -72,31 +74,41 @@ struct Watch {
   unsigned patience;
   int groups, group;
   bool again;      // one of those that started over
-  bool committed;  // all workgroups have been seen at work
+  bool committed;  // this workgroup has had input of a layer above 0: every workgroup has done its share of layer 0
+  bool settled;    // they have been counted, and the pass goes on: nobody counts again
 };
 __device__ __forceinline__ uint64_t* rank_word(uint32_t* sync, int b) { return (uint64_t*)(sync + 64 + RELAY_MAX_GROUPS) + b; }
 
-// Counts in the workgroups that are there and gives them ranks.  One wave of whoever has waited too long; the first in a pass does it.
+// What a rank word says of this pass: that it goes on (no workgroups), or who starts over
+__device__ __forceinline__ bool goes_on(uint32_t word) { return word >> 16 == 0; }
+
+// Counts the workgroups that are there, and says in all rank words what becomes of the pass.  One wave of whoever has waited too long; the
+// first in a pass does it.  A workgroup that is counted (state 3) finds out when it commits or ends, and looks at its rank word then.
 __device__ __forceinline__ void count_in(const Watch& c, int lane) {
   int mine = 0;
   if (lane == 0) mine = __hip_atomic_exchange(c.sync + 2, c.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != c.epoch;
   if (!__builtin_amdgcn_readfirstlane(mine)) return;
-  int n = 0;
-  unsigned in = 0;  // bit i: workgroup i * 64 + lane
+  int n = 0, done = 0;
+  bool past = false;  // somebody has been past layer 0
+  unsigned in = 0;    // bit i: workgroup i * 64 + lane
   for (int i = 0; i < RELAY_MAX_GROUPS / 64; ++i) {
     uint32_t was = c.epoch * 4 + 1;
     const int b = i * 64 + lane;
     const bool got = b < c.groups && __hip_atomic_compare_exchange_strong(c.sync + 64 + b, &was, c.epoch * 4 + 3, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     in |= (unsigned)got << i;
     n += __popcll(__ballot(got));
+    done += __popcll(__ballot(b < c.groups && !got && was == c.epoch * 4));
+    past = past || __any(b < c.groups && !got && was == c.epoch * 4 + 2);
   }
+  const bool on = past || n + done == c.groups;
+  if (!on && lane == 0) __hip_atomic_fetch_add(c.sync + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   int before = 0;
   for (int i = 0; i < RELAY_MAX_GROUPS / 64; ++i) {
     const int b = i * 64 + lane;
     const bool got = (in >> i) & 1;
     const unsigned long long all = __ballot(got);
     const int rank = got ? before + __popcll(all & ((1ull << lane) - 1)) : 0xFFFF;
-    if (b < c.groups) __hip_atomic_store(rank_word(c.sync, b), (uint64_t)c.epoch << 32 | (uint32_t)n << 16 | (uint32_t)rank, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (b < c.groups) __hip_atomic_store(rank_word(c.sync, b), (uint64_t)c.epoch << 32 | (on ? 0u : (uint32_t)n << 16 | (uint32_t)rank), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     before += __popcll(all);
   }
 }
@@ -104,7 +116,10 @@ __device__ __forceinline__ void count_in(const Watch& c, int lane) {
 // Now and then during a wait (all lanes of a wave): is it over for another reason than its words?
 __device__ __forceinline__ bool must_leave(const Watch& c, int lane) {
   if (get32(c.sync + 1) == c.epoch) return true;
-  if (!c.again && (uint32_t)(get(rank_word(c.sync, c.group)) >> 32) == c.epoch) return true;
+  if (!c.again) {
+    const uint64_t word = get(rank_word(c.sync, c.group));
+    if ((uint32_t)(word >> 32) == c.epoch && !goes_on((uint32_t)word)) return true;
+  }
   const unsigned long long waited = wall_clock64() - c.start;
   if (waited > RELAY_GIVE_UP) {
     if (lane == 0) {
@@ -113,7 +128,14 @@ __device__ __forceinline__ bool must_leave(const Watch& c, int lane) {
     }
     return true;
   }
-  return !c.again && !c.committed && waited > c.patience;
+  return !c.again && !c.committed && !c.settled && waited > c.patience;
+}
+
+// This workgroup has had input of layer l: above 0, it says so, once.  was: what its state was (thread 0; needed at the end only).
+__device__ __forceinline__ void commit(Watch& c, int l, int tid, int& was) {
+  if (l == 0 || c.again || c.committed) return;
+  c.committed = true;
+  if (tid == 0) was = (int)__hip_atomic_exchange(c.sync + 64 + c.group, c.epoch * 4 + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Brings this lane's words at(i) with that tag; also: what else is requested in every turn.  False: leave.  (How many words is a
@@ -594,10 +616,7 @@ __device__ __forceinline__ bool relay_product(RelaySmem& sm, unsigned char* x, R
   }
   pin(inv);
   multiply<BF>(sm, x, wts, u, step, R, HD, wave, lane);
-  if (l > 0 && !leave && !watch.again && !watch.committed) {  // every workgroup has done its share of layer 0
-    watch.committed = true;
-    if (tid == 0) commit_was = (int)__hip_atomic_exchange(watch.sync + 64 + watch.group, watch.epoch * 4 + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (!leave) commit(watch, l, tid, commit_was);
   __syncthreads();
   if (leave) return false;
   if (resid) {
@@ -748,7 +767,7 @@ __device__ __forceinline__ void relay_merge(RelaySmem& sm, const float* o_s, int
 // NL - 1; the dot products' partial sums are reduced over the lanes of a key so that lane (g, c) ends with the score of key
 // 4 c + g (as the float32 models' kernel does).
 template <int HD>
-__device__ __forceinline__ bool relay_attend_f32(RelaySmem& sm, unsigned char* x, RelayPtr A, Watch& watch, const Step& at, int unit) {
+__device__ __forceinline__ bool relay_attend_f32(RelaySmem& sm, unsigned char* x, RelayPtr A, Watch& watch, const Step& at, int unit, int& commit_was) {
   using S = AttnF32<HD>;
   typedef float T;
   constexpr int NL = S::NL, BK = S::BK, E = S::E, KPL = S::KPL, EPL = S::EPL, PC = S::PC;
@@ -844,6 +863,7 @@ __device__ __forceinline__ bool relay_attend_f32(RelaySmem& sm, unsigned char* x
   }
   __syncthreads();
   if (sm.leave) return false;
+  commit(watch, l, tid, commit_was);
   constexpr float scale = 1.0f / (HD == 64 ? 8.0f : 11.3137085f);
   auto exponential = [](float v) { return expf(v); };
   {
@@ -982,7 +1002,7 @@ struct AttnBf {
 };
 
 template <int HD>
-__device__ __forceinline__ bool relay_attend_bf16(RelaySmem& sm, unsigned char* x, RelayPtr A, Watch& watch, const Step& at, int unit) {
+__device__ __forceinline__ bool relay_attend_bf16(RelaySmem& sm, unsigned char* x, RelayPtr A, Watch& watch, const Step& at, int unit, int& commit_was) {
   using S = AttnBf<HD>;
   constexpr int PC = S::PC, BK = S::BK, KT = S::KT, KS = S::KS, DB = S::DB;
   constexpr int CH = HD / 8, KPL = 64 / CH, NV = BK / KPL;  // V: 16-byte chunks of a row, keys a load covers, loads
@@ -1103,6 +1123,7 @@ __device__ __forceinline__ bool relay_attend_bf16(RelaySmem& sm, unsigned char* 
   }
   __syncthreads();
   if (sm.leave) return false;
+  commit(watch, l, tid, commit_was);
   constexpr float scale = ATTN_LOG2E / (HD == 64 ? 8.0f : 11.3137085f);
   float m_run = -INFINITY, l_run = 0.f;
   attn_floatx4 acc[DB];
@@ -1253,9 +1274,9 @@ __device__ __forceinline__ bool relay_run(RelaySmem& sm, unsigned char* x, const
       for (int u = step == 0 ? u0[0] : step == 1 ? u0[1] : step == 2 ? u0[2] : step == 3 ? u0[3] : u0[4]; u < n; u += groups) {
         bool ok = true;
         if constexpr (BF) {
-          if (step == RS_ATTN) ok = relay_attend_bf16<HD>(sm, x, A, watch, at, u);
+          if (step == RS_ATTN) ok = relay_attend_bf16<HD>(sm, x, A, watch, at, u, commit_was);
         } else {
-          if (step == RS_ATTN) ok = relay_attend_f32<HD>(sm, x, A, watch, at, u);
+          if (step == RS_ATTN) ok = relay_attend_f32<HD>(sm, x, A, watch, at, u, commit_was);
         }
         if (step != RS_ATTN) ok = relay_product<BF, HD>(sm, x, A, watch, at, step, u, fresh, parity, commit_was);
         if (!ok) return false;
@@ -1279,7 +1300,7 @@ __global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   watch.patience = A->patience;
   watch.groups = gridDim.x;
   watch.group = blockIdx.x;
-  watch.again = watch.committed = false;
+  watch.again = watch.committed = watch.settled = false;
   if (watch.group >= A->present) return;
   watch.epoch = __builtin_amdgcn_readfirstlane(*watch.sync);
   if (tid == 0) __hip_atomic_store(watch.sync + 64 + watch.group, watch.epoch * 4 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1293,21 +1314,30 @@ __global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     __syncthreads();
     done = done && !sm.leave;
     __syncthreads();
-    if (tid == 0) {  // counted in among those that start over?
-      if (done && !watch.committed) commit_was = (int)__hip_atomic_exchange(watch.sync + 64 + watch.group, watch.epoch * 4 + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      sm.leave = done && (uint32_t)commit_was != watch.epoch * 4 + 3 ? 1 : 0;
+    if (tid < 64) {  // what becomes of this workgroup: nothing more, unless it was counted or has left
+      if (done && !watch.committed && tid == 0) commit_was = (int)__hip_atomic_exchange(watch.sync + 64 + watch.group, watch.epoch * 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint64_t word[1] = {0};
+      if (!done || __builtin_amdgcn_readfirstlane(commit_was) == (int)(watch.epoch * 4 + 3)) {
+        if (!done && !watch.committed) count_in(watch, tid);
+        Watch w = watch;
+        w.again = true;  // (a wait that ends with its word, or with the pass)
+        if (!collect(word, [&](int) { return (const uint64_t*)rank_word(watch.sync, watch.group); }, watch.epoch, w, tid)) word[0] = 0xFFFFFFFFu;
+      }
+      if (tid == 0) sm.verdict = (uint32_t)word[0];
     }
     __syncthreads();
-    if (sm.leave) return;
-    if (get32(watch.sync + 1) == watch.epoch) return;  // given up
-    if (tid < 64) count_in(watch, tid);
-    uint64_t word[1];
-    watch.again = true;
-    if (!collect(word, [&](int) { return (const uint64_t*)rank_word(watch.sync, watch.group); }, watch.epoch, watch, tid & 63)) return;
-    rank = __builtin_amdgcn_readfirstlane((int)(word[0] & 0xFFFF));
-    groups = __builtin_amdgcn_readfirstlane((int)(word[0] >> 16 & 0xFFFF));
-    if (rank == 0xFFFF) return;
-    __syncthreads();  // (before sm.leave is cleared)
+    const uint32_t verdict = (uint32_t)__builtin_amdgcn_readfirstlane((int)sm.verdict);
+    if (!goes_on(verdict)) {
+      rank = (int)(verdict & 0xFFFF);
+      groups = (int)(verdict >> 16);
+      if (rank == 0xFFFF) return;  // not one of those that start over, or given up
+      watch.again = true;
+    } else {
+      // It goes on.  Whoever has left was still waiting in layer 0, or for the first time in layer 1: what it has not made all of layer 2 waits for,
+      // so that layer 0's words are as they were, and its units of layer 0 once more make the same words.
+      if (done) return;
+      watch.settled = true;
+    }
   }
 }
 

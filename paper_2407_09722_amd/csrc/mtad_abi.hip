@@ -64,7 +64,7 @@ struct mtad_ctx {
   uint64_t* relay_mail;  // one-launch pass of small models (relay.h); null: the workspace has no room for it
   size_t relay_mail_n;
   uint32_t* relay_sync;
-  unsigned relay_patience;  // ticks of the 100 MHz clock after which its workgroups count out those that have not started
+  unsigned relay_patience;  // ticks of the 100 MHz clock after which its workgroups count those that have started
   int relay_absent;         // (tests: so many of its workgroups never start)
   // set by mtad_verify_tree around its pass: the logsumexp kernel of a bf16 pass then also gathers logp_cond
   const mtad_tree* gather_tree;
@@ -590,7 +590,7 @@ int mtad_create(mtad_ctx** out, const mtad_config* cfg, const mtad_model* target
     return MTAD_ESHAPE;
   }
   if (target->dtype == 1 || draft->dtype == 1) c->prompt_best = imax(c->cfg.prefill_rows, imin(PROMPT_PASS_ROWS / cfg->batch, cfg->max_context));
-  c->relay_patience = 20000;  // 0.2 ms: all of them have been seen at work after one or two layers
+  c->relay_patience = 20000;  // 0.2 ms; a workgroup that has input of layer 1 by then has no further use for it
   c->flow_on = 1;
   if (const char* e = getenv("MTAD_FUSED_PASS")) c->flow_on = atoi(e) < 0 ? 0 : (atoi(e) > 2 ? 2 : atoi(e));
   c->ws_need = carve(c, nullptr, c->prompt_best, true, true);
@@ -790,13 +790,22 @@ int mtad_kv_commit(mtad_ctx* c, mtad_kv* tkv, mtad_kv* dkv, const mtad_tree* tre
 // ---- component entry points (include/mtad_kernels.h) ------------------------------------------------------------
 
 // For the tests of the small models' one-launch pass: the workgroups that a pass of R rows a sequence of the target (draft: 1) takes, 0 where
-// it is not of that kind.  From now on `absent` of them never start, and the others count them out after `patience` ticks of 10 ns (0: as before).
+// it is not of that kind.  From now on `absent` of them never start, and the others count who is there after `patience` ticks of 10 ns (0: as before).
 extern "C" int mtad_test_relay(mtad_ctx* c, int draft, int R, int absent, unsigned patience) {
   if (!c || R < 1 || absent < 0) return MTAD_EINVAL;
   c->relay_absent = absent;
   if (patience) c->relay_patience = patience;
   RelayArgs a;
   return relay_shape(a, draft ? &c->dshape : &c->tshape, c->cfg.batch, R, c->cfg.max_context);
+}
+
+// What such passes have left behind (RELAY_SYNC_WORDS' first four): number of the last one, of the last one that was given up, of the last one
+// whose workgroups were counted, and how many have started over.  Waits for the device.
+extern "C" int mtad_test_relay_state(mtad_ctx* c, uint32_t* out) {
+  if (!c || !out || !c->relay_sync) return MTAD_EINVAL;
+  HIP_TRY(c, hipDeviceSynchronize());
+  HIP_TRY(c, hipMemcpy(out, c->relay_sync, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost));
+  return MTAD_OK;
 }
 
 #ifdef MTAD_FLOW_PROFILE

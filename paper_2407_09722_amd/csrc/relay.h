@@ -22,9 +22,10 @@ struct RelayMail {
   int slot;                         // words of a layer
 };
 // Words that say who takes part (uint32_t unless noted); epoch: the number of this pass, counted by the row descriptors' kernel.
-//   [0] epoch   [1] last pass that was given up   [2] last pass whose workgroups were counted out
-//   [64 + b]    state of workgroup b: epoch * 4 + 1 present, 2 past the point where all have been seen at work, 3 counted in
-//   [64 + RELAY_MAX_GROUPS + 2 b]  (uint64_t) epoch << 32 | number of workgroups << 16 | rank of b (0xFFFF: not one of them)
+//   [0] epoch   [1] last pass that was given up   [2] last pass whose workgroups were counted   [3] passes that have started over
+//   [64 + b]    state of workgroup b: epoch * 4 + 1 present, 2 past layer 0, 3 present and counted, 0 done without having been past layer 0
+//   [64 + RELAY_MAX_GROUPS + 2 b]  (uint64_t) epoch << 32 | number of workgroups that start over << 16 | rank of b (0xFFFF: not one of
+//                                  them); no workgroups: the pass goes on
 constexpr int RELAY_SYNC_WORDS = 64 + 3 * RELAY_MAX_GROUPS;
 
 struct RelayArgs {
@@ -45,7 +46,7 @@ struct RelayArgs {
   float* h;       // float32 models: the hidden states
   bf16_t* xg;     // bf16 models: h * final gain as hi / lo terms (act_offset), and
   float* ssq;     // sums of squares of h per strip, [rows][d / 16]
-  unsigned patience;  // ticks of the 100 MHz clock after which a workgroup that waits counts out those that have not started
+  unsigned patience;  // ticks of the 100 MHz clock after which a workgroup that waits in layer 0 counts those that have started
   int present;        // workgroups that take part (all but in tests)
 };
 

@@ -74,12 +74,12 @@ def test_long_caches(dtype, hd, heads, kv_heads, batch, gamma, beam, n):
     assert err < (1e-5 if dtype == "fp32" else TOLERANCE)
 
 
-def _engine(dtype, hd=64, rows=4, n=600):
+def _engine(dtype, hd=64, rows=4, n=600, prompt=None):
     from paper_2407_09722_amd.engine import DeviceModel, Engine
     shape = si.ModelShape(3, 4 * hd, 4, 2, hd, 352, 512, dtype)
     m = DeviceModel(shape, _weights(shape, 7, "target", boost=2.0), DEV)
     eng = Engine(m, m, batch=1, gamma=rows - 1, beam=1, mode="mtad", max_context=n + 100, device=DEV, fused_pass=1)
-    eng.prefill(np.random.default_rng(2).integers(0, 512, (1, n)).astype(np.int32))
+    eng.prefill(np.random.default_rng(2).integers(0, 512, (1, prompt or n)).astype(np.int32))
     eng.draft_phase()
     eng.verify_phase()
     torch.cuda.synchronize()
@@ -135,6 +135,82 @@ def test_waits_that_fail_in_a_merge(dtype, hd):
             got = _verify(eng, absent, patience)
             assert mb.mtad_device_status(eng.ctx) == 0
             assert all(torch.equal(a, b) for a, b in zip(got, want)), (absent, patience)
+    eng.close()
+
+
+def _state(eng):
+    """Numbers of the last pass, of the last one that was given up, of the last one whose workgroups were counted, and passes that started over."""
+    from paper_2407_09722_amd import binding as mb
+    out = (C.c_uint32 * 4)()
+    assert mb.lib().mtad_test_relay_state(eng.ctx, out) == 0
+    return list(out)
+
+
+def test_which_passes_start_over():
+    """With workgroups that never start all do, with all of them there none does, however short the patience."""
+    eng = _engine("bf16")
+    n = _relay(eng, 0, 4)
+    for absent, patience in ((1, 300), (0, 1), (n - 1, 1), (0, 300), (n // 2, 300), (0, 3000)):
+        _relay(eng, 0, 4, absent, patience)
+        before = _state(eng)
+        for _ in range(5):
+            eng.verify_phase()
+        now = _state(eng)
+        assert now[0] == before[0] + 5 and now[3] - before[3] == (5 if absent else 0), (absent, patience)
+    eng.close()
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_workgroups_that_are_counted_and_all_there(dtype):
+    """Attention over so long a cache that whoever waits for it runs out of patience in layer 0 of every pass: all are there, so the pass goes on."""
+    from paper_2407_09722_amd import binding as mb
+    eng = _engine(dtype, n=100000, prompt=600)
+    eng.tkv.k.normal_(generator=torch.Generator(DEV).manual_seed(1))
+    eng.tkv.v.normal_(generator=torch.Generator(DEV).manual_seed(2))
+    eng.tkv.len.fill_(100000)
+    _relay(eng, 0, 4, 0, 0xFFFFFFFF)
+    eng.verify_phase()
+    torch.cuda.synchronize()
+    want, counted = eng.logits.cpu(), 0
+    for patience in (1, 100, 1000):
+        _relay(eng, 0, 4, 0, patience)
+        for _ in range(5):
+            before = _state(eng)
+            eng.verify_phase()
+            now = _state(eng)
+            assert torch.equal(eng.logits.cpu(), want) and now[3] == before[3], patience
+            counted += now[2] == now[0]
+    print(f"{dtype}: counted in {counted} of 15 passes", flush=True)
+    assert counted > 0 and mb.mtad_device_status(eng.ctx) == 0
+    eng.close()
+
+
+@pytest.mark.parametrize("layers", [12, 24, 48])
+@pytest.mark.parametrize("heads,kv_heads,ffn,dtype,several", [(12, 12, 2048, "bf16", (1, 5, 8)), (12, 1, 2048, "bf16", (1, 5, 8)), (16, 16, 2816, "bf16", (1, 5)),
+                                                              (8, 8, 1408, "fp32", (1, 5))])
+def test_long_passes_do_not_start_over(layers, heads, kv_heads, ffn, dtype, several):
+    """Passes of many layers, longer than what a workgroup's patience ever was, on models some of whose workgroups have attention units only: at the
+    patience that a program has, with nothing else on the machine, none starts over."""
+    from paper_2407_09722_amd import binding as mb
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    shape = si.ModelShape(layers, heads * 64, heads, kv_heads, 64, ffn, 512, dtype)
+    one = si.make_weights(shape.with_layers(1), 3, "target", threads=8)
+    m = DeviceModel(shape, {n: one[n if n in one else "L0." + n.split(".")[1]] for n in si.tensor_names(shape)}, DEV)
+    eng = Engine(m, m, batch=1, gamma=7, beam=1, mode="mtad", max_context=400, device=DEV)
+    eng.prefill(np.random.default_rng(2).integers(0, 512, (1, 300)).astype(np.int32))
+    eng.draft_phase()
+    for rows in several:
+        tree = eng.ar_tree if rows == 1 else mb.mtad_tree(rows, eng.tree.tok, eng.tree.parent, eng.tree.depth, eng.tree.src_beam, eng.tree.anc_mask, eng.tree.qref)
+        assert _relay(eng, 0, rows) > 0
+        before, ev = _state(eng), [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        for _ in range(5):
+            mb.mtad_verify_tree(eng.ctx, m.desc, eng.tkv.desc, eng.root_tok, tree, eng.logp_cond, eng.row_lse, eng.logits, None)
+        ev[1].record()
+        now = _state(eng)
+        print(f"{dtype} {layers} layers, {heads} on {kv_heads} x 64, ffn {ffn}, {rows} rows: {ev[0].elapsed_time(ev[1]) * 200:.0f} us a pass", flush=True)
+        assert now[0] == before[0] + 5 and now[3] == before[3], (rows, now, before)
+    assert mb.mtad_device_status(eng.ctx) == 0
     eng.close()
 
 
