@@ -30,7 +30,6 @@ namespace mtad {
 namespace {
 
 constexpr int RT = 512, RWAVES = RT / 64;
-constexpr unsigned RELAY_GIVE_UP = 20000000u;  // 0.2 s of the 100 MHz clock
 constexpr int TILES = 16;                      // bf16: weight tiles of a wave, all requested ahead: reductions of up to 4096 terms, with two strips 2048
 constexpr int QUADS = 16;                      // float32: weight quads of a lane: up to 2048 terms, with two strips 1024
 __host__ __device__ constexpr int most_terms(bool bf, int strips) { return (bf ? TILES * 32 : QUADS * 16) * RWAVES / strips; }
@@ -71,7 +70,7 @@ struct Watch {
   uint32_t *sync, *status;
   uint32_t epoch;
   unsigned long long start;
-  unsigned patience;
+  unsigned patience, give_up;
   int groups, group;
   bool again;      // one of those that started over
   bool committed;  // this workgroup has had input of a layer above 0: every workgroup has done its share of layer 0
@@ -121,7 +120,7 @@ __device__ __forceinline__ bool must_leave(const Watch& c, int lane) {
     if ((uint32_t)(word >> 32) == c.epoch && !goes_on((uint32_t)word)) return true;
   }
   const unsigned long long waited = wall_clock64() - c.start;
-  if (waited > RELAY_GIVE_UP) {
+  if (waited > c.give_up) {
     if (lane == 0) {
       atomicOr(c.status, (uint32_t)ST_TIMEOUT);
       __hip_atomic_store(c.sync + 1, c.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1298,6 +1297,7 @@ __global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   watch.status = A->status;
   watch.start = wall_clock64();
   watch.patience = A->patience;
+  watch.give_up = A->give_up;
   watch.groups = gridDim.x;
   watch.group = blockIdx.x;
   watch.again = watch.committed = watch.settled = false;
@@ -1335,7 +1335,8 @@ __global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     } else {
       // It goes on.  Whoever has left was still waiting in layer 0, or for the first time in layer 1: what it has not made all of layer 2 waits for,
       // so that layer 0's words are as they were, and its units of layer 0 once more make the same words.
-      if (done) return;
+      // Once: whoever leaves after that, or from beyond layer 0, does so because the pass is given up.
+      if (done || watch.committed || watch.settled) return;
       watch.settled = true;
     }
   }

@@ -65,6 +65,7 @@ struct mtad_ctx {
   size_t relay_mail_n;
   uint32_t* relay_sync;
   unsigned relay_patience;  // ticks of the 100 MHz clock after which its workgroups count those that have started
+  unsigned relay_give_up;   // ticks after which a workgroup that waits gives the pass up
   int relay_absent;         // (tests: so many of its workgroups never start)
   // set by mtad_verify_tree around its pass: the logsumexp kernel of a bf16 pass then also gathers logp_cond
   const mtad_tree* gather_tree;
@@ -493,6 +494,7 @@ int relay_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, RelayArgs& a
   a.sync = c->relay_sync; a.status = c->status;
   a.h = c->h; a.xg = (bf16_t*)c->xg; a.ssq = c->ssq;
   a.patience = c->relay_patience;
+  a.give_up = c->relay_give_up;
   a.present = imax(1, groups - c->relay_absent);
   c->pass_np = m->d_model / 16;
   HIP_TRY(c, launch_relay(a, m->dtype, m->head_dim, groups, s));
@@ -591,6 +593,7 @@ int mtad_create(mtad_ctx** out, const mtad_config* cfg, const mtad_model* target
   }
   if (target->dtype == 1 || draft->dtype == 1) c->prompt_best = imax(c->cfg.prefill_rows, imin(PROMPT_PASS_ROWS / cfg->batch, cfg->max_context));
   c->relay_patience = 20000;  // 0.2 ms; a workgroup that has input of layer 1 by then has no further use for it
+  c->relay_give_up = 20000000;  // 0.2 s
   c->flow_on = 1;
   if (const char* e = getenv("MTAD_FUSED_PASS")) c->flow_on = atoi(e) < 0 ? 0 : (atoi(e) > 2 ? 2 : atoi(e));
   c->ws_need = carve(c, nullptr, c->prompt_best, true, true);
@@ -797,6 +800,13 @@ extern "C" int mtad_test_relay(mtad_ctx* c, int draft, int R, int absent, unsign
   if (patience) c->relay_patience = patience;
   RelayArgs a;
   return relay_shape(a, draft ? &c->dshape : &c->tshape, c->cfg.batch, R, c->cfg.max_context);
+}
+
+// Such passes are given up by a workgroup that waits after `give_up` ticks of 10 ns.
+extern "C" int mtad_test_relay_give_up(mtad_ctx* c, unsigned give_up) {
+  if (!c) return MTAD_EINVAL;
+  c->relay_give_up = give_up;
+  return MTAD_OK;
 }
 
 // What such passes have left behind (RELAY_SYNC_WORDS' first four): number of the last one, of the last one that was given up, of the last one

@@ -146,6 +146,13 @@ def _state(eng):
     return list(out)
 
 
+def _status(eng):
+    from paper_2407_09722_amd import binding as mb
+    bits = C.c_uint32()
+    mb.lib().mtad_device_status(eng.ctx, C.byref(bits), None)
+    return bits.value
+
+
 def test_which_passes_start_over():
     """With workgroups that never start all do, with all of them there none does, however short the patience."""
     eng = _engine("bf16")
@@ -182,6 +189,19 @@ def test_workgroups_that_are_counted_and_all_there(dtype):
             counted += now[2] == now[0]
     print(f"{dtype}: counted in {counted} of 15 passes", flush=True)
     assert counted > 0 and mb.mtad_device_status(eng.ctx) == 0
+    # counted, found to be all there, and then given up while they wait: the pass ends, and the next one is right
+    _relay(eng, 0, 4, 0, 1)
+    for ticks in (2, 3000, 5000):
+        print(f"{dtype}: given up after {ticks} ticks", flush=True)
+        mb.lib().mtad_test_relay_give_up(eng.ctx, C.c_uint(ticks))
+        eng.verify_phase()
+        now = _state(eng)
+        print(f"{dtype}: {now}, status {_status(eng):#x}", flush=True)
+        assert now[1] == now[0] or ticks > 2
+    mb.lib().mtad_test_relay_give_up(eng.ctx, C.c_uint(20000000))
+    eng.verify_phase()
+    torch.cuda.synchronize()
+    assert torch.equal(eng.logits.cpu(), want) and _status(eng) == 8
     eng.close()
 
 
