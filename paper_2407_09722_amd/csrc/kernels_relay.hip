@@ -16,7 +16,7 @@
 //     launch holds the compute units that some of them need, whoever has waited too long in layer 0 counts those that have started.  If some
 //     have not, the others share all units among themselves from the first layer on, with words of their own (nothing they write differs
 //     from what was there); if all have, or one has been past layer 0 and so has seen a result of everybody, the pass goes on and nobody
-//     counts again.  Every wait ends, at the latest after 0.2 s with the status bit of a pass that was given up.
+//     counts again.  Every wait ends, at the latest after 0.2 s of this one wait with the status bit of a pass that was given up.
 #include "attn_mfma_device.h"
 #include "gemm.h"
 #include "gemm_device.h"
@@ -69,7 +69,6 @@ struct RelaySmem {
 struct Watch {
   uint32_t *sync, *status;
   uint32_t epoch;
-  unsigned long long start;
   unsigned patience, give_up;
   int groups, group;
   bool again;      // one of those that started over
@@ -112,14 +111,16 @@ __device__ __forceinline__ void count_in(const Watch& c, int lane) {
   }
 }
 
-// Now and then during a wait (all lanes of a wave): is it over for another reason than its words?
-__device__ __forceinline__ bool must_leave(const Watch& c, int lane) {
+// Now and then during a wait (all lanes of a wave): is it over for another reason than its words?  since: when this was first asked in it, 0 before.
+__device__ __forceinline__ bool must_leave(const Watch& c, int lane, unsigned long long& since) {
   if (get32(c.sync + 1) == c.epoch) return true;
   if (!c.again) {
     const uint64_t word = get(rank_word(c.sync, c.group));
     if ((uint32_t)(word >> 32) == c.epoch && !goes_on((uint32_t)word)) return true;
   }
-  const unsigned long long waited = wall_clock64() - c.start;
+  const unsigned long long now = wall_clock64();
+  if (!since) since = now;
+  const unsigned long long waited = now - since;
   if (waited > c.give_up) {
     if (lane == 0) {
       atomicOr(c.status, (uint32_t)ST_TIMEOUT);
@@ -144,6 +145,7 @@ struct Nothing {
 };
 template <int N, typename At, typename Also = Nothing>
 __device__ __forceinline__ bool collect(uint64_t (&w)[N], At at, uint32_t tag, const Watch& c, int lane, Also also = Also()) {
+  unsigned long long since = 0;
 #pragma unroll 1
   for (int turns = 1;; ++turns) {
     also();
@@ -154,7 +156,7 @@ __device__ __forceinline__ bool collect(uint64_t (&w)[N], At at, uint32_t tag, c
     for (int i = 0; i < N; ++i) differ |= (uint32_t)(w[i] >> 32) ^ tag;
     const bool there = differ == 0;
     if (__all(there)) return true;
-    if ((turns & 31) == 0 && must_leave(c, lane)) return false;
+    if ((turns & 31) == 0 && must_leave(c, lane, since)) return false;
   }
 }
 
@@ -620,10 +622,11 @@ __device__ __forceinline__ bool relay_product(RelaySmem& sm, unsigned char* x, R
   if (leave) return false;
   if (resid) {
     bool stay = true;
+    unsigned long long since = 0;
     float hn = ends ? result(sm, s, m, j) : 0.f;
     for (int turns = 1; stay && __any(adds && !tagged(before, before_tag)); ++turns) {  // (there, but this load was the earlier one)
       if (adds && !tagged(before, before_tag)) before = get(before_words + before_at);
-      if ((turns & 31) == 0 && must_leave(watch, lane)) stay = false;
+      if ((turns & 31) == 0 && must_leave(watch, lane, since)) stay = false;
     }
     if (!stay) sm.leave = 1;  // (seen by all after the next barrier)
     if (ends) hn += payload(before);
@@ -1295,7 +1298,6 @@ __global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   Watch watch;
   watch.sync = A->sync;
   watch.status = A->status;
-  watch.start = wall_clock64();
   watch.patience = A->patience;
   watch.give_up = A->give_up;
   watch.groups = gridDim.x;

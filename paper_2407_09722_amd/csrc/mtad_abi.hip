@@ -65,7 +65,7 @@ struct mtad_ctx {
   size_t relay_mail_n;
   uint32_t* relay_sync;
   unsigned relay_patience;  // ticks of the 100 MHz clock after which its workgroups count those that have started
-  unsigned relay_give_up;   // ticks after which a workgroup that waits gives the pass up
+  unsigned relay_give_up;   // ticks after which a workgroup whose wait lasts gives the pass up
   int relay_absent;         // (tests: so many of its workgroups never start)
   // set by mtad_verify_tree around its pass: the logsumexp kernel of a bf16 pass then also gathers logp_cond
   const mtad_tree* gather_tree;
@@ -592,8 +592,8 @@ int mtad_create(mtad_ctx** out, const mtad_config* cfg, const mtad_model* target
     return MTAD_ESHAPE;
   }
   if (target->dtype == 1 || draft->dtype == 1) c->prompt_best = imax(c->cfg.prefill_rows, imin(PROMPT_PASS_ROWS / cfg->batch, cfg->max_context));
-  c->relay_patience = 20000;  // 0.2 ms; a workgroup that has input of layer 1 by then has no further use for it
-  c->relay_give_up = 20000000;  // 0.2 s
+  c->relay_patience = 20000;  // 0.2 ms, of one wait in layer 0
+  c->relay_give_up = 20000000;  // 0.2 s: a wait lasts as long as one step of a layer at the most, which a single workgroup does in some milliseconds
   c->flow_on = 1;
   if (const char* e = getenv("MTAD_FUSED_PASS")) c->flow_on = atoi(e) < 0 ? 0 : (atoi(e) > 2 ? 2 : atoi(e));
   c->ws_need = carve(c, nullptr, c->prompt_best, true, true);
@@ -802,7 +802,7 @@ extern "C" int mtad_test_relay(mtad_ctx* c, int draft, int R, int absent, unsign
   return relay_shape(a, draft ? &c->dshape : &c->tshape, c->cfg.batch, R, c->cfg.max_context);
 }
 
-// Such passes are given up by a workgroup that waits after `give_up` ticks of 10 ns.
+// Such passes are given up by a workgroup one of whose waits lasts `give_up` ticks of 10 ns.
 extern "C" int mtad_test_relay_give_up(mtad_ctx* c, unsigned give_up) {
   if (!c) return MTAD_EINVAL;
   c->relay_give_up = give_up;

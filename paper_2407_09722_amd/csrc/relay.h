@@ -46,8 +46,8 @@ struct RelayArgs {
   float* h;       // float32 models: the hidden states
   bf16_t* xg;     // bf16 models: h * final gain as hi / lo terms (act_offset), and
   float* ssq;     // sums of squares of h per strip, [rows][d / 16]
-  unsigned patience;  // ticks of the 100 MHz clock after which a workgroup that waits in layer 0 counts those that have started
-  unsigned give_up;   // ticks after which one that waits gives the pass up
+  unsigned patience;  // ticks of the 100 MHz clock after which a workgroup whose wait in layer 0 lasts counts those that have started
+  unsigned give_up;   // ticks after which one whose wait lasts gives the pass up
   int present;        // workgroups that take part (all but in tests)
 };
 

@@ -205,6 +205,40 @@ def test_workgroups_that_are_counted_and_all_there(dtype):
     eng.close()
 
 
+def test_a_pass_that_lasts_is_not_given_up():
+    """Three workgroups for a ragged batch, which share the long sequence's heads unevenly: they wait for each other in every layer, and the pass is
+    several times as long as one wait may last."""
+    from paper_2407_09722_amd import binding as mb
+    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    shape, draft, n = si.ModelShape(8, 17 * 64, 17, 17, 64, 704, 512, "bf16"), si.ModelShape(1, 64, 1, 1, 64, 160, 512, "bf16"), 12000
+    eng = Engine(DeviceModel(shape, _weights(shape, 3, "target"), DEV), DeviceModel(draft, _weights(draft, 3, "draft"), DEV), batch=8, gamma=1, beam=1,
+                 mode="mtad", max_context=n + 100, prefill_rows=8, device=DEV)
+    eng.tkv.k.normal_(generator=torch.Generator(DEV).manual_seed(1))
+    eng.tkv.v.normal_(generator=torch.Generator(DEV).manual_seed(2))
+    eng.tkv.len.copy_(torch.tensor([n, 5, 40, 17, 100, 64, 3, 80], dtype=torch.int32))
+
+    def one():
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        mb.mtad_verify_tree(eng.ctx, eng.target.desc, eng.tkv.desc, eng.root_tok, eng.ar_tree, eng.logp_cond, eng.row_lse, eng.logits, None)
+        ev[1].record()
+        torch.cuda.synchronize()
+        return eng.logits[:, 0].cpu(), ev[0].elapsed_time(ev[1])
+
+    groups = _relay(eng, 0, 1, 0, 300)
+    assert groups > 3
+    one()
+    want, _ = one()
+    _relay(eng, 0, 1, groups - 3, 300)
+    mb.lib().mtad_test_relay_give_up(eng.ctx, C.c_uint(100000))           # 1 ms
+    before = _state(eng)
+    got, ms = one()
+    now = _state(eng)
+    print(f"{groups} workgroups, 3 there: {ms:.1f} ms, {now}, status {_status(eng)}", flush=True)
+    assert now[3] == before[3] + 1 and ms > 2 and _status(eng) == 0 and torch.equal(got, want)
+    eng.close()
+
+
 @pytest.mark.parametrize("layers", [12, 24, 48])
 @pytest.mark.parametrize("heads,kv_heads,ffn,dtype,several", [(12, 12, 2048, "bf16", (1, 5, 8)), (12, 1, 2048, "bf16", (1, 5, 8)), (16, 16, 2816, "bf16", (1, 5)),
                                                               (8, 8, 1408, "fp32", (1, 5))])
