@@ -1,6 +1,7 @@
 // Internal views of the caller's beam history, tree and accept buffers, and the launchers of kernels_beam.hip.
 #pragma once
 #include "common.h"
+#include "relay.h"
 
 #define MTAD_MAX_ROWS 64
 #define MTAD_MAX_GAMMA 64
@@ -23,9 +24,9 @@ struct AcceptView {
 };
 
 hipError_t launch_draft_rows(const RowDesc& rd, const int32_t* len, BeamView hist, const int32_t* cu_tok, const int32_t* cu_cnt,
-                             int step, int B, int R, int gamma, int beam, int cap, uint32_t* status, uint32_t* epoch, hipStream_t s);
+                             int step, int B, int R, int gamma, int beam, int cap, uint32_t* status, const PassCount& count, hipStream_t s);
 hipError_t launch_verify_rows(const RowDesc& rd, const int32_t* len, const int32_t* root_tok, TreeView tree, int B, int cap,
-                              uint32_t* status, uint32_t* epoch, hipStream_t s);
+                              uint32_t* status, const PassCount& count, hipStream_t s);
 hipError_t launch_prefill_rows(const RowDesc& rd, const int32_t* len, const int32_t* tokens, int n, int c0, int B, int R, int cap,
                                uint32_t* status, hipStream_t s);
 hipError_t launch_advance_len(int32_t* len, const int32_t* nspec, int B, int cap, hipStream_t s);

@@ -35,11 +35,10 @@ __device__ __forceinline__ float uniform01(uint64_t key, uint64_t idx) {
 // chain mask: bits 0..r
 __device__ __forceinline__ uint64_t chain_bits(int r) { return (r >= 63) ? ~0ull : ((1ull << (r + 1)) - 1ull); }
 
-__global__ void draft_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, BeamView hist, const int32_t* __restrict__ cu_tok,
-                                  const int32_t* __restrict__ cu_cnt, int step, int B, int R, int gamma, int beam, int cap,
-                                  uint32_t* __restrict__ status, uint32_t* __restrict__ epoch) {
+__device__ __forceinline__ void draft_row(const RowDesc& rd, const int32_t* __restrict__ len, const BeamView& hist, const int32_t* __restrict__ cu_tok,
+                                          const int32_t* __restrict__ cu_cnt, int step, int B, int R, int gamma, int beam, int cap,
+                                          uint32_t* __restrict__ status) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx == 0 && epoch) *epoch += 1;  // the pass's number
   if (idx >= B * R) return;
   const int s = idx / R, r = idx % R;
   int cnt = cu_cnt[s];
@@ -85,18 +84,25 @@ __global__ void draft_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, B
   rd.mask[idx] = mask;
 }
 
+__global__ void draft_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, BeamView hist, const int32_t* __restrict__ cu_tok,
+                                  const int32_t* __restrict__ cu_cnt, int step, int B, int R, int gamma, int beam, int cap,
+                                  uint32_t* __restrict__ status, PassCount count) {
+  const uint32_t last = last_pass(count);
+  draft_row(rd, len, hist, cu_tok, cu_cnt, step, B, R, gamma, beam, cap, status);
+  if (blockIdx.x == 0) count_pass(count, last, threadIdx.x);
+}
+
 hipError_t launch_draft_rows(const RowDesc& rd, const int32_t* len, BeamView hist, const int32_t* cu_tok, const int32_t* cu_cnt,
-                             int step, int B, int R, int gamma, int beam, int cap, uint32_t* status, uint32_t* epoch, hipStream_t s) {
+                             int step, int B, int R, int gamma, int beam, int cap, uint32_t* status, const PassCount& count, hipStream_t s) {
   hipLaunchKernelGGL(draft_rows_kernel, dim3((B * R + 63) / 64), dim3(64), 0, s, rd, len, hist, cu_tok, cu_cnt, step, B, R, gamma,
-                     beam, cap, status, epoch);
+                     beam, cap, status, count);
   return hipGetLastError();
 }
 
-__global__ void verify_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, const int32_t* __restrict__ root_tok, TreeView tree,
-                                   int B, int cap, uint32_t* __restrict__ status, uint32_t* __restrict__ epoch) {
+__device__ __forceinline__ void verify_row(const RowDesc& rd, const int32_t* __restrict__ len, const int32_t* __restrict__ root_tok, const TreeView& tree,
+                                           int B, int cap, uint32_t* __restrict__ status) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int M = tree.M;
-  if (idx == 0 && epoch) *epoch += 1;  // the pass's number
   if (idx >= B * M) return;
   const int s = idx / M, r = idx % M;
   const int n = len[s];
@@ -112,9 +118,16 @@ __global__ void verify_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, 
   if (r == 0) rd.nspec[s] = M;
 }
 
+__global__ void verify_rows_kernel(RowDesc rd, const int32_t* __restrict__ len, const int32_t* __restrict__ root_tok, TreeView tree,
+                                   int B, int cap, uint32_t* __restrict__ status, PassCount count) {
+  const uint32_t last = last_pass(count);
+  verify_row(rd, len, root_tok, tree, B, cap, status);
+  if (blockIdx.x == 0) count_pass(count, last, threadIdx.x);
+}
+
 hipError_t launch_verify_rows(const RowDesc& rd, const int32_t* len, const int32_t* root_tok, TreeView tree, int B, int cap,
-                              uint32_t* status, uint32_t* epoch, hipStream_t s) {
-  hipLaunchKernelGGL(verify_rows_kernel, dim3((B * tree.M + 63) / 64), dim3(64), 0, s, rd, len, root_tok, tree, B, cap, status, epoch);
+                              uint32_t* status, const PassCount& count, hipStream_t s) {
+  hipLaunchKernelGGL(verify_rows_kernel, dim3((B * tree.M + 63) / 64), dim3(64), 0, s, rd, len, root_tok, tree, B, cap, status, count);
   return hipGetLastError();
 }
 

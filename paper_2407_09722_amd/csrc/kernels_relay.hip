@@ -1265,7 +1265,7 @@ __device__ __forceinline__ bool relay_run(RelaySmem& sm, unsigned char* x, const
     at.l = l;
     at.rank = rank;
     at.groups = groups;
-    at.tag = watch.epoch << 6 | (uint32_t)l;
+    at.tag = watch.epoch << 6 | (uint32_t)(l + 1);
     at.words = words + (size_t)(l & 1) * slot;
     at.h_words = words + (size_t)(~l & 1) * slot + A->mail.hd;
 #pragma unroll 1

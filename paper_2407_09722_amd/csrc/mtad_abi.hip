@@ -687,7 +687,7 @@ int mtad_draft_beam_step(mtad_ctx* c, const mtad_model* draft, mtad_kv* dkv, mta
   const int R = (step == 0) ? gamma + 1 : beam;
   const BeamView hv{hist->tok, hist->parent, hist->cum_logq};
   HIP_TRY(c, launch_draft_rows(c->rd, dkv->len, hv, st->catchup_tok, st->catchup_cnt, step, B, R, gamma, beam,
-                               dkv->page_size * dkv->max_pages, c->status, c->relay_sync, s));
+                               dkv->page_size * dkv->max_pages, c->status, PassCount{c->relay_sync, c->relay_mail, c->relay_mail_n}, s));
   c->lse_later = draft->dtype == 1 && c->warp_k == 0 && beam > 1;  // (warping and a saved row of log q read them first)
   const bool lse_later = c->lse_later;
   int rc = decoder_pass(c, draft, dkv, R, s, c->dlogits, c->lse);
@@ -720,7 +720,7 @@ int mtad_verify_tree(mtad_ctx* c, const mtad_model* target, mtad_kv* tkv, const 
   if (tree->M < 1 || tree->M > c->Rmax) return MTAD_ESHAPE;
   hipStream_t s = (hipStream_t)stream;
   const int B = c->cfg.batch, M = tree->M;
-  HIP_TRY(c, launch_verify_rows(c->rd, tkv->len, root_tok, tview(tree), B, tkv->page_size * tkv->max_pages, c->status, c->relay_sync, s));
+  HIP_TRY(c, launch_verify_rows(c->rd, tkv->len, root_tok, tview(tree), B, tkv->page_size * tkv->max_pages, c->status, PassCount{c->relay_sync, c->relay_mail, c->relay_mail_n}, s));
   c->gather_tree = c->warp_k > 0 ? nullptr : tree;  // warped rows are gathered after the warp
   c->gather_out = c->warp_k > 0 ? nullptr : logp_cond;
   int rc = decoder_pass(c, target, tkv, M, s, logits, row_lse);
@@ -806,6 +806,14 @@ extern "C" int mtad_test_relay(mtad_ctx* c, int draft, int R, int absent, unsign
 extern "C" int mtad_test_relay_give_up(mtad_ctx* c, unsigned give_up) {
   if (!c) return MTAD_EINVAL;
   c->relay_give_up = give_up;
+  return MTAD_OK;
+}
+
+// The number of the last such pass becomes `epoch`.
+extern "C" int mtad_test_relay_epoch(mtad_ctx* c, uint32_t epoch) {
+  if (!c || !c->relay_sync) return MTAD_EINVAL;
+  HIP_TRY(c, hipDeviceSynchronize());
+  HIP_TRY(c, hipMemcpy(c->relay_sync, &epoch, sizeof(epoch), hipMemcpyHostToDevice));
   return MTAD_OK;
 }
 

@@ -5,7 +5,7 @@
 
 namespace mtad {
 
-constexpr int RELAY_MAX_LAYERS = 48;  // weight pointers travel in the kernel arguments
+constexpr int RELAY_MAX_LAYERS = 48;  // weight pointers travel in the kernel arguments; below 63 (tags)
 constexpr int RELAY_MAX_ROWS = 8;     // rows of a pass, all sequences together
 constexpr int RELAY_MAX_SPLITS = 8;   // key splits of an attention unit
 constexpr int RELAY_MAX_GROUPS = 512;  // workgroups
@@ -21,12 +21,34 @@ struct RelayMail {
   int qkv, att, part, hm, act, hd;  // first word of: q, k, v [rows][packed features]; attention [rows][d]; its splits; residual stream after o; act; after down
   int slot;                         // words of a layer
 };
-// Words that say who takes part (uint32_t unless noted); epoch: the number of this pass, counted by the row descriptors' kernel.
+// Words that say who takes part (uint32_t unless noted); epoch: the number of this pass, counted by the row descriptors' kernel (PassCount).
 //   [0] epoch   [1] last pass that was given up   [2] last pass whose workgroups were counted   [3] passes that have started over
 //   [64 + b]    state of workgroup b: epoch * 4 + 1 present, 2 past layer 0, 3 present and counted, 0 done without having been past layer 0
 //   [64 + RELAY_MAX_GROUPS + 2 b]  (uint64_t) epoch << 32 | number of workgroups that start over << 16 | rank of b (0xFFFF: not one of
 //                                  them); no workgroups: the pass goes on
 constexpr int RELAY_SYNC_WORDS = 64 + 3 * RELAY_MAX_GROUPS;
+
+// A word's tag is epoch << 6 | layer + 1, so that it comes round after 2^26 passes (an hour and a half of short ones).  Whenever the low 26 bits
+// of the epoch become 0 all words become 0, which no tag is, as they are when a workspace is bound, and the states those of the pass
+// before: nothing that is found with a pass's tag is older than the pass.
+struct PassCount {
+  uint32_t* sync;  // null: not counted
+  uint64_t* words;
+  size_t n;
+};
+__device__ __forceinline__ uint32_t last_pass(const PassCount& c) { return c.sync ? c.sync[0] : 0; }  // (requested before the rows, used after them)
+__device__ __forceinline__ void count_pass(const PassCount& c, uint32_t last, int lane) {  // one wave, before the pass
+  if (!c.sync) return;
+  const uint32_t epoch = (uint32_t)__builtin_amdgcn_readfirstlane((int)last) + 1u;
+  if (lane == 0) c.sync[0] = epoch;
+  if (epoch << 6) return;
+  for (size_t i = lane; i < c.n; i += 64) c.words[i] = 0;
+  for (int i = lane; i < RELAY_MAX_GROUPS; i += 64) {
+    c.sync[64 + i] = epoch * 4u - 1u;
+    ((uint64_t*)(c.sync + 64 + RELAY_MAX_GROUPS))[i] = (uint64_t)(epoch - 1u) << 32;
+  }
+  if (lane == 0) c.sync[1] = c.sync[2] = epoch - 1u;
+}
 
 struct RelayArgs {
   const void* w[RELAY_MAX_LAYERS * 6 + 3];  // the model's weight list (order of mtad_model.weights)

@@ -268,6 +268,43 @@ def test_long_passes_do_not_start_over(layers, heads, kv_heads, ffn, dtype, seve
     eng.close()
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_tags_that_come_round(dtype):
+    """26 bits of a pass's number are in its words' tags.  Passes on both sides of the place where they come round, the words never written
+    before among them, and words that the pass 2^26 earlier left: neither may be taken for a result."""
+    from paper_2407_09722_amd import binding as mb
+    eng = _engine(dtype)
+    n, absent = _relay(eng, 0, 4), lambda a: _relay(eng, 0, 4, a, 300)
+    eng.verify_phase()
+    want = eng.logits.cpu()
+    token = eng.t_tok[0, 1].clone()
+
+    def passes(first, last, missing):
+        assert mb.lib().mtad_test_relay_epoch(eng.ctx, C.c_uint32(first - 1 & 0xFFFFFFFF)) == 0
+        absent(missing)
+        for e in range(first, last + 1):
+            eng.verify_phase()
+            assert torch.equal(eng.logits.cpu(), want), (hex(e), missing)
+            assert _state(eng)[0] == e & 0xFFFFFFFF
+
+    # (no number twice.)  Starting over, the second copy of the words has never been written
+    for first, missing in ((0x3fffffe, n - 2), (0x7fffffe, 0), (0xfffffffe, n - 2)):
+        print(f"{dtype}: from pass {first:#x}, {missing} missing", flush=True)
+        passes(first, first + 5, missing)
+    # words of another pass in both copies, 2^26 passes earlier
+    eng.t_tok[0, 1] = token ^ 1
+    assert mb.lib().mtad_test_relay_epoch(eng.ctx, C.c_uint32(0xc000004)) == 0
+    for missing in (n - 2, 0):
+        absent(missing)
+        eng.verify_phase()
+        assert not torch.equal(eng.logits.cpu(), want)
+    eng.t_tok[0, 1] = token
+    passes(0xffffffe, 0x10000006, n - 2)
+    passes(0x10000007, 0x10000008, 0)
+    assert mb.mtad_device_status(eng.ctx) == 0
+    eng.close()
+
+
 def test_a_pass_that_is_given_up():
     """A workgroup missing and nobody allowed to count it out: the pass ends all the same, the status says so, and the next one is right."""
     from paper_2407_09722_amd import binding as mb
