@@ -417,17 +417,6 @@ __device__ __forceinline__ void pin(T& v) {
   asm volatile("" : "+v"(v));
 }
 
-// 1 / sqrt(x) and 1 / x to the last place or two: the instruction's result and a Newton step, a quarter of the exact functions'
-// instructions.  For results that are handed on as two bf16 terms (16 bits).
-__device__ __forceinline__ float inverse_root(float x) {
-  const float r = __builtin_amdgcn_rsqf(x);
-  return fmaf(r, 0.5f * fmaf(-x * r, r, 1.0f), r);
-}
-__device__ __forceinline__ float inverse(float x) {  // (of infinity: 0)
-  const float r = __builtin_amdgcn_rcpf(x);
-  return x < 3e38f ? fmaf(r, fmaf(-x, r, 1.0f), r) : r;
-}
-
 // One unit of a product.  fresh: its input is not in LDS yet.
 template <bool BF, int HD>
 __device__ __forceinline__ bool relay_product(RelaySmem& sm, unsigned char* x, RelayPtr A, Watch& watch, const Step& at, int step, int unit, bool fresh, int& parity, int& commit_was) {
@@ -613,7 +602,7 @@ __device__ __forceinline__ bool relay_product(RelaySmem& sm, unsigned char* x, R
       const float t = sm.ssq[parity][w];
       ssq += (unsigned)(w - m * wpr) < (unsigned)wpr ? t : 0.f;
     }
-    inv = BF ? inverse_root(ssq * (1.0f / (float)u.K) + eps) : 1.0f / sqrtf(ssq / (float)u.K + eps);
+    inv = 1.0f / sqrtf(ssq / (float)u.K + eps);
   }
   pin(inv);
   multiply<BF>(sm, x, wts, u, step, R, HD, wave, lane);
@@ -654,7 +643,7 @@ __device__ __forceinline__ bool relay_product(RelaySmem& sm, unsigned char* x, R
   const float y0 = result(sm, s, m, j), yp = result(sm, s, m, j + 8);
   float y1 = y0 * inv, y2 = yp * inv;
   if (step == RS_GU) {
-    put(at.words + out, at.tag, BF ? y1 * y2 * inverse(1.0f + __builtin_amdgcn_exp2f(-ATTN_LOG2E * y1)) : y1 / (1.0f + expf(-y1)) * y2);
+    put(at.words + out, at.tag, y1 / (1.0f + expf(-y1)) * y2);
     return true;
   }
   if (turned) {
