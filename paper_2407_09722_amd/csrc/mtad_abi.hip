@@ -501,12 +501,29 @@ int relay_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, RelayArgs& a
   return MTAD_OK;
 }
 
+// Whether launches on a stream may use every compute unit; a stream that cannot be asked may.
+bool whole_machine(const mtad_ctx* c, hipStream_t s) {
+  uint32_t mask[RELAY_MAX_GROUPS / 32] = {};
+  const int words = (c->n_cus + 31) / 32;
+  if (words > RELAY_MAX_GROUPS / 32) return true;
+  if (hipExtStreamGetCUMask(s, (uint32_t)words, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  int n = 0;
+  for (int i = 0; i < words; ++i) n += __builtin_popcount(mask[i]);
+  return n == 0 || n >= c->n_cus;
+}
+
 // The pass, followed by final norm + lm_head + row logsumexp when `logits` is given.
 int decoder_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStream_t s, float* logits, float* lse) {
   if (logits && c->flow_on == 1 && c->relay_mail) {
     RelayArgs a;
     const int groups = relay_shape(a, m, c->cfg.batch, R, c->cfg.max_context);
-    if (groups > 0 && (size_t)4 * relay_mail_words(a.rows, a.d, a.f, a.H, a.KVH, m->head_dim, a.splits, nullptr) <= c->relay_mail_n) {
+    // All its workgroups have to be on the machine together.  On a stream of fewer compute units every pass would find some missing and start over with
+    // the others: 12 layers x 768 of 5 rows on 192 / 128 / 64 units 513 / 584 / 680 us, a launch a step 314 / 316 / 351.  (124 workgroups did so on a
+    // stream of 124 units as well: they are dealt to the XCDs in turn, whatever units a mask leaves there.)
+    if (groups > 0 && (size_t)4 * relay_mail_words(a.rows, a.d, a.f, a.H, a.KVH, m->head_dim, a.splits, nullptr) <= c->relay_mail_n && whole_machine(c, s)) {
       const int rc = relay_pass(c, m, kv, a, groups, s);
       return rc ? rc : lm_head(c, m, a.rows, logits, lse, s);
     }

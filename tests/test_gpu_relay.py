@@ -320,6 +320,51 @@ def test_a_pass_that_is_given_up():
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_streams_of_fewer_compute_units(dtype):
+    """On a stream that has not all compute units a pass is launched a step at a time, on one that has them it is not; neither starts over, eager
+    or captured."""
+    from paper_2407_09722_amd import binding as mb
+    hip, eng = C.CDLL("libamdhip64.so"), _engine(dtype)
+    groups, cus = _relay(eng, 0, 4), torch.cuda.get_device_properties(0).multi_processor_count
+    eng.verify_phase()
+    relay = eng.logits.cpu()
+    mb.mtad_set_fused_pass(eng.ctx, 0)
+    eng.verify_phase()
+    steps = eng.logits.cpu()
+    mb.mtad_set_fused_pass(eng.ctx, 1)
+    assert not torch.equal(relay, steps)                # the two forms add in different orders
+    for n in (groups // 2, groups, cus - 1, cus):
+        words = (cus + 31) // 32
+        mask = (C.c_uint32 * words)(*[((1 << max(0, min(32, n - 32 * i))) - 1) for i in range(words)])
+        made = C.c_void_p()
+        assert hip.hipExtStreamCreateWithCUMask(C.byref(made), C.c_uint32(words), mask) == 0
+        stream = torch.cuda.ExternalStream(made.value)
+        before = _state(eng)
+        print(f"{dtype}: {groups} workgroups, {n} compute units", flush=True)
+        for _ in range(3):
+            eng.logits.zero_()
+            torch.cuda.synchronize()
+            eng.verify_phase(stream=stream)
+            now = _state(eng)
+            assert torch.equal(eng.logits.cpu(), relay if n == cus else steps), n
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            eng.verify_phase(stream=stream)
+        for _ in range(3):
+            eng.logits.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(stream):
+                graph.replay()
+            now = _state(eng)
+            assert torch.equal(eng.logits.cpu(), relay if n == cus else steps), n
+        assert now[3] == before[3] and mb.mtad_device_status(eng.ctx) == 0, n
+        del graph
+        torch.cuda.synchronize()
+        assert hip.hipStreamDestroy(made) == 0
+    eng.close()
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_captured_iterations(dtype):
     """Iterations replayed from a graph, with eager work between, and two engines on streams of their own at the same time."""
     from paper_2407_09722_amd import binding as mb
