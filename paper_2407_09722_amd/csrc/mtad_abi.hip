@@ -609,7 +609,9 @@ int mtad_create(mtad_ctx** out, const mtad_config* cfg, const mtad_model* target
     return MTAD_ESHAPE;
   }
   if (target->dtype == 1 || draft->dtype == 1) c->prompt_best = imax(c->cfg.prefill_rows, imin(PROMPT_PASS_ROWS / cfg->batch, cfg->max_context));
-  c->relay_patience = 20000;  // 0.2 ms, of one wait in layer 0
+  // 50 us of one wait in layer 0.  Beside another stream (products of 8192, 2048 and 512 features, or a second engine) passes take the same time with 50 and
+  // 200 us; with 20 two engines of the 4-layer float32 model start over in a third of their passes, 144 us a pair instead of 118.
+  c->relay_patience = 5000;
   c->relay_give_up = 20000000;  // 0.2 s: a wait lasts as long as one step of a layer at the most, which a single workgroup does in some milliseconds
   c->flow_on = 1;
   if (const char* e = getenv("MTAD_FUSED_PASS")) c->flow_on = atoi(e) < 0 ? 0 : (atoi(e) > 2 ? 2 : atoi(e));
