@@ -1365,19 +1365,31 @@ int relay_mail_words(int rows, int d, int f, int H, int KVH, int hd, int splits,
 
 namespace {
 // Where one launch is the faster.  us of a pass of four layers, a launch a step / one launch, on 256 tokens (bf16 heads x dims, ffn):
-//   12 x 64, 2048 one row 99 / 65, 4 rows 104 / 83, 8 rows 115 / 99, 8 sequences 120 / 104; 16 x 64, 2816 110 / 69, 5 rows 123 / 104;
-//   16 on 4 x 64, 4096 (30 MB a layer) 113 / 86, 4 rows 128 / 114; 24 x 64, 4096 (57 MB) 130 / 110, but 4 sequences of 1500 tokens 173 / 182, and
-//   12 x 128, 4096 (57 MB) 133 / 123, 4 rows 143 / 151;
-//   float32 4 x 64, 688 92 / 67, 8 rows 112 / 89; 8 x 64, 1408 111 / 81, 5 rows 126 / 108; 8 on 2 x 64, 2048 108 / 90, 4 rows 120 / 105, but 8 sequences 116 / 126.
-// Every workgroup of a step reads all words of the step before: 12 x 64, 3072 at 5 rows, 15360 words, still 119 / 100.  And attention units in
-// excess of the workgroups that the products leave free are on those which the next step waits for: 12 x 64, 2048, 8 sequences of 1500 tokens
-// (192 units, 16384 words) 140 / 144, of 4000 187 / 204, 16 x 64, 2816, 4 rows on 4000 tokens (128 units, 11264 words) 137 / 136; float32
-// 8 x 64, 1408, 5 rows on 1500 tokens (120 units, 7040 words) 130 / 151; few words a step leave room: bf16 4 x 64, 704, 8 sequences of 4000 (256 units) 116 / 98.
-bool relay_pays(const RelayArgs& a, int dtype, int hd) {
-  const int64_t layer = (int64_t)(dtype == 1 ? 2 : 4) * ((int64_t)(a.H + 2 * a.KVH) * hd * a.d + (int64_t)a.d * a.H * hd + (int64_t)3 * a.d * a.f);
-  const int words = a.rows * a.f, attn = a.units[RS_ATTN] * (dtype == 1 ? hd / 64 : 1);  // (units of half as many keys at 128 dims)
-  if (dtype == 1) return layer <= (int64_t)(a.rows == 1 ? 56 : 32) << 20 && words <= 16384 && attn <= (words <= 6144 ? 192 : words <= 12288 ? 128 : 96);
-  return layer <= (int64_t)16 << 20 && words <= 8192 && attn <= (layer <= (int64_t)4 << 20 ? 256 : words <= 6144 ? 128 : 64);
+//   12 x 64, 2048 one row 96 / 69, 5 rows 111 / 96, 8 rows 112 / 103, 8 sequences 117 / 106; 16 on 4 x 64, 4096 (29 MB a layer) 112 / 93;
+//   24 x 64, 4096 (54 MB) 128 / 113; float32 4 x 64, 688 5 rows 101 / 84, 8 rows 107 / 93; 8 x 64, 1408 one row 108 / 84, 5 rows 122 / 110.
+// What it saves grows with the layers, what it costs once does not; 12 x 64, 2048 of 5 rows, 2 / 12 / 24 / 48 layers: 61 / 57, 308 / 252, 604 / 486, 1193 / 948.
+// Against it count the words that are handed on in a layer (everybody who needs them polls for them), those of the activation most, which all of
+// down's units read; attention units (their splits are one more hand-over); units in excess of the compute units (a workgroup with units of two steps
+// in a row requests the second one's weights late); more than one sequence; and, bound by their arithmetic, float32 weights.  The lines are drawn
+// through 1200 shapes of 1 to 24 heads, with 1, 2, 4 and 12 layers each, contexts of 32 to 4000 tokens and 1 to 8 rows of 1 to 8 sequences, measured on
+// both sides.  What they admit keeps nine tenths of what could be gained (of float32 models with heads of 64, and of one layer with heads of 128, half) and
+// takes at most 1.02 of a launch a step (in 900 further passes of 2 to 24 layers: 1.02 once, else 1.01).  What they leave out took up to 1.19: 8 x 128, 3264 of 5 rows 42.5 / 47.0, 70 / 76, 359 / 382 (1, 2, 12
+// layers); 16 on 8 x 64, 3296 of 4 sequences, 12 layers 1.16; float32 4 on 1 x 64, 768 of 2 x 4 rows on 2200 tokens 1.18, 1.14, 1.16 (1, 2, 4 layers).
+bool relay_pays(const RelayArgs& a, int dtype, int hd, int cus) {
+  const int qkv = (a.H + 2 * a.KVH) * hd, L = a.n_layers;
+  const double mb = (double)((int64_t)(dtype == 1 ? 2 : 4) * ((int64_t)qkv * a.d + (int64_t)a.d * a.H * hd + (int64_t)3 * a.d * a.f)) / (1 << 20);
+  const int act = a.rows * a.f, units = a.units[RS_ATTN], over = a.first[RS_GU] + a.units[RS_GU] - cus;
+  const double words = (double)a.rows * (qkv + a.H * hd + 2 * a.d + a.f) / 1024;
+  double against = words + 2 * act / 1024.0 + units / 10.0 + (over > 0 ? over / 20.0 : 0) + (a.B > 1 ? 4 : 0);
+  if (dtype == 1) {
+    const int attn = units * (hd / 64);  // (units of half as many keys at 128 dims)
+    if (mb > (a.rows == 1 ? 56 : 32) || act > 16384 || attn > (act <= 6144 ? 192 : act <= 12288 ? 128 : 96)) return false;
+    if (a.B == 1 && mb <= 16 && L >= (hd == 64 ? 4 : 8)) return true;  // (at most 1.00 in all that were measured)
+    return against <= (hd == 64 ? (L == 1 ? 38 : L >= 4 ? 52 : mb <= 20 ? 61 : 47) : (L == 1 ? 17 : L < 4 ? 41 : 54));
+  }
+  if (mb > 16 || act > 8192 || units > (mb <= 4 ? 256 : act <= 6144 ? 128 : 64)) return false;
+  against += mb;
+  return against <= (hd == 64 ? (L == 1 ? 10 : L < 4 ? 34 : L < 8 ? 33 : 52) : (L == 1 ? 39 : 55));
 }
 
 int most_staged(const RelayArgs& a, int hd) {
@@ -1386,7 +1398,7 @@ int most_staged(const RelayArgs& a, int hd) {
 }
 }  // namespace
 
-int relay_plan(RelayArgs& a, int dtype, int hd, int max_context) {
+int relay_plan(RelayArgs& a, int dtype, int hd, int max_context, bool any) {
   const int R = a.rows, hhd = a.H * hd, qw = (a.H + 2 * a.KVH) * hd, most = device_cus();
   if (R < 1 || R > RELAY_MAX_ROWS || a.n_layers < 1 || a.n_layers > RELAY_MAX_LAYERS || (hd != 64 && hd != 128)) return 0;
   if (a.d % 16 || a.f % 8 || most > RELAY_MAX_GROUPS || a.B * a.KVH > most || (int64_t)4 * R * most_staged(a, hd) > RELAY_MAX_LDS) return 0;
@@ -1422,7 +1434,7 @@ int relay_plan(RelayArgs& a, int dtype, int hd, int max_context) {
     const int end = a.first[s] + a.units[s];
     if (end > groups) groups = end;
   }
-  if (!relay_pays(a, dtype, hd)) return 0;
+  if (!any && !relay_pays(a, dtype, hd, most)) return 0;
   return groups < most ? groups : most;
 }
 

@@ -67,6 +67,7 @@ struct mtad_ctx {
   unsigned relay_patience;  // ticks of the 100 MHz clock after which its workgroups count those that have started
   unsigned relay_give_up;   // ticks after which a workgroup whose wait lasts gives the pass up
   int relay_absent;         // (tests: so many of its workgroups never start)
+  bool relay_any;           // (tests: also where it is not the faster form)
   // set by mtad_verify_tree around its pass: the logsumexp kernel of a bf16 pass then also gathers logp_cond
   const mtad_tree* gather_tree;
   float* gather_out;
@@ -105,14 +106,15 @@ int shape_ok(const mtad_model* m) {
 // would double the workspace for prompts longer than 4096 tokens.
 constexpr int PROMPT_PASS_ROWS = 4096;
 
-// The one-launch pass of small models, B sequences of R rows: fills in what depends on shapes alone and returns its workgroups, 0 where
+// The one-launch pass of small models, R rows a sequence: fills in what depends on shapes alone and returns its workgroups, 0 where
 // the steps are launched one by one.
-int relay_shape(RelayArgs& a, const mtad_model* m, int B, int R, int max_context) {
+int relay_shape(const mtad_ctx* c, RelayArgs& a, const mtad_model* m, int R) {
+  const int B = c->cfg.batch;
   memset(&a, 0, sizeof(a));
   a.n_layers = m->n_layers; a.d = m->d_model; a.f = m->d_ffn; a.H = m->n_heads; a.KVH = m->n_kv_heads; a.vocab = m->vocab;
   a.eps = m->rms_eps;
   a.rows = B * R; a.Rseq = R; a.B = B;
-  return relay_plan(a, m->dtype, m->head_dim, max_context);
+  return relay_plan(a, m->dtype, m->head_dim, c->cfg.max_context, c->relay_any);
 }
 
 struct Carver {
@@ -200,7 +202,7 @@ size_t carve(mtad_ctx* c, char* base, int prompt_rows, bool roomy, bool relay) {
     for (const mtad_model* m : {&t, &d})
       for (int R = 1; R <= c->Rmax && c->cfg.batch * R <= RELAY_MAX_ROWS; ++R) {
         RelayArgs a;
-        if (relay_shape(a, m, c->cfg.batch, R, c->cfg.max_context) < 1) continue;
+        if (relay_shape(c, a, m, R) < 1) continue;
         c->relay_mail_n = imax64(c->relay_mail_n, (size_t)4 * relay_mail_words(a.rows, a.d, a.f, a.H, a.KVH, m->head_dim, a.splits, nullptr));
       }
     if (c->relay_mail_n) {
@@ -519,7 +521,7 @@ bool whole_machine(const mtad_ctx* c, hipStream_t s) {
 int decoder_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStream_t s, float* logits, float* lse) {
   if (logits && c->flow_on == 1 && c->relay_mail) {
     RelayArgs a;
-    const int groups = relay_shape(a, m, c->cfg.batch, R, c->cfg.max_context);
+    const int groups = relay_shape(c, a, m, R);
     // All its workgroups have to be on the machine together.  On a stream of fewer compute units every pass would find some missing and start over with
     // the others: 12 layers x 768 of 5 rows on 192 / 128 / 64 units 513 / 584 / 680 us, a launch a step 314 / 316 / 351.  (124 workgroups did so on a
     // stream of 124 units as well: they are dealt to the XCDs in turn, whatever units a mask leaves there.)
@@ -818,7 +820,16 @@ extern "C" int mtad_test_relay(mtad_ctx* c, int draft, int R, int absent, unsign
   c->relay_absent = absent;
   if (patience) c->relay_patience = patience;
   RelayArgs a;
-  return relay_shape(a, draft ? &c->dshape : &c->tshape, c->cfg.batch, R, c->cfg.max_context);
+  return relay_shape(c, a, draft ? &c->dshape : &c->tshape, R);
+}
+
+// Every pass that can be of that kind is from now on; the workspace has to be bound anew (mtad_workspace_bytes).
+extern "C" int mtad_test_relay_any(mtad_ctx* c) {
+  if (!c) return MTAD_EINVAL;
+  c->relay_any = true;
+  c->ws = nullptr;
+  c->ws_need = carve(c, nullptr, c->prompt_best, true, true);
+  return MTAD_OK;
 }
 
 // Such passes are given up by a workgroup one of whose waits lasts `give_up` ticks of 10 ns.

@@ -74,8 +74,9 @@ struct RelayArgs {
 };
 
 int relay_mail_words(int rows, int d, int f, int H, int KVH, int hd, int splits, RelayMail* m);  // lays a layer's words out
-// Units, their places and the key splits of a pass (a.rows, Rseq, B, d, f, H, KVH, kv are set); returns the workgroups, 0: no such pass
-int relay_plan(RelayArgs& a, int dtype, int hd, int max_context);
+// Units, their places and the key splits of a pass (n_layers, a.rows, Rseq, B, d, f, H, KVH are set); returns the workgroups, 0: no such pass, or
+// one that is no faster (any: that one too)
+int relay_plan(RelayArgs& a, int dtype, int hd, int max_context, bool any);
 hipError_t launch_relay(const RelayArgs& a, int dtype, int hd, int groups, hipStream_t s);
 
 }  // namespace mtad
