@@ -28,6 +28,21 @@ def _any(eng):
     mb.mtad_bind_workspace(eng.ctx, eng.workspace)
 
 
+@pytest.fixture
+def in_one_launch(monkeypatch):
+    """Engines made by the test take it for every verify pass and every draft step of at most 8 rows, and say so."""
+    from paper_2407_09722_amd import engine
+
+    class Engine(engine.Engine):
+        def __init__(self, *args, **more):
+            super().__init__(*args, **more)
+            _any(self)
+            for draft, rows in ((0, self.M), (1, self.gamma + 1), (1, self.beam)):
+                assert self.B * rows > 8 or _relay(self, draft, rows) > 0
+
+    monkeypatch.setattr(engine, "Engine", Engine)
+
+
 @pytest.mark.parametrize("dtype,heads,kv_heads,hd,ffn,layers,batch,gamma,beam,n", [
     ("fp32", 1, 1, 64, 8, 1, 1, 1, 1, 1),        # one layer, a reduction of 8 terms, an empty cache
     ("fp32", 2, 1, 64, 1032, 3, 1, 6, 1, 40),    # 129 strips of gate and up: the last unit has one of two
@@ -36,23 +51,21 @@ def _any(eng):
     ("fp32", 2, 1, 128, 344, 2, 1, 5, 2, 520),   # draft steps of two beams; a second split of the keys
     ("bf16", 1, 1, 64, 32, 1, 1, 1, 1, 1),
     ("bf16", 6, 2, 64, 1056, 3, 1, 7, 1, 40),    # 132 strips of gate and up; 33 k tiles of down over 8 waves
-    ("bf16", 12, 12, 64, 160, 2, 8, 1, 1, 30),   # 144 strips of q, k and v; draft steps of 8 sequences
+    ("bf16", 12, 12, 64, 160, 2, 4, 1, 1, 30),   # 144 strips of q, k and v: two a unit
+    ("fp32", 12, 12, 64, 160, 2, 4, 1, 1, 30),
+    ("bf16", 2, 2, 64, 160, 2, 8, 1, 1, 30),     # 16 rows a step at a time; draft steps of 8 sequences
     ("bf16", 5, 1, 128, 352, 2, 2, 3, 2, 270),   # 20 pairs a KV head: three units of 8, 8 and 4; a second split
     ("bf16", 2, 2, 128, 96, 40, 1, 4, 3, 20),    # many layers
 ])
-def test_pass_against_the_oracle(dtype, heads, kv_heads, hd, ffn, layers, batch, gamma, beam, n):
+def test_pass_against_the_oracle(in_one_launch, dtype, heads, kv_heads, hd, ffn, layers, batch, gamma, beam, n):
     """Every iteration, logits and cache, of a target whose passes are of that kind; the draft's beam steps likewise."""
-    from paper_2407_09722_amd.engine import DeviceModel, Engine
+    from paper_2407_09722_amd.engine import DeviceModel
     ts = si.ModelShape(layers, heads * hd, heads, kv_heads, hd, ffn, 512, dtype)
     ds = si.ModelShape(1, 64, 1, 1, 64, 160, 512, dtype)
     wt, wd = _weights(ts, 61, "target", boost=2.0), _weights(ds, 61, "draft", boost=2.0)
     prompt = np.random.default_rng(n).integers(0, ts.vocab, (batch, n)).astype(np.int32)
     print(f"one launch {dtype} {heads}/{kv_heads} x {hd} ffn {ffn} layers {layers} batch {batch} gamma {gamma} beam {beam} n {n}", flush=True)
     tm, dm = DeviceModel(ts, wt, DEV), DeviceModel(ds, wd, DEV)
-    eng = Engine(tm, dm, batch=batch, gamma=gamma, beam=beam, mode="mtad", max_context=n + 64, prefill_rows=16, device=DEV)
-    assert _relay(eng, 0, 1 + gamma) > 0 or (1 + gamma) * batch > 8
-    assert _relay(eng, 1, beam) > 0 or beam * batch > 8
-    eng.close()
     st = run_pair(ts, ds, wt, wd, prompt, 2 * gamma + 2, gamma=gamma, beam=beam, mode="mtad", tau=0.0, seed=5, check_kv=True, prefill_rows=16, fused_pass=1,
                   device_models=(tm, dm))
     assert st["excused"] == 0 and all(e == gamma for e in st["eta"])
@@ -65,7 +78,7 @@ def test_pass_against_the_oracle(dtype, heads, kv_heads, hd, ffn, layers, batch,
     (64, 4, 2, 2, 3, 1, 1025),       # a split of one key
     (128, 6, 2, 4, 1, 1, 257),       # empty and nearly empty caches beside a second split
 ])
-def test_long_caches(dtype, hd, heads, kv_heads, batch, gamma, beam, n):
+def test_long_caches(in_one_launch, dtype, hd, heads, kv_heads, batch, gamma, beam, n):
     """Splits of the keys, their merge, running maxima that move from block to block, sequences shorter than a split."""
     print(f"long {dtype} hd {hd} heads {heads}/{kv_heads} batch {batch} rows {1 + gamma * beam} n {n}", flush=True)
     r = np.random.default_rng(heads + n)
