@@ -319,6 +319,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       else
         __builtin_amdgcn_global_load_lds((GlobalWords)(src[i] + (unsigned)lane * 16u), (LdsWords)(lds_dma + s_in + dst[i]), 16, 0, 0);
       src[i] += step[i];
+      // Side-by-side tiles: the address moves on where it is.  Left to itself the compiler computes those of two requests ahead of both and copies them
+      // back, three to five more scalar instructions a k tile, between a barrier and the requests.
+      if constexpr (TALL) {
+        asm volatile("" : "+s"(src[i]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     if constexpr (TO == LPW) s_in = s_in + SLOT == D * SLOT ? 0 : s_in + SLOT;
   };
