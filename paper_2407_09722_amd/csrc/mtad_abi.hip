@@ -517,18 +517,27 @@ bool whole_machine(const mtad_ctx* c, hipStream_t s) {
   return n == 0 || n >= c->n_cus;
 }
 
-// The pass, followed by final norm + lm_head + row logsumexp when `logits` is given.
-int decoder_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStream_t s, float* logits, float* lse) {
-  if (logits && c->flow_on == 1 && c->relay_mail) {
-    RelayArgs a;
-    const int groups = relay_shape(c, a, m, R);
-    // All its workgroups have to be on the machine together.  On a stream of fewer compute units every pass would find some missing and start over with
-    // the others: 12 layers x 768 of 5 rows on 192 / 128 / 64 units 513 / 584 / 680 us, a launch a step 314 / 316 / 351.  (124 workgroups did so on a
-    // stream of 124 units as well: they are dealt to the XCDs in turn, whatever units a mask leaves there.)
-    if (groups > 0 && (size_t)4 * relay_mail_words(a.rows, a.d, a.f, a.H, a.KVH, m->head_dim, a.splits, nullptr) <= c->relay_mail_n && whole_machine(c, s)) {
-      const int rc = relay_pass(c, m, kv, a, groups, s);
-      return rc ? rc : lm_head(c, m, a.rows, logits, lse, s);
-    }
+// Workgroups of the one-launch pass of R rows a sequence, 0: this one is launched a step at a time.
+int relay_groups(const mtad_ctx* c, RelayArgs& a, const mtad_model* m, int R, hipStream_t s) {
+  if (c->flow_on != 1 || !c->relay_mail) return 0;
+  const int groups = relay_shape(c, a, m, R);
+  if (groups < 1 || (size_t)4 * relay_mail_words(a.rows, a.d, a.f, a.H, a.KVH, m->head_dim, a.splits, nullptr) > c->relay_mail_n) return 0;
+  // All its workgroups have to be on the machine together.  On a stream of fewer compute units every pass would find some missing and start over with
+  // the others: 12 layers x 768 of 5 rows on 192 / 128 / 64 units 513 / 584 / 680 us, a launch a step 314 / 316 / 351.  (124 workgroups did so on a
+  // stream of 124 units as well: they are dealt to the XCDs in turn, whatever units a mask leaves there.)
+  return whole_machine(c, s) ? groups : 0;
+}
+// What the row descriptors' kernel counts ahead of such a pass
+PassCount pass_count(const mtad_ctx* c, int groups) {
+  return groups > 0 ? PassCount{c->relay_sync, c->relay_mail, c->relay_mail_n} : PassCount{nullptr, nullptr, 0};
+}
+
+// The pass, followed by final norm + lm_head + row logsumexp when `logits` is given.  groups, one: the one-launch pass (relay_groups).
+int decoder_pass(mtad_ctx* c, const mtad_model* m, const mtad_kv* kv, int R, hipStream_t s, float* logits, float* lse, int groups = 0,
+                 RelayArgs* one = nullptr) {
+  if (groups > 0) {
+    const int rc = relay_pass(c, m, kv, *one, groups, s);
+    return rc ? rc : lm_head(c, m, one->rows, logits, lse, s);
   }
   if (m->dtype == 1) return decoder_pass_bf16(c, m, kv, R, s, logits, lse);
   int rc = decoder_pass_f32(c, m, kv, R, s, !logits);
@@ -707,11 +716,13 @@ int mtad_draft_beam_step(mtad_ctx* c, const mtad_model* draft, mtad_kv* dkv, mta
   const int B = c->cfg.batch, gamma = c->cfg.gamma, beam = c->cfg.beam;
   const int R = (step == 0) ? gamma + 1 : beam;
   const BeamView hv{hist->tok, hist->parent, hist->cum_logq};
+  RelayArgs one;
+  const int groups = relay_groups(c, one, draft, R, s);
   HIP_TRY(c, launch_draft_rows(c->rd, dkv->len, hv, st->catchup_tok, st->catchup_cnt, step, B, R, gamma, beam,
-                               dkv->page_size * dkv->max_pages, c->status, PassCount{c->relay_sync, c->relay_mail, c->relay_mail_n}, s));
+                               dkv->page_size * dkv->max_pages, c->status, pass_count(c, groups), s));
   c->lse_later = draft->dtype == 1 && c->warp_k == 0 && beam > 1;  // (warping and a saved row of log q read them first)
   const bool lse_later = c->lse_later;
-  int rc = decoder_pass(c, draft, dkv, R, s, c->dlogits, c->lse);
+  int rc = decoder_pass(c, draft, dkv, R, s, c->dlogits, c->lse, groups, &one);
   c->lse_later = false;
   if (rc) return rc;
   if (c->warp_k > 0) HIP_TRY(c, launch_warp_rows(c->dlogits, c->lse, B * R, draft->vocab, c->warp_k, c->warp_p, s));
@@ -741,10 +752,12 @@ int mtad_verify_tree(mtad_ctx* c, const mtad_model* target, mtad_kv* tkv, const 
   if (tree->M < 1 || tree->M > c->Rmax) return MTAD_ESHAPE;
   hipStream_t s = (hipStream_t)stream;
   const int B = c->cfg.batch, M = tree->M;
-  HIP_TRY(c, launch_verify_rows(c->rd, tkv->len, root_tok, tview(tree), B, tkv->page_size * tkv->max_pages, c->status, PassCount{c->relay_sync, c->relay_mail, c->relay_mail_n}, s));
+  RelayArgs one;
+  const int groups = relay_groups(c, one, target, M, s);
+  HIP_TRY(c, launch_verify_rows(c->rd, tkv->len, root_tok, tview(tree), B, tkv->page_size * tkv->max_pages, c->status, pass_count(c, groups), s));
   c->gather_tree = c->warp_k > 0 ? nullptr : tree;  // warped rows are gathered after the warp
   c->gather_out = c->warp_k > 0 ? nullptr : logp_cond;
-  int rc = decoder_pass(c, target, tkv, M, s, logits, row_lse);
+  int rc = decoder_pass(c, target, tkv, M, s, logits, row_lse, groups, &one);
   const bool gathered = c->gather_out == nullptr;
   c->gather_tree = nullptr;
   c->gather_out = nullptr;
