@@ -1372,9 +1372,10 @@ namespace {
 // down's units read; attention units (their splits are one more hand-over); units in excess of the compute units (a workgroup with units of two steps
 // in a row requests the second one's weights late); more than one sequence; and, bound by their arithmetic, float32 weights.  The lines are drawn
 // through 1200 shapes of 1 to 24 heads, with 1, 2, 4 and 12 layers each, contexts of 32 to 4000 tokens and 1 to 8 rows of 1 to 8 sequences, measured on
-// both sides.  What they admit keeps nine tenths of what could be gained (of float32 models with heads of 64, and of one layer with heads of 128, half) and
-// takes at most 1.02 of a launch a step (in 900 further passes of 2 to 24 layers: 1.02 once, else 1.01).  What they leave out took up to 1.19: 8 x 128, 3264 of 5 rows 42.5 / 47.0, 70 / 76, 359 / 382 (1, 2, 12
-// layers); 16 on 8 x 64, 3296 of 4 sequences, 12 layers 1.16; float32 4 on 1 x 64, 768 of 2 x 4 rows on 2200 tokens 1.18, 1.14, 1.16 (1, 2, 4 layers).
+// both sides.  What they admit keeps nine tenths of what could be gained (of float32 models with heads of 64, and of one layer with heads of 128, half);
+// of 2500 further passes of 2 to 24 layers eight took 1.01 to 1.03 of a launch a step, the others less.  What they leave out took up to 1.19: 8 x 128, 3264
+// of 5 rows 42.5 / 47.0, 70 / 76, 359 / 382 (1, 2, 12 layers); 16 on 8 x 64, 3296 of 4 sequences, 12 layers 1.16; float32 4 on 1 x 64, 768 of 2 x 4
+// rows on 2200 tokens 1.18, 1.14, 1.16 (1, 2, 4 layers).
 bool relay_pays(const RelayArgs& a, int dtype, int hd, int cus) {
   const int qkv = (a.H + 2 * a.KVH) * hd, L = a.n_layers;
   const double mb = (double)((int64_t)(dtype == 1 ? 2 : 4) * ((int64_t)qkv * a.d + (int64_t)a.d * a.H * hd + (int64_t)3 * a.d * a.f)) / (1 << 20);
@@ -1384,8 +1385,8 @@ bool relay_pays(const RelayArgs& a, int dtype, int hd, int cus) {
   if (dtype == 1) {
     const int attn = units * (hd / 64);  // (units of half as many keys at 128 dims)
     if (mb > (a.rows == 1 ? 56 : 32) || act > 16384 || attn > (act <= 6144 ? 192 : act <= 12288 ? 128 : 96)) return false;
-    if (a.B == 1 && mb <= 16 && L >= (hd == 64 ? 4 : 8)) return true;  // (at most 1.00 in all that were measured)
-    return against <= (hd == 64 ? (L == 1 ? 38 : L >= 4 ? 52 : mb <= 20 ? 61 : 47) : (L == 1 ? 17 : L < 4 ? 41 : 54));
+    if (a.B == 1 && mb <= 20 && L >= (hd == 64 ? 2 : 8)) return true;  // (1.03 once, 1.02 and 1.01 of two layers, else at most 1.00)
+    return against <= (hd == 64 ? (L == 1 ? 38 : L < 4 ? 47 : 52) : (L == 1 ? 17 : L < 4 ? 41 : 54));
   }
   if (mb > 16 || act > 8192 || units > (mb <= 4 ? 256 : act <= 6144 ? 128 : 64)) return false;
   against += mb;

@@ -48,6 +48,8 @@ def test_slower_in_one_launch(layers, heads, kv_heads, hd, ffn, dtype, batch, ro
     (12, 12, 12, 64, 2048, "bf16", 1, 5, 3400),   # 373 / 314
     (48, 12, 12, 64, 2048, "bf16", 1, 8, 255),    # 1206 / 1023
     (2, 12, 12, 64, 3072, "bf16", 1, 4, 513),     # a draft step: 79.0 / 77.5
+    (2, 12, 12, 64, 3072, "bf16", 1, 4, 2100),    # 90.2 / 79.5
+    (2, 10, 10, 64, 2496, "bf16", 1, 5, 3552),    # 0.90
     (4, 8, 8, 64, 1376, "bf16", 1, 5, 300),       # 112 / 94
     (48, 16, 16, 64, 2816, "bf16", 1, 1, 700),    # 1210 / 899
     (24, 24, 24, 64, 4096, "bf16", 1, 1, 256),    # 713 / 639
