@@ -145,11 +145,22 @@ def layer_weight_bytes(shape):
     return (shape.qkv_rows * d + d * shape.n_heads * shape.head_dim + 3 * f * d) * e
 
 
-def pass_kernel_name(w, one_launch):
+def pass_form(w):
+    """How the target pass runs: "flow", one launch (large layers, few rows); "relay", all layers in one launch (small models: a chain over
+    layers of a few megabytes); else a launch per step."""
+    rows, layer, pairs = w.batch * w.tree_rows, layer_weight_bytes(w.target), w.target.n_heads // w.target.n_kv_heads * w.tree_rows
+    if rows <= 8 and layer <= (16 << 20):
+        return "relay"
+    return "flow" if w.target.dtype == "bf16" and 4 <= rows <= 8 and pairs <= 16 and layer >= (64 << 20) else ""
+
+
+def pass_kernel_name(w, form):
     rows = w.batch * w.tree_rows
+    if form == "relay":
+        return f"relay_kernel<{'true' if w.target.dtype == 'bf16' else 'false'}, {w.target.head_dim}> (one launch = all layers; lm_head and logsumexp after it)"
     if w.target.dtype != "bf16":
         return "gemm_f32_kernel (+ attention kernels): one launch per product"
-    if one_launch:
+    if form == "flow":
         return f"flow_pass_kernel<{w.target.head_dim}> (one launch = the whole target pass)"
     return ("gemm_bf16_strips_kernel / gemm_bf16_kernel" if rows <= 8 else "gemm_bf16_multi_kernel / gemm_bf16_kernel" if rows < 25 else
             "gemm_bf16_dma_kernel / gemm_bf16_multi_kernel" if rows < 65 else "gemm_bf16_dma_kernel") + " (+ tree_attn_mfma_kernel): one launch per product"
@@ -208,13 +219,12 @@ def workload_block(w, K, W, threads, dev, mb, torch, DeviceModel, Engine):
     torch.cuda.synchronize()
     draft_ms = ev[0].elapsed_time(ev[1]) / K
     _, _, verify = verify_block(eng, w, K, torch, stream)
-    one_launch = w.target.dtype == "bf16" and w.batch * w.tree_rows <= 8 and layer_weight_bytes(w.target) >= (64 << 20)
     out = {"workload": f"{w.mode.upper()} gamma={w.gamma} beam={w.beam} batch={w.batch} prompt={w.prompt_len}, target "
                        f"L{w.target.n_layers} d{w.target.d_model} {w.target.dtype}, draft L{w.draft.n_layers} d{w.draft.d_model}; seed {w.seed}",
            "steps": K, "tau": w.tau, "value": res["tau"]["tokens_per_s"], "unit": "tokens/s",
            "ms_per_step": res["tau"]["ms_per_step"], "tokens_per_iteration": res["tau"]["tokens_per_iteration"],
            "iterations_per_s": round(1e3 / res["tau"]["ms_per_step"], 2), "tau0": res["tau0"],
-           "draft_phase_ms": round(draft_ms, 4), "verify": verify, "pass_kernels": pass_kernel_name(w, one_launch),
+           "draft_phase_ms": round(draft_ms, 4), "verify": verify, "pass_kernels": pass_kernel_name(w, pass_form(w)),
            "weights_setup_s": round(t_weights, 1), "device_status": mb.mtad_device_status(eng.ctx)}
     eng.close()
     del eng, tm, dm
@@ -252,7 +262,7 @@ def gemm_replay_block(w, tm, eng, rows, dt_id, mb, torch, stream, dev, K):
     torch.cuda.synchronize()
     gemm_ms = ev[0].elapsed_time(ev[1]) / (reps * len(launches))
     bpl = gemm_bytes / len(launches)
-    out = {"kernels": "gemm_f32_kernel" if not dt_id else pass_kernel_name(w, False).split(" (+")[0],
+    out = {"kernels": "gemm_f32_kernel" if not dt_id else pass_kernel_name(w, "").split(" (+")[0],
            "launches": len(launches), "bytes_per_launch": int(bpl), "avg_launch_us": round(gemm_ms * 1e3, 3),
            "GBps": round(bpl / gemm_ms / 1e6, 1), "frac_of_hbm_peak": round(bpl / gemm_ms / 1e6 / HBM_PEAK_GBS, 4)}
     tfile = os.path.join(ROOT, "profiles", "c3_gemm_hbm_traffic.txt")
@@ -376,7 +386,8 @@ def main():
     #     the interval also holds the embedding and log-sum-exp kernels of the pass, a few microseconds)
     rows = w.batch * M
     dt_id = 1 if w.target.dtype == "bf16" else 0
-    one_launch = bool(dt_id) and rows <= 8 and layer_weight_bytes(w.target) >= (64 << 20)
+    form = pass_form(w)
+    one_launch = form == "flow"
     traffic, traffic_detail = None, None
     tfile = os.path.join(ROOT, "profiles", f"{w.name.lower()}_verify_hbm_traffic.txt")
     if os.path.exists(tfile):                          # per-pass HBM bytes from the committed rocprofv3 counter runs
@@ -385,7 +396,7 @@ def main():
                           "write_bytes_per_launch": int(float(kv["write_bytes_per_launch"])),
                           "source": kv.get("source", "profiles/")}
         traffic = traffic_detail["fetch_bytes_per_launch"] + traffic_detail["write_bytes_per_launch"]
-    roofline = {"kernel": pass_kernel_name(w, one_launch),
+    roofline = {"kernel": pass_kernel_name(w, form),
                 "bound": "hbm", "achieved": verify["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": verify["frac_of_hbm_peak"], "traffic": traffic, "traffic_detail": traffic_detail,
                 "bytes_per_launch": int(verify_bytes), "avg_launch_us": round(verify_ms * 1e3, 2),

@@ -152,7 +152,11 @@ int mtad_bind_workspace(mtad_ctx *ctx, void *device_buf, size_t bytes);
  * launch instead of one per step (same arithmetic; the form every larger pass takes).  on = 0: never; 1 (the default): where it is the
  * faster form, for models of small layers (float32 and bf16) and for bf16 passes of 4 rows and more whose layers hold at least 64 MiB of
  * weights; 2: for every bf16 pass, as the latter.  Waits inside a one-launch pass are bounded: one that gives up sets status
- * bit 3 and the pass runs to its end.  The environment variable MTAD_FUSED_PASS=0|1|2 sets the same at context creation. */
+ * bit 3 and the pass runs to its end.  A small model's one launch holds up to a workgroup per compute unit until it ends, and all have to be on
+ * the machine together: beside another stream's kernels it takes no longer than a launch per step, and where some of its workgroups find no room
+ * for 50 us the others do their work.  On a stream made for part of the compute units it is not used; a graph captured elsewhere and launched on
+ * such a stream loses 50 us in each of these passes and up to half as much again as a launch per step takes.  The environment variable
+ * MTAD_FUSED_PASS=0|1|2 sets the same at context creation. */
 int mtad_set_fused_pass(mtad_ctx *ctx, int32_t on);
 /* Warped distributions (appendix "Hyper-parameter Details"; the footnote of Section 3.2 allows approximating p~ with
  * q~): with top_k > 0 every next-token distribution of both models is warped before it is used: the top_k most likely

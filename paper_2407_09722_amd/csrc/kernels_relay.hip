@@ -403,7 +403,7 @@ __device__ __forceinline__ float2 turn_of(double ang) {
 // ---- the pass ------------------------------------------------------------------------------------------------------
 
 struct Step {  // where a layer's words are
-  int l, rank, groups;
+  int l, groups;
   uint32_t tag;
   uint64_t *words;          // this layer's
   const uint64_t* h_words;  // the residual stream that the layer before left
@@ -1252,7 +1252,6 @@ __device__ __forceinline__ bool relay_run(RelaySmem& sm, unsigned char* x, const
   for (int l = 0; l < L; ++l) {
     Step at;
     at.l = l;
-    at.rank = rank;
     at.groups = groups;
     at.tag = watch.epoch << 6 | (uint32_t)(l + 1);
     at.words = words + (size_t)(l & 1) * slot;
