@@ -155,7 +155,7 @@ int mtad_bind_workspace(mtad_ctx *ctx, void *device_buf, size_t bytes);
  * bit 3 and the pass runs to its end.  A small model's one launch holds up to a workgroup per compute unit until it ends, and all have to be on
  * the machine together: beside another stream's kernels it takes no longer than a launch per step, and where some of its workgroups find no room
  * for 50 us the others do their work.  On a stream made for part of the compute units it is not used; a graph captured elsewhere and launched on
- * such a stream loses 50 us in each of these passes and up to half as much again as a launch per step takes.  The environment variable
+ * such a stream waits these 50 us in every pass and takes up to twice what a launch per step does.  The environment variable
  * MTAD_FUSED_PASS=0|1|2 sets the same at context creation. */
 int mtad_set_fused_pass(mtad_ctx *ctx, int32_t on);
 /* Warped distributions (appendix "Hyper-parameter Details"; the footnote of Section 3.2 allows approximating p~ with
